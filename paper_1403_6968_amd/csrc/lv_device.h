@@ -26,6 +26,24 @@ template <typename T> __device__ __forceinline__ void st16_nt(T* p, const V16<T>
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4, x), reinterpret_cast<u32x4*>(p));
 }
 
+// x[0 .. N) = p[0 .. N), 16 bytes at a time where the row is long enough (p
+// is then 16-byte aligned: factor slabs have rows of a power of two entries,
+// and a level's columns begin at a multiple of its rank).
+template <typename T, int N, int M> __device__ __forceinline__ void load_row(const T* p, T (&x)[M]) {
+  constexpr int E = 16 / (int)sizeof(T);
+  if constexpr (N >= E) {
+#pragma unroll
+    for (int c = 0; c < N; c += E) {
+      const V16<T> v = ld16(p + c);
+#pragma unroll
+      for (int e = 0; e < E; ++e) x[c + e] = v.v[e];
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < N; ++c) x[c] = p[c];
+  }
+}
+
 // Value of x in lane l (l uniform), broadcast to the whole wave.
 template <typename T> __device__ __forceinline__ T lane_bcast(T x, int l) {
   if constexpr (sizeof(T) == 4) {

@@ -17,11 +17,10 @@ constexpr int kPadOrder = 256;
 // Largest level rank handled by the register-resident fused pass; larger
 // ranks run the skinny products in chunks of this many factor columns.
 constexpr int kMaxFusedRank = 16;
-// Rows per block of the fused level pass for level rank R: a wave streams
-// RB rows of its 16-byte column group per step.
-constexpr int fused_row_block(int R) { return R >= 8 ? 8 : 4; }
-// Row blocks of the fused pass in flight beyond the one being processed.
-constexpr int fused_prefetch(int R) { return R >= 8 ? 0 : 1; }
+// Rows per block of the fused level pass: a wave streams this many rows of
+// its 16-byte column group per step (it fixes which wave sums which rows of
+// Y, so it is the same at every rank).
+constexpr int kFusedRowBlock = 4;
 // Largest level of the exponential model (k <= 2^kMaxLevel).
 constexpr int kMaxLevel = 10;
 // Pipelined batches: at most this many stage streams and factor-slab slots
@@ -66,6 +65,9 @@ template <typename T> struct FusedDesc {
   const T* Vy = nullptr;                // Y operand of the sums pass
   const T* Ud = nullptr; int Wd = 0;    // general form: extra X operand (row stride Wd)
   T* partX3 = nullptr;                  //   and its partials
+  // several updates in one pass: from one update's factors and partials to
+  // the next one's (elements)
+  int64_t sstride = 0, xstride = 0, ystride = 0, gstride = 0;
 };
 template <typename T> struct GramDesc {
   const T* Uj; const T* Vj; int W; int n_pad; int tile_rows; double* partG;
@@ -160,11 +162,10 @@ inline bool gram_in_pass(int R, int elem) { return R <= kMaxFusedRank && !skinny
 // The powers' fused pass of a level with rank R can also form X for Q_j (R
 // more columns, views with sums) and for xd columns of a general-form operand
 // (xd a power of two up to 8) when the level runs the fused vector pass and
-// the X width stays within fused_x_cap(R): 16 columns with the 8-row blocks
-// of R = 8, 12 with the 16-row blocks below (the LDS of two blocks per CU).
-constexpr int fused_x_cap(int R) { return R >= 8 ? 16 : 12; }
+// the X width stays within kFusedXCap columns (one lane per X sum of a block).
+constexpr int kFusedXCap = 64 / kFusedRowBlock;
 inline bool fused_extra_fits(int R, bool q, int xd) {
-  return R <= 8 && (xd == 0 || xd == 1 || xd == 2 || xd == 4 || xd == 8) && R + (q ? R : 0) + xd <= fused_x_cap(R);
+  return R <= 8 && (xd == 0 || xd == 1 || xd == 2 || xd == 4 || xd == 8) && R + (q ? R : 0) + xd <= kFusedXCap;
 }
 inline bool fused_vector_level(int R, int elem, bool shadowed) { return !shadowed && !skinny_on_mfma(R, elem); }
 // The sums pass (Y = S^T V_j and the rank update of S in one pass) on the
