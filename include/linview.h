@@ -325,8 +325,11 @@ lv_status lv_view_timing(lv_view* v, lv_timing* out);
 
 /* Rows per tile of the level pass of `level` (0 <= level < log2 k): the
  * height of the P_j tiles whose partial sums of P_j^T V_j are reduced by the
- * tail, so it fixes the summation order of the update.  Default 512;
- * lv_batch_create sets it by autotuning.  Allowed values: multiples of 64
+ * tail, so it fixes the summation order of the update.  Default 512, which
+ * stands for at most 512 rows: a matrix too small to fill the device with
+ * 512-row tiles is cut finer (by its order, element type and the update's
+ * rank alone).  Other heights are taken as they are.  lv_batch_create sets it
+ * by autotuning.  Allowed values: multiples of 64
  * in [256, 1024].  Two views with equal tiles, inputs and updates hold equal
  * values bit for bit whichever entry point applies the updates. */
 lv_status lv_view_tile_rows(const lv_view* v, int level, int* rows);

@@ -255,7 +255,7 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
   if (j > 0 && sums_fused(R, (int)sizeof(T))) {
     // one pass over S_j: Y = S_j^T V_j (old S_j), S_j += Q_j W_j^T
     st = timed(v, 0, s, "sums: pass", [&] {
-      return launch_sums_fused<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->tile_rows[j], v->slabQ<T>(), v->slabW<T>(), sV,
+      return launch_sums_fused<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(), v->slabW<T>(), sV,
                                   L.W, v->partYs<T>(j), s);
     });
     if (st == LV_OK)
@@ -266,10 +266,10 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
   } else if (j > 0) {
     st = timed(v, 0, s, "sums: S^T V", [&] {
       if (skinny_on_mfma(R, (int)sizeof(T)))
-        return launch_skinny_f32(R, reinterpret_cast<const float*>(v->S<T>(j)), L.ldp, L.n_pad, v->tile_rows[j],
+        return launch_skinny_f32(R, reinterpret_cast<const float*>(v->S<T>(j)), L.ldp, L.n_pad, v->rows(j, R),
                                  v->slabQ<float>(), reinterpret_cast<const float*>(sV), L.W,
                                  reinterpret_cast<float*>(v->partX<T>(j)), v->partYs<float>(j), s, kWantY);
-      return launch_level_readonly<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->tile_rows[j], v->slabQ<T>(),
+      return launch_level_readonly<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(),
                                       sV + (L.W - R), L.W, v->partX<T>(j), v->partYs<T>(j), s);
     });
     if (st == LV_OK)
@@ -283,7 +283,7 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
     if (st != LV_OK) return st;
   }
   return timed(v, 1, s, "sums: tail", [&] {
-    return launch_sums_tail<T>(R, v->partXs<T>(j), v->partYs<T>(j), v->partGs(j), L.nct, v->nrt(j), L.n_pad,
+    return launch_sums_tail<T>(R, v->partXs<T>(j), v->partYs<T>(j), v->partGs(j), L.nct, v->nrt(j, R), L.n_pad,
                                v->slabQ<T>(), v->slabW<T>(), sU, sV, L.W, j == 0, s);
   });
 }
@@ -298,10 +298,10 @@ lv_status general_pass(lv_view* v, int j, hipStream_t s) {
   const T* Dj = v->D<T>(j & 1);
   return timed(v, 0, s, "general: P D", [&] {
     if (skinny_on_mfma(L.pp, (int)sizeof(T)))
-      return launch_skinny_f32(L.pp, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->tile_rows[j],
+      return launch_skinny_f32(L.pp, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->rows(j, L.pp),
                                reinterpret_cast<const float*>(Dj), reinterpret_cast<const float*>(Dj), L.pp,
                                v->partXT<float>(), v->partYT<float>(), s, kWantX);
-    return launch_level_readonly<T>(L.pp, v->P<T>(j), L.ldp, L.n_pad, v->tile_rows[j], Dj, Dj, L.pp,
+    return launch_level_readonly<T>(L.pp, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, L.pp), Dj, Dj, L.pp,
                                     v->partXT<T>(), v->partYT<T>(), s);
   });
 }
@@ -364,10 +364,10 @@ lv_status gfac_pass(lv_view* v, int j, int ru, const T* sU, hipStream_t s) {
   const int R = gW(ru, j);
   return timed(v, 0, s, "general: P Y", [&] {
     if (skinny_on_mfma(R, (int)sizeof(T)))
-      return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->tile_rows[j],
+      return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->rows(j, R),
                                reinterpret_cast<const float*>(Yj), reinterpret_cast<const float*>(Yj), sy,
                                v->partXT<float>(), v->partYT<float>(), s, kWantX);
-    return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->tile_rows[j], Yj, Yj, sy, v->partXT<T>(),
+    return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), Yj, Yj, sy, v->partXT<T>(),
                                     v->partYT<T>(), s);
   });
 }
@@ -433,7 +433,8 @@ lv_status gfac_skip(lv_view* v, int ru, const T* sU, const T* sV, hipStream_t s)
         return launch_skinny_f32(wp, reinterpret_cast<const float*>(v->P<T>(L.m)), L.ldp, L.n_pad, kTileRows,
                                  reinterpret_cast<const float*>(Yp), reinterpret_cast<const float*>(Yp), sp,
                                  v->partXT<float>(), v->partYT<float>(), s, kWantX);
-      return launch_level_readonly<T>(wp, v->P<T>(L.m), L.ldp, L.n_pad, kTileRows, Yp, Yp, sp, v->partXT<T>(),
+      return launch_level_readonly<T>(wp, v->P<T>(L.m), L.ldp, L.n_pad,
+                                      slice_rows(L.n_pad, L.elem, wp, v->on_cores(wp), kTileRows), Yp, Yp, sp, v->partXT<T>(),
                                       v->partYT<T>(), s);
     });
     if (st == LV_OK)
@@ -502,10 +503,10 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
     // sums: X_s = P_j Q_j with the OLD P_j, before this level's update
     st = timed(v, 0, s, "sums: P Q", [&] {
       if (skinny_on_mfma(R, (int)sizeof(T)))
-        return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->tile_rows[j],
+        return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->rows(j, R),
                                  v->slabQ<float>(), reinterpret_cast<const float*>(sV), L.W, v->partXs<float>(j),
                                  v->partYs<float>(j), s, kWantX);
-      return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->tile_rows[j], v->slabQ<T>(),
+      return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(),
                                       sV + (L.W - R), L.W, v->partXs<T>(j), v->partYs<T>(j), s);
     });
     if (st != LV_OK) return st;
@@ -521,9 +522,9 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
       // P_j), else the update pass follows
       const bool fused_upd = !v->shadowed() && skinny_fuses_update(R);
       st = timed(v, 0, s, "skinny", [&] {
-        return v->shadowed() ? launch_skinny_bf16(R, v->shadow(j), L.ldp, L.n_pad, v->tile_rows[j], sU, sV, L.W,
+        return v->shadowed() ? launch_skinny_bf16(R, v->shadow(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W,
                                                   v->partX<float>(j), v->partY<float>(j), s)
-                             : launch_skinny_f32(R, v->P<float>(j), L.ldp, L.n_pad, v->tile_rows[j], sU, sV, L.W,
+                             : launch_skinny_f32(R, v->P<float>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W,
                                                  v->partX<float>(j), v->partY<float>(j), s, kWantX | kWantY,
                                                  fused_upd);
       });
@@ -538,7 +539,7 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
         });
       if (st == LV_OK)
         st = timed(v, 1, s, "level tail", [&] {
-          return launch_level_tail<float>(R, v->partX<float>(j), v->partY<float>(j), v->partG(j), L.nct, v->nrt(j),
+          return launch_level_tail<float>(R, v->partX<float>(j), v->partY<float>(j), v->partG(j), L.nct, v->nrt(j, R),
                                           1, L.n_pad, sU, sV, L.W, s);
         });
     }
@@ -548,18 +549,18 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
       if (q_in_pass || d_in_pass) {
         const T* Dop = !d_in_pass ? nullptr : L.gfac ? v->Yf<T>(j) : v->D<T>(j & 1);
         const int ldd = L.gfac ? L.WY[j] : L.pp;
-        return launch_level_fused_x<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->tile_rows[j], sU, sV, L.W, v->partX<T>(j),
+        return launch_level_fused_x<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W, v->partX<T>(j),
                                        v->partY<T>(j), v->partG(j), q_in_pass ? v->slabQ<T>() : nullptr,
                                        v->partXs<T>(j), Dop, ldd, d_in_pass ? xd : 0, v->partXT<T>(), s);
       }
-      return launch_level_fused<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->tile_rows[j], sU, sV, L.W, v->partX<T>(j),
+      return launch_level_fused<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W, v->partX<T>(j),
                                    v->partY<T>(j), v->partG(j), s,
-                                   pipelined ? pipe_slice_groups(L.nct, v->nrt(j)) : 0);
+                                   pipelined ? pipe_slice_groups(L.nct, v->nrt(j, R)) : 0);
     });
     if (st == LV_OK)
       st = timed(v, 1, s, "level tail", [&] {
-        return launch_level_tail<T>(R, v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, v->nrt(j),
-                                    gram_in_pass(R, (int)sizeof(T)) ? v->nrt(j) : 1, L.n_pad, sU, sV, L.W, s);
+        return launch_level_tail<T>(R, v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, v->nrt(j, R),
+                                    gram_in_pass(R, (int)sizeof(T)) ? v->nrt(j, R) : 1, L.n_pad, sU, sV, L.W, s);
       });
   }
   if (st == LV_OK && L.general)

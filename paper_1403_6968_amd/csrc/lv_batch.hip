@@ -152,10 +152,12 @@ lv_status autotune(lv_batch* b, hipStream_t s) {
         for (int c : cands) {
           // skip a candidate that gives every view the same row-tile count as one already timed
           int sig = 0;
-          for (lv_view* v : g.second) sig = sig * 131 + (int)((v->L.n_pad + c - 1) / c);
+          for (lv_view* v : g.second) {
+            v->tile_rows[j] = c;
+            sig = sig * 131 + v->nrt(j, g.first);
+          }
           if (std::find(seen_nrt.begin(), seen_nrt.end(), sig) != seen_nrt.end()) continue;
           seen_nrt.push_back(sig);
-          for (lv_view* v : g.second) v->tile_rows[j] = c;
           b->bl.plan = b->mode == LV_FP64 ? make_plan<double>(b->views, in) : make_plan<float>(b->views, in);
           st = upload_plan(b, s);
           if (st != LV_OK) break;

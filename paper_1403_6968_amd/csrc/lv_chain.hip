@@ -56,12 +56,15 @@ k_chain_tail(const T* __restrict__ partX, int nct, const T* __restrict__ partY, 
 
 struct lv_chain {
   int64_t n, n_pad;
-  int k, s, model, r_max, r_pad, elem, nct, nrt;
+  int k, s, model, r_max, r_pad, elem, nct;
   lv_mode mode;
   std::vector<int> pw;       // stored powers, pw[0] = 1
   std::vector<int> Wd;       // padded slab width of each stored matrix
   struct Step { int c, a, b; };
   std::vector<Step> steps;   // products in evaluation order (indices into pw)
+  // rows per slice of a pass of rank R, and its slices
+  int rows(int R) const { return slice_rows(n_pad, elem, R, skinny_on_mfma(R, elem), kTileRows); }
+  int nrt(int R) const { return (int)((n_pad + rows(R) - 1) / rows(R)); }
   std::vector<size_t> P, sU, sV;
   size_t partX = 0, partY = 0, partXd = 0, partG = 0, d64[3] = {};
   size_t total = 0;
@@ -131,7 +134,6 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
   c.elem = mode == LV_FP64 ? 8 : 4;
   c.n_pad = round_up(n, kPadOrder);
   c.nct = (int)(c.n_pad / tile_cols_bytes(c.elem));
-  c.nrt = (int)((c.n_pad + kTileRows - 1) / kTileRows);
   lv_status st = plan_chain(c);
   if (st != LV_OK) return st;
   const int ns = (int)c.pw.size();
@@ -151,7 +153,7 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
   }
   c.partX = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
   c.partXd = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
-  c.partY = off; off = align_up(off + (size_t)c.nrt * c.n_pad * maxW * c.elem);
+  c.partY = off; off = align_up(off + (size_t)c.n_pad * slice_cols(c.n_pad, c.elem, maxW, false) * c.elem);
   c.partG = off; off = align_up(off + (size_t)(c.n_pad / kAtbRows) * maxG * sizeof(double));
   if (mode == LV_FP32 && ns > 1)
     for (int i = 0; i < 3; ++i) { c.d64[i] = off; off = align_up(off + (size_t)c.n_pad * c.n_pad * sizeof(double)); }
@@ -209,10 +211,10 @@ lv_status step_products(lv_chain* c, const lv_chain::Step& q, hipStream_t s) {
   const T* Va = c->V<T>(q.a);
   auto pass = [&](const T* P, int R, const T* op1, const T* op2, T* px, T* py, int want) -> hipError_t {
     if (skinny_on_mfma(R, (int)sizeof(T)))
-      return launch_skinny_f32(R, reinterpret_cast<const float*>(P), np, np, kTileRows,
+      return launch_skinny_f32(R, reinterpret_cast<const float*>(P), np, np, c->rows(R),
                                reinterpret_cast<const float*>(op1), reinterpret_cast<const float*>(op2), R,
                                reinterpret_cast<float*>(px), reinterpret_cast<float*>(py), s, want);
-    return launch_level_readonly<T>(R, P, np, np, kTileRows, op1, op2, R, px, py, s);
+    return launch_level_readonly<T>(R, P, np, np, c->rows(R), op1, op2, R, px, py, s);
   };
   if (q.a == q.b)
     return hip_check(pass(c->Pm<T>(q.a), Wa, Ub, Va, c->pX<T>(), c->pY<T>(), kWantX | kWantY), "P U, P^T V");
@@ -234,7 +236,7 @@ lv_status chain_update(lv_chain* c, const T* U, const T* V, int r, int64_t ldu, 
       st = hip_check(launch_atb<T>(Wa, Wb, c->V<T>(q.a), Wa, c->U<T>(q.b), Wb, np, c->pG(), s), "V_a^T U_b");
     if (st == LV_OK) {
       hipLaunchKernelGGL((k_chain_tail<T>), dim3((unsigned)((np * Wc + 255) / 256)), dim3(256), 0, s, c->pX<T>(),
-                         c->nct, c->pY<T>(), c->nrt, c->pG(), c->U<T>(q.a), Wa, c->pw[q.a] * c->r_pad, c->V<T>(q.b),
+                         c->nct, c->pY<T>(), c->nrt(Wa), c->pG(), c->U<T>(q.a), Wa, c->pw[q.a] * c->r_pad, c->V<T>(q.b),
                          Wb, c->pw[q.b] * c->r_pad, c->U<T>(q.c), c->V<T>(q.c), Wc, np);
       st = hip_check(hipGetLastError(), "chain tail");
     }

@@ -57,7 +57,7 @@ k_glin_tail(const T* __restrict__ partX, int nct, const T* __restrict__ full, co
 
 struct lv_glin {
   int64_t n, n_pad;
-  int k, p, pp, r_max, r_pad, elem, nct, nrt, strategy, maxw;
+  int k, p, pp, r_max, r_pad, elem, nct, strategy, maxw;
   lv_mode mode;
   size_t A, Tb, Bb, D[2], sU, sV, partX, partY, full, atbA, atbG, Yb, Zb, A64, gT[2], gB, total;
   size_t Toff(int i) const { return Tb + (size_t)i * align_up((size_t)n_pad * pp * elem); }
@@ -93,7 +93,6 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.r_pad = (int)next_pow2(r_max);
   g.pp = p <= kGlinNarrow ? (int)next_pow2(p) : (int)round_up(p, 128);
   g.nct = (int)(g.n_pad / tile_cols_bytes(g.elem));
-  g.nrt = (int)((g.n_pad + kTileRows - 1) / kTileRows);
   g.maxw = strategy == LV_GLIN_INCR ? (int)next_pow2((int64_t)k * g.r_pad) : 1;
   const size_t e = g.elem, np = g.n_pad, pp = g.pp;
   const int xw = strategy == LV_GLIN_INCR ? g.maxw : (g.pp <= kGlinNarrow ? g.pp : 1);   // read-only pass width
@@ -106,7 +105,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.sU = take(np * g.r_pad * e);
   g.sV = take(np * g.r_pad * e);
   g.partX = take((size_t)g.nct * np * xw * e);
-  g.partY = take((size_t)g.nrt * np * xw * e);
+  g.partY = take(np * slice_cols(g.n_pad, g.elem, xw, false) * e);
   g.atbA = take((np / kAtbRows) * g.r_pad * pp * sizeof(double));
   g.D[0] = g.D[1] = g.full = g.atbG = g.Yb = g.Zb = 0;
   if (strategy == LV_GLIN_HYBRID) { g.D[0] = take(np * pp * e); g.D[1] = take(np * pp * e); }
@@ -165,12 +164,13 @@ lv_status glin_amul(lv_glin* g, const T* M, int w, int sm, hipStream_t s, int* n
     return hip_check(launch_gemm_rect<T>(g->at<T>(g->A), np, M, sm, g->at<T>(g->full), g->pp, np, w, np, s), "A M");
   }
   *nct_out = g->nct;
+  const int rows = slice_rows(np, g->elem, w, skinny_on_mfma(w, g->elem), kTileRows);
   if (skinny_on_mfma(w, (int)sizeof(T)))
-    return hip_check(launch_skinny_f32(w, reinterpret_cast<const float*>(g->at<T>(g->A)), np, np, kTileRows,
+    return hip_check(launch_skinny_f32(w, reinterpret_cast<const float*>(g->at<T>(g->A)), np, np, rows,
                                        reinterpret_cast<const float*>(M), reinterpret_cast<const float*>(M), sm,
                                        g->at<float>(g->partX), g->at<float>(g->partY), s, kWantX),
                      "A M");
-  return hip_check(launch_level_readonly<T>(w, g->at<T>(g->A), np, np, kTileRows, M, M, sm, g->at<T>(g->partX),
+  return hip_check(launch_level_readonly<T>(w, g->at<T>(g->A), np, np, rows, M, M, sm, g->at<T>(g->partX),
                                             g->at<T>(g->partY), s),
                    "A M");
 }

@@ -171,6 +171,35 @@ inline bool fused_vector_level(int R, int elem, bool shadowed) { return !shadowe
 // The sums pass (Y = S^T V_j and the rank update of S in one pass) on the
 // vector kernel, below the ranks that run on the matrix cores.
 inline bool sums_fused(int R, int elem) { return R <= kMaxFusedRank && !skinny_on_mfma(R, elem); }
+// Rows per slice of a level pass of rank R over a matrix of padded order
+// n_pad, for a view's tile rows.  The passes take (column tile, row slice)
+// work-groups, and 512-row slices leave most of the device idle below
+// n_pad = 8192 (128 work-groups at 4096, 4 at 512).  The default, kTileRows,
+// therefore stands for 512 rows or as many as give kFillBlocks work-groups
+// (one per compute unit), whichever is less, but not below 8 R rows, so that
+// a slice's Y partial stays under 1/16 of the bytes it streams, nor below
+// `unit` rows: a block of kFusedRowBlock rows for each of the four waves, or a
+// 64-row chunk of the matrix-core passes (`cores`).  A single FP64 update at
+// n = 256: 102 us at 512 rows, 46 us so; the read-only float pass at n = 4096
+// 38 us and 22 us.  Other heights are taken as they are: rounds over many
+// views fill the device anyway and lose by finer slices (32 views of 512 to
+// 4096: 2.34 ms with tuned heights, 2.52 ms when every height was cut).
+constexpr int kTileRows = 512;      // default rows per tile of a level pass
+constexpr int kFillBlocks = 256;
+inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, int tile_rows) {
+  if (tile_rows != kTileRows) return tile_rows;
+  const int unit = cores ? 64 : 4 * kFusedRowBlock;
+  const int64_t nct = n_pad / tile_cols_bytes(elem);
+  const int64_t ns = (kFillBlocks + nct - 1) / nct;
+  int64_t rows = round_up((n_pad + ns - 1) / ns, unit);
+  if (rows < 8 * R) rows = round_up(8 * R, unit);
+  return rows < tile_rows ? (int)rows : tile_rows;
+}
+inline int slice_count(int64_t n_pad, int elem, int R, bool cores, int tile_rows) {
+  const int rows = slice_rows(n_pad, elem, R, cores, tile_rows);
+  return (int)((n_pad + rows - 1) / rows);
+}
+
 // Work-groups of a tail launch / Gram pairs per work-group for rank R.
 // Level ranks from which the tail works on column slices of min(R, 32)
 // columns, one column per lane and kTailRowsPerThread rows per thread.

@@ -154,13 +154,14 @@ __device__ __forceinline__ void tail_body(const T* __restrict__ partX, const T* 
     for (int idx = tid; idx < R * R; idx += 256) {
       double g = 0.0;
       int t = 0;
-      for (; t + 4 <= ng; t += 4) {
-        double v[4];
+      for (; t + 16 <= ng; t += 16) {
+        double v[16];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = partG[(int64_t)(t + e) * R * R + idx];
+        for (int e = 0; e < 16; ++e) v[e] = partG[(int64_t)(t + e) * R * R + idx];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) g += v[e];
+        for (int e = 0; e < 16; ++e) g += v[e];
       }
+#pragma unroll 4
       for (; t < ng; ++t) g += partG[(int64_t)t * R * R + idx];
       G[idx] = g;
     }
@@ -172,7 +173,9 @@ __device__ __forceinline__ void tail_body(const T* __restrict__ partX, const T* 
     const int64_t i = idx / R;
     const int c = (int)(idx % R);
     double x = 0.0, y = 0.0, ug = 0.0;
+#pragma unroll 4
     for (int t = sl; t < nct; t += TL) x += (double)partX[(int64_t)t * strideX + idx];
+#pragma unroll 4
     for (int t = sl; t < nrt; t += TL) y += (double)partY[(int64_t)t * strideX + idx];
 #pragma unroll
     for (int d = sl; d < R; d += TL) ug = fma((double)Ucur[i * W + d], G[d * R + c], ug);

@@ -369,7 +369,7 @@ k_ols_stage_row(const T* __restrict__ dx, int64_t n, const T* __restrict__ X, co
 
 struct lv_ols {
   int64_t m, n, p, m_pad, n_pad;
-  int pp, elem, nct, nrt;
+  int pp, elem, nct, nrt, rows;   // rows: per slice of the pass over W
   lv_mode mode;
   size_t X, Y, W, C, beta, ubuf, vbuf, Pk, Qk, Rs, Ss, partX, partY, vec;
   size_t pXu, pUu, pUy, dpart, spart, sums, red;
@@ -399,7 +399,8 @@ void layout_ols(lv_ols& o, int64_t m, int64_t n, int64_t p, lv_mode mode) {
   o.n_pad = round_up(n, kPadOrder);
   o.pp = (int)next_pow2(p);
   o.nct = (int)(o.n_pad / tile_cols_bytes(o.elem));
-  o.nrt = (int)((o.n_pad + kTileRows - 1) / kTileRows);
+  o.rows = slice_rows(o.n_pad, o.elem, 4, false, kTileRows);
+  o.nrt = (int)((o.n_pad + o.rows - 1) / o.rows);
   const size_t e = o.elem, np = o.n_pad, mp = o.m_pad, pp = o.pp;
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
@@ -534,7 +535,7 @@ lv_status ols_update(lv_ols* o, int64_t row, const T* dx, hipStream_t s) {
     }
   }
   if (st == LV_OK)
-    st = hip_check(launch_level_readonly<T>(4, o->at<T>(o->W), np, np, kTileRows, o->at<T>(o->Pk), o->at<T>(o->Qk), 4,
+    st = hip_check(launch_level_readonly<T>(4, o->at<T>(o->W), np, np, o->rows, o->at<T>(o->Pk), o->at<T>(o->Qk), 4,
                                             o->at<T>(o->partX), o->at<T>(o->partY), s),
                    "W [p1 p2 v], W^T [q1 q2]");
   if (st != LV_OK) return st;

@@ -136,8 +136,8 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
       const Layout& L = v->L;
       if (j > L.m) continue;
       const int R = L.r_pad << j;
-      const int trows = j < L.m ? v->tile_rows[j] : 0;
-      const int nrt = j < L.m ? v->nrt(j) : 0;
+      const int trows = j < L.m ? v->rows(j, R) : 0;
+      const int nrt = j < L.m ? v->nrt(j, R) : 0;
       T* sU = v->slabU<T>();
       T* sV = v->slabV<T>();
       const T* Vj = sV + (L.W - R);

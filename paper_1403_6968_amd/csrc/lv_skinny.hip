@@ -702,7 +702,7 @@ __global__ void __launch_bounds__(UPD ? 512 : 256) k_skinny_f32_multi(const Skin
 // X-only float pass on the matrix cores: partial X = P U for R <= 16 NB
 // factor columns (zero-padded), P streamed from HBM straight into the MFMA
 // operand registers: no LDS staging of P, no exchange between waves.
-// Block: kXWaves waves over kXRows rows x 256 columns of P; wave w takes
+// Block: kXWaves waves over tile_rows rows x 256 columns of P; wave w takes
 // the 16-row strips w, w + kXWaves, ..., each read in two halves of 128
 // columns, the next half requested before the current one is multiplied.
 // v_mfma_f32_16x16x4f32: A (16 x 4): lane l holds A[l % 16][l / 16];
@@ -713,7 +713,13 @@ __global__ void __launch_bounds__(UPD ? 512 : 256) k_skinny_f32_multi(const Skin
 // 8 products takes the e-th of these floats as its summation index, and the
 // B operand the matching U row.
 constexpr int kXWaves = 8;
-constexpr int kXRows = 512;
+constexpr int kXRows = 512;   // rows per block where that gives kXBlocks blocks
+constexpr int kXBlocks = 512; // else as few (at least a strip per wave) as give so many
+inline int xprod_rows(int64_t n_pad) {
+  const int64_t nct = n_pad / TCB, ns = (kXBlocks + nct - 1) / nct;
+  const int64_t rows = round_up((n_pad + ns - 1) / ns, 16 * kXWaves);
+  return rows < kXRows ? (int)rows : kXRows;
+}
 constexpr int XUS = 4;   // LDS row padding of the U tile (floats): rows 4 apart in distinct banks
 
 template <int NB>
@@ -726,8 +732,8 @@ __global__ void __launch_bounds__(64 * kXWaves) k_xprod_f32(const SkinnyDesc d) 
   const int l16 = lane % 16, lq = lane / 16;
   const int ct = blockIdx.x;
   const int col0 = ct * TCB;
-  const int row0 = blockIdx.y * kXRows;
-  const int nstrips = (min(row0 + kXRows, d.n_pad) - row0) / 16;
+  const int row0 = blockIdx.y * d.tile_rows;
+  const int nstrips = (min(row0 + d.tile_rows, d.n_pad) - row0) / 16;
   const float* __restrict__ P = static_cast<const float*>(d.src);
 
   f32x4 bufA[4][2], bufB[4][2];
@@ -849,10 +855,11 @@ hipError_t launch_skinny_f32(int R, const float* P, int64_t ldp, int64_t n_pad, 
     // X only: the direct-operand pass (row tiling of its own; the X partials
     // do not depend on it)
     const int nct = (int)(n_pad / TCB);
-    const dim3 grid((unsigned)nct, (unsigned)((n_pad + kXRows - 1) / kXRows));
+    const int xrows = xprod_rows(n_pad);
+    const dim3 grid((unsigned)nct, (unsigned)((n_pad + xrows - 1) / xrows));
     const int per = R <= 64 ? R : 64;
     for (int c0 = 0; c0 < R; c0 += per) {
-      const SkinnyDesc d{P, ldp, (int)n_pad, kXRows, slabU + c0, nullptr, W, per, partX + c0, nullptr, R, nct, 0,
+      const SkinnyDesc d{P, ldp, (int)n_pad, xrows, slabU + c0, nullptr, W, per, partX + c0, nullptr, R, nct, 0,
                          kWantX};
       if (per <= 16)
         hipLaunchKernelGGL((k_xprod_f32<1>), grid, dim3(64 * kXWaves), 0, s, d);

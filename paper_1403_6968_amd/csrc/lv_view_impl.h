@@ -23,15 +23,41 @@ constexpr size_t kAlign = 256;
 constexpr int64_t kMaxOrder = 65536;
 constexpr int kMaxK = 1024;
 constexpr int kMaxWidth = 2 * kMaxLevelRank;   // k * r_pad: width of the top-level factors
-constexpr int kTileRows = 512;      // default rows per tile of a level pass
 constexpr int kMinTileRows = 256;   // tile rows a level pass may be set to:
 constexpr int kMaxTileRows = 1024;  //   multiples of 64 in [256, 1024]
 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
+// Sizes of a level's partials for ranks up to R (an update may have a lower
+// rank than the view's r_max, and lower ranks may be cut into more slices):
+// factor columns of Y over all slices, and Gram entries over all slices (or
+// over the row tiles of the stand-alone Gram), each for the tile rows that
+// give most slices: the smallest height, or the default's finer cut.
+inline size_t slice_cols(int64_t n_pad, int elem, int R, bool shadow) {
+  size_t most = 0;
+  for (int q = 1; q <= R; q *= 2) {
+    const bool cores = shadow || skinny_on_mfma(q, elem);
+    for (const int rows : {kMinTileRows, kTileRows}) {
+      const size_t c = (size_t)slice_count(n_pad, elem, q, cores, rows) * q;
+      most = c > most ? c : most;
+    }
+  }
+  return most;
+}
+inline size_t gram_partials(int64_t n_pad, int elem, int R) {
+  size_t most = (size_t)gram_tiles(n_pad) * R * R;
+  for (int q = 1; q <= R && gram_in_pass(q, elem); q *= 2) {
+    for (const int rows : {kMinTileRows, kTileRows}) {
+      const size_t c = (size_t)slice_count(n_pad, elem, q, false, rows) * q * q;
+      most = c > most ? c : most;
+    }
+  }
+  return most;
+}
+
 struct Layout {
   int64_t n_pad = 0, ldp = 0;
-  int m = 0, r_pad = 0, W = 0, elem = 0, nct = 0, nrt_max = 0, tile_rows = 0;
+  int m = 0, r_pad = 0, W = 0, elem = 0, nct = 0, tile_rows = 0;
   size_t P[kMaxLevel + 1] = {};
   size_t slabU = 0, slabV = 0;   // the update's factor slabs (every level's U_j, V_j)
   // factor-slab pairs of the pipelined batch (plain views with m >= 2): slot
@@ -129,7 +155,6 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
   L.W = k * L.r_pad;
   L.tile_rows = kTileRows;
   L.nct = (int)(L.n_pad / tile_cols_bytes(L.elem));
-  L.nrt_max = (int)((L.n_pad + kMinTileRows - 1) / kMinTileRows);   // partials sized for the smallest tiles
   size_t off = 0;
   const size_t mat = (size_t)L.n_pad * L.ldp * L.elem;
   if (!ext_powers)
@@ -150,18 +175,29 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
     L.zfac = off;
     off = align_up(off + (size_t)L.n_pad * L.r_pad * L.elem);
   }
+  const bool shadow = mode == LV_FP32_BF16SHADOW;
+  const size_t parts = off;
   for (int j = 0; j < L.m; ++j) {
     const size_t R = (size_t)L.r_pad << j;
+    if (ext_powers) off = parts;   // one level's partials at a time
     L.partX[j] = off; off = align_up(off + (size_t)L.nct * L.n_pad * R * L.elem);
-    L.partY[j] = off; off = align_up(off + (size_t)L.nrt_max * L.n_pad * R * L.elem);
-    const size_t ng = (size_t)(gram_tiles(L.n_pad) > L.nrt_max ? gram_tiles(L.n_pad) : L.nrt_max);
-    L.partG[j] = off; off = align_up(off + ng * R * R * sizeof(double));
+    L.partY[j] = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, (int)R, shadow) * L.elem);
+    L.partG[j] = off; off = align_up(off + gram_partials(L.n_pad, L.elem, (int)R) * sizeof(double));
   }
   if (ext_powers) {
-    L.total = off;
+    // the bytes that linview.h states for a shape (every level's partials
+    // side by side): they decide which shapes the entry point takes
+    size_t stated = parts;
+    for (int j = 0; j < L.m; ++j) {
+      const size_t R = (size_t)L.r_pad << j, part = (size_t)L.n_pad * R * L.elem, ng = gram_tiles(L.n_pad);
+      stated = align_up(stated + L.nct * part);
+      stated = align_up(stated + (L.n_pad / kMinTileRows) * part);
+      stated = align_up(stated + ng * R * R * sizeof(double));
+    }
+    L.total = stated;
     return L;
   }
-  if (mode == LV_FP32_BF16SHADOW)
+  if (shadow)
     for (int j = 0; j < L.m; ++j) { L.shadow[j] = off; off = align_up(off + (size_t)L.n_pad * L.ldp * 2); }
   if (mode != LV_FP64 && (L.m > 0 || L.general)) {
     const size_t dmat = (size_t)L.n_pad * L.n_pad * sizeof(double);
@@ -175,7 +211,7 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
     for (int j = 0; j < L.m; ++j) {
       const size_t R = (size_t)L.r_pad << j;
       L.partXs[j] = off; off = align_up(off + (size_t)L.nct * L.n_pad * R * L.elem);
-      L.partYs[j] = off; off = align_up(off + (size_t)L.nrt_max * L.n_pad * R * L.elem);
+      L.partYs[j] = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, (int)R, shadow) * L.elem);
       L.partGs[j] = off; off = align_up(off + (size_t)gram_tiles(L.n_pad) * R * R * sizeof(double));
     }
     if (mode != LV_FP64 && (L.m > 0 || L.general)) {
@@ -216,13 +252,13 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
       }
       const size_t xmat = (size_t)L.n_pad * wmax * L.elem;
       L.partXT = off; off = align_up(off + (size_t)L.nct * xmat);
-      L.partYT = off; off = align_up(off + (size_t)L.nrt_max * xmat);
+      L.partYT = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, wmax, shadow) * L.elem);
       L.atbG = off; off = align_up(off + (size_t)(L.n_pad / kAtbRows) * rmax * wmax * sizeof(double));
     } else {
       L.D[0] = off; off = align_up(off + gmat);
       L.D[1] = off; off = align_up(off + gmat);
       L.partXT = off; off = align_up(off + (size_t)L.nct * gmat);
-      L.partYT = off; off = align_up(off + (size_t)L.nrt_max * gmat);
+      L.partYT = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, L.pp, shadow) * L.elem);
     }
     const size_t atb = (size_t)(L.n_pad / kAtbRows) * rmax * L.pp * sizeof(double);
     L.atbA = off; off = align_up(off + atb);
@@ -270,7 +306,10 @@ struct lv_view {
   // batch autotuner or lv_view_set_tile_rows; every path uses the same value,
   // which fixes the reduction order of the partial sums).
   int tile_rows[lv::kMaxLevel];
-  int nrt(int j) const { return (int)((L.n_pad + tile_rows[j] - 1) / tile_rows[j]); }
+  // rows per slice and slices of the level's pass of rank R
+  bool on_cores(int R) const { return shadowed() || lv::skinny_on_mfma(R, L.elem); }
+  int rows(int j, int R) const { return lv::slice_rows(L.n_pad, L.elem, R, on_cores(R), tile_rows[j]); }
+  int nrt(int j, int R) const { return lv::slice_count(L.n_pad, L.elem, R, on_cores(R), tile_rows[j]); }
 
   // Kernel timing (diagnostics): event pairs per launch kind, resolved by
   // lv_view_timing.
