@@ -481,11 +481,16 @@ lv_status gfac_finish(lv_view* v, int ru, const T* sU, hipStream_t s) {
 // for float storage at large level rank and with bfloat16 shadows, the
 // read-only skinny pass, the Gram and the update pass), then the sums' and
 // the general form's level steps.  Stream-ordered on s.
+// nver > 1 (pipelined batches, vector levels): nver successive updates, whose
+// slabs follow sU, sV at the slots' stride, in one pass and one tail.
 template <typename T>
-lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, bool pipelined = false) {
+lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, bool pipelined = false, int nver = 1) {
   const Layout& L = v->L;
   lv_status st = LV_OK;
   const int R = r_pad << j;
+  const int nrt = v->nrt(j, R);
+  const Strides vs = {(int64_t)(L.slot_stride / sizeof(T)), (int64_t)L.nct * L.n_pad * R, (int64_t)nrt * L.n_pad * R,
+                      (int64_t)nrt * R * R};
   // The general form's product with the OLD P_j: P_j D_j (hybrid) or P_j Y_j
   // (factored; at level 0 Y_0 = U_0, so the powers' own X serves).  It
   // rides on the powers' fused pass when the X width allows, like P_j Q_j
@@ -539,8 +544,8 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
         });
       if (st == LV_OK)
         st = timed(v, 1, s, "level tail", [&] {
-          return launch_level_tail<float>(R, v->partX<float>(j), v->partY<float>(j), v->partG(j), L.nct, v->nrt(j, R),
-                                          1, L.n_pad, sU, sV, L.W, s);
+          return launch_level_tail<float>(R, v->partX<float>(j), v->partY<float>(j), v->partG(j), L.nct, nrt, 1,
+                                           L.n_pad, sU, sV, L.W, s);
         });
     }
   }
@@ -554,13 +559,13 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
                                        v->partXs<T>(j), Dop, ldd, d_in_pass ? xd : 0, v->partXT<T>(), s);
       }
       return launch_level_fused<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W, v->partX<T>(j),
-                                   v->partY<T>(j), v->partG(j), s,
-                                   pipelined ? pipe_slice_groups(L.nct, v->nrt(j, R)) : 0);
+                                   v->partY<T>(j), v->partG(j), s, pipelined ? pipe_slice_groups(L.nct, nrt) : 0, nver,
+                                   vs);
     });
     if (st == LV_OK)
       st = timed(v, 1, s, "level tail", [&] {
-        return launch_level_tail<T>(R, v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, v->nrt(j, R),
-                                    gram_in_pass(R, (int)sizeof(T)) ? v->nrt(j, R) : 1, L.n_pad, sU, sV, L.W, s);
+        return launch_level_tail<T>(R, v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, nrt,
+                                    gram_in_pass(R, (int)sizeof(T)) ? nrt : 1, L.n_pad, sU, sV, L.W, s, nver, vs);
       });
   }
   if (st == LV_OK && L.general)
@@ -612,8 +617,15 @@ lv_status update_one(lv_view* v, const T* U, const T* V, int r, int64_t ldu, int
 // them: while a stage works on update t the earlier stages already work on
 // t+1, t+2, ...  Each update in flight holds one of pipe_slots factor-slab
 // pairs; a slab is reused only after the top level of the update that held
-// it has finished.  Every kernel sees exactly the inputs of the sequential
-// order, so the results are bit-identical to it.
+// it has finished.
+//
+// Level j of an update reads P_j and that update's factors only, and level
+// j - 1 does not wait for it: a level can take several updates in turn before
+// the next level sees the first.  Updates therefore go through in chunks of
+// chunk(r_pad), and a vector level's pass takes chain_updates(R) of a chunk at
+// one read and write of P_j (fused_body), the top update the whole chunk.
+// Every sum and rounding is that of the sequential order, so the results
+// are bit-identical to it.
 inline int pipe_stage(const lv_view* v, int j) { return j * v->pipe_nstages / v->L.m; }
 
 lv_status pipe_setup(lv_view* v) {
@@ -660,31 +672,62 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
   st = pipe_fork(v, s);
   if (st != LV_OK) return st;
   const int r_pad = (int)next_pow2(r);
-  const int D = L.pipe_slots;
+  const int Rm = r_pad << L.m;
+  // the slots hold D chunks of C updates
+  const int C = v->chunk(r_pad), D = L.pipe_slots / C;
+  const int64_t sstride = (int64_t)(L.slot_stride / sizeof(T));
   auto stream_of = [&](int j) { const int q = pipe_stage(v, j); return q == 0 ? s : v->pstream[q]; };
   auto ev = [&](hipError_t e, const char* what) { return e == hipSuccess ? LV_OK : fail(LV_EDEVICE, "%s failed", what); };
-  for (int64_t t = 0; t < count && st == LV_OK; ++t) {
-    const int sl = (int)(t % D);
-    T* sU = v->slabU<T>(sl);
-    T* sV = v->slabV<T>(sl);
+  int64_t chunk = 0;
+  for (int64_t t = 0; t < count && st == LV_OK; ++chunk) {
+    // a chunk ends where a drift check is due
+    int64_t n = count - t < C ? count - t : C;
+    if (v->drift_every > 0 && n > v->drift_every - v->updates % v->drift_every)
+      n = v->drift_every - v->updates % v->drift_every;
+    const int cnt = (int)n, slot = (int)(chunk % D) * C;
     const T* Ut = reinterpret_cast<const T*>(U + (size_t)(t * strideU) * sizeof(T));
     const T* Vt = reinterpret_cast<const T*>(V + (size_t)(t * strideV) * sizeof(T));
-    // the slab is free once the top level of update t - D is done with it
-    if (t >= D) st = ev(hipStreamWaitEvent(s, v->pfree[sl], 0), "hipStreamWaitEvent");
-    if (st == LV_OK) st = hip_check(launch_prep<T>(Ut, ldu, Vt, ldv, v->n, r, r_pad, sU, sV, L.W, L.n_pad, s), "prep");
+    // the slots are free once the top level of chunk - D is done with them
+    if (chunk >= D) st = ev(hipStreamWaitEvent(s, v->pfree[slot], 0), "hipStreamWaitEvent");
+    if (st == LV_OK)
+      st = hip_check(launch_prep<T>(Ut, ldu, Vt, ldv, v->n, r, r_pad, v->slabU<T>(slot), v->slabV<T>(slot), L.W, L.n_pad,
+                                    s, cnt, strideU, strideV, sstride),
+                     "prep");
     for (int j = 0; j < L.m && st == LV_OK; ++j) {
       hipStream_t sj = stream_of(j);
-      if (j > 0 && pipe_stage(v, j - 1) != pipe_stage(v, j))
-        st = ev(hipStreamWaitEvent(sj, v->pready[j - 1][sl], 0), "hipStreamWaitEvent");
-      if (st == LV_OK) st = level_step<T>(v, j, r_pad, sU, sV, sj, true);
-      if (st == LV_OK && j + 1 < L.m && pipe_stage(v, j + 1) != pipe_stage(v, j))
-        st = ev(hipEventRecord(v->pready[j][sl], sj), "hipEventRecord");
+      const bool waits = j > 0 && pipe_stage(v, j - 1) != pipe_stage(v, j);
+      const bool tells = j + 1 < L.m && pipe_stage(v, j + 1) != pipe_stage(v, j);
+      const int R = r_pad << j;
+      // groups of the chunk's updates that share the level's pass: halving
+      // with the level's rank, so each lies inside one of the level below
+      const int most = fused_vector_level(R, (int)sizeof(T), v->shadowed()) ? chain_updates(R) : 1;
+      for (int a = 0, g = 0; a < cnt && st == LV_OK; a += g) {
+        for (g = most; g > cnt - a; g /= 2) {}
+        const int last = slot + a + g - 1;
+        // the event of the lower level's group that holds the last update
+        // is recorded on its own last slot
+        if (waits) st = ev(hipStreamWaitEvent(sj, v->pready[j - 1][v->pgroup[j - 1][last]], 0), "hipStreamWaitEvent");
+        if (st == LV_OK)
+          st = level_step<T>(v, j, r_pad, v->slabU<T>(slot + a), v->slabV<T>(slot + a), sj, true, g);
+        for (int q = a; q < a + g; ++q) v->pgroup[j][slot + q] = last;
+        if (st == LV_OK && tells) st = ev(hipEventRecord(v->pready[j][last], sj), "hipEventRecord");
+      }
     }
     hipStream_t st_top = stream_of(L.m - 1);
-    if (st == LV_OK) st = top_step<T>(v, r_pad, sU, sV, st_top);
-    if (st == LV_OK) st = ev(hipEventRecord(v->pfree[sl], st_top), "hipEventRecord");
+    if (cnt > 1 && !v->shadowed() && Rm <= kMaxLevelRank) {
+      // the chunk's top updates in one read and write of P_m
+      if (st == LV_OK)
+        st = hip_check(launch_level_update_chain<T>(Rm, v->P<T>(L.m), L.ldp, L.n_pad, v->slabU<T>(slot),
+                                                    v->slabV<T>(slot), L.W, cnt, sstride, st_top),
+                       "top update");
+    } else {
+      for (int a = 0; a < cnt && st == LV_OK; ++a)
+        st = top_step<T>(v, r_pad, v->slabU<T>(slot + a), v->slabV<T>(slot + a), st_top);
+    }
+    if (st == LV_OK) st = ev(hipEventRecord(v->pfree[slot], st_top), "hipEventRecord");
     if (st != LV_OK) break;
-    v->updates += 1;
+    t += cnt;
+    v->updates += cnt;
     if (v->drift_every > 0 && v->updates % v->drift_every == 0) {
       // the drift check reads every power: all stages join, then fork again
       st = pipe_join(v, s);

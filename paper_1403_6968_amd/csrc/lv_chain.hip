@@ -153,7 +153,7 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
   }
   c.partX = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
   c.partXd = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
-  c.partY = off; off = align_up(off + (size_t)c.n_pad * slice_cols(c.n_pad, c.elem, maxW, false) * c.elem);
+  c.partY = off; off = align_up(off + (size_t)c.n_pad * slice_cols(c.n_pad, c.elem, maxW) * c.elem);
   c.partG = off; off = align_up(off + (size_t)(c.n_pad / kAtbRows) * maxG * sizeof(double));
   if (mode == LV_FP32 && ns > 1)
     for (int i = 0; i < 3; ++i) { c.d64[i] = off; off = align_up(off + (size_t)c.n_pad * c.n_pad * sizeof(double)); }

@@ -26,6 +26,12 @@ template <typename T> __device__ __forceinline__ void st16_nt(T* p, const V16<T>
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4, x), reinterpret_cast<u32x4*>(p));
 }
 
+// base + off bytes; a uniform base and a 32-bit offset per lane make one
+// address register per load instead of two.
+template <typename T> __device__ __forceinline__ const T* at_byte(const T* base, unsigned off) {
+  return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + off);
+}
+
 // x[0 .. N) = p[0 .. N), 16 bytes at a time where the row is long enough (p
 // is then 16-byte aligned: factor slabs have rows of a power of two entries,
 // and a level's columns begin at a multiple of its rank).

@@ -73,18 +73,20 @@ template <int S, typename T> __device__ __forceinline__ T merge_lanes(T a, T b, 
   }
 }
 
-template <int S, int N, typename T> __device__ __forceinline__ T sum_lanes(const T (&x)[N], const int lane) {
-  if constexpr (S == 6) {
-    static_assert(N == 1, "at most 64 sums");
+template <int S, int N, int END = 6, typename T>
+__device__ __forceinline__ T sum_lanes(const T (&x)[N], const int lane) {
+  if constexpr (S == END) {
+    static_assert(N == 1, "too many sums for the steps");
     return x[0];
   } else {
     T y[(N + 1) / 2];
 #pragma unroll
     for (int i = 0; i < (N + 1) / 2; ++i)
       y[i] = merge_lanes<S, T>(x[2 * i], N == 1 ? x[0] : 2 * i + 1 < N ? x[2 * i + 1] : T(0), lane);
-    return sum_lanes<S + 1, (N + 1) / 2, T>(y, lane);
+    return sum_lanes<S + 1, (N + 1) / 2, END, T>(y, lane);
   }
 }
+constexpr int log2c(int n) { return n <= 1 ? 0 : 1 + log2c(n / 2); }
 __device__ __forceinline__ int sum_index(const int lane) { return (int)(__brev((unsigned)lane) >> 26); }
 
 // ---------------------------------------------------------------- fused pass
@@ -110,11 +112,15 @@ __device__ __forceinline__ int sum_index(const int lane) { return (int)(__brev((
 // per block, update t's products are formed from the rows as update t - 1
 // left them in registers.  Every sum and every rounding is the one of TT
 // passes with TT = 1, so the results are the same bit for bit.  Factors and
-// partials of update t lie t * sstride, t * xstride, ... further on.  HBM
+// partials of update t lie t * vs.s, t * vs.x, ... further on.  HBM
 // bounds the pass up to TT R = 8 (6 TT R flops per element against 8 bytes:
-// 0.75 TT R flop/B where the vector units' ridge is 9.8); the registers
-// (12 TT R for the lane's factors and sums) keep TT R <= 8 at two waves per
-// SIMD.
+// 0.75 TT R flop/B where the vector units' ridge is 9.8), the vector units
+// slightly at 16.
+//
+// LF: the lane's factor rows (8 TT R values) do not fit the registers beside
+// its 4 TT R sums of Y: they stay in LDS, staged once per tile (the four waves
+// share the columns), [factor column][lane] so that a wave reads 1 KiB in a
+// row, and are read once per block, up to 4 factor columns at a time.
 //
 // UPD = false gives the read-only variant used for ranks above 16: the
 // skinny products of 16 factor columns at a time (partials written with row
@@ -141,12 +147,17 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
   static_assert(!SP || (UPD && XE == 0 && XD == 0), "the sums pass updates and forms no X");
   static_assert(TT == 1 || (UPD && !SP && XE == 0 && XD == 0), "several updates: the plain pass only");
   static_assert(SP || NX <= 64, "one lane per X sum");
+  constexpr bool LF = !SP && XE == 0 && XD == 0 && (C > 8 || TT > 1);
+  constexpr int CH = R < 4 ? R : 4;             // factor columns read at a time (LF)
   constexpr int YC = C < 4 ? C : 4;             // Y columns exchanged at a time
   constexpr int FB = RB * C;                    // factor entries per block and operand
   constexpr int FN = (FB + 63) / 64;
 
   __shared__ __align__(16) T facs[4][UPD ? 2 : 1][FB];
-  __shared__ __align__(16) T ybuf[4 * TC * YC];
+  // the lanes' factor rows (LF: U, then V), and the exchange of the Y sums
+  constexpr int NF = LF ? (UPD ? 2 : 1) * C * TC : 0;
+  __shared__ __align__(16) T lbuf[NF > 4 * TC * YC ? NF : 4 * TC * YC];
+  T* const ybuf = lbuf;
 
   T* __restrict__ P = d.P;
   const int64_t ldp = d.ldp;
@@ -166,12 +177,14 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
   const int lc = col0 + lane * EPL;
 
   // entry e = (t TT + v) R + c of a block's factor rows (row t, update v,
-  // column c) sits in lane e % 64 of f[e / 64]
-  int64_t foff[FN];
+  // column c) sits in lane e % 64 of f[e / 64]; foff: byte offset of the
+  // lane's entry from the block's first factor row (32 bits: eight slabs of
+  // the largest order and width stay below 2^31 bytes)
+  unsigned foff[FN];
 #pragma unroll
   for (int f = 0; f < FN; ++f) {
     const int e = lane + 64 * f < FB ? lane + 64 * f : 0;
-    foff[f] = (TT > 1 ? (e / R % TT) * d.sstride : 0) + (int64_t)(e / C) * W + e % R;
+    foff[f] = (unsigned)(((TT > 1 ? (e / R % TT) * d.vs.s : 0) + (int64_t)(e / C) * W + e % R) * sizeof(T));
   }
   V16<T> p[RB], pn[RB];
   T fy[FN], fu[UPD ? FN : 1], fyn[FN], fun[UPD ? FN : 1];
@@ -180,32 +193,47 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     for (int t = 0; t < RB; ++t) pp[t] = ld16_nt(P + (r0 + t) * ldp + lc);
 #pragma unroll
     for (int f = 0; f < FN; ++f) {
-      y[f] = Yop[r0 * W + foff[f]];
-      if constexpr (UPD) u[f] = Uj[r0 * W + foff[f]];
+      y[f] = *at_byte(Yop + r0 * W, foff[f]);
+      if constexpr (UPD) u[f] = *at_byte(Uj + r0 * W, foff[f]);
     }
   };
   if (wave < nblocks) load_block(p, fy, fu, blk_row(wave));
 
   // the lane's factor rows
-  T ucol[TT][EPL][XR], vcol[TT][EPL][UPD ? R : 1], yacc[TT][EPL][R];
+  T ucol[LF ? 1 : TT][EPL][XR], vcol[LF ? 1 : TT][EPL][UPD ? R : 1], yacc[TT][EPL][R];
+  if constexpr (LF) {
+    constexpr int OPS = UPD ? 2 : 1;
+#pragma unroll
+    for (int i = 0; i < (OPS * TT * TC + 255) / 256; ++i) {
+      const int idx = tid + 256 * i, col = idx % TC, v = idx / TC % TT, op = idx / (TC * TT);
+      if (OPS * TT * TC % 256 != 0 && idx >= OPS * TT * TC) continue;
+      const unsigned g = (unsigned)((col0 + col) * W * (int)sizeof(T));
+      T f[R];
+      load_row<T, R>(at_byte((op ? Vj : Uj) + v * d.vs.s, g), f);
+#pragma unroll
+      for (int c = 0; c < R; ++c) lbuf[(op * C + v * R + c) * TC + col] = f[c];
+    }
+    __syncthreads();
+  }
 #pragma unroll
   for (int v = 0; v < TT; ++v)
 #pragma unroll
     for (int q = 0; q < EPL; ++q) {
-      const int64_t g = (int64_t)(lc + q) * W + v * d.sstride;
-      load_row<T, UPD ? R : 0>(Vj + g, vcol[v][q]);
+#pragma unroll
+      for (int c = 0; c < R; ++c) yacc[v][q][c] = T(0);
+      if constexpr (LF) continue;
+      const unsigned g = (unsigned)((lc + q) * W * (int)sizeof(T));
+      load_row<T, UPD ? R : 0>(at_byte(Vj + v * d.vs.s, g), vcol[v][q]);
       if constexpr (!SP) {
         T u[R];
-        load_row<T, R>(Uj + g, u);
+        load_row<T, R>(at_byte(Uj + v * d.vs.s, g), u);
 #pragma unroll
         for (int c = 0; c < R; ++c) ucol[v][q][c] = u[c];
 #pragma unroll
-        for (int c = 0; c < XE; ++c) ucol[v][q][R + c] = d.Ux[g + c];
+        for (int c = 0; c < XE; ++c) ucol[v][q][R + c] = at_byte(d.Ux, g)[c];
 #pragma unroll
         for (int c = 0; c < XD; ++c) ucol[v][q][R + XE + c] = d.Ud[(int64_t)(lc + q) * d.Wd + c];
       }
-#pragma unroll
-      for (int c = 0; c < R; ++c) yacc[v][q][c] = T(0);
     }
 
   // where the lane's X sum of a block goes: sum i = (t TT + v) XR + c
@@ -216,7 +244,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     const int t = i / (TT * XR), v = i / XR % TT, c = i % XR;
     const int64_t row = (int64_t)ct * n_pad + t;
     if (i < NX) {
-      if (c < R) { xs = pR; xdst = d.partX + v * d.xstride + row * pR + c; }
+      if (c < R) { xs = pR; xdst = d.partX + v * d.vs.x + row * pR + c; }
       if constexpr (XE > 0)
         if (c >= R && c < R + XE) { xs = XE; xdst = d.partX2 + row * XE + c - R; }
       if constexpr (XD > 0)
@@ -240,9 +268,79 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-    T x[SP ? 1 : NX];
+    if constexpr (LF) {
+      // (re-read in every block: held in registers across blocks, as the
+      // compiler would otherwise do, they spill)
+      asm volatile("" ::: "memory");
+      const T* lu = lbuf + lane * EPL;
+      T xs1[RB * TT];   // sums over the lanes of the steps that R columns take
 #pragma unroll
-    for (int t = 0; t < RB; ++t) {
+      for (int v = 0; v < TT; ++v) {
+        T s[RB][EPL], xc[RB][R / CH];
+#pragma unroll
+        for (int c0 = 0; c0 < R; c0 += CH) {
+          V16<T> uc[CH], vc[UPD ? CH : 1];
+#pragma unroll
+          for (int c = 0; c < CH; ++c) {
+            uc[c] = ld16(lu + (v * R + c0 + c) * TC);
+            if constexpr (UPD) vc[c] = ld16(lu + (C + v * R + c0 + c) * TC);
+          }
+#pragma unroll
+          for (int t = 0; t < RB; ++t) {
+            T vi[CH], x[CH];
+            load_row<T, CH>(fac_y + (t * TT + v) * R + c0, vi);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+#pragma unroll
+              for (int q = 0; q < EPL; ++q) yacc[v][q][c0 + c] = fma(p[t].v[q], vi[c], yacc[v][q][c0 + c]);
+              x[c] = p[t].v[0] * uc[c].v[0];
+#pragma unroll
+              for (int q = 1; q < EPL; ++q) x[c] = fma(p[t].v[q], uc[c].v[q], x[c]);
+            }
+            xc[t][c0 / CH] = sum_lanes<0, CH, log2c(CH), T>(x, lane);
+            if constexpr (UPD) {
+              T ui[CH];
+              load_row<T, CH>(fac_u + (t * TT + v) * R + c0, ui);
+#pragma unroll
+              for (int q = 0; q < EPL; ++q) {
+                if constexpr (R == 1) {
+                  s[t][q] = fma(ui[0], vc[0].v[q], p[t].v[q]);
+                } else {
+                  s[t][q] = c0 == 0 ? ui[0] * vc[0].v[q] : fma(ui[0], vc[0].v[q], s[t][q]);
+#pragma unroll
+                  for (int c = 1; c < CH; ++c) s[t][q] = fma(ui[c], vc[c].v[q], s[t][q]);
+                }
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int t = 0; t < RB; ++t) {
+          xs1[t * TT + v] = sum_lanes<log2c(CH), R / CH, log2c(R), T>(xc[t], lane);
+          if constexpr (UPD) {
+#pragma unroll
+            for (int q = 0; q < EPL; ++q) p[t].v[q] = R == 1 ? s[t][q] : p[t].v[q] + s[t][q];
+          }
+        }
+        // Y's sums are due here: the compiler would otherwise form them at the
+        // block's end and keep (spill) every update's rows until then
+        if constexpr (TT > 1) {
+#pragma unroll
+          for (int q = 0; q < EPL; ++q)
+#pragma unroll
+            for (int c = 0; c < R; ++c) asm volatile("" : "+v"(yacc[v][q][c]));
+        }
+      }
+      if constexpr (UPD) {
+#pragma unroll
+        for (int t = 0; t < RB; ++t) st16_nt(P + (r0 + t) * ldp + lc, p[t]);
+      }
+      const T s = sum_lanes<log2c(R), RB * TT, 6, T>(xs1, lane);
+      if (xs != 0) xdst[r0 * xs] = s;
+    }
+    T x[SP || LF ? 1 : NX];
+#pragma unroll
+    for (int t = 0; t < (LF ? 0 : RB); ++t) {
 #pragma unroll
       for (int v = 0; v < TT; ++v) {
         T vi[R];
@@ -278,8 +376,8 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
       }
       if constexpr (UPD) st16_nt(P + (r0 + t) * ldp + lc, p[t]);
     }
-    if constexpr (!SP) {
-      const T s = sum_lanes<0, NX, T>(x, lane);
+    if constexpr (!SP && !LF) {
+      const T s = sum_lanes<0, NX, 6, T>(x, lane);
       if (xs != 0) xdst[r0 * xs] = s;
     }
 #pragma unroll
@@ -311,7 +409,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
       const T s = ((ybuf[(0 * TC + cc) * YC + c] + ybuf[(1 * TC + cc) * YC + c]) +
                    ybuf[(2 * TC + cc) * YC + c]) + ybuf[(3 * TC + cc) * YC + c];
       const int v = (c0 + c) / R;
-      d.partY[v * d.ystride + ((int64_t)rt * n_pad + col0 + cc) * pR + (c0 + c) % R] = s;
+      d.partY[v * d.vs.y + ((int64_t)rt * n_pad + col0 + cc) * pR + (c0 + c) % R] = s;
     }
   }
 
@@ -327,8 +425,8 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     const int g0 = tid % 32;
     for (int pair = ct + nct * (tid / 32); pair < TT * NP; pair += 8 * nct) {
       const int v = pair / NP, ab = pair % NP;
-      const T* vp = Vj + v * d.sstride + ab / R;
-      const T* up = Uj + v * d.sstride + ab % R;
+      const T* vp = Vj + v * d.vs.s + ab / R;
+      const T* up = Uj + v * d.vs.s + ab % R;
       double g = 0.0;
 #pragma unroll 4
       for (int q = g0; q < nsr; q += 32) {
@@ -337,13 +435,17 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
       }
 #pragma unroll
       for (int off = 16; off > 0; off >>= 1) g += __shfl_xor(g, off, 32);
-      if (g0 == 0) d.partG[v * d.gstride + (int64_t)rt * NP + ab] = g;
+      if (g0 == 0) d.partG[v * d.vs.g + (int64_t)rt * NP + ab] = g;
     }
   }
 }
 
+// Two waves per SIMD for the widest passes over several updates, which would
+// otherwise take a few registers more than that leaves.
+template <int R, int TT> constexpr int fused_min_waves() { return TT > 1 ? 2 : 1; }
+
 template <typename T, int R, int TT, bool UPD>
-__global__ void __launch_bounds__(256) k_level_fused(const FusedDesc<T> d) {
+__global__ void __launch_bounds__(256, (fused_min_waves<R, TT>())) k_level_fused(const FusedDesc<T> d) {
   fused_body<T, R, TT, UPD>(d, blockIdx.x, blockIdx.y);
 }
 
@@ -384,7 +486,7 @@ __global__ void __launch_bounds__(256) k_level_fused_multi(const FusedDesc<T>* _
 template <typename T, int R, int TT, bool UPD>
 hipError_t fused_launch(const FusedDesc<T>& d, hipStream_t s, int slice_groups = 0) {
   const int ns = (d.n_pad + d.tile_rows - 1) / d.tile_rows;
-  if constexpr (UPD && R <= 8) {
+  if constexpr (UPD && R <= 8 && TT == 1) {
     if (slice_groups > 0 && slice_groups < ns) {
       hipLaunchKernelGGL((k_level_fused_grouped<T, R, TT, UPD>), dim3((unsigned)d.nct, (unsigned)slice_groups),
                          dim3(256), 0, s, d);
@@ -395,14 +497,23 @@ hipError_t fused_launch(const FusedDesc<T>& d, hipStream_t s, int slice_groups =
   return hipGetLastError();
 }
 
+// The fused pass over nver updates (1, 2, 4, ..., up to chain_updates(R)).
+template <typename T, int R, int TT>
+hipError_t fused_chain(const FusedDesc<T>& d, hipStream_t s, int slice_groups, int nver) {
+  if (nver == TT) return fused_launch<T, R, TT, true>(d, s, slice_groups);
+  if constexpr (2 * TT <= chain_updates(R)) return fused_chain<T, R, 2 * TT>(d, s, slice_groups, nver);
+  return hipErrorInvalidValue;
+}
+
 // One level with rank R: for R <= 16 the fused pass; above, the skinny
 // products in 16-column chunks (read-only passes), the Gram, then the rank-R
 // update pass.
 template <typename T, int R>
-hipError_t fused_r(const FusedDesc<T>& d, hipStream_t s, int slice_groups) {
+hipError_t fused_r(const FusedDesc<T>& d, hipStream_t s, int slice_groups, int nver) {
   if constexpr (R <= kMaxFusedRank) {
-    return fused_launch<T, R, 1, true>(d, s, slice_groups);
+    return fused_chain<T, R, 1>(d, s, slice_groups, nver);
   } else {
+    if (nver != 1) return hipErrorInvalidValue;
     constexpr int RC = kMaxFusedRank;
     for (int c0 = 0; c0 < R; c0 += RC) {
       FusedDesc<T> c = d;
@@ -432,9 +543,10 @@ FusedDesc<T> fused_desc(int R, T* P, int64_t ldp, int64_t n_pad, int tile_rows, 
 template <typename T>
 hipError_t launch_level_fused(int R, T* P, int64_t ldp, int64_t n_pad, int tile_rows,
                               const T* slabU, const T* slabV, int W, T* partX, T* partY,
-                              double* partG, hipStream_t s, int slice_groups) {
-  const FusedDesc<T> d = fused_desc<T>(R, P, ldp, n_pad, tile_rows, slabU, slabV + (W - R), W, partX, partY, partG);
-  LV_RANK_SWITCH(R, return (fused_r<T, RR>(d, s, slice_groups)))
+                              double* partG, hipStream_t s, int slice_groups, int nver, const Strides& vs) {
+  FusedDesc<T> d = fused_desc<T>(R, P, ldp, n_pad, tile_rows, slabU, slabV + (W - R), W, partX, partY, partG);
+  d.vs = vs;
+  LV_RANK_SWITCH(R, return (fused_r<T, RR>(d, s, slice_groups, nver)))
 }
 
 // Launch k_level_fused_x for level rank R with XE (0 or R) and xd (0, 1, 2,
@@ -553,9 +665,9 @@ template hipError_t launch_level_readonly<double>(int, const double*, int64_t, i
                                                   const double*, int, double*, double*, hipStream_t);
 
 template hipError_t launch_level_fused<float>(int, float*, int64_t, int64_t, int, const float*, const float*, int,
-                                              float*, float*, double*, hipStream_t, int);
+                                              float*, float*, double*, hipStream_t, int, int, const Strides&);
 template hipError_t launch_level_fused<double>(int, double*, int64_t, int64_t, int, const double*, const double*,
-                                               int, double*, double*, double*, hipStream_t, int);
+                                               int, double*, double*, double*, hipStream_t, int, int, const Strides&);
 template hipError_t launch_level_fused_x<float>(int, float*, int64_t, int64_t, int, const float*, const float*, int,
                                                 float*, float*, double*, const float*, float*, const float*, int, int,
                                                 float*, hipStream_t);

@@ -105,7 +105,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.sU = take(np * g.r_pad * e);
   g.sV = take(np * g.r_pad * e);
   g.partX = take((size_t)g.nct * np * xw * e);
-  g.partY = take(np * slice_cols(g.n_pad, g.elem, xw, false) * e);
+  g.partY = take(np * slice_cols(g.n_pad, g.elem, xw) * e);
   g.atbA = take((np / kAtbRows) * g.r_pad * pp * sizeof(double));
   g.D[0] = g.D[1] = g.full = g.atbG = g.Yb = g.Zb = 0;
   if (strategy == LV_GLIN_HYBRID) { g.D[0] = take(np * pp * e); g.D[1] = take(np * pp * e); }

@@ -26,7 +26,16 @@ constexpr int kMaxLevel = 10;
 // Pipelined batches: at most this many stage streams and factor-slab slots
 // (updates in flight).
 constexpr int kPipeStreams = 4;
-constexpr int kMaxPipeSlots = 5;
+constexpr int kMaxPipeSlots = 24;
+// Updates of a batch whose rank is r_pad that go through the levels together
+// (a chunk; a level's pass takes up to chain_updates(R) of them at one read
+// and write of P), and the chunks in flight.
+constexpr int kChainCols = 16;     // factor columns of a pass over several updates
+constexpr int kChainUpdates = 8;
+constexpr int kPipeChunks = 3;
+constexpr int chain_updates(int R) {
+  return R >= kChainCols ? 1 : kChainCols / R < kChainUpdates ? kChainCols / R : kChainUpdates;
+}
 // Work-groups a fused level pass is cut into inside a pipelined batch: one
 // per compute unit (the device has 256), so that the passes of two stages
 // share every unit instead of one pass filling the device with two
@@ -55,6 +64,10 @@ inline int tile_cols_bytes(int elem) { return 64 * (16 / elem); }
 // by block_begin (the first work-group of each view) and the work-group
 // finds its view by binary search.
 
+// Several updates in one launch: elements from one update's factor slabs and
+// partials to the next one's (s: both slabs; x, y, g: partial X, Y and Gram).
+struct Strides { int64_t s = 0, x = 0, y = 0, g = 0; };
+
 template <typename T> struct FusedDesc {
   T* P; int64_t ldp; int n_pad; int tile_rows;
   const T* Uj; const T* Vj; int W;      // U_j = Uj[i*W + c], V_j = Vj[i*W + c]
@@ -65,9 +78,7 @@ template <typename T> struct FusedDesc {
   const T* Vy = nullptr;                // Y operand of the sums pass
   const T* Ud = nullptr; int Wd = 0;    // general form: extra X operand (row stride Wd)
   T* partX3 = nullptr;                  //   and its partials
-  // several updates in one pass: from one update's factors and partials to
-  // the next one's (elements)
-  int64_t sstride = 0, xstride = 0, ystride = 0, gstride = 0;
+  Strides vs = {};                      // several updates in one pass
 };
 template <typename T> struct GramDesc {
   const T* Uj; const T* Vj; int W; int n_pad; int tile_rows; double* partG;
@@ -77,6 +88,7 @@ template <typename T> struct TailDesc {
   const T* partX; const T* partY; const double* partG; int nct; int nrt; int n_pad;
   T* slabU; T* slabV; int W; int block_begin;   // blocks: ceil(n_pad * R / 256)
   int ng;                                       // Gram partials to add (1: already summed)
+  Strides vs = {};                              // update blockIdx.y (single-view launches)
 };
 // Sum of ng Gram partials (count doubles each) into the first.
 struct GramSumDesc {
@@ -86,6 +98,7 @@ template <typename T> struct UpdateDesc {
   T* P; int64_t ldp; int n_pad; int tile_rows; const T* Uj; const T* Vj; int W;
   int nct; int block_begin;             // blocks: nct x ceil(n_pad / tile_rows)
   uint16_t* S;                          // bfloat16 shadow of P rewritten by the pass, or null
+  int nver = 1; int64_t sstride = 0;    // updates applied in turn, slab to slab (elements)
 };
 // Products a read-only skinny pass forms.
 constexpr int kWantX = 1, kWantY = 2;
@@ -102,6 +115,7 @@ struct SkinnyDesc {
 template <typename T> struct PrepDesc {
   const T* U; int64_t ldu; const T* V; int64_t ldv; int64_t n; int r; int r_pad;
   T* slabU; T* slabV; int W; int64_t n_pad; int block_begin;   // blocks: ceil(n_pad * r_pad / 256)
+  int64_t strideU = 0, strideV = 0, sstride = 0;               // update blockIdx.y (single-view launches)
 };
 
 // Descriptor v of a multi-view launch, read through the constant address
@@ -229,27 +243,32 @@ hipError_t launch_copy_pad(const Tin* src, int64_t lds, int64_t n, Tout* dst, in
 
 // Factor slab set-up: slab U columns [0, r_pad) and slab V columns
 // [W - r_pad, W) receive U and V (n x r), zero-filled up to r_pad columns and
-// n_pad rows.
+// n_pad rows.  nver > 1: that many updates, strideU / strideV apart in U and V
+// and sstride apart in the slabs.
 template <typename T>
 hipError_t launch_prep(const T* U, int64_t ldu, const T* V, int64_t ldv, int64_t n, int r,
-                       int r_pad, T* slabU, T* slabV, int W, int64_t n_pad, hipStream_t s);
+                       int r_pad, T* slabU, T* slabV, int W, int64_t n_pad, hipStream_t s, int nver = 1,
+                       int64_t strideU = 0, int64_t strideV = 0, int64_t sstride = 0);
 
 // Fused level pass for level rank R: partial X = P U_j, partial Y = P^T V_j,
 // partial Gram V_j^T U_j (column tile 0 only), and P += U_j V_j^T, in one
 // read and one write of P.  slice_groups > 0: that many work-groups per
 // column tile, each taking several row slices in turn (same partials, bit
-// for bit; see pipe_slice_groups).
+// for bit; see pipe_slice_groups).  nver > 1 (a power of two up to
+// chain_updates(R)): nver successive updates in the one read and write, the
+// same results as nver launches.
 template <typename T>
 hipError_t launch_level_fused(int R, T* P, int64_t ldp, int64_t n_pad, int tile_rows,
                               const T* slabU, const T* slabV, int W, T* partX, T* partY,
-                              double* partG, hipStream_t s, int slice_groups = 0);
+                              double* partG, hipStream_t s, int slice_groups = 0, int nver = 1,
+                              const Strides& vs = {});
 
 // Tail of level j: reduce partials in a fixed order, G = sum of the ng
 // partial Grams, U_{j+1} = [U_j, X + U_j G], V_{j+1} = [Y, V_j].
 template <typename T>
 hipError_t launch_level_tail(int R, const T* partX, const T* partY, const double* partG,
                              int nct, int nrt, int ng, int64_t n_pad, T* slabU, T* slabV, int W,
-                             hipStream_t s);
+                             hipStream_t s, int nver = 1, const Strides& vs = {});
 
 // Update-only pass: P += U_j V_j^T for rank R (the top stored power).  With a
 // non-null shadow S (float only) the pass also writes S = bf16(P) of the new
@@ -259,6 +278,13 @@ template <typename T>
 hipError_t launch_level_update(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU,
                                const T* slabV, int W, hipStream_t s, uint16_t* S = nullptr,
                                bool split = false);
+
+// P += U_t V_t^T for nver successive updates (rank R >= 4, slabs sstride
+// apart) in one read and one write of P, each delta formed from zero and added
+// once: the results of nver launch_level_update calls bit for bit.
+template <typename T>
+hipError_t launch_level_update_chain(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU, const T* slabV, int W,
+                                     int nver, int64_t sstride, hipStream_t s);
 
 // Gram V_j^T U_j in double: gram_tiles(n_pad) partials of kGramRows rows,
 // then their sum in fixed order into partG[0 .. R*R).

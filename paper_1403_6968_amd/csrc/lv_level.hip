@@ -267,7 +267,9 @@ __device__ __forceinline__ void tail_body(const T* __restrict__ partX, const T* 
 
 template <typename T, int R>
 __global__ void __launch_bounds__(256) k_level_tail(const TailDesc<T> d) {
-  tail_body<T, R>(d.partX, d.partY, d.partG, d.nct, d.nrt, d.ng, d.n_pad, d.slabU, d.slabV, d.W, blockIdx.x);
+  const int64_t v = blockIdx.y;
+  tail_body<T, R>(d.partX + v * d.vs.x, d.partY + v * d.vs.y, d.partG + v * d.vs.g, d.nct, d.nrt, d.ng, d.n_pad,
+                  d.slabU + v * d.vs.s, d.slabV + v * d.vs.s, d.W, blockIdx.x);
 }
 
 template <typename T, int R>
@@ -475,22 +477,32 @@ __device__ __forceinline__ void update_body(T* __restrict__ P, const int64_t ldp
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// P += U_j V_j^T on the matrix cores for float storage and R >= 32
-// (v_mfma_f32_32x32x2f32: float products, float accumulation).  Tile
-// 128 x 128; wave (wm, wn) owns the 64 x 64 quarter as 2 x 2 blocks of
-// 32 x 32.  The tile's factor rows pass through LDS 32 columns at a time.
-// In the four steps of a column group, lanes 0-31 supply column c0 + e and
-// lanes 32-63 column c0 + 4 + e (e = 0..3) for both U and V, so every
-// column of the sum is taken once.  The delta is accumulated from zero and
-// added to the old values (requested before the products) once.
+// P += U_j V_j^T on the matrix cores for float storage: ranks from 32, and
+// runs of successive updates at any rank from 4 (v_mfma_f32_32x32x2f32: float
+// products, float accumulation).  Tile 128 x 128; wave (wm, wn) owns the
+// 64 x 64 quarter as 2 x 2 blocks of 32 x 32.  The tile's factor rows pass
+// through LDS up to 32 columns at a time, the even columns of each group of 8
+// before the odd ones: step e of a group takes columns 2 e (lanes 0-31) and
+// 2 e + 1 (lanes 32-63), and the instruction adds the two products one after
+// the other with one rounding each, so the delta is the chain of fused
+// multiply-adds over the columns in order that the vector kernel forms, bit
+// for bit.  It is accumulated from zero and added to the old values
+// (requested before the products) once.  nver > 1: the updates of successive
+// slabs (sstride apart) one after the other, P read and written once; up to
+// 16 columns the next slab's factors are requested before the products.
 // Accumulator element v of lane l is row 8 (v / 4) + 4 (l / 32) + v % 4,
 // column l % 32 of its block.
 template <int R, bool SH>
 __device__ __forceinline__ void update_mfma_body(float* __restrict__ P, const int64_t ldp,
                                                  const float* __restrict__ Uj, const float* __restrict__ Vj,
-                                                 const int W, uint16_t* __restrict__ S, const int ct, const int rt) {
-  constexpr int TT = kMfmaUpdateTile, KC = 32, KP = KC + 4;
-  static_assert(R % KC == 0, "rank must be a multiple of 32");
+                                                 const int W, uint16_t* __restrict__ S, const int ct, const int rt,
+                                                 const int nver = 1, const int64_t sstride = 0) {
+  constexpr int TT = kMfmaUpdateTile, KC = R < 32 ? R : 32, KP = KC + 4;
+  constexpr int G = KC < 8 ? KC : 8;         // columns of a group
+  constexpr int F4 = KC / 4;                 // 16-byte pieces of a staged row
+  constexpr int NQ = (TT * F4 + 255) / 256;  // pieces per thread
+  constexpr bool AHEAD = KC <= 16;
+  static_assert(R % KC == 0 && KC % 4 == 0, "rank must be 4, 8, 16 or a multiple of 32");
   __shared__ __align__(16) float sU[TT][KP];
   __shared__ __align__(16) float sV[TT][KP];
   const int tid = threadIdx.x;
@@ -509,41 +521,84 @@ __device__ __forceinline__ void update_mfma_body(float* __restrict__ P, const in
       for (int v = 0; v < 16; ++v)
         p[a][b][v] = __builtin_nontemporal_load(&P[(int64_t)(row0 + wm * 64 + a * 32 + 8 * (v / 4) + 4 * lh +
                                                          (v % 4)) * ldp + col0 + wn * 64 + b * 32 + l32]);
-  v16f acc[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-  for (int kc = 0; kc < R; kc += KC) {
-    __syncthreads();
+  float4 nu[AHEAD ? NQ : 1], nw[AHEAD ? NQ : 1];
+  auto piece = [&](const int i, int& r, int& c4) {
+    const int q = tid + 256 * i;
+    r = q / F4;
+    c4 = q % F4 * 4;
+    return TT * F4 % 256 == 0 || q < TT * F4;
+  };
+  auto fetch = [&](const float* u, const float* w) {
 #pragma unroll
-    for (int i = 0; i < TT * KC / 4 / 256; ++i) {
-      const int q = tid + 256 * i;
-      const int r = q >> 3, c4 = (q & 7) * 4;
-      *reinterpret_cast<float4*>(&sU[r][c4]) = *reinterpret_cast<const float4*>(Uj + (int64_t)(row0 + r) * W + kc + c4);
-      *reinterpret_cast<float4*>(&sV[r][c4]) = *reinterpret_cast<const float4*>(Vj + (int64_t)(col0 + r) * W + kc + c4);
+    for (int i = 0; i < NQ; ++i) {
+      int r, c4;
+      if (piece(i, r, c4)) {
+        nu[i] = *reinterpret_cast<const float4*>(u + (int64_t)(row0 + r) * W + c4);
+        nw[i] = *reinterpret_cast<const float4*>(w + (int64_t)(col0 + r) * W + c4);
+      }
     }
-    __syncthreads();
+  };
+  // columns c4 .. c4 + 3 of a staged row: even ones first within the group
+  auto put = [&](float (&dst)[KP], const int c4, const float4 x) {
+    const int at = c4 / G * G + c4 % G / 2;
+    *reinterpret_cast<float2*>(&dst[at]) = make_float2(x.x, x.z);
+    *reinterpret_cast<float2*>(&dst[at + G / 2]) = make_float2(x.y, x.w);
+  };
+  if constexpr (AHEAD) fetch(Uj, Vj);
+
+  for (int ver = 0; ver < nver; ++ver, Uj += sstride, Vj += sstride) {
+    v16f acc[2][2];
 #pragma unroll
-    for (int c0 = 0; c0 < KC; c0 += 8) {
-      float4 ua[2], vb[2];
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int a = 0; a < 2; ++a) ua[a] = *reinterpret_cast<const float4*>(&sU[wm * 64 + a * 32 + l32][c0 + 4 * lh]);
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) vb[b] = *reinterpret_cast<const float4*>(&sV[wn * 64 + b * 32 + l32][c0 + 4 * lh]);
+        for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+
+    for (int kc = 0; kc < R; kc += KC) {
+      __syncthreads();
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[a].x, vb[b].x, acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[a].y, vb[b].y, acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[a].z, vb[b].z, acc[a][b], 0, 0, 0);
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[a].w, vb[b].w, acc[a][b], 0, 0, 0);
+      for (int i = 0; i < NQ; ++i) {
+        int r, c4;
+        if (piece(i, r, c4)) {
+          if constexpr (AHEAD) {
+            put(sU[r], c4, nu[i]);
+            put(sV[r], c4, nw[i]);
+          } else {
+            put(sU[r], c4, *reinterpret_cast<const float4*>(Uj + (int64_t)(row0 + r) * W + kc + c4));
+            put(sV[r], c4, *reinterpret_cast<const float4*>(Vj + (int64_t)(col0 + r) * W + kc + c4));
+          }
         }
+      }
+      __syncthreads();
+      if constexpr (AHEAD)
+        if (ver + 1 < nver) fetch(Uj + sstride, Vj + sstride);
+#pragma unroll
+      for (int c0 = 0; c0 < KC; c0 += G) {
+        float ua[2][G / 2], vb[2][G / 2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int e = 0; e < G / 2; ++e) {
+            ua[a][e] = sU[wm * 64 + a * 32 + l32][c0 + G / 2 * lh + e];
+            vb[a][e] = sV[wn * 64 + a * 32 + l32][c0 + G / 2 * lh + e];
+          }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < G / 2; ++e)
+              acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(ua[a][e], vb[b][e], acc[a][b], 0, 0, 0);
+      }
     }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) p[a][b][v] += acc[a][b][v];
   }
 
 #pragma unroll
@@ -554,10 +609,121 @@ __device__ __forceinline__ void update_mfma_body(float* __restrict__ P, const in
       for (int v = 0; v < 16; ++v) {
         const int64_t o = (int64_t)(row0 + wm * 64 + a * 32 + 8 * (v / 4) + 4 * lh + (v % 4)) * ldp + col0 +
                           wn * 64 + b * 32 + l32;
-        const float x = p[a][b][v] + acc[a][b][v];
-        __builtin_nontemporal_store(x, &P[o]);
-        if constexpr (SH) S[o] = bf16_rne(x);
+        __builtin_nontemporal_store(p[a][b][v], &P[o]);
+        if constexpr (SH) S[o] = bf16_rne(p[a][b][v]);
       }
+}
+
+// The same for runs of successive updates in double storage, any rank from 4
+// (v_mfma_f64_16x16x4f64, whose four products are added in index order with
+// one rounding each: the vector kernel's chain bit for bit).  Tile 64 x 64;
+// wave (wm, wn) owns 32 x 32 of it as 2 x 2 blocks of 16 x 16.
+// 16x16x4 layouts: A: lane l holds A[l % 16][l / 16]; B: B[l / 16][l % 16];
+// C: element v of lane l is C[4 v + l / 16][l % 16].
+constexpr int kF64UpdateRows = 64, kF64UpdateCols = 64;
+typedef double v4d __attribute__((ext_vector_type(4)));
+template <int R>
+__device__ __forceinline__ void update_f64_body(double* __restrict__ P, const int64_t ldp,
+                                                const double* __restrict__ Uj, const double* __restrict__ Vj,
+                                                const int W, const int ct, const int rt, const int nver,
+                                                const int64_t sstride) {
+  constexpr int KC = R < 16 ? R : 16, KP = KC + 2, F2 = KC / 2;
+  constexpr int NU = (kF64UpdateRows * F2 + 255) / 256, NV = (kF64UpdateCols * F2 + 255) / 256;
+  static_assert(R % KC == 0 && KC % 4 == 0, "rank must be 4, 8 or a multiple of 16");
+  __shared__ __align__(16) double sU[kF64UpdateRows][KP];
+  __shared__ __align__(16) double sV[kF64UpdateCols][KP];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = wave_id();
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int row0 = rt * kF64UpdateRows, col0 = ct * kF64UpdateCols;
+  double* Pw = P + (int64_t)(row0 + wm * 32 + lq) * ldp + col0 + wn * 32 + l16;
+
+  double p[2][2][4];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) p[a][b][v] = __builtin_nontemporal_load(Pw + (int64_t)(a * 16 + 4 * v) * ldp + b * 16);
+
+  double2 nu[NU], nw[NV];
+  auto fetch = [&](const double* u, const double* w) {
+#pragma unroll
+    for (int i = 0; i < NU; ++i) {
+      const int q = tid + 256 * i;
+      if (kF64UpdateRows * F2 % 256 == 0 || q < kF64UpdateRows * F2)
+        nu[i] = *reinterpret_cast<const double2*>(u + (int64_t)(row0 + q / F2) * W + q % F2 * 2);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int q = tid + 256 * i;
+      if (kF64UpdateCols * F2 % 256 == 0 || q < kF64UpdateCols * F2)
+        nw[i] = *reinterpret_cast<const double2*>(w + (int64_t)(col0 + q / F2) * W + q % F2 * 2);
+    }
+  };
+  fetch(Uj, Vj);
+  for (int ver = 0; ver < nver; ++ver) {
+    v4d acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
+    for (int kc = 0; kc < R; kc += KC) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NU; ++i) {
+        const int q = tid + 256 * i;
+        if (kF64UpdateRows * F2 % 256 == 0 || q < kF64UpdateRows * F2)
+          *reinterpret_cast<double2*>(&sU[q / F2][q % F2 * 2]) = nu[i];
+      }
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int q = tid + 256 * i;
+        if (kF64UpdateCols * F2 % 256 == 0 || q < kF64UpdateCols * F2)
+          *reinterpret_cast<double2*>(&sV[q / F2][q % F2 * 2]) = nw[i];
+      }
+      __syncthreads();
+      if (kc + KC < R) fetch(Uj + ver * sstride + kc + KC, Vj + ver * sstride + kc + KC);
+      else if (ver + 1 < nver) fetch(Uj + (ver + 1) * sstride, Vj + (ver + 1) * sstride);
+#pragma unroll
+      for (int c0 = 0; c0 < KC; c0 += 4) {
+        double ua[2], vb[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) ua[a] = sU[wm * 32 + a * 16 + l16][c0 + lq];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) vb[b] = sV[wn * 32 + b * 16 + l16][c0 + lq];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(ua[a], vb[b], acc[a][b], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) p[a][b][v] += acc[a][b][v];
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) __builtin_nontemporal_store(p[a][b][v], Pw + (int64_t)(a * 16 + 4 * v) * ldp + b * 16);
+}
+
+template <typename T, int R>
+__global__ void __launch_bounds__(256, 2) k_level_update_chain(const UpdateDesc<T> d) {
+  if constexpr (sizeof(T) == 4)
+    update_mfma_body<R, false>(d.P, d.ldp, d.Uj, d.Vj, d.W, nullptr, blockIdx.x, blockIdx.y, d.nver, d.sstride);
+  else
+    update_f64_body<R>(d.P, d.ldp, d.Uj, d.Vj, d.W, blockIdx.x, blockIdx.y, d.nver, d.sstride);
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -747,7 +913,9 @@ __device__ __forceinline__ void prep_body(const T* __restrict__ U, const int64_t
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_prep(const PrepDesc<T> d) {
-  prep_body<T>(d.U, d.ldu, d.V, d.ldv, d.n, d.r, d.r_pad, d.slabU, d.slabV, d.W, d.n_pad, blockIdx.x);
+  const int64_t v = blockIdx.y;
+  prep_body<T>(d.U + v * d.strideU, d.ldu, d.V + v * d.strideV, d.ldv, d.n, d.r, d.r_pad, d.slabU + v * d.sstride,
+               d.slabV + v * d.sstride, d.W, d.n_pad, blockIdx.x);
 }
 
 template <typename T>
@@ -781,6 +949,18 @@ hipError_t update_r(T* P, int64_t ldp, int64_t n_pad, const T* Uj, const T* Vj, 
   return hipGetLastError();
 }
 
+template <typename T, int R>
+hipError_t update_chain_r(const UpdateDesc<T>& d, hipStream_t s) {
+  if constexpr (R >= 4) {
+    const int tr = sizeof(T) == 4 ? kMfmaUpdateTile : kF64UpdateRows;
+    const int tc = sizeof(T) == 4 ? kMfmaUpdateTile : kF64UpdateCols;
+    hipLaunchKernelGGL((k_level_update_chain<T, R>), dim3((unsigned)(d.n_pad / tc), (unsigned)(d.n_pad / tr)), dim3(256),
+                       0, s, d);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
 // Stand-alone Gram: gram_tiles(n_pad) partials, then their sum into the first.
 template <typename T, int R>
 hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG, hipStream_t s) {
@@ -797,9 +977,9 @@ hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG,
 
 template <typename T, int R>
 hipError_t tail_r(const T* partX, const T* partY, const double* partG, int nct, int nrt, int ng,
-                  int64_t n_pad, T* slabU, T* slabV, int W, hipStream_t s) {
-  const TailDesc<T> d{partX, partY, partG, nct, nrt, (int)n_pad, slabU, slabV, W, 0, ng};
-  hipLaunchKernelGGL((k_level_tail<T, R>), dim3((unsigned)tail_blocks(n_pad, R)), dim3(256), 0, s, d);
+                  int64_t n_pad, T* slabU, T* slabV, int W, hipStream_t s, int nver, const Strides& vs) {
+  const TailDesc<T> d{partX, partY, partG, nct, nrt, (int)n_pad, slabU, slabV, W, 0, ng, vs};
+  hipLaunchKernelGGL((k_level_tail<T, R>), dim3((unsigned)tail_blocks(n_pad, R), (unsigned)nver), dim3(256), 0, s, d);
   return hipGetLastError();
 }
 
@@ -815,17 +995,20 @@ hipError_t launch_copy_pad(const Tin* src, int64_t lds, int64_t n, Tout* dst, in
 
 template <typename T>
 hipError_t launch_prep(const T* U, int64_t ldu, const T* V, int64_t ldv, int64_t n, int r,
-                       int r_pad, T* slabU, T* slabV, int W, int64_t n_pad, hipStream_t s) {
-  const PrepDesc<T> d{U, ldu, V, ldv, n, r, r_pad, slabU, slabV, W, n_pad, 0};
-  hipLaunchKernelGGL((k_prep<T>), dim3((unsigned)((n_pad * r_pad + 255) / 256)), dim3(256), 0, s, d);
+                       int r_pad, T* slabU, T* slabV, int W, int64_t n_pad, hipStream_t s, int nver, int64_t strideU,
+                       int64_t strideV, int64_t sstride) {
+  const PrepDesc<T> d{U, ldu, V, ldv, n, r, r_pad, slabU, slabV, W, n_pad, 0, strideU, strideV, sstride};
+  hipLaunchKernelGGL((k_prep<T>), dim3((unsigned)((n_pad * r_pad + 255) / 256), (unsigned)nver), dim3(256), 0, s, d);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_level_tail(int R, const T* partX, const T* partY, const double* partG, int nct,
-                             int nrt, int ng, int64_t n_pad, T* slabU, T* slabV, int W, hipStream_t s) {
-  if (R == kMaxLevelRank) return tail_r<T, kMaxLevelRank>(partX, partY, partG, nct, nrt, ng, n_pad, slabU, slabV, W, s);
-  LV_RANK_SWITCH(R, return (tail_r<T, RR>(partX, partY, partG, nct, nrt, ng, n_pad, slabU, slabV, W, s)))
+                             int nrt, int ng, int64_t n_pad, T* slabU, T* slabV, int W, hipStream_t s, int nver,
+                             const Strides& vs) {
+  if (R == kMaxLevelRank)
+    return tail_r<T, kMaxLevelRank>(partX, partY, partG, nct, nrt, ng, n_pad, slabU, slabV, W, s, nver, vs);
+  LV_RANK_SWITCH(R, return (tail_r<T, RR>(partX, partY, partG, nct, nrt, ng, n_pad, slabU, slabV, W, s, nver, vs)))
 }
 
 template <typename T>
@@ -836,6 +1019,14 @@ hipError_t launch_level_update(int R, T* P, int64_t ldp, int64_t n_pad, const T*
   if (R == 2 * kMaxLevelRank) return update_r<T, 2 * kMaxLevelRank>(P, ldp, n_pad, Uj, Vj, W, s, S, split);
   if (R == kMaxLevelRank) return update_r<T, kMaxLevelRank>(P, ldp, n_pad, Uj, Vj, W, s, S, split);
   LV_RANK_SWITCH(R, return (update_r<T, RR>(P, ldp, n_pad, Uj, Vj, W, s, S, split)))
+}
+
+template <typename T>
+hipError_t launch_level_update_chain(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU, const T* slabV, int W,
+                                     int nver, int64_t sstride, hipStream_t s) {
+  const UpdateDesc<T> d{P, ldp, (int)n_pad, 0, slabU, slabV + (W - R), W, 0, 0, nullptr, nver, sstride};
+  if (R == kMaxLevelRank) return update_chain_r<T, kMaxLevelRank>(d, s);
+  LV_RANK_SWITCH(R, return (update_chain_r<T, RR>(d, s)))
 }
 
 template <typename T>
@@ -951,9 +1142,11 @@ hipError_t launch_prep_multi(const PrepDesc<T>* ds, int nd, int blocks, hipStrea
 
 #define LV_INST(T)                                                                              \
   template hipError_t launch_prep<T>(const T*, int64_t, const T*, int64_t, int64_t, int, int,     \
-                                     T*, T*, int, int64_t, hipStream_t);                          \
+                                     T*, T*, int, int64_t, hipStream_t, int, int64_t, int64_t, int64_t); \
   template hipError_t launch_level_tail<T>(int, const T*, const T*, const double*, int, int, int, \
-                                           int64_t, T*, T*, int, hipStream_t);                    \
+                                           int64_t, T*, T*, int, hipStream_t, int, const Strides&); \
+  template hipError_t launch_level_update_chain<T>(int, T*, int64_t, int64_t, const T*, const T*, int, int, int64_t, \
+                                                   hipStream_t);                                  \
   template hipError_t launch_level_update<T>(int, T*, int64_t, int64_t, const T*, const T*, int,  \
                                              hipStream_t, uint16_t*, bool);                       \
   template hipError_t launch_level_gram<T>(int, const T*, const T*, int, int64_t, double*,        \

@@ -33,22 +33,23 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // factor columns of Y over all slices, and Gram entries over all slices (or
 // over the row tiles of the stand-alone Gram), each for the tile rows that
 // give most slices: the smallest height, or the default's finer cut.
-inline size_t slice_cols(int64_t n_pad, int elem, int R, bool shadow) {
+// chained: of the updates that share a pass, side by side.
+inline size_t slice_cols(int64_t n_pad, int elem, int R, bool chained = false) {
   size_t most = 0;
   for (int q = 1; q <= R; q *= 2) {
-    const bool cores = shadow || skinny_on_mfma(q, elem);
+    const bool cores = skinny_on_mfma(q, elem);   // (a level on shadows has no more slices)
     for (const int rows : {kMinTileRows, kTileRows}) {
-      const size_t c = (size_t)slice_count(n_pad, elem, q, cores, rows) * q;
+      const size_t c = (size_t)slice_count(n_pad, elem, q, cores, rows) * q * (chained ? chain_updates(q) : 1);
       most = c > most ? c : most;
     }
   }
   return most;
 }
-inline size_t gram_partials(int64_t n_pad, int elem, int R) {
+inline size_t gram_partials(int64_t n_pad, int elem, int R, bool chained = false) {
   size_t most = (size_t)gram_tiles(n_pad) * R * R;
   for (int q = 1; q <= R && gram_in_pass(q, elem); q *= 2) {
     for (const int rows : {kMinTileRows, kTileRows}) {
-      const size_t c = (size_t)slice_count(n_pad, elem, q, false, rows) * q * q;
+      const size_t c = (size_t)slice_count(n_pad, elem, q, false, rows) * q * q * (chained ? chain_updates(q) : 1);
       most = c > most ? c : most;
     }
   }
@@ -61,9 +62,10 @@ struct Layout {
   size_t P[kMaxLevel + 1] = {};
   size_t slabU = 0, slabV = 0;   // the update's factor slabs (every level's U_j, V_j)
   // factor-slab pairs of the pipelined batch (plain views with m >= 2): slot
-  // 0 is slabU / slabV, slots 1 .. pipe_slots - 1 follow
-  int pipe_slots = 0;
-  size_t pslabU[kMaxPipeSlots] = {}, pslabV[kMaxPipeSlots] = {};
+  // 0 is slabU / slabV, slots 1 .. pipe_slots - 1 follow at a fixed stride;
+  // chain: updates of rank r_max that a chunk of the batch takes together
+  int pipe_slots = 0, chain = 1;
+  size_t slot_stride = 0;
   // n_pad x r_pad zeros (set at creation): the factors of the zero updates
   // that lv_view_autotune times (P + 0 0^T = P exactly)
   size_t zfac = 0;
@@ -162,14 +164,15 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
   const size_t slab = (size_t)L.n_pad * L.W * L.elem;
   L.slabU = off; off = align_up(off + slab);
   L.slabV = off; off = align_up(off + slab);
-  L.pslabU[0] = L.slabU;
-  L.pslabV[0] = L.slabV;
-  if (!ext_powers && !L.sums && L.m >= 2) {
-    L.pipe_slots = L.m + 1 < kMaxPipeSlots ? L.m + 1 : kMaxPipeSlots;
-    for (int q = 1; q < L.pipe_slots; ++q) {
-      L.pslabU[q] = off; off = align_up(off + slab);
-      L.pslabV[q] = off; off = align_up(off + slab);
-    }
+  L.slot_stride = off - L.slabU;
+  const bool piped = !ext_powers && !L.sums && L.m >= 2;
+  if (piped) {
+    // an update in flight per level up to 5; kPipeChunks chunks where several
+    // updates share a pass
+    L.chain = chain_updates(L.r_pad);
+    L.pipe_slots = L.m + 1 < 5 ? L.m + 1 : 5;
+    if (L.chain > 1 && L.pipe_slots < kPipeChunks * L.chain) L.pipe_slots = kPipeChunks * L.chain;
+    off += (L.pipe_slots - 1) * L.slot_stride;
   }
   if (!ext_powers) {
     L.zfac = off;
@@ -180,9 +183,11 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
   for (int j = 0; j < L.m; ++j) {
     const size_t R = (size_t)L.r_pad << j;
     if (ext_powers) off = parts;   // one level's partials at a time
-    L.partX[j] = off; off = align_up(off + (size_t)L.nct * L.n_pad * R * L.elem);
-    L.partY[j] = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, (int)R, shadow) * L.elem);
-    L.partG[j] = off; off = align_up(off + gram_partials(L.n_pad, L.elem, (int)R) * sizeof(double));
+    // a chunk's updates side by side (most columns at R = 2 and above)
+    const size_t xcols = piped && R < kChainCols ? (R == 1 ? kChainUpdates : kChainCols) : R;
+    L.partX[j] = off; off = align_up(off + (size_t)L.nct * L.n_pad * xcols * L.elem);
+    L.partY[j] = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, (int)R, piped) * L.elem);
+    L.partG[j] = off; off = align_up(off + gram_partials(L.n_pad, L.elem, (int)R, piped) * sizeof(double));
   }
   if (ext_powers) {
     // the bytes that linview.h states for a shape (every level's partials
@@ -211,7 +216,7 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
     for (int j = 0; j < L.m; ++j) {
       const size_t R = (size_t)L.r_pad << j;
       L.partXs[j] = off; off = align_up(off + (size_t)L.nct * L.n_pad * R * L.elem);
-      L.partYs[j] = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, (int)R, shadow) * L.elem);
+      L.partYs[j] = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, (int)R) * L.elem);
       L.partGs[j] = off; off = align_up(off + (size_t)gram_tiles(L.n_pad) * R * R * sizeof(double));
     }
     if (mode != LV_FP64 && (L.m > 0 || L.general)) {
@@ -252,13 +257,13 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
       }
       const size_t xmat = (size_t)L.n_pad * wmax * L.elem;
       L.partXT = off; off = align_up(off + (size_t)L.nct * xmat);
-      L.partYT = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, wmax, shadow) * L.elem);
+      L.partYT = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, wmax) * L.elem);
       L.atbG = off; off = align_up(off + (size_t)(L.n_pad / kAtbRows) * rmax * wmax * sizeof(double));
     } else {
       L.D[0] = off; off = align_up(off + gmat);
       L.D[1] = off; off = align_up(off + gmat);
       L.partXT = off; off = align_up(off + (size_t)L.nct * gmat);
-      L.partYT = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, L.pp, shadow) * L.elem);
+      L.partYT = off; off = align_up(off + (size_t)L.n_pad * slice_cols(L.n_pad, L.elem, L.pp) * L.elem);
     }
     const size_t atb = (size_t)(L.n_pad / kAtbRows) * rmax * L.pp * sizeof(double);
     L.atbA = off; off = align_up(off + atb);
@@ -327,6 +332,7 @@ struct lv_view {
   int pipe_nstages = 0;
   hipStream_t pstream[lv::kPipeStreams] = {};
   hipEvent_t pready[lv::kMaxLevel][lv::kMaxPipeSlots] = {};
+  int pgroup[lv::kMaxLevel][lv::kMaxPipeSlots] = {};   // last slot of the group that holds a slot's update
   hipEvent_t pfree[lv::kMaxPipeSlots] = {};
   hipEvent_t pfork = nullptr;
   hipEvent_t pjoin[lv::kPipeStreams] = {};
@@ -337,8 +343,15 @@ struct lv_view {
   template <typename T> T* P(int j) const { return reinterpret_cast<T*>(pext[j] ? pext[j] : base + L.P[j]); }
   template <typename T> T* slabU() const { return reinterpret_cast<T*>(base + L.slabU); }
   template <typename T> T* slabV() const { return reinterpret_cast<T*>(base + L.slabV); }
-  template <typename T> T* slabU(int slot) const { return reinterpret_cast<T*>(base + L.pslabU[slot]); }
-  template <typename T> T* slabV(int slot) const { return reinterpret_cast<T*>(base + L.pslabV[slot]); }
+  template <typename T> T* slabU(int slot) const { return reinterpret_cast<T*>(base + L.slabU + slot * L.slot_stride); }
+  template <typename T> T* slabV(int slot) const { return reinterpret_cast<T*>(base + L.slabV + slot * L.slot_stride); }
+  // updates of padded rank r_pad (at most the view's) that a chunk of a
+  // batch takes: two chunks must fit the slots
+  int chunk(int r_pad) const {
+    int c = shadowed() ? 1 : lv::chain_updates(r_pad);   // no shared pass with shadows
+    while (c > 1 && L.pipe_slots < 2 * c) c /= 2;
+    return c;
+  }
   template <typename T> T* partX(int j) const { return reinterpret_cast<T*>(base + L.partX[j]); }
   template <typename T> T* partY(int j) const { return reinterpret_cast<T*>(base + L.partY[j]); }
   double* partG(int j) const { return reinterpret_cast<double*>(base + L.partG[j]); }
