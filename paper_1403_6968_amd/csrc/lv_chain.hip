@@ -4,7 +4,7 @@
 // matrices (linear: a = 1, b = c - 1; skip-s: a = s, b = c - s beyond s;
 // exponential: a = b = c/2), and its delta is factored as
 //     U_c = [U_a, P_a U_b + U_a (V_a^T U_b)],   V_c = [P_b^T V_a, V_b]
-// from the OLD matrices; then every stored matrix takes P_c += U_c V_c^T.
+// from the OLD matrices; and every stored matrix takes P_c += U_c V_c^T.
 // Each stored matrix has its own factor slabs (width c * r_pad padded to a
 // power of two): in the linear and skip models U_b is transformed, not
 // extended, so the prefix layout of the exponential view does not apply.
@@ -24,34 +24,88 @@ namespace {
 constexpr int kMaxChainWidth = 128;   // k * r_pad (the read-only passes take up to 128 columns)
 constexpr int kMaxChainStored = 128;
 
-// One thread per (row, column) of the new slabs, column < Wc:
-//   col < wa:           U_c = U_a,                 V_c = sum_t partY[t]  (P_b^T V_a)
-//   wa <= col < wa+wb:  U_c = sum_t partX[t] + U_a G  (P_a U_b + U_a (V_a^T U_b)),  V_c = V_b
-//   otherwise zero.  Partial sums in tile order, double accumulation.
+// Lanes of eight per (row, column j < wa): the lane group sums the partials of
+// X and Y (lane l the partials l, l + 8, ...; a butterfly adds the lane sums in
+// double) and writes column wb + j of U_c and column j of V_c; the group of
+// j = 0 also copies the row's U_b and V_b and writes the zero columns.
+constexpr int kKrylovLanes = 8;
+constexpr int kKrylovGramCap = 64;    // Gram partials are summed here up to 8 columns
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_chain_tail(const T* __restrict__ partX, int nct, const T* __restrict__ partY, int nrt, const double* __restrict__ G,
-             const T* __restrict__ Ua, int Wa, int wa, const T* __restrict__ Vb, int Wb, int wb,
-             T* __restrict__ Uc, T* __restrict__ Vc, int Wc, int64_t n_pad) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= n_pad * Wc) return;
-  const int64_t row = idx / Wc;
-  const int col = (int)(idx % Wc);
-  double u = 0.0, v = 0.0;
-  if (col < wa) {
-    u = (double)Ua[row * Wa + col];
-    for (int t = 0; t < nrt; ++t) v += (double)partY[((int64_t)t * n_pad + row) * Wa + col];
-  } else if (col < wa + wb) {
-    const int j = col - wa;
-    for (int t = 0; t < nct; ++t) u += (double)partX[((int64_t)t * n_pad + row) * Wb + j];
-    for (int d = 0; d < wa; ++d) u = fma((double)Ua[row * Wa + d], G[d * Wb + j], u);
-    v = (double)Vb[row * Wb + j];
+k_krylov_tail(int wa, const T* __restrict__ partX, int nct, const T* __restrict__ partY, int nrt,
+              const double* __restrict__ partG, int ng, const T* __restrict__ Ua, int Wa, const T* __restrict__ Ub,
+              const T* __restrict__ Vb, int Wb, int wb, T* Uc, T* Vc, int Wc, int64_t n_pad) {
+  constexpr int TL = kKrylovLanes;
+  __shared__ double Gs[kKrylovGramCap];
+  const int tid = threadIdx.x;
+  const double* G = partG;
+  if (ng > 1) {
+    // wa^2 <= 64 entries, 256 / wa^2 threads each (shuffled together when
+    // they share a wave)
+    const int cnt = wa * wa, per = 256 / cnt < 32 ? 256 / cnt : 32;
+    const int e = tid / per, l = tid % per;
+    double g = 0.0;
+    if (e < cnt)
+      for (int t = l; t < ng; t += per) g += partG[(int64_t)t * cnt + e];
+    for (int off = per / 2; off > 0; off >>= 1) g += __shfl_xor(g, off, per);
+    if (e < cnt && l == 0) Gs[e] = g;
+    __syncthreads();
+    G = Gs;
   }
-  Uc[idx] = (T)u;
-  Vc[idx] = (T)v;
+  const int64_t idx = (int64_t)blockIdx.x * (256 / TL) + tid / TL;
+  const int sl = tid % TL;
+  if (idx >= n_pad * wa) return;   // whole lane groups leave together
+  const int64_t row = idx / wa;
+  const int j = (int)(idx % wa);
+  const int64_t stride = n_pad * wa;
+  double x = 0.0, y = 0.0;
+#pragma unroll 4
+  for (int t = sl; t < nct; t += TL) x += (double)partX[t * stride + idx];
+  if (Vc != nullptr) {
+#pragma unroll 4
+    for (int t = sl; t < nrt; t += TL) y += (double)partY[t * stride + idx];
+  }
+  for (int d = sl; d < wa; d += TL) x = fma((double)Ua[row * Wa + d], G[d * wa + j], x);
+#pragma unroll
+  for (int off = TL / 2; off > 0; off >>= 1) {
+    x += __shfl_xor(x, off, TL);
+    y += __shfl_xor(y, off, TL);
+  }
+  if (sl == 0) {
+    Uc[row * Wc + wb + j] = (T)x;
+    if (Vc != nullptr) Vc[row * Wc + j] = (T)y;
+  }
+  if (Ub != nullptr && j == 0) {
+    for (int c = sl; c < wb; c += TL) {
+      Uc[row * Wc + c] = Ub[row * Wb + c];
+      if (Vc != nullptr) Vc[row * Wc + wa + c] = Vb[row * Wb + c];
+    }
+    for (int c = wa + wb + sl; Vc != nullptr && c < Wc; c += TL) {
+      Uc[row * Wc + c] = T(0);
+      Vc[row * Wc + c] = T(0);
+    }
+  }
 }
 
 }  // namespace
+
+template <typename T>
+hipError_t launch_krylov_tail(int wa, const T* partX, int nct, const T* partY, int nrt, const double* partG, int ng,
+                              const T* Ua, int Wa, const T* Ub, const T* Vb, int Wb, int wb, T* Uc, T* Vc, int Wc,
+                              int64_t n_pad, hipStream_t s) {
+  if (ng > 1 && wa * wa > kKrylovGramCap) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)((n_pad * wa * kKrylovLanes + 255) / 256);
+  hipLaunchKernelGGL((k_krylov_tail<T>), dim3(blocks), dim3(256), 0, s, wa, partX, nct, partY, nrt, partG, ng, Ua, Wa,
+                     Ub, Vb, Wb, wb, Uc, Vc, Wc, n_pad);
+  return hipGetLastError();
+}
+#define LV_INST(T)                                                                                                 \
+  template hipError_t launch_krylov_tail<T>(int, const T*, int, const T*, int, const double*, int, const T*, int,  \
+                                            const T*, const T*, int, int, T*, T*, int, int64_t, hipStream_t);
+LV_INST(float)
+LV_INST(double)
+#undef LV_INST
+
 }  // namespace lv
 
 struct lv_chain {
@@ -62,6 +116,8 @@ struct lv_chain {
   std::vector<int> Wd;       // padded slab width of each stored matrix
   struct Step { int c, a, b; };
   std::vector<Step> steps;   // products in evaluation order (indices into pw)
+  std::vector<int> left_last;   // last step that reads a stored matrix as P_a (-1: none)
+  std::vector<char> done;       // matrices that an update's steps have updated already
   // rows per slice of a pass of rank R, and its slices
   int rows(int R) const { return slice_rows(n_pad, elem, R, skinny_on_mfma(R, elem), kTileRows); }
   int nrt(int R) const { return (int)((n_pad + rows(R) - 1) / rows(R)); }
@@ -107,6 +163,8 @@ lv_status plan_chain(lv_chain& c) {
     if (ai < 0 || bi != ci - 1) return fail(LV_EINVAL, "internal: product %d has no stored operands", prods[q].first);
     c.steps.push_back({ci, ai, bi});
   }
+  c.left_last.assign(c.pw.size(), -1);
+  for (size_t q = 0; q < c.steps.size(); ++q) c.left_last[c.steps[q].a] = (int)q;
   return LV_OK;
 }
 
@@ -154,7 +212,8 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
   c.partX = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
   c.partXd = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
   c.partY = off; off = align_up(off + (size_t)c.n_pad * slice_cols(c.n_pad, c.elem, maxW) * c.elem);
-  c.partG = off; off = align_up(off + (size_t)(c.n_pad / kAtbRows) * maxG * sizeof(double));
+  const size_t ng = (size_t)(c.n_pad / kAtbRows) * maxG, nk = gram_partials(c.n_pad, c.elem, kMaxKrylovCols);
+  c.partG = off; off = align_up(off + (ng > nk ? ng : nk) * sizeof(double));
   if (mode == LV_FP32 && ns > 1)
     for (int i = 0; i < 3; ++i) { c.d64[i] = off; off = align_up(off + (size_t)c.n_pad * c.n_pad * sizeof(double)); }
   c.total = off;
@@ -198,29 +257,61 @@ lv_status build_chain_model(lv_chain* c, hipStream_t s) {
   }
 }
 
-// Read-only products of one step: X = P_a U_b (column-tile partials, width
-// W_b) and Y = P_b^T V_a (row-tile partials, width W_a).  One pass when
-// a = b; otherwise one pass over each matrix (the unused product of each
-// pass goes to a discard buffer on the vector path; the float matrix-core
-// pass from width 16 computes only what is asked).
+// One step, the product P_c = P_a P_b, with w = pw[a] r_pad columns of P_a's
+// factors: X = P_a M for the last w columns M of U_b (column-tile partials),
+// Y = P_b^T V_a (row-slice partials) and the Gram V_a^T M, all from the OLD
+// matrices.  Two columns of U_c that apply f(M) = P_a M + U_a (V_a^T M) to
+// equal columns are equal, and U_b = [U_a, f(U_a), f(f(U_a)), ...] by induction
+// over the steps with this left operand (a = 1 or s, b = a, 2 a, ...), so of
+//     U_c = [U_a, f(U_b)] = [U_b, f(M)]
+// only f(M) is new: the products take w columns instead of U_b's whole width.
+// Up to 8 columns the vector passes run, one read of the matrix when a = b;
+// else X and Y in one launch, P_b taking its own update in the pass that
+// reads it (*updated) where no later step reads it as P_a.
 template <typename T>
-lv_status step_products(lv_chain* c, const lv_chain::Step& q, hipStream_t s) {
+lv_status step_products(lv_chain* c, const lv_chain::Step& q, hipStream_t s, int* ng, bool* updated) {
   const int64_t np = c->n_pad;
   const int Wa = c->Wd[q.a], Wb = c->Wd[q.b];
-  const T* Ub = c->U<T>(q.b);
+  const int w = c->pw[q.a] * c->r_pad;   // = Wa: the left operands' powers are powers of two
+  const T* M = c->U<T>(q.b) + (c->pw[q.b] - c->pw[q.a]) * c->r_pad;
   const T* Va = c->V<T>(q.a);
-  auto pass = [&](const T* P, int R, const T* op1, const T* op2, T* px, T* py, int want) -> hipError_t {
-    if (skinny_on_mfma(R, (int)sizeof(T)))
-      return launch_skinny_f32(R, reinterpret_cast<const float*>(P), np, np, c->rows(R),
-                               reinterpret_cast<const float*>(op1), reinterpret_cast<const float*>(op2), R,
+  *updated = false;
+  if (w <= kMaxKrylovCols) {
+    *ng = c->nrt(w);
+    if (q.a == q.b)
+      return hip_check(launch_fused_xgram<T>(w, c->Pm<T>(q.a), np, np, c->rows(w), M, Wb, Va, Wa, c->pX<T>(),
+                                             c->pY<T>(), c->pG(), s), "P U, P^T V");
+    if (Wb <= kMaxFusedRank && c->left_last[q.b] < 0) {
+      *updated = true;
+      return hip_check(launch_krylov_step<T>(Wb, w, c->Pm<T>(q.a), c->Pm<T>(q.b), np, np, c->rows(w), c->rows(w), M,
+                                             c->U<T>(q.b), c->V<T>(q.b), Wb, Va, Wa, c->pX<T>(), c->pY<T>(), c->pG(),
+                                             s), "P_a U_b, P_b^T V_a, P_b += U_b V_b^T");
+    }
+    lv_status st = hip_check(launch_fused_xgram<T>(w, c->Pm<T>(q.a), np, np, c->rows(w), M, Wb, Va, Wa, c->pX<T>(),
+                                                   nullptr, c->pG(), s), "P_a U_b");
+    if (st != LV_OK) return st;
+    return hip_check(launch_level_readonly<T>(w, c->Pm<T>(q.b), np, np, c->rows(w), Va, Va, Wa, c->pXd<T>(),
+                                              c->pY<T>(), s), "P_b^T V_a");
+  }
+  // wider: the float matrix cores form only what is asked, the vector pass
+  // sends the unused product to the discard buffer
+  auto pass = [&](const T* P, const T* op1, const T* op2, int W, T* px, T* py, int want) -> hipError_t {
+    if (skinny_on_mfma(w, (int)sizeof(T)))
+      return launch_skinny_f32(w, reinterpret_cast<const float*>(P), np, np, c->rows(w),
+                               reinterpret_cast<const float*>(op1), reinterpret_cast<const float*>(op2), W,
                                reinterpret_cast<float*>(px), reinterpret_cast<float*>(py), s, want);
-    return launch_level_readonly<T>(R, P, np, np, c->rows(R), op1, op2, R, px, py, s);
+    return launch_level_readonly<T>(w, P, np, np, c->rows(w), op1, op2, W, px, py, s);
   };
-  if (q.a == q.b)
-    return hip_check(pass(c->Pm<T>(q.a), Wa, Ub, Va, c->pX<T>(), c->pY<T>(), kWantX | kWantY), "P U, P^T V");
-  lv_status st = hip_check(pass(c->Pm<T>(q.a), Wb, Ub, Ub, c->pX<T>(), c->pY<T>(), kWantX), "P_a U_b");
+  *ng = 1;
+  lv_status st = LV_OK;
+  if (q.a == q.b) {
+    st = hip_check(pass(c->Pm<T>(q.a), M, Va, Wa, c->pX<T>(), c->pY<T>(), kWantX | kWantY), "P U, P^T V");
+  } else {
+    st = hip_check(pass(c->Pm<T>(q.a), M, M, Wb, c->pX<T>(), c->pY<T>(), kWantX), "P_a U_b");
+    if (st == LV_OK) st = hip_check(pass(c->Pm<T>(q.b), Va, Va, Wa, c->pXd<T>(), c->pY<T>(), kWantY), "P_b^T V_a");
+  }
   if (st != LV_OK) return st;
-  return hip_check(pass(c->Pm<T>(q.b), Wa, Va, Va, c->pXd<T>(), c->pY<T>(), kWantY), "P_b^T V_a");
+  return hip_check(launch_atb<T>(w, w, Va, Wa, M, Wb, np, c->pG(), s), "V_a^T U_b");
 }
 
 template <typename T>
@@ -228,22 +319,24 @@ lv_status chain_update(lv_chain* c, const T* U, const T* V, int r, int64_t ldu, 
   const int64_t np = c->n_pad;
   lv_status st = hip_check(launch_prep<T>(U, ldu, V, ldv, c->n, r, c->r_pad, c->U<T>(0), c->V<T>(0), c->r_pad, np, s),
                            "prep");
+  std::vector<char>& done = c->done;
+  done.assign(c->pw.size(), 0);
   for (auto& q : c->steps) {
     if (st != LV_OK) return st;
-    const int Wa = c->Wd[q.a], Wb = c->Wd[q.b], Wc = c->Wd[q.c];
-    st = step_products<T>(c, q, s);
+    const int w = c->pw[q.a] * c->r_pad;
+    int ng = 1;
+    bool updated = false;
+    st = step_products<T>(c, q, s, &ng, &updated);
+    if (updated) done[q.b] = 1;
     if (st == LV_OK)
-      st = hip_check(launch_atb<T>(Wa, Wb, c->V<T>(q.a), Wa, c->U<T>(q.b), Wb, np, c->pG(), s), "V_a^T U_b");
-    if (st == LV_OK) {
-      hipLaunchKernelGGL((k_chain_tail<T>), dim3((unsigned)((np * Wc + 255) / 256)), dim3(256), 0, s, c->pX<T>(),
-                         c->nct, c->pY<T>(), c->nrt(Wa), c->pG(), c->U<T>(q.a), Wa, c->pw[q.a] * c->r_pad, c->V<T>(q.b),
-                         Wb, c->pw[q.b] * c->r_pad, c->U<T>(q.c), c->V<T>(q.c), Wc, np);
-      st = hip_check(hipGetLastError(), "chain tail");
-    }
+      st = hip_check(launch_krylov_tail<T>(w, c->pX<T>(), c->nct, c->pY<T>(), c->nrt(w), c->pG(), ng, c->U<T>(q.a),
+                                           c->Wd[q.a], c->U<T>(q.b), c->V<T>(q.b), c->Wd[q.b], c->pw[q.b] * c->r_pad,
+                                           c->U<T>(q.c), c->V<T>(q.c), c->Wd[q.c], np, s), "chain tail");
   }
   for (size_t i = 0; i < c->pw.size() && st == LV_OK; ++i)
-    st = hip_check(launch_level_update<T>(c->Wd[i], c->Pm<T>((int)i), np, np, c->U<T>((int)i), c->V<T>((int)i),
-                                          c->Wd[i], s), "P += U V^T");
+    if (!done[i])
+      st = hip_check(launch_level_update<T>(c->Wd[i], c->Pm<T>((int)i), np, np, c->U<T>((int)i), c->V<T>((int)i),
+                                            c->Wd[i], s), "P += U V^T");
   return st;
 }
 

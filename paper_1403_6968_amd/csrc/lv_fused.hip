@@ -134,9 +134,14 @@ __device__ __forceinline__ int sum_index(const int lane) { return (int)(__brev((
 //            extra blocks' partials go to partX2 (row stride XE) and partX3
 //            (row stride XD).  The powers' pass thus also yields P_j Q_j
 //            (sums) and P_j D_j (the general form's delta or factor slab).
-//   SP       the sums pass: no X; Y = S^T Vy with the old S and the rank
-//            update S += Uj Vj^T (Uj = Q_j, Vj = W_j), no Gram.
-template <typename T, int R, int TT, bool UPD, int XE = 0, bool SP = false, int XD = 0>
+//   SP       no X: Y = S^T Vy with the old S for RY columns of another factor
+//            Vy, and the rank update S += Uj Vj^T; no Gram.  The sums pass
+//            (Uj = Q_j, Vj = W_j, Vy = V_j), and the step of the linear and
+//            skip models that forms the next factor from P_b^T V_a and
+//            updates P_b.
+//   GR       (UPD = false) the Gram Vy^T Uj is formed as well; WY = false: no Y.
+template <typename T, int R, int TT, bool UPD, int XE = 0, bool SP = false, int XD = 0, int RY = R, bool GR = UPD && !SP,
+          bool WY = true>
 __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, const int rt) {
   constexpr int RB = kFusedRowBlock;
   constexpr int EPL = 16 / (int)sizeof(T);
@@ -144,16 +149,20 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
   constexpr int C = R * TT;                     // factor columns of all the updates
   constexpr int XR = SP ? 1 : R + XE + XD;      // columns of X per update
   constexpr int NX = RB * TT * XR;              // lane sums per block
+  constexpr int CY = SP ? RY : C;               // columns of Y
   static_assert(!SP || (UPD && XE == 0 && XD == 0), "the sums pass updates and forms no X");
   static_assert(TT == 1 || (UPD && !SP && XE == 0 && XD == 0), "several updates: the plain pass only");
+  static_assert(SP || RY == R, "Y has the factors' columns");
+  static_assert(WY || (!UPD && R <= 8), "passes without Y read only");
   static_assert(SP || NX <= 64, "one lane per X sum");
   constexpr bool LF = !SP && XE == 0 && XD == 0 && (C > 8 || TT > 1);
   constexpr int CH = R < 4 ? R : 4;             // factor columns read at a time (LF)
-  constexpr int YC = C < 4 ? C : 4;             // Y columns exchanged at a time
-  constexpr int FB = RB * C;                    // factor entries per block and operand
-  constexpr int FN = (FB + 63) / 64;
+  constexpr int YC = CY < 4 ? CY : 4;           // Y columns exchanged at a time
+  constexpr int FB = RB * C, FBY = RB * CY;     // factor entries per block: U, and the Y operand
+  constexpr int FM = FB > FBY ? FB : FBY;
+  constexpr int FN = (FM + 63) / 64;
 
-  __shared__ __align__(16) T facs[4][UPD ? 2 : 1][FB];
+  __shared__ __align__(16) T facs[4][UPD ? 2 : 1][FM];
   // the lanes' factor rows (LF: U, then V), and the exchange of the Y sums
   constexpr int NF = LF ? (UPD ? 2 : 1) * C * TC : 0;
   __shared__ __align__(16) T lbuf[NF > 4 * TC * YC ? NF : 4 * TC * YC];
@@ -180,11 +189,15 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
   // column c) sits in lane e % 64 of f[e / 64]; foff: byte offset of the
   // lane's entry from the block's first factor row (32 bits: eight slabs of
   // the largest order and width stay below 2^31 bytes)
-  unsigned foff[FN];
+  unsigned foff[FN], foffy[SP ? FN : 1];
 #pragma unroll
   for (int f = 0; f < FN; ++f) {
     const int e = lane + 64 * f < FB ? lane + 64 * f : 0;
     foff[f] = (unsigned)(((TT > 1 ? (e / R % TT) * d.vs.s : 0) + (int64_t)(e / C) * W + e % R) * sizeof(T));
+    if constexpr (SP) {
+      const int ey = lane + 64 * f < FBY ? lane + 64 * f : 0;
+      foffy[f] = (unsigned)(((int64_t)(ey / RY) * d.Wy + ey % RY) * sizeof(T));
+    }
   }
   V16<T> p[RB], pn[RB];
   T fy[FN], fu[UPD ? FN : 1], fyn[FN], fun[UPD ? FN : 1];
@@ -193,14 +206,15 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     for (int t = 0; t < RB; ++t) pp[t] = ld16_nt(P + (r0 + t) * ldp + lc);
 #pragma unroll
     for (int f = 0; f < FN; ++f) {
-      y[f] = *at_byte(Yop + r0 * W, foff[f]);
+      if constexpr (SP) y[f] = *at_byte(Yop + r0 * d.Wy, foffy[f]);
+      else if constexpr (WY) y[f] = *at_byte(Yop + r0 * W, foff[f]);
       if constexpr (UPD) u[f] = *at_byte(Uj + r0 * W, foff[f]);
     }
   };
   if (wave < nblocks) load_block(p, fy, fu, blk_row(wave));
 
   // the lane's factor rows
-  T ucol[LF ? 1 : TT][EPL][XR], vcol[LF ? 1 : TT][EPL][UPD ? R : 1], yacc[TT][EPL][R];
+  T ucol[LF ? 1 : TT][EPL][XR], vcol[LF ? 1 : TT][EPL][UPD ? R : 1], yacc[TT][EPL][SP ? RY : R];
   if constexpr (LF) {
     constexpr int OPS = UPD ? 2 : 1;
 #pragma unroll
@@ -220,7 +234,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
 #pragma unroll
     for (int q = 0; q < EPL; ++q) {
 #pragma unroll
-      for (int c = 0; c < R; ++c) yacc[v][q][c] = T(0);
+      for (int c = 0; c < (SP ? RY : R); ++c) yacc[v][q][c] = T(0);
       if constexpr (LF) continue;
       const unsigned g = (unsigned)((lc + q) * W * (int)sizeof(T));
       load_row<T, UPD ? R : 0>(at_byte(Vj + v * d.vs.s, g), vcol[v][q]);
@@ -258,10 +272,10 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     const int64_t r0 = blk_row(b);
 #pragma unroll
     for (int f = 0; f < FN; ++f) {
-      if (lane + 64 * f < FB) {
-        fac_y[lane + 64 * f] = fy[f];
-        if constexpr (UPD) fac_u[lane + 64 * f] = fu[f];
-      }
+      if constexpr (WY)
+        if (lane + 64 * f < FBY) fac_y[lane + 64 * f] = fy[f];
+      if constexpr (UPD)
+        if (lane + 64 * f < FB) fac_u[lane + 64 * f] = fu[f];
     }
     if (b + 4 < nblocks) load_block(pn, fyn, fun, blk_row(b + 4));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -343,12 +357,15 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     for (int t = 0; t < (LF ? 0 : RB); ++t) {
 #pragma unroll
       for (int v = 0; v < TT; ++v) {
-        T vi[R];
-        load_row<T, R>(fac_y + (t * TT + v) * R, vi);
+        constexpr int YR = SP ? RY : R;
+        if constexpr (WY) {
+          T vi[YR];
+          load_row<T, YR>(fac_y + (t * TT + v) * YR, vi);
 #pragma unroll
-        for (int q = 0; q < EPL; ++q)
+          for (int q = 0; q < EPL; ++q)
 #pragma unroll
-          for (int c = 0; c < R; ++c) yacc[v][q][c] = fma(p[t].v[q], vi[c], yacc[v][q][c]);
+            for (int c = 0; c < YR; ++c) yacc[v][q][c] = fma(p[t].v[q], vi[c], yacc[v][q][c]);
+        }
         if constexpr (!SP) {
 #pragma unroll
           for (int c = 0; c < XR; ++c) {
@@ -394,22 +411,23 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 
-  // Y partial of this tile: the four waves' sums, YC of the C columns
+  // Y partial of this tile: the four waves' sums, YC of the CY columns
   // (update v, column c: v R + c) at a time.
+  constexpr int YR = SP ? RY : R;
 #pragma unroll
-  for (int c0 = 0; c0 < C; c0 += YC) {
+  for (int c0 = 0; c0 < (WY ? CY : 0); c0 += YC) {
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < EPL; ++q)
 #pragma unroll
-      for (int c = 0; c < YC; ++c) ybuf[(wave * TC + lane * EPL + q) * YC + c] = yacc[(c0 + c) / R][q][(c0 + c) % R];
+      for (int c = 0; c < YC; ++c) ybuf[(wave * TC + lane * EPL + q) * YC + c] = yacc[(c0 + c) / YR][q][(c0 + c) % YR];
     __syncthreads();
     for (int idx = tid; idx < TC * YC; idx += 256) {
       const int cc = idx / YC, c = idx % YC;
       const T s = ((ybuf[(0 * TC + cc) * YC + c] + ybuf[(1 * TC + cc) * YC + c]) +
                    ybuf[(2 * TC + cc) * YC + c]) + ybuf[(3 * TC + cc) * YC + c];
-      const int v = (c0 + c) / R;
-      d.partY[v * d.vs.y + ((int64_t)rt * n_pad + col0 + cc) * pR + (c0 + c) % R] = s;
+      const int v = (c0 + c) / YR;
+      d.partY[v * d.vs.y + ((int64_t)rt * n_pad + col0 + cc) * pR + (c0 + c) % YR] = s;
     }
   }
 
@@ -418,20 +436,22 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
   // p mod nct), so no block carries much more work than the others; 32
   // consecutive lanes take a pair, lane g the rows g, g + 32, ... of the slice
   // (counted in slice order), and their sums are added by a butterfly.
-  if constexpr (UPD && !SP) {
+  if constexpr (GR) {
     constexpr int NP = R * R;
+    const T* __restrict__ Vg = UPD ? Vj : d.Vy;
+    const int Wg = UPD ? W : d.Wy;
     const int nct = n_pad / TC;
     const int nsr = nblocks * RB;   // rows of the slice
     const int g0 = tid % 32;
     for (int pair = ct + nct * (tid / 32); pair < TT * NP; pair += 8 * nct) {
       const int v = pair / NP, ab = pair % NP;
-      const T* vp = Vj + v * d.vs.s + ab / R;
+      const T* vp = Vg + v * d.vs.s + ab / R;
       const T* up = Uj + v * d.vs.s + ab % R;
       double g = 0.0;
 #pragma unroll 4
       for (int q = g0; q < nsr; q += 32) {
         const int64_t i = blk_row(q / RB) + q % RB;
-        g = fma((double)vp[i * W], (double)up[i * W], g);
+        g = fma((double)vp[i * Wg], (double)up[i * W], g);
       }
 #pragma unroll
       for (int off = 16; off > 0; off >>= 1) g += __shfl_xor(g, off, 32);
@@ -473,6 +493,24 @@ __global__ void __launch_bounds__(256) k_level_fused_x(const FusedDesc<T> d) {
 template <typename T, int R>
 __global__ void __launch_bounds__(256) k_sums_fused(const FusedDesc<T> d) {
   fused_body<T, R, 1, true, 0, true>(d, blockIdx.x, blockIdx.y);
+}
+
+// A step of the linear and skip models in one launch: work-groups of the
+// first nsx slices form X = P_a M with the Gram (dx, RY columns), the others
+// Y = P_b^T V_a and P_b += U_b V_b^T (dy, update rank R).  The two passes are
+// independent, and each alone leaves the device half idle at small orders.
+template <typename T, int R, int RY>
+__global__ void __launch_bounds__(256) k_krylov_step(const FusedDesc<T> dx, const FusedDesc<T> dy, const int nsx) {
+  if ((int)blockIdx.y < nsx)
+    fused_body<T, RY, 1, false, 0, false, 0, RY, true, false>(dx, blockIdx.x, blockIdx.y);
+  else
+    fused_body<T, R, 1, true, 0, true, 0, RY>(dy, blockIdx.x, (int)blockIdx.y - nsx);
+}
+
+// Read-only: X = P Uj with the Gram Vy^T Uj, and Y = P^T Vj if WY.
+template <typename T, int R, bool WY>
+__global__ void __launch_bounds__(256) k_fused_xgram(const FusedDesc<T> d) {
+  fused_body<T, R, 1, false, 0, false, 0, R, true, WY>(d, blockIdx.x, blockIdx.y);
 }
 
 template <typename T, int R, bool UPD>
@@ -601,6 +639,7 @@ hipError_t launch_sums_fused(int R, T* S, int64_t ldp, int64_t n_pad, int tile_r
   const int nct = (int)(n_pad / tile_cols<T>());
   FusedDesc<T> d{S, ldp, (int)n_pad, tile_rows, slabQ, slabW + (W - R), W, nullptr, partY, nullptr, R, nct, 0};
   d.Vy = slabV + (W - R);
+  d.Wy = W;
   const dim3 grid((unsigned)nct, (unsigned)((n_pad + tile_rows - 1) / tile_rows));
   switch (R) {
     case 1: hipLaunchKernelGGL((k_sums_fused<T, 1>), grid, dim3(256), 0, s, d); break;
@@ -611,6 +650,62 @@ hipError_t launch_sums_fused(int R, T* S, int64_t ldp, int64_t n_pad, int tile_r
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+template <typename T, int RY>
+hipError_t krylov_step_r(int R, const FusedDesc<T>& dx, const FusedDesc<T>& dy, hipStream_t s) {
+  const int nsx = (dx.n_pad + dx.tile_rows - 1) / dx.tile_rows, nsy = (dy.n_pad + dy.tile_rows - 1) / dy.tile_rows;
+  const dim3 grid((unsigned)dx.nct, (unsigned)(nsx + nsy));
+#define LV_STEP_CASE(RR)                                                                      \
+  case RR:                                                                                    \
+    if constexpr (RR >= RY) {                                                                 \
+      hipLaunchKernelGGL((k_krylov_step<T, RR, RY>), grid, dim3(256), 0, s, dx, dy, nsx);     \
+      return hipGetLastError();                                                               \
+    }                                                                                         \
+    return hipErrorInvalidValue;
+  switch (R) {
+    LV_STEP_CASE(1) LV_STEP_CASE(2) LV_STEP_CASE(4) LV_STEP_CASE(8) LV_STEP_CASE(16)
+    default: return hipErrorInvalidValue;
+  }
+#undef LV_STEP_CASE
+}
+
+template <typename T>
+hipError_t launch_krylov_step(int R, int RY, const T* Pa, T* Pb, int64_t ldp, int64_t n_pad, int rows_x, int rows_y,
+                              const T* M, const T* Ub, const T* Vb, int Wb, const T* Va, int Wa, T* partX, T* partY,
+                              double* partG, hipStream_t s) {
+  FusedDesc<T> dx = fused_desc<T>(RY, const_cast<T*>(Pa), ldp, n_pad, rows_x, M, nullptr, Wb, partX, nullptr, partG);
+  FusedDesc<T> dy = fused_desc<T>(RY, Pb, ldp, n_pad, rows_y, Ub, Vb, Wb, nullptr, partY, nullptr);
+  dx.Vy = dy.Vy = Va;
+  dx.Wy = dy.Wy = Wa;
+  switch (RY) {
+    case 1: return krylov_step_r<T, 1>(R, dx, dy, s);
+    case 2: return krylov_step_r<T, 2>(R, dx, dy, s);
+    case 4: return krylov_step_r<T, 4>(R, dx, dy, s);
+    case 8: return krylov_step_r<T, 8>(R, dx, dy, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T>
+hipError_t launch_fused_xgram(int R, const T* P, int64_t ldp, int64_t n_pad, int tile_rows, const T* U, int W,
+                              const T* V, int Wv, T* partX, T* partY, double* partG, hipStream_t s) {
+  // P is not written; Y takes the factors' stride, so it needs V beside U
+  FusedDesc<T> d = fused_desc<T>(R, const_cast<T*>(P), ldp, n_pad, tile_rows, U, V, W, partX, partY, partG);
+  if (partY != nullptr && W != Wv) return hipErrorInvalidValue;
+  d.Vy = V;
+  d.Wy = Wv;
+  const dim3 grid((unsigned)d.nct, (unsigned)((n_pad + tile_rows - 1) / tile_rows));
+#define LV_XGRAM_CASE(RR)                                                                                     \
+  case RR:                                                                                                    \
+    if (partY != nullptr) hipLaunchKernelGGL((k_fused_xgram<T, RR, true>), grid, dim3(256), 0, s, d);         \
+    else hipLaunchKernelGGL((k_fused_xgram<T, RR, false>), grid, dim3(256), 0, s, d);                         \
+    return hipGetLastError();
+  switch (R) {
+    LV_XGRAM_CASE(1) LV_XGRAM_CASE(2) LV_XGRAM_CASE(4) LV_XGRAM_CASE(8)
+    default: return hipErrorInvalidValue;
+  }
+#undef LV_XGRAM_CASE
 }
 
 template <typename T>
@@ -678,6 +773,14 @@ template hipError_t launch_sums_fused<float>(int, float*, int64_t, int64_t, int,
                                              const float*, int, float*, hipStream_t);
 template hipError_t launch_sums_fused<double>(int, double*, int64_t, int64_t, int, const double*, const double*,
                                               const double*, int, double*, hipStream_t);
+#define LV_INST(T)                                                                                                \
+  template hipError_t launch_krylov_step<T>(int, int, const T*, T*, int64_t, int64_t, int, int, const T*, const T*,    \
+                                            const T*, int, const T*, int, T*, T*, double*, hipStream_t);          \
+  template hipError_t launch_fused_xgram<T>(int, const T*, int64_t, int64_t, int, const T*, int, const T*, int, T*, T*, \
+                                            double*, hipStream_t);
+LV_INST(float)
+LV_INST(double)
+#undef LV_INST
 template hipError_t launch_fused_multi<float>(int, bool, const FusedDesc<float>*, int, int, hipStream_t);
 template hipError_t launch_fused_multi<double>(int, bool, const FusedDesc<double>*, int, int, hipStream_t);
 

@@ -141,11 +141,65 @@ k_gfac_z(const double* __restrict__ a, const T* __restrict__ Zt, int wy, const d
   Ztnew[idx] = z;
 }
 
+// Partial V^T T_i over a tile of rows (blockIdx.x) for T_i (blockIdx.z), double:
+// pairs (a, b) of V's and T's columns over the threads; below 256 pairs the
+// threads form groups that take every group-th row and meet in LDS.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_vtt(const T* __restrict__ V, int R, const T* __restrict__ Tm, int64_t tstride, int pp, int rows,
+      double* __restrict__ part) {
+  __shared__ double sums[256];
+  const int pairs = R * pp, tid = threadIdx.x;
+  const int per = pairs < 256 ? pairs : 256, groups = 256 / per;
+  const int pair = (int)blockIdx.y * 256 + tid % per, grp = tid / per;
+  const int64_t r0 = (int64_t)blockIdx.x * rows;
+  Tm += blockIdx.z * tstride;
+  double acc = 0.0;
+  if (pair < pairs && grp < groups) {
+    const int a = pair / pp, b = pair % pp;
+#pragma unroll 8
+    for (int i = grp; i < rows; i += groups)
+      acc = fma((double)V[(r0 + i) * R + a], (double)Tm[(r0 + i) * pp + b], acc);
+  }
+  sums[tid] = acc;
+  __syncthreads();
+  if (tid < per && pair < pairs) {
+    for (int g = 1; g < groups; ++g) acc += sums[g * per + tid];
+    part[((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * pairs + pair] = acc;
+  }
+}
+
+// Z block (cnt - 1 - i) = sum over the tiles of part (i = blockIdx.y).
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_vtt_sum(const double* __restrict__ part, int tiles, int pairs, T* __restrict__ Z) {
+  const int pair = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (pair >= pairs) return;
+  const double* src = part + (int64_t)blockIdx.y * tiles * pairs + pair;
+  double z = 0.0;
+  int t = 0;
+  for (; t + 16 <= tiles; t += 16) {
+    double v[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = src[(int64_t)(t + e) * pairs];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) z += v[e];
+  }
+#pragma unroll 4
+  for (; t < tiles; ++t) z += src[(int64_t)t * pairs];
+  Z[(int64_t)(gridDim.y - 1 - blockIdx.y) * pairs + pair] = (T)z;
+}
+
 // Tm[row][col] += sum_c Y[row][c] Zt[c][col] (double), one thread per element.
+// Several T in one launch (gridDim.y = cnt): T_{i+1} = Tm + i tstride takes
+// the first (i + 1) w columns of Y and Zt from row (cnt - 1 - i) w on.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_rank_rect(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __restrict__ Zt, int w, int64_t n_pad,
-            int pp) {
+            int pp, int64_t tstride) {
+  Tm += blockIdx.y * tstride;
+  Zt += (int64_t)(gridDim.y - 1 - blockIdx.y) * w * pp;
+  w *= (int)blockIdx.y + 1;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= n_pad * pp) return;
   const int64_t row = idx / pp;
@@ -161,8 +215,11 @@ k_rank_rect(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __rest
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_rank_rect4(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __restrict__ Zt, int w, int64_t n_pad,
-             int pp) {
+             int pp, int64_t tstride) {
   typedef T v4 __attribute__((ext_vector_type(4)));
+  Tm += blockIdx.y * tstride;
+  Zt += (int64_t)(gridDim.y - 1 - blockIdx.y) * w * pp;
+  w *= (int)blockIdx.y + 1;
   const int q4 = pp / 4;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= (n_pad / 4) * q4) return;
@@ -214,14 +271,28 @@ hipError_t launch_gfac_z(const double* a, const T* Zt, int wy, const double* b, 
 }
 
 template <typename T>
-hipError_t launch_rank_rect(T* Tm, const T* Y, int sy, const T* Zt, int w, int64_t n_pad, int pp, hipStream_t s) {
+hipError_t launch_rank_rect(T* Tm, const T* Y, int sy, const T* Zt, int w, int64_t n_pad, int pp, hipStream_t s,
+                            int cnt, int64_t tstride) {
   if (pp % 4 == 0 && n_pad % 4 == 0) {
-    hipLaunchKernelGGL((k_rank_rect4<T>), dim3((unsigned)((n_pad / 4 * (pp / 4) + 255) / 256)), dim3(256), 0, s, Tm,
-                       Y, sy, Zt, w, n_pad, pp);
+    hipLaunchKernelGGL((k_rank_rect4<T>), dim3((unsigned)((n_pad / 4 * (pp / 4) + 255) / 256), (unsigned)cnt), dim3(256),
+                       0, s, Tm, Y, sy, Zt, w, n_pad, pp, tstride);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((k_rank_rect<T>), dim3((unsigned)((n_pad * pp + 255) / 256)), dim3(256), 0, s, Tm, Y, sy, Zt, w,
-                     n_pad, pp);
+  hipLaunchKernelGGL((k_rank_rect<T>), dim3((unsigned)((n_pad * pp + 255) / 256), (unsigned)cnt), dim3(256), 0, s, Tm,
+                     Y, sy, Zt, w, n_pad, pp, tstride);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_vtt(int R, int pp, const T* V, const T* Tm, int64_t tstride, int cnt, int64_t n_pad, double* part,
+                      T* Z, hipStream_t s) {
+  const int pairs = R * pp, tiles = vtt_tiles(n_pad, pairs);
+  const unsigned cols = (unsigned)((pairs + 255) / 256);
+  hipLaunchKernelGGL((k_vtt<T>), dim3((unsigned)tiles, cols, (unsigned)cnt), dim3(256), 0, s, V, R, Tm, tstride, pp,
+                     vtt_rows(pairs), part);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_vtt_sum<T>), dim3(cols, (unsigned)cnt), dim3(256), 0, s, part, tiles, pairs, Z);
   return hipGetLastError();
 }
 
@@ -277,7 +348,9 @@ LV_INST(double)
                                        T*, int, int64_t, hipStream_t);                                         \
   template hipError_t launch_gfac_z<T>(const double*, const T*, int, const double*, int, T*, int, int,         \
                                        hipStream_t);                                                           \
-  template hipError_t launch_rank_rect<T>(T*, const T*, int, const T*, int, int64_t, int, hipStream_t);
+  template hipError_t launch_rank_rect<T>(T*, const T*, int, const T*, int, int64_t, int, hipStream_t, int,    \
+                                          int64_t);                                                            \
+  template hipError_t launch_vtt<T>(int, int, const T*, const T*, int64_t, int, int64_t, double*, T*, hipStream_t);
 LV_INST(float)
 LV_INST(double)
 #undef LV_INST

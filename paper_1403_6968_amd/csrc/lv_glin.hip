@@ -8,6 +8,10 @@
 //   incremental    Delta T_i = Y_i Z_i^T, Y_1 = U, Z_1 = T_0^T V,
 //                  Y_i = [U, A Y_{i-1} + U (V^T Y_{i-1})], Z_i = [T_{i-1}^T V, Z_{i-1}]
 //                  (old A and T; widths i r), then every T_i += Y_i Z_i^T;
+//                  with f(M) = A M + U (V^T M), Y_i = [U, f(U), f(f(U)), ..]
+//                  holds Y_{i-1} as its first columns, so each step forms
+//                  only f of the last r columns, and one slab of k r columns
+//                  serves every T_i;
 // and A += U V^T after the hybrid and incremental steps.  Products with A
 // run as read-only passes (width <= 128; from 16 on the float matrix cores)
 // or, for wide operands (p > 64), on the MFMA GEMM.
@@ -59,12 +63,9 @@ struct lv_glin {
   int64_t n, n_pad;
   int k, p, pp, r_max, r_pad, elem, nct, strategy, maxw;
   lv_mode mode;
-  size_t A, Tb, Bb, D[2], sU, sV, partX, partY, full, atbA, atbG, Yb, Zb, A64, gT[2], gB, total;
+  size_t A, Tb, Bb, D[2], sU, sV, partX, partY, full, atbA, atbG, Y, Z, A64, gT[2], gB, total;
   size_t Toff(int i) const { return Tb + (size_t)i * align_up((size_t)n_pad * pp * elem); }
-  int wy(int i) const { return i * r_pad; }                         // width of Y_i, Z_i
-  int WY(int i) const { return (int)next_pow2(wy(i)); }
-  size_t Yoff(int i) const { return Yb + (size_t)(i - 2) * align_up((size_t)n_pad * maxw * elem); }   // i >= 2
-  size_t Zoff(int i) const { return Zb + (size_t)(i - 1) * align_up((size_t)maxw * pp * elem); }
+  int64_t Tstride() const { return (int64_t)(align_up((size_t)n_pad * pp * elem) / elem); }
   char* base = nullptr;
   int64_t updates = 0;
   template <typename T> T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
@@ -95,7 +96,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.nct = (int)(g.n_pad / tile_cols_bytes(g.elem));
   g.maxw = strategy == LV_GLIN_INCR ? (int)next_pow2((int64_t)k * g.r_pad) : 1;
   const size_t e = g.elem, np = g.n_pad, pp = g.pp;
-  const int xw = strategy == LV_GLIN_INCR ? g.maxw : (g.pp <= kGlinNarrow ? g.pp : 1);   // read-only pass width
+  const int xw = strategy == LV_GLIN_INCR ? g.r_pad : (g.pp <= kGlinNarrow ? g.pp : 1);   // read-only pass width
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
   g.A = take(np * np * e);
@@ -106,16 +107,18 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.sV = take(np * g.r_pad * e);
   g.partX = take((size_t)g.nct * np * xw * e);
   g.partY = take(np * slice_cols(g.n_pad, g.elem, xw) * e);
-  g.atbA = take((np / kAtbRows) * g.r_pad * pp * sizeof(double));
-  g.D[0] = g.D[1] = g.full = g.atbG = g.Yb = g.Zb = 0;
+  const size_t pairs = (size_t)g.r_pad * pp;
+  g.atbA = take((strategy == LV_GLIN_INCR ? (size_t)k * vtt_tiles(g.n_pad, (int)pairs) : np / kAtbRows) * pairs *
+                sizeof(double));
+  g.D[0] = g.D[1] = g.full = g.atbG = g.Y = g.Z = 0;
   if (strategy == LV_GLIN_HYBRID) { g.D[0] = take(np * pp * e); g.D[1] = take(np * pp * e); }
   if (strategy != LV_GLIN_INCR && g.pp > kGlinNarrow) g.full = take(np * pp * e);
   if (strategy == LV_GLIN_INCR) {
-    g.atbG = take((np / kAtbRows) * g.r_pad * g.maxw * sizeof(double));
-    g.Yb = off;
-    for (int i = 2; i <= k; ++i) take(np * g.maxw * e);
-    g.Zb = off;
-    for (int i = 1; i <= k; ++i) take((size_t)g.maxw * pp * e);
+    // Gram partials of a step: one per 64 rows, or per slice of the pass
+    const size_t ng = np / kAtbRows * g.r_pad * g.r_pad, nk = gram_partials(g.n_pad, g.elem, kMaxKrylovCols);
+    g.atbG = take((ng > nk ? ng : nk) * sizeof(double));
+    g.Y = take(np * g.maxw * e);                            // f^q(U) in columns q r .. q r + r - 1
+    g.Z = take((size_t)k * g.r_pad * pp * e);               // V^T T_i in rows (k - 1 - i) r ..
   }
   g.A64 = take(mode == LV_FP32 ? np * np * sizeof(double) : 0);
   g.gT[0] = take(np * pp * sizeof(double));
@@ -225,31 +228,35 @@ lv_status glin_update(lv_glin* g, const T* U, const T* V, int r, int64_t ldu, in
     }
     return st == LV_OK ? update_A() : st;
   }
-  // incremental: Z_1^T = V^T T_0, Y_1 = U; then Y_i, Z_i; then every T_i += Y_i Z_i^T
-  st = hip_check(launch_atb<T>(R, pp, sV, R, g->at<T>(g->Toff(0)), pp, np, g->d64(g->atbA), s), "V^T T_0");
-  if (st == LV_OK)
-    st = hip_check(launch_gfac_z<T>(g->d64(g->atbA), nullptr, 0, nullptr, R, g->at<T>(g->Zoff(1)), g->WY(1), pp, s),
-                   "Z_1");
-  for (int i = 2; i <= g->k && st == LV_OK; ++i) {
-    const T* Yp = i == 2 ? sU : g->at<T>(g->Yoff(i - 1));
-    const int sp = i == 2 ? R : g->WY(i - 1);
-    st = glin_amul<T>(g, Yp, g->WY(i - 1), sp, s, &nct);
+  // incremental: Z (every V^T T_i, i < k, from the old T), then the columns
+  // f^q(U), then every T_i += Y_i Z_i^T with Y_i the first i r columns of Y and
+  // Z_i^T the last i r rows of Z
+  const int k = g->k, W = g->maxw;
+  T* Y = g->at<T>(g->Y);
+  T* Z = g->at<T>(g->Z);
+  double* G = g->d64(g->atbG);
+  st = hip_check(launch_vtt<T>(R, pp, sV, g->at<T>(g->Toff(0)), g->Tstride(), k, np, g->d64(g->atbA), Z, s), "V^T T");
+  const int rows = slice_rows(np, g->elem, R, false, kTileRows);
+  for (int q = 1; q < k && st == LV_OK; ++q) {
+    const T* M = q == 1 ? sU : Y + (q - 1) * R;
+    const int sm = q == 1 ? R : W;
+    int ng = 1;
+    if (R <= kMaxKrylovCols) {
+      ng = (int)((np + rows - 1) / rows);
+      nct = g->nct;
+      st = hip_check(launch_fused_xgram<T>(R, g->at<T>(g->A), np, np, rows, M, sm, sV, R, g->at<T>(g->partX), nullptr,
+                                           G, s), "A M, V^T M");
+    } else {
+      st = glin_amul<T>(g, M, R, sm, s, &nct);
+      if (st == LV_OK) st = hip_check(launch_atb<T>(R, R, sV, R, M, sm, np, G, s), "V^T M");
+    }
     if (st == LV_OK)
-      st = hip_check(launch_atb<T>(R, g->WY(i - 1), sV, R, Yp, sp, np, g->d64(g->atbG), s), "V^T Y");
-    if (st == LV_OK)
-      st = hip_check(launch_atb<T>(R, pp, sV, R, g->at<T>(g->Toff(i - 1)), pp, np, g->d64(g->atbA), s), "V^T T");
-    if (st == LV_OK)
-      st = hip_check(launch_gfac_y<T>(g->at<T>(g->partX), nct, g->WY(i - 1), sU, nullptr, R, R, g->d64(g->atbG),
-                                      g->WY(i - 1), g->wy(i - 1), g->at<T>(g->Yoff(i)), g->WY(i), np, s),
-                     "Y");
-    if (st == LV_OK)
-      st = hip_check(launch_gfac_z<T>(g->d64(g->atbA), g->at<T>(g->Zoff(i - 1)), g->wy(i - 1), nullptr, R,
-                                      g->at<T>(g->Zoff(i)), g->WY(i), pp, s),
-                     "Z");
+      st = hip_check(launch_krylov_tail<T>(R, g->at<T>(g->partX), nct, nullptr, 0, G, ng, sU, R, q == 1 ? sU : nullptr,
+                                           nullptr, R, q * R, Y, nullptr, W, np, s), "Y");
   }
-  for (int i = 1; i <= g->k && st == LV_OK; ++i)
-    st = hip_check(launch_rank_rect<T>(g->at<T>(g->Toff(i)), i == 1 ? sU : g->at<T>(g->Yoff(i)), i == 1 ? R : g->WY(i),
-                                       g->at<T>(g->Zoff(i)), g->wy(i), np, pp, s),
+  if (st == LV_OK)
+    st = hip_check(launch_rank_rect<T>(g->at<T>(g->Toff(1)), k == 1 ? sU : Y, k == 1 ? R : W, Z, R, np, pp, s, k,
+                                       g->Tstride()),
                    "T += Y Z^T");
   return st == LV_OK ? update_A() : st;
 }

@@ -75,7 +75,8 @@ template <typename T> struct FusedDesc {
   int nct; int block_begin;             // blocks: nct x ceil(n_pad / tile_rows)
   const T* Ux = nullptr;                // extra X operand (powers' pass of a view with sums)
   T* partX2 = nullptr;                  //   and its partials
-  const T* Vy = nullptr;                // Y operand of the sums pass
+  const T* Vy = nullptr; int Wy = 0;    // Y operand of the passes that update with other factors (row stride
+                                        //   Wy); V operand of the Gram in the read-only passes that form it
   const T* Ud = nullptr; int Wd = 0;    // general form: extra X operand (row stride Wd)
   T* partX3 = nullptr;                  //   and its partials
   Strides vs = {};                      // several updates in one pass
@@ -350,6 +351,36 @@ hipError_t launch_level_fused_x(int R, T* P, int64_t ldp, int64_t n_pad, int til
 template <typename T>
 hipError_t launch_sums_fused(int R, T* S, int64_t ldp, int64_t n_pad, int tile_rows, const T* slabQ,
                              const T* slabW, const T* slabV, int W, T* partY, hipStream_t s);
+// One launch for a step of the linear and skip models (RY <= 8 columns, R <=
+// 16, powers of two, RY <= R): partial X = P_a M and the Gram partials
+// V_a^T M (one per slice, RY x RY doubles) with M RY columns of row stride
+// Wb; partial Y = P_b^T V_a with the old P_b and P_b += U_b V_b^T (R columns,
+// row stride Wb), P_b read and written once.  V_a has row stride Wa; rows_x,
+// rows_y are the rows per slice of the two passes.
+template <typename T>
+hipError_t launch_krylov_step(int R, int RY, const T* Pa, T* Pb, int64_t ldp, int64_t n_pad, int rows_x, int rows_y,
+                              const T* M, const T* Ub, const T* Vb, int Wb, const T* Va, int Wa, T* partX, T* partY,
+                              double* partG, hipStream_t s);
+// Read-only, R <= 8: partial X = P U (row stride W), the Gram partials of
+// V^T U (row stride Wv; one per slice, R x R doubles) and, with a non-null
+// partY (Wv = W), partial Y = P^T V.
+template <typename T>
+hipError_t launch_fused_xgram(int R, const T* P, int64_t ldp, int64_t n_pad, int tile_rows, const T* U, int W,
+                              const T* V, int Wv, T* partX, T* partY, double* partG, hipStream_t s);
+// The next factor block of a model whose products share their left operand
+// (U_c = [U_b, f(last wa columns of U_b)], f(M) = P_a M + U_a (V_a^T M); V_c =
+// [P_b^T V_a, V_b]): per row, wa columns of X (nct partials [nct][n_pad][wa])
+// plus U_a G, with G the sum of ng partials (wa x wa doubles, wa <= 8 if
+// ng > 1), go to Uc + wb; with Ub non-null U_b (wb columns) goes before them;
+// with Vc non-null wa columns of Y (nrt partials [nrt][n_pad][wa]) go to Vc,
+// V_b after them, and zeros to columns wa + wb .. Wc - 1 of Uc and Vc.  Row
+// strides: Ua Wa, Ub and Vb Wb, Uc and Vc Wc.
+constexpr int kMaxKrylovCols = 8;     // columns that the vector passes of these steps take
+template <typename T>
+hipError_t launch_krylov_tail(int wa, const T* partX, int nct, const T* partY, int nrt, const double* partG, int ng,
+                              const T* Ua, int Wa, const T* Ub, const T* Vb, int Wb, int wb, T* Uc, T* Vc, int Wc,
+                              int64_t n_pad, hipStream_t s);
+
 // G = Vop^T Uop (R x R, double) into partG[0 .. R*R), operands given by
 // their first columns (row stride W).
 template <typename T>
@@ -399,8 +430,19 @@ template <typename T>
 hipError_t launch_gfac_z(const double* a, const T* Zt, int wy, const double* b, int R, T* Ztnew, int WYn, int pp,
                          hipStream_t s);
 // Tm (n_pad x pp) += Y (w columns, row stride sy) Zt (w x pp), double sums.
+// cnt > 1: for i = 0 .. cnt - 1, Tm + i tstride, the first (i + 1) w columns
+// of Y, and Zt from row (cnt - 1 - i) w on.
 template <typename T>
-hipError_t launch_rank_rect(T* Tm, const T* Y, int sy, const T* Zt, int w, int64_t n_pad, int pp, hipStream_t s);
+hipError_t launch_rank_rect(T* Tm, const T* Y, int sy, const T* Zt, int w, int64_t n_pad, int pp, hipStream_t s,
+                            int cnt = 1, int64_t tstride = 0);
+// Z (cnt R x pp, rows in blocks of R): block cnt - 1 - i = V^T T_i for T_i =
+// Tm + i tstride (n_pad x pp), V n_pad x R; part holds cnt vtt_tiles(n_pad, R
+// pp) R pp doubles.
+inline int vtt_rows(int pairs) { return pairs < 256 ? 256 : 64; }
+inline int vtt_tiles(int64_t n_pad, int pairs) { return (int)(n_pad / vtt_rows(pairs)); }
+template <typename T>
+hipError_t launch_vtt(int R, int pp, const T* V, const T* Tm, int64_t tstride, int cnt, int64_t n_pad, double* part,
+                      T* Z, hipStream_t s);
 // G[0 .. count) = sum over t < ng of G[t count + ...] (fixed order).
 hipError_t launch_gram_sum(double* G, int ng, int count, hipStream_t s);
 
