@@ -21,6 +21,8 @@ constexpr int kMaxFusedRank = 16;
 // its 16-byte column group per step (it fixes which wave sums which rows of
 // Y, so it is the same at every rank).
 constexpr int kFusedRowBlock = 4;
+// Memory-side cache of the device (bytes).
+constexpr int64_t kCacheBytes = int64_t(256) << 20;
 // Largest level of the exponential model (k <= 2^kMaxLevel).
 constexpr int kMaxLevel = 10;
 // Pipelined batches: at most this many stage streams and factor-slab slots
