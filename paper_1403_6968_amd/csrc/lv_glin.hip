@@ -106,7 +106,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.sU = take(np * g.r_pad * e);
   g.sV = take(np * g.r_pad * e);
   g.partX = take((size_t)g.nct * np * xw * e);
-  g.partY = take(np * slice_cols(g.n_pad, g.elem, xw) * e);
+  g.partY = take(np * slice_cols(g.n_pad, g.elem, xw, false, true) * e);
   const size_t pairs = (size_t)g.r_pad * pp;
   g.atbA = take((strategy == LV_GLIN_INCR ? (size_t)k * vtt_tiles(g.n_pad, (int)pairs) : np / kAtbRows) * pairs *
                 sizeof(double));
@@ -115,7 +115,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   if (strategy != LV_GLIN_INCR && g.pp > kGlinNarrow) g.full = take(np * pp * e);
   if (strategy == LV_GLIN_INCR) {
     // Gram partials of a step: one per 64 rows, or per slice of the pass
-    const size_t ng = np / kAtbRows * g.r_pad * g.r_pad, nk = gram_partials(g.n_pad, g.elem, kMaxKrylovCols);
+    const size_t ng = np / kAtbRows * g.r_pad * g.r_pad, nk = gram_partials(g.n_pad, g.elem, kMaxKrylovCols, false, true);
     g.atbG = take((ng > nk ? ng : nk) * sizeof(double));
     g.Y = take(np * g.maxw * e);                            // f^q(U) in columns q r .. q r + r - 1
     g.Z = take((size_t)k * g.r_pad * pp * e);               // V^T T_i in rows (k - 1 - i) r ..
@@ -167,7 +167,7 @@ lv_status glin_amul(lv_glin* g, const T* M, int w, int sm, hipStream_t s, int* n
     return hip_check(launch_gemm_rect<T>(g->at<T>(g->A), np, M, sm, g->at<T>(g->full), g->pp, np, w, np, s), "A M");
   }
   *nct_out = g->nct;
-  const int rows = slice_rows(np, g->elem, w, skinny_on_mfma(w, g->elem), kTileRows);
+  const int rows = slice_rows(np, g->elem, w, skinny_on_mfma(w, g->elem), kTileRows, true);
   if (skinny_on_mfma(w, (int)sizeof(T)))
     return hip_check(launch_skinny_f32(w, reinterpret_cast<const float*>(g->at<T>(g->A)), np, np, rows,
                                        reinterpret_cast<const float*>(M), reinterpret_cast<const float*>(M), sm,
@@ -236,7 +236,7 @@ lv_status glin_update(lv_glin* g, const T* U, const T* V, int r, int64_t ldu, in
   T* Z = g->at<T>(g->Z);
   double* G = g->d64(g->atbG);
   st = hip_check(launch_vtt<T>(R, pp, sV, g->at<T>(g->Toff(0)), g->Tstride(), k, np, g->d64(g->atbA), Z, s), "V^T T");
-  const int rows = slice_rows(np, g->elem, R, false, kTileRows);
+  const int rows = slice_rows(np, g->elem, R, false, kTileRows, true);
   for (int q = 1; q < k && st == LV_OK; ++q) {
     const T* M = q == 1 ? sU : Y + (q - 1) * R;
     const int sm = q == 1 ? R : W;

@@ -202,18 +202,25 @@ inline bool sums_fused(int R, int elem) { return R <= kMaxFusedRank && !skinny_o
 // views fill the device anyway and lose by finer slices (32 views of 512 to
 // 4096: 2.34 ms with tuned heights, 2.52 ms when every height was cut).
 constexpr int kTileRows = 512;      // default rows per tile of a level pass
+//
+// Twice as many work-groups for passes that only read (`reads`) and for 128
+// and more bytes of factors per row, whose long row blocks leave one wave per
+// SIMD waiting: OLS row change n = 4096 63 -> 60 us, IncrLin n = 5000 1.63 -> 1.56
+// ms, FP64 rank-3 batch n = 3001 1.90 -> 1.81 ms; the other updating passes
+// lose by it (FP32 update n = 4194 217 -> 228 us).
 constexpr int kFillBlocks = 256;
-inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, int tile_rows) {
+inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, int tile_rows, bool reads = false) {
   if (tile_rows != kTileRows) return tile_rows;
   const int unit = cores ? 64 : 4 * kFusedRowBlock;
   const int64_t nct = n_pad / tile_cols_bytes(elem);
-  const int64_t ns = (kFillBlocks + nct - 1) / nct;
+  const int64_t fill = reads || R * elem >= 128 ? 2 * kFillBlocks : kFillBlocks;
+  const int64_t ns = (fill + nct - 1) / nct;
   int64_t rows = round_up((n_pad + ns - 1) / ns, unit);
   if (rows < 8 * R) rows = round_up(8 * R, unit);
   return rows < tile_rows ? (int)rows : tile_rows;
 }
-inline int slice_count(int64_t n_pad, int elem, int R, bool cores, int tile_rows) {
-  const int rows = slice_rows(n_pad, elem, R, cores, tile_rows);
+inline int slice_count(int64_t n_pad, int elem, int R, bool cores, int tile_rows, bool reads = false) {
+  const int rows = slice_rows(n_pad, elem, R, cores, tile_rows, reads);
   return (int)((n_pad + rows - 1) / rows);
 }
 

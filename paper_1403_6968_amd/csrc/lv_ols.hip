@@ -188,11 +188,13 @@ k_ols_vectors(const T* __restrict__ partX, int nct, const T* __restrict__ partY,
   const int lr = (int)threadIdx.x >> 2, q = (int)threadIdx.x & 3;
   const int64_t j = (int64_t)blockIdx.x * kVecRows + lr;      // n_pad is a multiple of 256
   double x0 = 0.0, x1 = 0.0, x2 = 0.0, y0 = 0.0, y1 = 0.0;
+#pragma unroll 4
   for (int t = q; t < nct; t += 4) {
     double r[4];
     load4(partX + ((int64_t)t * n_pad + j) * 4, r);
     x0 += r[0]; x1 += r[1]; x2 += r[2];
   }
+#pragma unroll 4
   for (int t = q; t < nrt; t += 4) {
     double r[4];
     load4(partY + ((int64_t)t * n_pad + j) * 4, r);
@@ -226,20 +228,22 @@ k_ols_vectors(const T* __restrict__ partX, int nct, const T* __restrict__ partY,
   if (threadIdx.x < 4) dpart[blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// out[b] = sum over i < nblk of part[i * stride + b] for b = blockIdx.x:
-// 256 threads sum strided subsets, then a fixed-order tree.
-__global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__ part, int nblk, int stride,
-                                                      double* __restrict__ out) {
-  __shared__ double red[256];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < nblk; i += 256) acc += part[(int64_t)i * stride + blockIdx.x];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = 128; w >= 1; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
+// out[b] = sum over i < nblk of part[i * stride + b] for b < cnt, formed by
+// every work-group that needs the sums (a launch of its own would cost more
+// than the few partials do): each wave takes every fourth b, its lanes strided
+// subsets that a butterfly adds, in one order for every work-group.
+__device__ __forceinline__ void block_sums(const double* __restrict__ part, const int nblk, const int stride,
+                                           const int cnt, double* out) {
+  const int lane = (int)threadIdx.x & 63;
+  for (int b = wave_id(); b < cnt; b += 4) {
+    double acc = 0.0;
+#pragma unroll 2
+    for (int i = lane; i < nblk; i += 64) acc += part[(int64_t)i * stride + b];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+    if (lane == 0) out[b] = acc;
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = red[0];
+  __syncthreads();
 }
 
 // Update factors R = [r1, r2], S = [s1, s2] of Delta W, with the dots
@@ -253,10 +257,12 @@ __global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__
 // (rounded) S: spart[blk][e * pp + c], spart[blk][2 pp + e].
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_ols_rs(const double* __restrict__ vec, const double* __restrict__ dots, T* __restrict__ Rs,
+k_ols_rs(const double* __restrict__ vec, const double* __restrict__ dpart, int nvb, T* __restrict__ Rs,
          T* __restrict__ Ss, const T* __restrict__ C, const T* __restrict__ v, int pp, double* __restrict__ spart) {
   __shared__ double ls[2][256];
   __shared__ double red[2][256];
+  __shared__ double dots[4];
+  block_sums(dpart, nvb, 4, 4, dots);
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const double l1 = -1.0 / (1.0 + dots[0]);
   const double l2 = -1.0 / (1.0 + dots[3] + l1 * dots[2] * dots[1]);
@@ -314,9 +320,11 @@ k_ols_rs(const double* __restrict__ vec, const double* __restrict__ dots, T* __r
 // u = e_row) the thread of column 0 also applies X[row][j] += v[j].
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_ols_beta(const T* __restrict__ Rs, const double* __restrict__ vec, const double* __restrict__ st,
+k_ols_beta(const T* __restrict__ Rs, const double* __restrict__ vec, const double* __restrict__ spart, int nsb,
            const double* __restrict__ uy, const T* __restrict__ v, T* __restrict__ beta, T* __restrict__ C,
            int64_t n_pad, int pp, T* __restrict__ X, int64_t row) {
+  __shared__ double st[2 * kOlsMaxCols + 2];
+  block_sums(spart, nsb, 2 * pp + 2, 2 * pp + 2, st);
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n_pad * pp; e += (int64_t)gridDim.x * 256) {
     const int64_t j = e / pp;
     const int c = (int)(e % pp);
@@ -372,7 +380,7 @@ struct lv_ols {
   int pp, elem, nct, nrt, rows;   // rows: per slice of the pass over W
   lv_mode mode;
   size_t X, Y, W, C, beta, ubuf, vbuf, Pk, Qk, Rs, Ss, partX, partY, vec;
-  size_t pXu, pUu, pUy, dpart, spart, sums, red;
+  size_t pXu, pUu, pUy, dpart, spart, red;
   size_t Z, Xk, Xn, Tk, C64, B64;
   size_t total;
   char* base;
@@ -399,7 +407,7 @@ void layout_ols(lv_ols& o, int64_t m, int64_t n, int64_t p, lv_mode mode) {
   o.n_pad = round_up(n, kPadOrder);
   o.pp = (int)next_pow2(p);
   o.nct = (int)(o.n_pad / tile_cols_bytes(o.elem));
-  o.rows = slice_rows(o.n_pad, o.elem, 4, false, kTileRows);
+  o.rows = slice_rows(o.n_pad, o.elem, 4, false, kTileRows, true);
   o.nrt = (int)((o.n_pad + o.rows - 1) / o.rows);
   const size_t e = o.elem, np = o.n_pad, mp = o.m_pad, pp = o.pp;
   size_t off = 0;
@@ -422,7 +430,6 @@ void layout_ols(lv_ols& o, int64_t m, int64_t n, int64_t p, lv_mode mode) {
   o.pUu = take((mp / kAtbRows) * sizeof(double));
   o.pUy = take((mp / kAtbRows) * pp * sizeof(double));
   o.dpart = take((np / kVecRows) * 4 * sizeof(double));
-  o.sums = take((8 + 2 * kOlsMaxCols + 2) * sizeof(double));
   o.spart = take((np / 256) * (2 * pp + 2) * sizeof(double));
   o.red = take((kRedBlocks + 8) * sizeof(double));
   o.Z = take(np * np * sizeof(double));
@@ -542,19 +549,19 @@ lv_status ols_update(lv_ols* o, int64_t row, const T* dx, hipStream_t s) {
   const int nvb = (int)(np / kVecRows);
   hipLaunchKernelGGL((k_ols_vectors<T>), dim3((unsigned)nvb), dim3(256), 0, s, o->at<T>(o->partX), o->nct,
                      o->at<T>(o->partY), o->nrt, np, o->at<T>(o->Pk), o->at<T>(o->Qk), o->d(o->vec), o->d(o->dpart));
-  hipLaunchKernelGGL(k_sum_partials, dim3(4), dim3(256), 0, s, o->d(o->dpart), nvb, 4, o->d(o->sums));
-  hipLaunchKernelGGL((k_ols_rs<T>), dim3(gv), dim3(256), 0, s, o->d(o->vec), o->d(o->sums),
-                     o->at<T>(o->Rs), o->at<T>(o->Ss), o->at<T>(o->C), o->at<T>(o->vbuf), pp, o->d(o->spart));
+  hipLaunchKernelGGL((k_ols_rs<T>), dim3(gv), dim3(256), 0, s, o->d(o->vec), o->d(o->dpart),
+                     nvb, o->at<T>(o->Rs), o->at<T>(o->Ss), o->at<T>(o->C), o->at<T>(o->vbuf), pp, o->d(o->spart));
   st = hip_check(hipGetLastError(), "Sherman-Morrison factors");
   if (st == LV_OK)
     st = hip_check(launch_level_update<T>(2, o->at<T>(o->W), np, np, o->at<T>(o->Rs), o->at<T>(o->Ss), 2, s),
                    "W += R S^T");
   if (st != LV_OK) return st;
-  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)(2 * pp + 2)), dim3(256), 0, s, o->d(o->spart), (int)gv,
-                     2 * pp + 2, o->d(o->sums) + 8);
-  hipLaunchKernelGGL((k_ols_beta<T>), dim3((unsigned)((np * pp + 255) / 256)), dim3(256), 0, s, o->at<T>(o->Rs),
-                     o->d(o->vec), o->d(o->sums) + 8, o->d(o->pUy), o->at<T>(o->vbuf), o->at<T>(o->beta),
-                     o->at<T>(o->C), np, pp, row >= 0 ? o->at<T>(o->X) : nullptr, row);
+  // (the work-groups each add the partials of S^T C: no more of them than the
+  // device has compute units)
+  const unsigned gb = (unsigned)((np * pp + 255) / 256);
+  hipLaunchKernelGGL((k_ols_beta<T>), dim3(gb < 256 ? gb : 256), dim3(256), 0, s, o->at<T>(o->Rs), o->d(o->vec),
+                     o->d(o->spart), (int)gv, o->d(o->pUy), o->at<T>(o->vbuf), o->at<T>(o->beta), o->at<T>(o->C), np, pp,
+                     row >= 0 ? o->at<T>(o->X) : nullptr, row);
   if (row < 0)
     hipLaunchKernelGGL((k_rank1<T>), dim3(2048), dim3(256), 0, s, o->at<T>(o->X), mp, np, o->at<T>(o->ubuf),
                        o->at<T>(o->vbuf));

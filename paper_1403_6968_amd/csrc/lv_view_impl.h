@@ -34,22 +34,22 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // over the row tiles of the stand-alone Gram), each for the tile rows that
 // give most slices: the smallest height, or the default's finer cut.
 // chained: of the updates that share a pass, side by side.
-inline size_t slice_cols(int64_t n_pad, int elem, int R, bool chained = false) {
+inline size_t slice_cols(int64_t n_pad, int elem, int R, bool chained = false, bool reads = false) {
   size_t most = 0;
   for (int q = 1; q <= R; q *= 2) {
     const bool cores = skinny_on_mfma(q, elem);   // (a level on shadows has no more slices)
     for (const int rows : {kMinTileRows, kTileRows}) {
-      const size_t c = (size_t)slice_count(n_pad, elem, q, cores, rows) * q * (chained ? chain_updates(q) : 1);
+      const size_t c = (size_t)slice_count(n_pad, elem, q, cores, rows, reads) * q * (chained ? chain_updates(q) : 1);
       most = c > most ? c : most;
     }
   }
   return most;
 }
-inline size_t gram_partials(int64_t n_pad, int elem, int R, bool chained = false) {
+inline size_t gram_partials(int64_t n_pad, int elem, int R, bool chained = false, bool reads = false) {
   size_t most = (size_t)gram_tiles(n_pad) * R * R;
   for (int q = 1; q <= R && gram_in_pass(q, elem); q *= 2) {
     for (const int rows : {kMinTileRows, kTileRows}) {
-      const size_t c = (size_t)slice_count(n_pad, elem, q, false, rows) * q * q * (chained ? chain_updates(q) : 1);
+      const size_t c = (size_t)slice_count(n_pad, elem, q, false, rows, reads) * q * q * (chained ? chain_updates(q) : 1);
       most = c > most ? c : most;
     }
   }
