@@ -258,7 +258,7 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
       return launch_sums_fused<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(), v->slabW<T>(), sV,
                                   L.W, v->partYs<T>(j), s);
     });
-    if (st == LV_OK)
+    if (st == LV_OK && !L.general)   // general-form views formed it with their own products
       st = timed(v, 0, s, "sums: gram", [&] {
         return launch_gram_cols<T>(R, sV + (L.W - R), v->slabQ<T>(), L.W, L.n_pad, v->partGs(j), s);
       });
@@ -272,7 +272,7 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
       return launch_level_readonly<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(),
                                       sV + (L.W - R), L.W, v->partX<T>(j), v->partYs<T>(j), s);
     });
-    if (st == LV_OK)
+    if (st == LV_OK && !L.general)   // general-form views formed it with their own products
       st = timed(v, 0, s, "sums: gram", [&] {
         return launch_gram_cols<T>(R, sV + (L.W - R), v->slabQ<T>(), L.W, L.n_pad, v->partGs(j), s);
       });
@@ -316,13 +316,14 @@ lv_status general_tail(lv_view* v, int j, int R, const T* sU, const T* sV, hipSt
   const Layout& L = v->L;
   const bool first = j < 0;
   const T* src = first ? v->T0<T>() : v->Tg<T>(j);
-  lv_status st = timed(v, 0, s, "general: V^T T", [&] {
-    return launch_atb<T>(R, L.pp, sV + (L.W - R), L.W, src, L.pp, L.n_pad, v->atbA(), s);
-  });
-  if (st == LV_OK && j > 0)
-    st = timed(v, 0, s, "general: W^T B", [&] {
-      return launch_atb<T>(R, L.pp, v->slabW<T>() + (L.W - R), L.W, v->Bg<T>(), L.pp, L.n_pad, v->atbB(), s);
-    });
+  const T* Vj = sV + (L.W - R);
+  AtbJobs<T> jobs;
+  jobs.add(R, L.pp, Vj, L.W, src, L.pp, v->atbA());
+  if (j > 0) {
+    jobs.add(R, L.pp, v->slabW<T>() + (L.W - R), L.W, v->Bg<T>(), L.pp, v->atbB());
+    jobs.add(R, R, v->slabQ<T>(), L.W, Vj, L.W, v->partGs(j));   // the sums' Gram Q_j^T V_j
+  }
+  const lv_status st = timed(v, 0, s, "general: V^T T, W^T B, Q^T V", [&] { return launch_atb_jobs<T>(jobs, L.n_pad, s); });
   if (st != LV_OK) return st;
   return timed(v, 1, s, "general: tail", [&] {
     return launch_general_tail<T>(v->partXT<T>(), first ? 0 : L.nct, sU, j > 0 ? v->slabQ<T>() : nullptr, L.W, R,
@@ -382,17 +383,14 @@ lv_status gfac_tail(lv_view* v, int j, int R, int ru, const T* sU, const T* sV, 
   const int sy = j == 0 ? L.W : L.WY[j];
   const int wj = gW(ru, j);
   const T* Vj = sV + (L.W - R);
-  lv_status st = timed(v, 0, s, "general: V^T Y", [&] {
-    return launch_atb<T>(R, wj, Vj, L.W, Yj, sy, L.n_pad, v->atbG(), s);
-  });
-  if (st == LV_OK)
-    st = timed(v, 0, s, "general: V^T T", [&] {
-      return launch_atb<T>(R, L.pp, Vj, L.W, v->Tg<T>(j), L.pp, L.n_pad, v->atbA(), s);
-    });
-  if (st == LV_OK && j > 0)
-    st = timed(v, 0, s, "general: W^T B", [&] {
-      return launch_atb<T>(R, L.pp, v->slabW<T>() + (L.W - R), L.W, v->Bg<T>(), L.pp, L.n_pad, v->atbB(), s);
-    });
+  AtbJobs<T> jobs;
+  jobs.add(R, wj, Vj, L.W, Yj, sy, v->atbG());
+  jobs.add(R, L.pp, Vj, L.W, v->Tg<T>(j), L.pp, v->atbA());
+  if (j > 0) {
+    jobs.add(R, L.pp, v->slabW<T>() + (L.W - R), L.W, v->Bg<T>(), L.pp, v->atbB());
+    jobs.add(R, R, v->slabQ<T>(), L.W, Vj, L.W, v->partGs(j));   // the sums' Gram Q_j^T V_j
+  }
+  lv_status st = timed(v, 0, s, "general: V^T [Y, T], W^T B, Q^T V", [&] { return launch_atb_jobs<T>(jobs, L.n_pad, s); });
   if (st == LV_OK)
     st = timed(v, 1, s, "general: Y", [&] {
       // X = P_j Y_j: at level 0 (Y_0 = U_0) the partials of the powers' pass
@@ -437,14 +435,11 @@ lv_status gfac_skip(lv_view* v, int ru, const T* sU, const T* sV, hipStream_t s)
                                       slice_rows(L.n_pad, L.elem, wp, v->on_cores(wp), kTileRows), Yp, Yp, sp, v->partXT<T>(),
                                       v->partYT<T>(), s);
     });
+    AtbJobs<T> jobs;
+    jobs.add(Rm, wp, Vm, L.W, Yp, sp, v->atbG());
+    jobs.add(Rm, L.pp, Vm, L.W, Tp, L.pp, v->atbA());
     if (st == LV_OK)
-      st = timed(v, 0, s, "general: V_s^T Y", [&] {
-        return launch_atb<T>(Rm, wp, Vm, L.W, Yp, sp, L.n_pad, v->atbG(), s);
-      });
-    if (st == LV_OK)
-      st = timed(v, 0, s, "general: V_s^T T", [&] {
-        return launch_atb<T>(Rm, L.pp, Vm, L.W, Tp, L.pp, L.n_pad, v->atbA(), s);
-      });
+      st = timed(v, 0, s, "general: V_s^T [Y, T]", [&] { return launch_atb_jobs<T>(jobs, L.n_pad, s); });
     if (st == LV_OK)
       st = timed(v, 1, s, "general: Y (skip)", [&] {
         return launch_gfac_y<T>(v->partXT<T>(), L.nct, wp, sU, L.m > 0 ? v->slabQ<T>() : nullptr, L.W, Rm,
@@ -463,16 +458,19 @@ template <typename T>
 lv_status gfac_finish(lv_view* v, int ru, const T* sU, hipStream_t s) {
   const Layout& L = v->L;
   lv_status st = LV_OK;
-  for (int j = 0; j <= L.m && st == LV_OK; ++j)
-    st = timed(v, 2, s, "general: T += Y Z^T", [&] {
-      return launch_rank_rect<T>(v->Tg<T>(j), j == 0 ? sU : v->Yf<T>(j), j == 0 ? L.W : L.WY[j], v->Ztf<T>(j),
-                                 gw(ru, j), L.n_pad, L.pp, s);
-    });
-  for (int q = 1; q <= L.nsk && st == LV_OK; ++q)
-    st = timed(v, 2, s, "general: T += Y Z^T (skip)", [&] {
-      return launch_rank_rect<T>(v->Tskp<T>(q), v->Yskp<T>(q), L.WYsk(q), v->Ztskp<T>(q), gwsk(L, ru, q), L.n_pad,
-                                 L.pp, s);
-    });
+  const int total = L.m + 1 + L.nsk;   // T_1 .. T_{2^m}, then the skip steps'
+  for (int i0 = 0; i0 < total && st == LV_OK; i0 += kMaxRectJobs) {
+    RectJobs<T> jobs;
+    int cnt = 0;
+    for (int i = i0; i < total && cnt < kMaxRectJobs; ++i) {
+      const int q = i - L.m;
+      if (i <= L.m)
+        jobs.job[cnt++] = {v->Tg<T>(i), i == 0 ? sU : v->Yf<T>(i), v->Ztf<T>(i), i == 0 ? L.W : L.WY[i], gw(ru, i)};
+      else
+        jobs.job[cnt++] = {v->Tskp<T>(q), v->Yskp<T>(q), v->Ztskp<T>(q), L.WYsk(q), gwsk(L, ru, q)};
+    }
+    st = timed(v, 2, s, "general: T += Y Z^T", [&] { return launch_rank_rect_jobs<T>(jobs, cnt, L.n_pad, L.pp, s); });
+  }
   return st;
 }
 

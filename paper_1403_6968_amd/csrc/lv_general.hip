@@ -22,18 +22,52 @@ namespace {
 // part[tile][a * p + b] = sum over the tile's rows of A[row][a] B[row][b]
 // (double), pairs (a, b) spread over threads and blocks.
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_atb(const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ldb, int R, int p,
-      double* __restrict__ part) {
-  const int tile = blockIdx.x;
-  const int pair = blockIdx.y * 256 + threadIdx.x;
-  if (pair >= R * p) return;
-  const int a = pair / p, b = pair % p;
+__device__ __forceinline__ void atb_body(const AtbJob<T>& d, const int tile, const int blk) {
+  const int pair = blk * 256 + (int)threadIdx.x;
+  if (pair >= d.R * d.p) return;
+  const int a = pair / d.p, b = pair % d.p;
   const int64_t r0 = (int64_t)tile * kAtbRows;
   double acc = 0.0;
-#pragma unroll 8
-  for (int i = 0; i < kAtbRows; ++i) acc = fma((double)A[(r0 + i) * lda + a], (double)B[(r0 + i) * ldb + b], acc);
-  part[(int64_t)tile * R * p + pair] = acc;
+#pragma unroll 16
+  for (int i = 0; i < kAtbRows; ++i)
+    acc = fma((double)d.A[(r0 + i) * d.lda + a], (double)d.B[(r0 + i) * d.ldb + b], acc);
+  d.part[(int64_t)tile * d.R * d.p + pair] = acc;
+}
+
+// Work-groups blockIdx.y of all the jobs in turn (256 pairs each).
+template <typename T>
+__global__ void __launch_bounds__(256) k_atb(const AtbJobs<T> jobs) {
+  int blk = blockIdx.y;
+  for (int j = 0; j < jobs.cnt; ++j) {
+    const int nb = (jobs.job[j].R * jobs.job[j].p + 255) / 256;
+    if (blk < nb) { atb_body(jobs.job[j], blockIdx.x, blk); return; }
+    blk -= nb;
+  }
+}
+
+// The sums of the jobs' partials over the tiles, in tile order, into the first.
+template <typename T>
+__global__ void __launch_bounds__(256) k_atb_sum(const AtbJobs<T> jobs, const int ntile) {
+  int blk = blockIdx.x;
+  for (int j = 0; j < jobs.cnt; ++j) {
+    const int count = jobs.job[j].R * jobs.job[j].p, nb = (count + 255) / 256;
+    if (blk >= nb) { blk -= nb; continue; }
+    const int idx = blk * 256 + (int)threadIdx.x;
+    if (idx >= count) return;
+    double* G = jobs.job[j].part + idx;
+    double g = 0.0;
+    int t = 0;
+    for (; t + 16 <= ntile; t += 16) {
+      double v[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = G[(int64_t)(t + e) * count];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) g += v[e];
+    }
+    for (; t < ntile; ++t) g += G[(int64_t)t * count];
+    G[0] = g;
+    return;
+  }
 }
 
 // One thread per (row, column) of the n_pad x pp delta:
@@ -191,15 +225,10 @@ k_vtt_sum(const double* __restrict__ part, int tiles, int pairs, T* __restrict__
 }
 
 // Tm[row][col] += sum_c Y[row][c] Zt[c][col] (double), one thread per element.
-// Several T in one launch (gridDim.y = cnt): T_{i+1} = Tm + i tstride takes
-// the first (i + 1) w columns of Y and Zt from row (cnt - 1 - i) w on.
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_rank_rect(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __restrict__ Zt, int w, int64_t n_pad,
-            int pp, int64_t tstride) {
-  Tm += blockIdx.y * tstride;
-  Zt += (int64_t)(gridDim.y - 1 - blockIdx.y) * w * pp;
-  w *= (int)blockIdx.y + 1;
+__device__ __forceinline__ void rank_rect_body(T* __restrict__ Tm, const T* __restrict__ Y, const int sy,
+                                               const T* __restrict__ Zt, const int w, const int64_t n_pad,
+                                               const int pp) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= n_pad * pp) return;
   const int64_t row = idx / pp;
@@ -213,13 +242,10 @@ k_rank_rect(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __rest
 // columns; n_pad and pp multiples of 4): each Zt row segment is loaded once
 // for the four rows, each Y value once for the four columns.
 template <typename T>
-__global__ void __launch_bounds__(256)
-k_rank_rect4(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __restrict__ Zt, int w, int64_t n_pad,
-             int pp, int64_t tstride) {
+__device__ __forceinline__ void rank_rect4_body(T* __restrict__ Tm, const T* __restrict__ Y, const int sy,
+                                                const T* __restrict__ Zt, const int w, const int64_t n_pad,
+                                                const int pp) {
   typedef T v4 __attribute__((ext_vector_type(4)));
-  Tm += blockIdx.y * tstride;
-  Zt += (int64_t)(gridDim.y - 1 - blockIdx.y) * w * pp;
-  w *= (int)blockIdx.y + 1;
   const int q4 = pp / 4;
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= (n_pad / 4) * q4) return;
@@ -230,6 +256,7 @@ k_rank_rect4(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __res
   for (int a = 0; a < 4; ++a)
 #pragma unroll
     for (int b = 0; b < 4; ++b) d[a][b] = 0.0;
+#pragma unroll 4
   for (int c = 0; c < w; ++c) {
     const v4 z = *reinterpret_cast<const v4*>(Zt + (int64_t)c * pp + col);
     const double zz[4] = {(double)z.x, (double)z.y, (double)z.z, (double)z.w};
@@ -250,6 +277,26 @@ k_rank_rect4(T* __restrict__ Tm, const T* __restrict__ Y, int sy, const T* __res
     t.w = (T)((double)t.w + d[a][3]);
     *tp = t;
   }
+}
+
+// Tm[row][col] += sum_c Y[row][c] Zt[c][col] (double); R4: the 4 x 4 form.
+// blockIdx.y = i < cnt: T_{i+1} = Tm + i tstride takes the first (i + 1) w
+// columns of Y and Zt from row (cnt - 1 - i) w on.
+template <typename T, bool R4>
+__global__ void __launch_bounds__(256)
+k_rank_rect(T* Tm, const T* Y, int sy, const T* Zt, int w, int64_t n_pad, int pp, int64_t tstride) {
+  const int i = blockIdx.y;
+  Tm += i * tstride;
+  Zt += (int64_t)((int)gridDim.y - 1 - i) * w * pp;
+  if constexpr (R4) rank_rect4_body<T>(Tm, Y, sy, Zt, (i + 1) * w, n_pad, pp);
+  else rank_rect_body<T>(Tm, Y, sy, Zt, (i + 1) * w, n_pad, pp);
+}
+
+template <typename T, bool R4>
+__global__ void __launch_bounds__(256) k_rank_rect_jobs(const RectJobs<T> jobs, int64_t n_pad, int pp) {
+  const RectJob<T>& d = jobs.job[blockIdx.y];
+  if constexpr (R4) rank_rect4_body<T>(d.Tm, d.Y, d.sy, d.Zt, d.w, n_pad, pp);
+  else rank_rect_body<T>(d.Tm, d.Y, d.sy, d.Zt, d.w, n_pad, pp);
 }
 
 }  // namespace
@@ -273,13 +320,24 @@ hipError_t launch_gfac_z(const double* a, const T* Zt, int wy, const double* b, 
 template <typename T>
 hipError_t launch_rank_rect(T* Tm, const T* Y, int sy, const T* Zt, int w, int64_t n_pad, int pp, hipStream_t s,
                             int cnt, int64_t tstride) {
-  if (pp % 4 == 0 && n_pad % 4 == 0) {
-    hipLaunchKernelGGL((k_rank_rect4<T>), dim3((unsigned)((n_pad / 4 * (pp / 4) + 255) / 256), (unsigned)cnt), dim3(256),
-                       0, s, Tm, Y, sy, Zt, w, n_pad, pp, tstride);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL((k_rank_rect<T>), dim3((unsigned)((n_pad * pp + 255) / 256), (unsigned)cnt), dim3(256), 0, s, Tm,
-                     Y, sy, Zt, w, n_pad, pp, tstride);
+  if (pp % 4 == 0 && n_pad % 4 == 0)
+    hipLaunchKernelGGL((k_rank_rect<T, true>), dim3((unsigned)((n_pad / 4 * (pp / 4) + 255) / 256), (unsigned)cnt),
+                       dim3(256), 0, s, Tm, Y, sy, Zt, w, n_pad, pp, tstride);
+  else
+    hipLaunchKernelGGL((k_rank_rect<T, false>), dim3((unsigned)((n_pad * pp + 255) / 256), (unsigned)cnt), dim3(256), 0,
+                       s, Tm, Y, sy, Zt, w, n_pad, pp, tstride);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_rank_rect_jobs(const RectJobs<T>& jobs, int cnt, int64_t n_pad, int pp, hipStream_t s) {
+  if (cnt <= 0) return hipSuccess;
+  if (pp % 4 == 0 && n_pad % 4 == 0)
+    hipLaunchKernelGGL((k_rank_rect_jobs<T, true>), dim3((unsigned)((n_pad / 4 * (pp / 4) + 255) / 256), (unsigned)cnt),
+                       dim3(256), 0, s, jobs, n_pad, pp);
+  else
+    hipLaunchKernelGGL((k_rank_rect_jobs<T, false>), dim3((unsigned)((n_pad * pp + 255) / 256), (unsigned)cnt),
+                       dim3(256), 0, s, jobs, n_pad, pp);
   return hipGetLastError();
 }
 
@@ -297,14 +355,24 @@ hipError_t launch_vtt(int R, int pp, const T* V, const T* Tm, int64_t tstride, i
 }
 
 template <typename T>
-hipError_t launch_atb(int R, int p, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t n_pad, double* part,
-                      hipStream_t s) {
+hipError_t launch_atb_jobs(const AtbJobs<T>& jobs, int64_t n_pad, hipStream_t s) {
+  if (jobs.cnt <= 0) return hipSuccess;
   const int ntile = (int)(n_pad / kAtbRows);
-  const dim3 grid((unsigned)ntile, (unsigned)((R * p + 255) / 256));
-  hipLaunchKernelGGL((k_atb<T>), grid, dim3(256), 0, s, A, lda, B, ldb, R, p, part);
+  unsigned blocks = 0;
+  for (int j = 0; j < jobs.cnt; ++j) blocks += (unsigned)((jobs.job[j].R * jobs.job[j].p + 255) / 256);
+  hipLaunchKernelGGL((k_atb<T>), dim3((unsigned)ntile, blocks), dim3(256), 0, s, jobs);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return launch_gram_sum(part, ntile, R * p, s);
+  hipLaunchKernelGGL((k_atb_sum<T>), dim3(blocks), dim3(256), 0, s, jobs, ntile);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_atb(int R, int p, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t n_pad, double* part,
+                      hipStream_t s) {
+  AtbJobs<T> jobs;
+  jobs.add(R, p, A, lda, B, ldb, part);
+  return launch_atb_jobs<T>(jobs, n_pad, s);
 }
 
 template <typename T>
@@ -338,6 +406,8 @@ hipError_t launch_copy_rect(const Tin* src, int64_t lds, int64_t n, int p, Tout*
 #define LV_INST(T)                                                                                            \
   template hipError_t launch_atb<T>(int, int, const T*, int64_t, const T*, int64_t, int64_t, double*,         \
                                     hipStream_t);                                                             \
+  template hipError_t launch_atb_jobs<T>(const AtbJobs<T>&, int64_t, hipStream_t);                            \
+  template hipError_t launch_rank_rect_jobs<T>(const RectJobs<T>&, int, int64_t, int, hipStream_t);           \
   template hipError_t launch_general_tail<T>(const T*, int, const T*, const T*, int, int, const double*,       \
                                              const double*, T*, T*, int64_t, int, hipStream_t);
 LV_INST(float)

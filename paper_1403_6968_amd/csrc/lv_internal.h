@@ -413,6 +413,19 @@ hipError_t launch_add(T* dst, const T* src, int64_t count, hipStream_t s, const 
 template <typename T>
 hipError_t launch_atb(int R, int p, const T* A, int64_t lda, const T* B, int64_t ldb, int64_t n_pad, double* part,
                       hipStream_t s);
+// Several such products (and their sums) in one launch each: the small
+// products of a level wait for the same factors, and each alone is shorter
+// than a launch.
+constexpr int kMaxAtbJobs = 4;
+template <typename T> struct AtbJob { int R, p; const T* A; int64_t lda; const T* B; int64_t ldb; double* part; };
+template <typename T> struct AtbJobs {
+  AtbJob<T> job[kMaxAtbJobs]; int cnt = 0;
+  void add(int R, int p, const T* A, int64_t lda, const T* B, int64_t ldb, double* part) {
+    job[cnt++] = {R, p, A, lda, B, ldb, part};
+  }
+};
+template <typename T>
+hipError_t launch_atb_jobs(const AtbJobs<T>& jobs, int64_t n_pad, hipStream_t s);
 // D = sum of nct partials of X + U a (+ Q b if Q is non-null), T += D
 // (n_pad x pp; U, Q with row stride W and R columns; a, b R x pp double).
 template <typename T>
@@ -439,11 +452,17 @@ template <typename T>
 hipError_t launch_gfac_z(const double* a, const T* Zt, int wy, const double* b, int R, T* Ztnew, int WYn, int pp,
                          hipStream_t s);
 // Tm (n_pad x pp) += Y (w columns, row stride sy) Zt (w x pp), double sums.
+// (jobs: up to kMaxRectJobs such updates of different Tm in one launch.)
 // cnt > 1: for i = 0 .. cnt - 1, Tm + i tstride, the first (i + 1) w columns
 // of Y, and Zt from row (cnt - 1 - i) w on.
 template <typename T>
 hipError_t launch_rank_rect(T* Tm, const T* Y, int sy, const T* Zt, int w, int64_t n_pad, int pp, hipStream_t s,
                             int cnt = 1, int64_t tstride = 0);
+constexpr int kMaxRectJobs = 16;
+template <typename T> struct RectJob { T* Tm; const T* Y; const T* Zt; int sy, w; };
+template <typename T> struct RectJobs { RectJob<T> job[kMaxRectJobs]; };
+template <typename T>
+hipError_t launch_rank_rect_jobs(const RectJobs<T>& jobs, int cnt, int64_t n_pad, int pp, hipStream_t s);
 // Z (cnt R x pp, rows in blocks of R): block cnt - 1 - i = V^T T_i for T_i =
 // Tm + i tstride (n_pad x pp), V n_pad x R; part holds cnt vtt_tiles(n_pad, R
 // pp) R pp doubles.
