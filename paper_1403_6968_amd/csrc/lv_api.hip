@@ -4,6 +4,7 @@
 #include "linview.h"
 #include "lv_internal.h"
 
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -524,7 +525,15 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
       // at R = 16 the skinny pass applies the update itself (one read of
       // P_j), else the update pass follows
       const bool fused_upd = !v->shadowed() && skinny_fuses_update(R);
-      st = timed(v, 0, s, "skinny", [&] {
+      const int slot = (int)((reinterpret_cast<char*>(sU) - v->base - L.slabU) / L.slot_stride);
+      if (v->wide16(R))
+        st = timed(v, 0, s, "bf16 factors", [&] {
+          return launch_fac16(v->fac16(R, j == 0 || R / 2 < kWide16Rank, slot), s);
+        });
+      if (st == LV_OK) st = timed(v, 0, s, "skinny", [&] {
+        if (v->wide16(R))
+          return launch_skinny_wide(v->shadow(j), L.ldp, L.n_pad, v->Ut16(slot), v->Vt16(slot) + (int64_t)(L.W - R) * L.n_pad, R, v->partX<float>(j),
+                                    v->partY<float>(j), s);
         return v->shadowed() ? launch_skinny_bf16(R, v->shadow(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W,
                                                   v->partX<float>(j), v->partY<float>(j), s)
                              : launch_skinny_f32(R, v->P<float>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W,
@@ -542,7 +551,9 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
         });
       if (st == LV_OK)
         st = timed(v, 1, s, "level tail", [&] {
-          return launch_level_tail<float>(R, v->partX<float>(j), v->partY<float>(j), v->partG(j), L.nct, nrt, 1,
+          const int px = v->wide16(R) ? wide_splits(L.n_pad) : L.nct;
+          const int py = v->wide16(R) ? wide_splits(L.n_pad) : nrt;
+          return launch_level_tail<float>(R, v->partX<float>(j), v->partY<float>(j), v->partG(j), px, py, 1,
                                            L.n_pad, sU, sV, L.W, s);
         });
     }
@@ -671,8 +682,10 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
   if (st != LV_OK) return st;
   const int r_pad = (int)next_pow2(r);
   const int Rm = r_pad << L.m;
-  // the slots hold D chunks of C updates
-  const int C = v->chunk(r_pad), D = L.pipe_slots / C;
+  // the slots hold D chunks of C updates; one update in flight per stage is
+  // enough where each has passes of its own (more only widen the working set:
+  // rank-4 shadow batches n = 8192 23.46 ms with 5, 23.74 ms with 12)
+  const int C = v->chunk(r_pad), D = C > 1 ? L.pipe_slots / C : std::min(L.pipe_slots, std::min(L.m + 1, 5));
   const int64_t sstride = (int64_t)(L.slot_stride / sizeof(T));
   auto stream_of = [&](int j) { const int q = pipe_stage(v, j); return q == 0 ? s : v->pstream[q]; };
   auto ev = [&](hipError_t e, const char* what) { return e == hipSuccess ? LV_OK : fail(LV_EDEVICE, "%s failed", what); };

@@ -142,7 +142,7 @@ __device__ __forceinline__ int sum_index(const int lane) { return (int)(__brev((
 //   GR       (UPD = false) the Gram Vy^T Uj is formed as well; WY = false: no Y.
 template <typename T, int R, int TT, bool UPD, int XE = 0, bool SP = false, int XD = 0, int RY = R, bool GR = UPD && !SP,
           bool WY = true>
-__device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, const int rt) {
+__device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, const int rt, const Strides& vs = {}) {
   constexpr int RB = kFusedRowBlock;
   constexpr int EPL = 16 / (int)sizeof(T);
   constexpr int TC = 64 * EPL;
@@ -193,7 +193,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
 #pragma unroll
   for (int f = 0; f < FN; ++f) {
     const int e = lane + 64 * f < FB ? lane + 64 * f : 0;
-    foff[f] = (unsigned)(((TT > 1 ? (e / R % TT) * d.vs.s : 0) + (int64_t)(e / C) * W + e % R) * sizeof(T));
+    foff[f] = (unsigned)(((TT > 1 ? (e / R % TT) * vs.s : 0) + (int64_t)(e / C) * W + e % R) * sizeof(T));
     if constexpr (SP) {
       const int ey = lane + 64 * f < FBY ? lane + 64 * f : 0;
       foffy[f] = (unsigned)(((int64_t)(ey / RY) * d.Wy + ey % RY) * sizeof(T));
@@ -235,7 +235,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
       if (OPS * TT * TC % 256 != 0 && idx >= OPS * TT * TC) continue;
       const unsigned g = (unsigned)((col0 + col) * W * (int)sizeof(T));
       T f[R];
-      load_row<T, R>(at_byte((op ? Vj : Uj) + v * d.vs.s, g), f);
+      load_row<T, R>(at_byte((op ? Vj : Uj) + v * vs.s, g), f);
 #pragma unroll
       for (int c = 0; c < R; ++c) lbuf[(op * C + v * R + c) * TC + col] = f[c];
     }
@@ -249,10 +249,10 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
       for (int c = 0; c < (SP ? RY : R); ++c) yacc[v][q][c] = T(0);
       if constexpr (LF) continue;
       const unsigned g = (unsigned)((lc + q) * W * (int)sizeof(T));
-      load_row<T, UPD ? R : 0>(at_byte(Vj + v * d.vs.s, g), vcol[v][q]);
+      load_row<T, UPD ? R : 0>(at_byte(Vj + v * vs.s, g), vcol[v][q]);
       if constexpr (!SP) {
         T u[R];
-        load_row<T, R>(at_byte(Uj + v * d.vs.s, g), u);
+        load_row<T, R>(at_byte(Uj + v * vs.s, g), u);
 #pragma unroll
         for (int c = 0; c < R; ++c) ucol[v][q][c] = u[c];
 #pragma unroll
@@ -270,7 +270,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     const int t = i / (TT * XR), v = i / XR % TT, c = i % XR;
     const int64_t row = (int64_t)ct * n_pad + t;
     if (i < NX) {
-      if (c < R) { xs = pR; xdst = d.partX + v * d.vs.x + row * pR + c; }
+      if (c < R) { xs = pR; xdst = d.partX + v * vs.x + row * pR + c; }
       if constexpr (XE > 0)
         if (c >= R && c < R + XE) { xs = XE; xdst = d.partX2 + row * XE + c - R; }
       if constexpr (XD > 0)
@@ -439,7 +439,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
       const T s = ((ybuf[(0 * TC + cc) * YC + c] + ybuf[(1 * TC + cc) * YC + c]) +
                    ybuf[(2 * TC + cc) * YC + c]) + ybuf[(3 * TC + cc) * YC + c];
       const int v = (c0 + c) / YR;
-      d.partY[v * d.vs.y + ((int64_t)rt * n_pad + col0 + cc) * pR + (c0 + c) % YR] = s;
+      d.partY[v * vs.y + ((int64_t)rt * n_pad + col0 + cc) * pR + (c0 + c) % YR] = s;
     }
   }
 
@@ -457,8 +457,8 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
     const int g0 = tid % 32;
     for (int pair = ct + nct * (tid / 32); pair < TT * NP; pair += 8 * nct) {
       const int v = pair / NP, ab = pair % NP;
-      const T* vp = Vg + v * d.vs.s + ab / R;
-      const T* up = Uj + v * d.vs.s + ab % R;
+      const T* vp = Vg + v * vs.s + ab / R;
+      const T* up = Uj + v * vs.s + ab % R;
       double g = 0.0;
 #pragma unroll 4
       for (int q = g0; q < nsr; q += 32) {
@@ -467,7 +467,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
       }
 #pragma unroll
       for (int off = 16; off > 0; off >>= 1) g += __shfl_xor(g, off, 32);
-      if (g0 == 0) d.partG[v * d.vs.g + (int64_t)rt * NP + ab] = g;
+      if (g0 == 0) d.partG[v * vs.g + (int64_t)rt * NP + ab] = g;
     }
   }
 }
@@ -477,8 +477,8 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
 template <int R, int TT> constexpr int fused_min_waves() { return TT > 1 ? 2 : 1; }
 
 template <typename T, int R, int TT, bool UPD>
-__global__ void __launch_bounds__(256, (fused_min_waves<R, TT>())) k_level_fused(const FusedDesc<T> d) {
-  fused_body<T, R, TT, UPD>(d, blockIdx.x, blockIdx.y);
+__global__ void __launch_bounds__(256, (fused_min_waves<R, TT>())) k_level_fused(const FusedDesc<T> d, const Strides vs) {
+  fused_body<T, R, TT, UPD>(d, blockIdx.x, blockIdx.y, vs);
 }
 
 // The same pass with gridDim.y below the slice count: row slices rt =
@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(256) k_level_fused_multi(const FusedDesc<T>* _
 }
 
 template <typename T, int R, int TT, bool UPD>
-hipError_t fused_launch(const FusedDesc<T>& d, hipStream_t s, int slice_groups = 0) {
+hipError_t fused_launch(const FusedDesc<T>& d, hipStream_t s, int slice_groups = 0, const Strides& vs = {}) {
   const int ns = (d.n_pad + d.tile_rows - 1) / d.tile_rows;
   if constexpr (UPD && R <= 8 && TT == 1) {
     if (slice_groups > 0 && slice_groups < ns) {
@@ -543,15 +543,15 @@ hipError_t fused_launch(const FusedDesc<T>& d, hipStream_t s, int slice_groups =
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((k_level_fused<T, R, TT, UPD>), dim3((unsigned)d.nct, (unsigned)ns), dim3(256), 0, s, d);
+  hipLaunchKernelGGL((k_level_fused<T, R, TT, UPD>), dim3((unsigned)d.nct, (unsigned)ns), dim3(256), 0, s, d, vs);
   return hipGetLastError();
 }
 
 // The fused pass over nver updates (1, 2, 4, ..., up to chain_updates(R)).
 template <typename T, int R, int TT>
-hipError_t fused_chain(const FusedDesc<T>& d, hipStream_t s, int slice_groups, int nver) {
-  if (nver == TT) return fused_launch<T, R, TT, true>(d, s, slice_groups);
-  if constexpr (2 * TT <= chain_updates(R)) return fused_chain<T, R, 2 * TT>(d, s, slice_groups, nver);
+hipError_t fused_chain(const FusedDesc<T>& d, hipStream_t s, int slice_groups, int nver, const Strides& vs) {
+  if (nver == TT) return fused_launch<T, R, TT, true>(d, s, slice_groups, vs);
+  if constexpr (2 * TT <= chain_updates(R)) return fused_chain<T, R, 2 * TT>(d, s, slice_groups, nver, vs);
   return hipErrorInvalidValue;
 }
 
@@ -559,9 +559,9 @@ hipError_t fused_chain(const FusedDesc<T>& d, hipStream_t s, int slice_groups, i
 // products in 16-column chunks (read-only passes), the Gram, then the rank-R
 // update pass.
 template <typename T, int R>
-hipError_t fused_r(const FusedDesc<T>& d, hipStream_t s, int slice_groups, int nver) {
+hipError_t fused_r(const FusedDesc<T>& d, hipStream_t s, int slice_groups, int nver, const Strides& vs) {
   if constexpr (R <= kMaxFusedRank) {
-    return fused_chain<T, R, 1>(d, s, slice_groups, nver);
+    return fused_chain<T, R, 1>(d, s, slice_groups, nver, vs);
   } else {
     if (nver != 1) return hipErrorInvalidValue;
     constexpr int RC = kMaxFusedRank;
@@ -594,9 +594,8 @@ template <typename T>
 hipError_t launch_level_fused(int R, T* P, int64_t ldp, int64_t n_pad, int tile_rows,
                               const T* slabU, const T* slabV, int W, T* partX, T* partY,
                               double* partG, hipStream_t s, int slice_groups, int nver, const Strides& vs) {
-  FusedDesc<T> d = fused_desc<T>(R, P, ldp, n_pad, tile_rows, slabU, slabV + (W - R), W, partX, partY, partG);
-  d.vs = vs;
-  LV_RANK_SWITCH(R, return (fused_r<T, RR>(d, s, slice_groups, nver)))
+  const FusedDesc<T> d = fused_desc<T>(R, P, ldp, n_pad, tile_rows, slabU, slabV + (W - R), W, partX, partY, partG);
+  LV_RANK_SWITCH(R, return (fused_r<T, RR>(d, s, slice_groups, nver, vs)))
 }
 
 // Launch k_level_fused_x for level rank R with XE (0 or R) and xd (0, 1, 2,

@@ -77,11 +77,11 @@ template <typename T> struct FusedDesc {
   int nct; int block_begin;             // blocks: nct x ceil(n_pad / tile_rows)
   const T* Ux = nullptr;                // extra X operand (powers' pass of a view with sums)
   T* partX2 = nullptr;                  //   and its partials
-  const T* Vy = nullptr; int Wy = 0;    // Y operand of the passes that update with other factors (row stride
+  const T* Vy = nullptr;                // Y operand of the passes that update with other factors (row stride
                                         //   Wy); V operand of the Gram in the read-only passes that form it
-  const T* Ud = nullptr; int Wd = 0;    // general form: extra X operand (row stride Wd)
-  T* partX3 = nullptr;                  //   and its partials
-  Strides vs = {};                      // several updates in one pass
+  const T* Ud = nullptr;                // general form: extra X operand (row stride Wd)
+  int Wd = 0, Wy = 0;
+  T* partX3 = nullptr;                  //   (Ud) and its partials
 };
 template <typename T> struct GramDesc {
   const T* Uj; const T* Vj; int W; int n_pad; int tile_rows; double* partG;
@@ -91,7 +91,6 @@ template <typename T> struct TailDesc {
   const T* partX; const T* partY; const double* partG; int nct; int nrt; int n_pad;
   T* slabU; T* slabV; int W; int block_begin;   // blocks: ceil(n_pad * R / 256)
   int ng;                                       // Gram partials to add (1: already summed)
-  Strides vs = {};                              // update blockIdx.y (single-view launches)
 };
 // Sum of ng Gram partials (count doubles each) into the first.
 struct GramSumDesc {
@@ -101,7 +100,6 @@ template <typename T> struct UpdateDesc {
   T* P; int64_t ldp; int n_pad; int tile_rows; const T* Uj; const T* Vj; int W;
   int nct; int block_begin;             // blocks: nct x ceil(n_pad / tile_rows)
   uint16_t* S;                          // bfloat16 shadow of P rewritten by the pass, or null
-  int nver = 1; int64_t sstride = 0;    // updates applied in turn, slab to slab (elements)
 };
 // Products a read-only skinny pass forms.
 constexpr int kWantX = 1, kWantY = 2;
@@ -114,11 +112,20 @@ struct SkinnyDesc {
   float* partX; float* partY; int pR;
   int nct; int block_begin;             // blocks: nct x ceil(n_pad / tile_rows)
   int want = kWantX | kWantY;           // products formed (float pass only)
+  // (products of kWide16Rank and more factor columns from the shadow: Uj and Vj address
+  // the factors in bfloat16, transposed, row c = column c, n_pad values)
 };
+// Factor columns rounded to bfloat16 and transposed: `cols` (a multiple of 32)
+// columns of U and of V (row stride W) to the rows of Ut and Vt.
+struct Fac16Desc {
+  const float* U; uint16_t* Ut;         // first column of U and its row of Ut
+  int W; int n_pad; int cols; int dv;   // V's first column is dv columns from U's in the next slab: V = U + n_pad W +
+  int block_begin;                      //   dv, Vt = Ut + (W + dv) n_pad; blocks: fac16_blocks
+};
+inline int fac16_blocks(const Fac16Desc& d) { return d.n_pad / 64 * (d.cols / 32) * 2; }
 template <typename T> struct PrepDesc {
   const T* U; int64_t ldu; const T* V; int64_t ldv; int64_t n; int r; int r_pad;
   T* slabU; T* slabV; int W; int64_t n_pad; int block_begin;   // blocks: ceil(n_pad * r_pad / 256)
-  int64_t strideU = 0, strideV = 0, sstride = 0;               // update blockIdx.y (single-view launches)
 };
 
 // Descriptor v of a multi-view launch, read through the constant address
@@ -312,6 +319,33 @@ hipError_t launch_skinny_bf16(int R, const uint16_t* S, int64_t ldp, int64_t n_p
 hipError_t launch_skinny_bf16_multi(int nb, const SkinnyDesc* ds, int nd, int blocks, hipStream_t s);
 // Factor blocks of 32 columns the bfloat16 skinny kernel needs for rank R.
 inline int skinny_blocks_for(int R) { return R <= 32 ? 1 : 2; }   // R <= 64 per launch
+
+// Level ranks R >= kWide16Rank with shadows: the same products from bfloat16
+// factors kept transposed (Ut, Vt: rows are the R factor columns), 64 or 128
+// factor columns per launch.  The summation ranges are split wide_splits()
+// ways, about two work-groups per compute unit in all and at least 512 rows or
+// columns each, with one partial of X and one of Y per split (n_pad / 512 at
+// most, fewer than the passes over 2-D tiles leave).
+constexpr int kWide16Rank = 64;
+inline __host__ __device__ int wide_splits(int64_t n_pad) {
+  const int64_t tiles = n_pad / 128 * 2;   // X and Y products of a launch
+  const int64_t want = (512 + tiles - 1) / tiles, most = n_pad / 512;
+  const int64_t s = want < most ? want : most;
+  return s < 1 ? 1 : (int)s;
+}
+inline int wide_cols(int R) { return R < 128 ? R : 128; }
+inline int wide_blocks(int64_t n_pad) { return (int)(2 * (n_pad / 128)) * wide_splits(n_pad); }
+inline int wide_blocks(const SkinnyDesc& d) { return wide_blocks((int64_t)d.n_pad); }
+inline SkinnyDesc wide_desc(const void* S, int64_t ldp, int64_t n_pad, const uint16_t* Ut, const uint16_t* Vt, int R,
+                            int c0, float* partX, float* partY) {
+  return {S, ldp, (int)n_pad, 0, reinterpret_cast<const float*>(Ut + (int64_t)c0 * n_pad),
+          reinterpret_cast<const float*>(Vt + (int64_t)c0 * n_pad), 0, wide_cols(R), partX + c0, partY + c0, R, 0, 0};
+}
+hipError_t launch_fac16(const Fac16Desc& d, hipStream_t s);
+hipError_t launch_fac16_multi(const Fac16Desc* ds, int nd, int blocks, hipStream_t s);
+hipError_t launch_skinny_wide(const uint16_t* S, int64_t ldp, int64_t n_pad, const uint16_t* Ut, const uint16_t* Vt,
+                              int R, float* partX, float* partY, hipStream_t s);
+hipError_t launch_skinny_wide_multi(int per, const SkinnyDesc* ds, int nd, int blocks, hipStream_t s);
 
 // The same products from the float power P (v_mfma_f32_32x32x2f32, float
 // products and accumulation), R <= kMaxLevelRank (32 factor columns per launch; X alone: 64).

@@ -266,10 +266,10 @@ __device__ __forceinline__ void tail_body(const T* __restrict__ partX, const T* 
 }
 
 template <typename T, int R>
-__global__ void __launch_bounds__(256) k_level_tail(const TailDesc<T> d) {
+__global__ void __launch_bounds__(256) k_level_tail(const TailDesc<T> d, const Strides vs) {
   const int64_t v = blockIdx.y;
-  tail_body<T, R>(d.partX + v * d.vs.x, d.partY + v * d.vs.y, d.partG + v * d.vs.g, d.nct, d.nrt, d.ng, d.n_pad,
-                  d.slabU + v * d.vs.s, d.slabV + v * d.vs.s, d.W, blockIdx.x);
+  tail_body<T, R>(d.partX + v * vs.x, d.partY + v * vs.y, d.partG + v * vs.g, d.nct, d.nrt, d.ng, d.n_pad,
+                  d.slabU + v * vs.s, d.slabV + v * vs.s, d.W, blockIdx.x);
 }
 
 template <typename T, int R>
@@ -719,11 +719,11 @@ __device__ __forceinline__ void update_f64_body(double* __restrict__ P, const in
 }
 
 template <typename T, int R>
-__global__ void __launch_bounds__(256, 2) k_level_update_chain(const UpdateDesc<T> d) {
+__global__ void __launch_bounds__(256, 2) k_level_update_chain(const UpdateDesc<T> d, const int nver, const int64_t sstride) {
   if constexpr (sizeof(T) == 4)
-    update_mfma_body<R, false>(d.P, d.ldp, d.Uj, d.Vj, d.W, nullptr, blockIdx.x, blockIdx.y, d.nver, d.sstride);
+    update_mfma_body<R, false>(d.P, d.ldp, d.Uj, d.Vj, d.W, nullptr, blockIdx.x, blockIdx.y, nver, sstride);
   else
-    update_f64_body<R>(d.P, d.ldp, d.Uj, d.Vj, d.W, blockIdx.x, blockIdx.y, d.nver, d.sstride);
+    update_f64_body<R>(d.P, d.ldp, d.Uj, d.Vj, d.W, blockIdx.x, blockIdx.y, nver, sstride);
 }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -912,10 +912,10 @@ __device__ __forceinline__ void prep_body(const T* __restrict__ U, const int64_t
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_prep(const PrepDesc<T> d) {
+__global__ void __launch_bounds__(256) k_prep(const PrepDesc<T> d, int64_t strideU, int64_t strideV, int64_t sstride) {
   const int64_t v = blockIdx.y;
-  prep_body<T>(d.U + v * d.strideU, d.ldu, d.V + v * d.strideV, d.ldv, d.n, d.r, d.r_pad, d.slabU + v * d.sstride,
-               d.slabV + v * d.sstride, d.W, d.n_pad, blockIdx.x);
+  prep_body<T>(d.U + v * strideU, d.ldu, d.V + v * strideV, d.ldv, d.n, d.r, d.r_pad, d.slabU + v * sstride,
+               d.slabV + v * sstride, d.W, d.n_pad, blockIdx.x);
 }
 
 template <typename T>
@@ -950,12 +950,12 @@ hipError_t update_r(T* P, int64_t ldp, int64_t n_pad, const T* Uj, const T* Vj, 
 }
 
 template <typename T, int R>
-hipError_t update_chain_r(const UpdateDesc<T>& d, hipStream_t s) {
+hipError_t update_chain_r(const UpdateDesc<T>& d, int nver, int64_t sstride, hipStream_t s) {
   if constexpr (R >= 4) {
     const int tr = sizeof(T) == 4 ? kMfmaUpdateTile : kF64UpdateRows;
     const int tc = sizeof(T) == 4 ? kMfmaUpdateTile : kF64UpdateCols;
     hipLaunchKernelGGL((k_level_update_chain<T, R>), dim3((unsigned)(d.n_pad / tc), (unsigned)(d.n_pad / tr)), dim3(256),
-                       0, s, d);
+                       0, s, d, nver, sstride);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -978,8 +978,9 @@ hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG,
 template <typename T, int R>
 hipError_t tail_r(const T* partX, const T* partY, const double* partG, int nct, int nrt, int ng,
                   int64_t n_pad, T* slabU, T* slabV, int W, hipStream_t s, int nver, const Strides& vs) {
-  const TailDesc<T> d{partX, partY, partG, nct, nrt, (int)n_pad, slabU, slabV, W, 0, ng, vs};
-  hipLaunchKernelGGL((k_level_tail<T, R>), dim3((unsigned)tail_blocks(n_pad, R), (unsigned)nver), dim3(256), 0, s, d);
+  const TailDesc<T> d{partX, partY, partG, nct, nrt, (int)n_pad, slabU, slabV, W, 0, ng};
+  hipLaunchKernelGGL((k_level_tail<T, R>), dim3((unsigned)tail_blocks(n_pad, R), (unsigned)nver), dim3(256), 0, s, d,
+                     vs);
   return hipGetLastError();
 }
 
@@ -997,8 +998,9 @@ template <typename T>
 hipError_t launch_prep(const T* U, int64_t ldu, const T* V, int64_t ldv, int64_t n, int r,
                        int r_pad, T* slabU, T* slabV, int W, int64_t n_pad, hipStream_t s, int nver, int64_t strideU,
                        int64_t strideV, int64_t sstride) {
-  const PrepDesc<T> d{U, ldu, V, ldv, n, r, r_pad, slabU, slabV, W, n_pad, 0, strideU, strideV, sstride};
-  hipLaunchKernelGGL((k_prep<T>), dim3((unsigned)((n_pad * r_pad + 255) / 256), (unsigned)nver), dim3(256), 0, s, d);
+  const PrepDesc<T> d{U, ldu, V, ldv, n, r, r_pad, slabU, slabV, W, n_pad, 0};
+  hipLaunchKernelGGL((k_prep<T>), dim3((unsigned)((n_pad * r_pad + 255) / 256), (unsigned)nver), dim3(256), 0, s, d,
+                     strideU, strideV, sstride);
   return hipGetLastError();
 }
 
@@ -1024,9 +1026,9 @@ hipError_t launch_level_update(int R, T* P, int64_t ldp, int64_t n_pad, const T*
 template <typename T>
 hipError_t launch_level_update_chain(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU, const T* slabV, int W,
                                      int nver, int64_t sstride, hipStream_t s) {
-  const UpdateDesc<T> d{P, ldp, (int)n_pad, 0, slabU, slabV + (W - R), W, 0, 0, nullptr, nver, sstride};
-  if (R == kMaxLevelRank) return update_chain_r<T, kMaxLevelRank>(d, s);
-  LV_RANK_SWITCH(R, return (update_chain_r<T, RR>(d, s)))
+  const UpdateDesc<T> d{P, ldp, (int)n_pad, 0, slabU, slabV + (W - R), W, 0, 0, nullptr};
+  if (R == kMaxLevelRank) return update_chain_r<T, kMaxLevelRank>(d, nver, sstride, s);
+  LV_RANK_SWITCH(R, return (update_chain_r<T, RR>(d, nver, sstride, s)))
 }
 
 template <typename T>

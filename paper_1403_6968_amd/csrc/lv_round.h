@@ -25,7 +25,7 @@
 
 namespace lv {
 
-enum Kind { kPrep, kFused, kChunk, kSkinny, kSkinnyF32, kGram, kGramSum, kUpdate, kUpdateShadow, kUpdateSplit, kTail };
+enum Kind { kPrep, kFused, kChunk, kFac16, kWide16, kSkinny, kSkinnyF32, kGram, kGramSum, kUpdate, kUpdateShadow, kUpdateSplit, kTail };
 
 // Views of equal padded rank form a class whose launches depend only on
 // each other; classes run as independent chains on up to kMaxLanes streams.
@@ -127,7 +127,8 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
     pl.level = j;
     std::map<int, std::vector<FusedDesc<T>>> fused;
     std::vector<FusedDesc<T>> chunks;
-    std::map<int, std::vector<SkinnyDesc>> skinny, skinny32;
+    std::map<int, std::vector<SkinnyDesc>> skinny, skinny32, wide;
+    std::vector<Fac16Desc> fac;
     std::map<int, std::vector<GramDesc<T>>> gram;
     std::vector<GramSumDesc> gsum;
     std::map<int, std::vector<UpdateDesc<T>>> upd, updsh, updsplit;
@@ -150,7 +151,14 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
       }
       if constexpr (sizeof(T) == 4) {
         if (v->shadowed() || skinny_on_mfma(R, 4)) {
-          if (v->shadowed()) {
+          if (v->wide16(R)) {
+            fac.push_back(v->fac16(R, j == 0 || R / 2 < kWide16Rank, 0));
+            const int per = wide_cols(R);
+            for (int c0 = 0; c0 < R; c0 += per)
+              wide[per].push_back(wide_desc(v->shadow(j), L.ldp, L.n_pad, v->Ut16(0),
+                                            v->Vt16(0) + (int64_t)(L.W - R) * L.n_pad, R, c0, v->partX<float>(j),
+                                            v->partY<float>(j)));
+          } else if (v->shadowed()) {
             const int per = R <= 64 ? R : 64;
             for (int c0 = 0; c0 < R; c0 += per)
               skinny[skinny_blocks_for(per)].push_back({v->shadow(j), L.ldp, (int)L.n_pad, trows, sU + c0, Vj + c0,
@@ -172,8 +180,9 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
           if (v->shadowed() || !skinny_fuses_update(R))
             (v->shadowed() ? updsh : upd)[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W,
                                                         upd_nct, 0, v->shadowed() ? v->shadow(j) : nullptr});
-          tail[R].push_back({v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, nrt, (int)L.n_pad, sU, sV, L.W,
-                             0, 1});
+          const bool wd = v->wide16(R);
+          tail[R].push_back({v->partX<T>(j), v->partY<T>(j), v->partG(j), wd ? wide_splits(L.n_pad) : L.nct,
+                             wd ? wide_splits(L.n_pad) : nrt, (int)L.n_pad, sU, sV, L.W, 0, 1});
           continue;
         }
       }
@@ -193,6 +202,8 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
     }
     for (auto& kv : fused) pl.add(kFused, kv.first, kv.second, &fused_blocks<T>);
     pl.add(kChunk, kMaxFusedRank, chunks, &fused_blocks<T>);
+    pl.add(kFac16, 0, fac, &fac16_blocks);
+    for (auto& kv : wide) pl.add(kWide16, kv.first, kv.second, [](const SkinnyDesc& d) { return wide_blocks(d); });
     for (auto& kv : skinny) pl.add(kSkinny, kv.first, kv.second, &skinny_blocks);
     for (auto& kv : skinny32) pl.add(kSkinnyF32, kv.first, kv.second, &skinny_blocks);
     for (auto& kv : gram) {
@@ -268,6 +279,8 @@ lv_status enqueue_round(const Plan& pl, const char* dbase, hipStream_t s0, const
       case kGram: e = launch_gram_multi<T>(l.R, static_cast<const GramDesc<T>*>(d), l.nd, l.blocks, s); break;
       case kGramSum: e = launch_gram_sum_multi(static_cast<const GramSumDesc*>(d), l.nd, l.blocks, s); break;
       case kSkinnyF32: e = launch_skinny_f32_multi(l.R, static_cast<const SkinnyDesc*>(d), l.nd, l.blocks, s); break;
+      case kFac16: e = launch_fac16_multi(static_cast<const Fac16Desc*>(d), l.nd, l.blocks, s); break;
+      case kWide16: e = launch_skinny_wide_multi(l.R, static_cast<const SkinnyDesc*>(d), l.nd, l.blocks, s); break;
       case kSkinny: e = launch_skinny_bf16_multi(l.R, static_cast<const SkinnyDesc*>(d), l.nd, l.blocks, s); break;
       case kUpdate:
         e = launch_update_multi<T>(l.R, false, false, static_cast<const UpdateDesc<T>*>(d), l.nd, l.blocks, s);

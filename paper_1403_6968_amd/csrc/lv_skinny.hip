@@ -237,6 +237,206 @@ __global__ void __launch_bounds__(256, 2) k_skinny_bf16_multi(const SkinnyDesc* 
 }
 
 
+// ---------------------------------------------------------------- ranks from 64
+//
+// The factors of these ranks are kept in bfloat16 as well, transposed (column
+// c of U_j is row c of Ut: n_pad values), so that every matrix-core operand but
+// one is 16 consecutive bytes and goes through LDS without conversion.  Y's B
+// operand needs 8 consecutive rows of one column: ds_read_b64_tr_b16, which
+// hands lane i of 16 the column i of the 4 x 16 block whose 16 pieces of 8
+// bytes the lanes address.
+
+// One block: rows [64 (blk % tiles), + 64) of 32 columns of U or V, transposed
+// and rounded into Ut / Vt.
+__device__ __forceinline__ void fac16_body(const Fac16Desc& d, int blk) {
+  __shared__ float t[64][33];
+  const int tid = threadIdx.x;
+  const int tiles = d.n_pad / 64, cols = d.cols / 32;
+  const int row0 = blk % tiles * 64;
+  blk /= tiles;
+  const bool isv = blk >= cols;
+  const int c0 = (isv ? blk - cols : blk) * 32;
+  const float* __restrict__ src = d.U + (isv ? (int64_t)d.n_pad * d.W + d.dv : 0) + (int64_t)row0 * d.W + c0;
+  uint16_t* __restrict__ dst = d.Ut + (int64_t)((isv ? d.W + d.dv : 0) + c0) * d.n_pad + row0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int e = tid + 256 * i;
+    t[e / 32][e % 32] = src[(int64_t)(e / 32) * d.W + e % 32];
+  }
+  __syncthreads();
+  const int c = tid / 8, r8 = tid % 8 * 8;
+  u16x8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = bf16_rne(t[r8 + e][c]);
+  *reinterpret_cast<u16x8*>(dst + (int64_t)c * d.n_pad + r8) = o;
+}
+
+__global__ void __launch_bounds__(256) k_fac16(const Fac16Desc d) { fac16_body(d, blockIdx.x); }
+
+__global__ void __launch_bounds__(256) k_fac16_multi(const Fac16Desc* __restrict__ ds, int nd) {
+  const Fac16Desc d = load_desc(ds, find_desc(ds, nd, (int)blockIdx.x));
+  fac16_body(d, (int)blockIdx.x - d.block_begin);
+}
+
+// Piece (16 bytes) g of a staged shadow row r sits at g ^ tr_swizzle(r): 4
+// pieces further per row, one per group of 4 rows.
+__device__ __forceinline__ int tr_swizzle(const int r) { return 4 * (r & 3) | ((r >> 2) & 3); }
+
+// B operand (32x32x16) of rows r0 .. r0 + 15 and columns c0 .. c0 + 31 of a
+// staged block with rows of LD values: lanes 16 g .. 16 g + 15 take rows 8 (g /
+// 2) .. + 7 of columns 16 (g % 2) .. + 15; lane i of a group addresses row i /
+// 4, columns 4 (i % 4) .. + 3 of each 4-row half.
+template <int LD> __device__ __forceinline__ bf16x8 tr_operand(uint16_t* s, const int r0, const int c0, const int lane) {
+  typedef short v4s __attribute__((ext_vector_type(4)));
+  typedef short v8s __attribute__((ext_vector_type(8)));
+  const int li = lane & 15;
+  const int c = c0 + (lane >> 4 & 1) * 16 + li % 4 * 4;
+  v4s h[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int r = r0 + 8 * (lane >> 5) + 4 * e + li / 4;
+    uint16_t* at = s + r * LD + ((c / 8) ^ tr_swizzle(r)) * 8 + c % 8;
+    h[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)at);
+  }
+  return __builtin_bit_cast(bf16x8, (v8s)__builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// X = S U and Y = S^T V as two products of their own in one launch, the
+// summation range split over wide_splits() work-groups.  What bounds it: the
+// partial sums.  One pass over 2-D tiles (skinny_body) leaves about 2
+// sqrt(work-groups) partials of each entry (42 at n = 7168: 308 MB at R = 256,
+// written and read again); a product on its own leaves as many as its range is
+// split (5 and 5 there), and reading the shadow twice costs less from R = 64
+// on.  Work-group: 128 rows (X) or columns (Y) of S by BN factor columns, 4
+// waves in 2 x 2, 64-deep steps through LDS, the next step in registers
+// meanwhile.
+//   X: A = S rows, B = Ut rows; Y: A = Vt rows, B = S columns (transposed reads).
+// 16-byte pieces of the staged rows are permuted so that the operand reads
+// touch all banks evenly.  At n = 7168 (the 2-D pass, which converts float
+// factors as it stages them -> this): R = 64 56.5 -> 48.0 us, R = 128 113 ->
+// 59 us, R = 256 226 -> 118 us, and the tail that adds the partials 51 -> 32 us
+// and 228 -> 153 us at R = 128 and 256.  At R = 32 the 2-D pass stays (39 us;
+// from bfloat16 factors 46 us).
+constexpr int kGemmTile = 128, kGemmStep = 64;
+template <int BN, bool YP>
+__device__ __forceinline__ void skinny_gemm_body(const SkinnyDesc& d, uint16_t* sS, uint16_t* sF, const int tile,
+                                                 const int split, const int splits) {
+  constexpr int TM = kGemmTile, KS = kGemmStep;
+  constexpr int SP = TM * KS / 8 / 256, FP = BN * KS / 8 / 256;   // pieces per thread
+  constexpr int WB = BN / 64;                                      // 32-wide factor blocks per wave
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = wave_id();
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int n_pad = d.n_pad, pR = d.pR;
+  const int m0 = tile * TM;
+  const int nsteps = n_pad / KS;
+  const int s0 = (int)((int64_t)nsteps * split / splits), s1 = (int)((int64_t)nsteps * (split + 1) / splits);
+  const uint16_t* __restrict__ S = static_cast<const uint16_t*>(d.src);
+  const uint16_t* __restrict__ F = reinterpret_cast<const uint16_t*>(YP ? d.Vj : d.Uj);
+
+  u16x8 ps[SP], pf[FP];
+  auto fetch = [&](const int st) {
+    const int64_t k0 = (int64_t)st * KS;
+    static_for<0, SP>([&](auto i) {
+      const int q = tid + 256 * i;
+      if constexpr (YP) ps[i] = *reinterpret_cast<const u16x8*>(S + (k0 + q / (TM / 8)) * d.ldp + m0 + q % (TM / 8) * 8);
+      else ps[i] = *reinterpret_cast<const u16x8*>(S + (int64_t)(m0 + q / 8) * d.ldp + k0 + q % 8 * 8);
+    });
+    static_for<0, FP>([&](auto i) {
+      const int q = tid + 256 * i;
+      pf[i] = *reinterpret_cast<const u16x8*>(F + (int64_t)(q / 8) * n_pad + k0 + q % 8 * 8);
+    });
+  };
+  // rows of 8 pieces (128 bytes): two rows apart by one piece
+  auto piece = [](const int r, const int g) { return r * KS + (g ^ ((r >> 1) & 7)) * 8; };
+  fetch(s0);
+  v16f acc[2][WB];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < WB; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+
+  for (int st = s0; st < s1; ++st) {
+    __syncthreads();
+    static_for<0, SP>([&](auto i) {
+      const int q = tid + 256 * i;
+      if constexpr (YP) {
+        const int r = q / (TM / 8);
+        *reinterpret_cast<u16x8*>(&sS[r * TM + ((q % (TM / 8)) ^ tr_swizzle(r)) * 8]) = ps[i];
+      } else {
+        *reinterpret_cast<u16x8*>(&sS[piece(q / 8, q % 8)]) = ps[i];
+      }
+    });
+    static_for<0, FP>([&](auto i) {
+      const int q = tid + 256 * i;
+      *reinterpret_cast<u16x8*>(&sF[piece(q / 8, q % 8)]) = pf[i];
+    });
+    __syncthreads();
+    if (st + 1 < s1) fetch(st + 1);
+#pragma unroll
+    for (int ks = 0; ks < KS / 16; ++ks) {
+      bf16x8 so[2], fo[WB];
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        if constexpr (YP) so[a] = tr_operand<TM>(sS, ks * 16, wm * 64 + a * 32, lane);
+        else so[a] = lds8(&sS[piece(wm * 64 + a * 32 + l32, 2 * ks + lh)]);
+      }
+#pragma unroll
+      for (int b = 0; b < WB; ++b) fo[b] = lds8(&sF[piece(wn * 32 * WB + b * 32 + l32, 2 * ks + lh)]);
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < WB; ++b)
+          acc[a][b] = YP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[b], so[a], acc[a][b], 0, 0, 0)
+                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(so[a], fo[b], acc[a][b], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < WB; ++b) {
+      const int m = m0 + wm * 64 + a * 32, c = wn * 32 * WB + b * 32;
+      if constexpr (YP) {
+        // values 4 q .. 4 q + 3 of a lane are four consecutive factor columns
+        float* py = d.partY + ((int64_t)split * n_pad + m + l32) * pR + c + 4 * lh;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4*>(py + 8 * q) =
+              f32x4{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
+      } else {
+        float* px = d.partX + ((int64_t)split * n_pad + m + 4 * lh) * pR + c + l32;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) px[(8 * (v / 4) + v % 4) * pR] = acc[a][b][v];
+      }
+    }
+}
+
+// Work-groups of one launch: the X products, then the Y products; tiles of one
+// split are neighbours (they share the factor rows of its range).
+template <int BN>
+__device__ __forceinline__ void skinny_gemm(const SkinnyDesc& d, int blk) {
+  __shared__ __align__(16) uint16_t sS[kGemmTile * kGemmStep];
+  __shared__ __align__(16) uint16_t sF[BN * kGemmStep];
+  const int tiles = d.n_pad / kGemmTile, splits = wide_splits(d.n_pad);
+  const bool yp = blk >= tiles * splits;
+  if (yp) blk -= tiles * splits;
+  if (yp) skinny_gemm_body<BN, true>(d, sS, sF, blk % tiles, blk / tiles, splits);
+  else skinny_gemm_body<BN, false>(d, sS, sF, blk % tiles, blk / tiles, splits);
+}
+
+template <int BN>
+__global__ void __launch_bounds__(256, 2) k_skinny_gemm(const SkinnyDesc d) { skinny_gemm<BN>(d, blockIdx.x); }
+
+template <int BN>
+__global__ void __launch_bounds__(256, 2) k_skinny_gemm_multi(const SkinnyDesc* __restrict__ ds, int nd) {
+  const SkinnyDesc d = load_desc(ds, find_skinny(ds, nd, (int)blockIdx.x));
+  skinny_gemm<BN>(d, (int)blockIdx.x - d.block_begin);
+}
+
 // Update fused into the float skinny pass (R = 16 or 32 factor columns, one
 // launch): blocks of 512 threads, waves 0-3 form X and Y on the matrix cores
 // as the read-only pass does and waves 4-7 apply P += U_j V_j^T to the same
@@ -829,6 +1029,42 @@ hipError_t launch_skinny_bf16_multi(int nb, const SkinnyDesc* ds, int nd, int bl
   switch (nb) {
     case 1: hipLaunchKernelGGL((k_skinny_bf16_multi<1>), dim3((unsigned)blocks), dim3(256), 0, s, ds, nd); break;
     case 2: hipLaunchKernelGGL((k_skinny_bf16_multi<2>), dim3((unsigned)blocks), dim3(256), 0, s, ds, nd); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_fac16(const Fac16Desc& d, hipStream_t s) {
+  if (d.cols % 32 != 0 || d.n_pad % 64 != 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_fac16, dim3((unsigned)fac16_blocks(d)), dim3(256), 0, s, d);
+  return hipGetLastError();
+}
+
+hipError_t launch_fac16_multi(const Fac16Desc* ds, int nd, int blocks, hipStream_t s) {
+  if (blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_fac16_multi, dim3((unsigned)blocks), dim3(256), 0, s, ds, nd);
+  return hipGetLastError();
+}
+
+hipError_t launch_skinny_wide(const uint16_t* S, int64_t ldp, int64_t n_pad, const uint16_t* Ut, const uint16_t* Vt,
+                              int R, float* partX, float* partY, hipStream_t s) {
+  if (R < kWide16Rank || R > kMaxLevelRank || (R & (R - 1)) != 0 || n_pad % TCB != 0) return hipErrorInvalidValue;
+  for (int c0 = 0; c0 < R; c0 += wide_cols(R)) {
+    const SkinnyDesc d = wide_desc(S, ldp, n_pad, Ut, Vt, R, c0, partX, partY);
+    const dim3 grid((unsigned)wide_blocks(n_pad));
+    if (R == 64) hipLaunchKernelGGL((k_skinny_gemm<64>), grid, dim3(256), 0, s, d);
+    else hipLaunchKernelGGL((k_skinny_gemm<128>), grid, dim3(256), 0, s, d);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_skinny_wide_multi(int per, const SkinnyDesc* ds, int nd, int blocks, hipStream_t s) {
+  if (blocks <= 0) return hipSuccess;
+  switch (per) {
+    case 64: hipLaunchKernelGGL((k_skinny_gemm_multi<64>), dim3((unsigned)blocks), dim3(256), 0, s, ds, nd); break;
+    case 128: hipLaunchKernelGGL((k_skinny_gemm_multi<128>), dim3((unsigned)blocks), dim3(256), 0, s, ds, nd); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

@@ -382,6 +382,25 @@ struct lv_view {
   double* gB() const { return reinterpret_cast<double*>(base + L.gB); }
   uint16_t* shadow(int j) const { return reinterpret_cast<uint16_t*>(base + L.shadow[j]); }
   bool shadowed() const { return mode == LV_FP32_BF16SHADOW; }
+  // Transposed bfloat16 factors of the levels from rank kWide16Rank (shadow
+  // mode): row c holds column c of a slot's slab.  They live in the squaring
+  // scratch, which only creation, re-anchoring and the drift check's gated
+  // chain use, each ordered after the update on its stream; an order too
+  // small for the slots of that scratch keeps the passes on float factors.
+  bool wide16(int R) const {
+    return shadowed() && R >= lv::kWide16Rank && (int64_t)(L.pipe_slots > 1 ? L.pipe_slots : 1) * 4 * L.W <= 16 * L.n_pad;
+  }
+  uint16_t* Ut16(int slot) const {
+    return reinterpret_cast<uint16_t*>(base + L.scratch[0]) + (int64_t)slot * 2 * L.W * L.n_pad;
+  }
+  uint16_t* Vt16(int slot) const { return Ut16(slot) + (int64_t)L.W * L.n_pad; }
+  // The columns of a level's factors that the level below has not converted:
+  // all of them at the first such level, else the block that its tail added.
+  lv::Fac16Desc fac16(int R, bool first, int slot) const {
+    const int cols = first ? R : R / 2, cu = R - cols, cv = L.W - R;
+    // (a float slab of n_pad x W values fills whole 256-byte units: V's follows U's directly)
+    return {slabU<float>(slot) + cu, Ut16(slot) + (int64_t)cu * L.n_pad, L.W, (int)L.n_pad, cols, cv - cu, 0};
+  }
   double* scratch(int i) const { return reinterpret_cast<double*>(base + L.scratch[i]); }
   double* zpad() const { return reinterpret_cast<double*>(base + L.probe); }
   double* drift_z() const { return reinterpret_cast<double*>(base + L.drift_z); }
