@@ -475,6 +475,27 @@ lv_status gfac_finish(lv_view* v, int ru, const T* sU, hipStream_t s) {
   return st;
 }
 
+// Level j of nver (2 or 4) successive updates of a batch in the bfloat16-shadow
+// mode (factors in successive slots): one pass, then Gram and tail of all.
+lv_status shadow_chain_step(lv_view* v, int j, int r_pad, float* sU, float* sV, hipStream_t s, int nver) {
+  const Layout& L = v->L;
+  const int R = r_pad << j;
+  const auto a = v->chain16(r_pad, j);
+  float *px = reinterpret_cast<float*>(a.px), *py = reinterpret_cast<float*>(a.py);
+  double* pg = reinterpret_cast<double*>(a.pg);
+  lv_status st = timed(v, 0, s, "level pass", [&] {
+    return launch_shadow_chain(R, {v->P<float>(j), v->shadow(j), L.ldp, (int)L.n_pad, v->rows(j, R), sU, sV + (L.W - R),
+                                   L.W, reinterpret_cast<uint16_t*>(a.f16), a.f32, px, py, a.vs}, nver, s);
+  });
+  if (st == LV_OK)
+    st = timed(v, 0, s, "gram", [&] { return launch_level_gram<float>(R, sU, sV, L.W, L.n_pad, pg, s, nver, a.vs); });
+  if (st == LV_OK)
+    st = timed(v, 1, s, "level tail", [&] {
+      return launch_level_tail<float>(R, px, py, pg, L.nct, v->nrt(j, R), 1, L.n_pad, sU, sV, L.W, s, nver, a.vs);
+    });
+  return st;
+}
+
 // Level j of one update (App. A exponential model; trigger of Sec. 4.4) with
 // the update's factors in the slabs sU, sV: the fused pass and the tail (or,
 // for float storage at large level rank and with bfloat16 shadows, the
@@ -487,6 +508,8 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
   const Layout& L = v->L;
   lv_status st = LV_OK;
   const int R = r_pad << j;
+  if constexpr (sizeof(T) == 4)
+    if (nver > 1 && v->shadowed()) return shadow_chain_step(v, j, r_pad, sU, sV, s, nver);
   const int nrt = v->nrt(j, R);
   const Strides vs = {(int64_t)(L.slot_stride / sizeof(T)), (int64_t)L.nct * L.n_pad * R, (int64_t)nrt * L.n_pad * R,
                       (int64_t)nrt * R * R};
@@ -685,7 +708,9 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
   // the slots hold D chunks of C updates; one update in flight per stage is
   // enough where each has passes of its own (more only widen the working set:
   // rank-4 shadow batches n = 8192 23.46 ms with 5, 23.74 ms with 12)
-  const int C = v->chunk(r_pad), D = C > 1 ? L.pipe_slots / C : std::min(L.pipe_slots, std::min(L.m + 1, 5));
+  const int C = v->chunk(r_pad);
+  const int D = C > 1 ? std::min(L.pipe_slots / C, v->shadowed() ? kPipeChunks : L.pipe_slots)
+                      : std::min(L.pipe_slots, std::min(L.m + 1, 5));
   const int64_t sstride = (int64_t)(L.slot_stride / sizeof(T));
   auto stream_of = [&](int j) { const int q = pipe_stage(v, j); return q == 0 ? s : v->pstream[q]; };
   auto ev = [&](hipError_t e, const char* what) { return e == hipSuccess ? LV_OK : fail(LV_EDEVICE, "%s failed", what); };
@@ -711,7 +736,8 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
       const int R = r_pad << j;
       // groups of the chunk's updates that share the level's pass: halving
       // with the level's rank, so each lies inside one of the level below
-      const int most = fused_vector_level(R, (int)sizeof(T), v->shadowed()) ? chain_updates(R) : 1;
+      const int most = v->shadowed() ? (v->chain16(r_pad, j).at ? chain16_updates(R) : 1)
+                       : fused_vector_level(R, (int)sizeof(T), false) ? chain_updates(R) : 1;
       for (int a = 0, g = 0; a < cnt && st == LV_OK; a += g) {
         for (g = most; g > cnt - a; g /= 2) {}
         const int last = slot + a + g - 1;
@@ -725,11 +751,11 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
       }
     }
     hipStream_t st_top = stream_of(L.m - 1);
-    if (cnt > 1 && !v->shadowed() && Rm <= kMaxLevelRank) {
+    if (cnt > 1 && Rm <= kMaxLevelRank) {
       // the chunk's top updates in one read and write of P_m
       if (st == LV_OK)
         st = hip_check(launch_level_update_chain<T>(Rm, v->P<T>(L.m), L.ldp, L.n_pad, v->slabU<T>(slot),
-                                                    v->slabV<T>(slot), L.W, cnt, sstride, st_top),
+                                                    v->slabV<T>(slot), L.W, cnt, sstride, st_top, v->shadowed()),
                        "top update");
     } else {
       for (int a = 0; a < cnt && st == LV_OK; ++a)

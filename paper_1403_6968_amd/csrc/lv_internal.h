@@ -301,13 +301,13 @@ hipError_t launch_level_update(int R, T* P, int64_t ldp, int64_t n_pad, const T*
 // once: the results of nver launch_level_update calls bit for bit.
 template <typename T>
 hipError_t launch_level_update_chain(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU, const T* slabV, int W,
-                                     int nver, int64_t sstride, hipStream_t s);
+                                     int nver, int64_t sstride, hipStream_t s, bool split = false);
 
 // Gram V_j^T U_j in double: gram_tiles(n_pad) partials of kGramRows rows,
 // then their sum in fixed order into partG[0 .. R*R).
 template <typename T>
 hipError_t launch_level_gram(int R, const T* slabU, const T* slabV, int W, int64_t n_pad, double* partG,
-                             hipStream_t s);
+                             hipStream_t s, int nver = 1, const Strides& vs = {});
 hipError_t launch_gram_sum_multi(const GramSumDesc* ds, int nd, int blocks, hipStream_t s);
 
 // Skinny products of level rank R (<= kMaxLevelRank) from the bfloat16 shadow S on the
@@ -345,6 +345,23 @@ hipError_t launch_fac16(const Fac16Desc& d, hipStream_t s);
 hipError_t launch_fac16_multi(const Fac16Desc* ds, int nd, int blocks, hipStream_t s);
 hipError_t launch_skinny_wide(const uint16_t* S, int64_t ldp, int64_t n_pad, const uint16_t* Ut, const uint16_t* Vt,
                               int R, float* partX, float* partY, hipStream_t s);
+// Shadowed levels of rank R <= kChain16Rank for nver = 2 or 4 successive
+// updates of a batch: the factors' operand forms, then both products
+// and the update of each in turn at one read and write of P.  f16, f32:
+// chain_factor_bytes(n_pad, R) in all for each update; partials as the single
+// updates' ones with row stride R, vs apart; S is rewritten.
+constexpr int kChain16Rank = 32;
+constexpr int kChain16Updates = 4;   // the larger of the two
+constexpr int chain16_updates(int R) { return R < 32 ? 4 : 2; }
+struct ChainDesc {
+  float* P; uint16_t* S; int64_t ldp; int n_pad; int tile_rows;
+  const float* U; const float* V; int W;   // first update's U_j and V_j
+  uint16_t* f16; void* f32;
+  float* partX; float* partY; Strides vs;
+};
+inline size_t chain_f16_bytes(int64_t n_pad, int R) { return (size_t)n_pad * 4 * R; }                  // per update
+inline size_t chain_f32_bytes(int64_t n_pad, int R) { return (size_t)n_pad * 8 * (R < 4 ? 4 : R); }    // per update
+hipError_t launch_shadow_chain(int R, const ChainDesc& d, int nver, hipStream_t s);
 hipError_t launch_skinny_wide_multi(int per, const SkinnyDesc* ds, int nd, int blocks, hipStream_t s);
 
 // The same products from the float power P (v_mfma_f32_32x32x2f32, float

@@ -73,8 +73,10 @@ __device__ __forceinline__ void gram_body(const T* __restrict__ Uj, const T* __r
 }
 
 template <typename T, int R>
-__global__ void __launch_bounds__(256) k_gram(const GramDesc<T> d) {
-  gram_body<T, R>(d.Uj, d.Vj, d.W, d.n_pad, d.tile_rows, d.partG, blockIdx.x, blockIdx.y);
+__global__ void __launch_bounds__(256) k_gram(const GramDesc<T> d, const int64_t sstride, const int64_t gstride) {
+  const int64_t v = blockIdx.z;
+  gram_body<T, R>(d.Uj + v * sstride, d.Vj + v * sstride, d.W, d.n_pad, d.tile_rows, d.partG + v * gstride, blockIdx.x,
+                  blockIdx.y);
 }
 
 template <typename T, int R>
@@ -103,7 +105,9 @@ __device__ __forceinline__ void gram_sum_body(double* __restrict__ G, const int 
   G[idx] = g;
 }
 
-__global__ void __launch_bounds__(256) k_gram_sum(const GramSumDesc d) { gram_sum_body(d.G, d.ng, d.count, blockIdx.x); }
+__global__ void __launch_bounds__(256) k_gram_sum(const GramSumDesc d, const int64_t gstride) {
+  gram_sum_body(d.G + blockIdx.y * gstride, d.ng, d.count, blockIdx.x);
+}
 
 __global__ void __launch_bounds__(256) k_gram_sum_multi(const GramSumDesc* __restrict__ ds, int nd) {
   const GramSumDesc d = load_desc(ds, find_desc(ds, nd, (int)blockIdx.x));
@@ -718,14 +722,6 @@ __device__ __forceinline__ void update_f64_body(double* __restrict__ P, const in
       for (int v = 0; v < 4; ++v) __builtin_nontemporal_store(p[a][b][v], Pw + (int64_t)(a * 16 + 4 * v) * ldp + b * 16);
 }
 
-template <typename T, int R>
-__global__ void __launch_bounds__(256, 2) k_level_update_chain(const UpdateDesc<T> d, const int nver, const int64_t sstride) {
-  if constexpr (sizeof(T) == 4)
-    update_mfma_body<R, false>(d.P, d.ldp, d.Uj, d.Vj, d.W, nullptr, blockIdx.x, blockIdx.y, nver, sstride);
-  else
-    update_f64_body<R>(d.P, d.ldp, d.Uj, d.Vj, d.W, blockIdx.x, blockIdx.y, nver, sstride);
-}
-
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
@@ -739,10 +735,11 @@ __device__ __forceinline__ float bf16_value(uint16_t h) { return __builtin_bit_c
 // Same tiles, waves and accumulator layout as update_mfma_body; a lane of a
 // 16-column step supplies factor columns 8 (l / 32) + e, e = 0..7, for both
 // operands.
-template <int R, bool SH>
+template <int R, bool SH, bool CHAIN = false>
 __device__ __forceinline__ void update_split_body(float* __restrict__ P, const int64_t ldp,
                                                   const float* __restrict__ Uj, const float* __restrict__ Vj,
-                                                  const int W, uint16_t* __restrict__ S, const int ct, const int rt) {
+                                                  const int W, uint16_t* __restrict__ S, const int ct, const int rt,
+                                                  const int nver = 1, const int64_t sstride = 0) {
   constexpr int TT = kMfmaUpdateTile, KC = 32, KP = KC + 8;
   static_assert(R % KC == 0, "rank must be a multiple of 32");
   __shared__ __align__(16) uint16_t sUh[TT][KP], sUl[TT][KP], sVh[TT][KP], sVl[TT][KP];
@@ -757,7 +754,7 @@ __device__ __forceinline__ void update_split_body(float* __restrict__ P, const i
   // products); from R = 128 after them, so that the products run without
   // the 64 registers they occupy (two waves per SIMD instead of one then
   // hide the latency; see update_min_waves)
-  constexpr bool LATE_P = R >= 128;
+  constexpr bool LATE_P = R >= 128 && !CHAIN;
   float p[2][2][16];
   auto load_p = [&]() {
 #pragma unroll
@@ -770,6 +767,23 @@ __device__ __forceinline__ void update_split_body(float* __restrict__ P, const i
                                                            (v % 4)) * ldp + col0 + wn * 64 + b * 32 + l32]);
   };
   if constexpr (!LATE_P) load_p();
+  // The factor values of the next column group are requested before the
+  // products of the current one (registers: 8 float4 per thread).
+  constexpr int SPT = TT * KC / 4 / 256;
+  float4 nu[SPT], nw[SPT];
+  auto fetch_uv = [&](const float* fu, const float* fv, const int kc) {
+#pragma unroll
+    for (int i = 0; i < SPT; ++i) {
+      const int q = tid + 256 * i;
+      const int r = q >> 3, c4 = (q & 7) * 4;
+      nu[i] = *reinterpret_cast<const float4*>(fu + (int64_t)(row0 + r) * W + kc + c4);
+      nw[i] = *reinterpret_cast<const float4*>(fv + (int64_t)(col0 + r) * W + kc + c4);
+    }
+  };
+  int kend = R;
+  if constexpr (CHAIN) asm("" : "+s"(kend));   // not unrolled: the old values take the registers
+  fetch_uv(Uj, Vj, 0);
+  for (int ver = 0; ver < nver; ++ver, Uj += sstride, Vj += sstride) {
   v16f acc[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -778,21 +792,7 @@ __device__ __forceinline__ void update_split_body(float* __restrict__ P, const i
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-  // The factor values of the next column group are requested before the
-  // products of the current one (registers: 8 float4 per thread).
-  constexpr int SPT = TT * KC / 4 / 256;
-  float4 nu[SPT], nw[SPT];
-  auto fetch_uv = [&](const int kc) {
-#pragma unroll
-    for (int i = 0; i < SPT; ++i) {
-      const int q = tid + 256 * i;
-      const int r = q >> 3, c4 = (q & 7) * 4;
-      nu[i] = *reinterpret_cast<const float4*>(Uj + (int64_t)(row0 + r) * W + kc + c4);
-      nw[i] = *reinterpret_cast<const float4*>(Vj + (int64_t)(col0 + r) * W + kc + c4);
-    }
-  };
-  fetch_uv(0);
-  for (int kc = 0; kc < R; kc += KC) {
+  for (int kc = 0; kc < kend; kc += KC) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < SPT; ++i) {
@@ -810,7 +810,8 @@ __device__ __forceinline__ void update_split_body(float* __restrict__ P, const i
       }
     }
     __syncthreads();
-    if (kc + KC < R) fetch_uv(kc + KC);
+    if (kc + KC < kend) fetch_uv(Uj, Vj, kc + KC);
+    else if (CHAIN && ver + 1 < nver) fetch_uv(Uj + sstride, Vj + sstride, 0);
 #pragma unroll
     for (int ks = 0; ks < KC; ks += 16) {
       bf16x8 ah[2], al[2], bh[2], bl[2];
@@ -841,13 +842,34 @@ __device__ __forceinline__ void update_split_body(float* __restrict__ P, const i
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
+      for (int v = 0; v < 16; ++v) p[a][b][v] += acc[a][b][v];
+  }
+
+  // (the loads' 64 addresses are not kept for the stores)
+  int ln = lane;
+  if constexpr (CHAIN) asm volatile("" : "+v"(ln));
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int64_t o = (int64_t)(row0 + wm * 64 + a * 32 + 8 * (v / 4) + 4 * lh + (v % 4)) * ldp + col0 +
-                          wn * 64 + b * 32 + l32;
-        const float x = p[a][b][v] + acc[a][b][v];
-        __builtin_nontemporal_store(x, &P[o]);
-        if constexpr (SH) S[o] = bf16_rne(x);
+        const int64_t o = (int64_t)(row0 + wm * 64 + a * 32 + 8 * (v / 4) + 4 * (ln >> 5) + (v % 4)) * ldp + col0 +
+                          wn * 64 + b * 32 + (ln & 31);
+        __builtin_nontemporal_store(p[a][b][v], &P[o]);
+        if constexpr (SH) S[o] = bf16_rne(p[a][b][v]);
       }
+}
+
+// Runs of successive updates (SPLIT: split products from rank 32).
+template <typename T, int R, bool SPLIT>
+__global__ void __launch_bounds__(256, 2) k_level_update_chain(const UpdateDesc<T> d, const int nver, const int64_t sstride) {
+  if constexpr (sizeof(T) == 4 && SPLIT && R >= kMfmaUpdateRank)
+    update_split_body<R, false, true>(d.P, d.ldp, d.Uj, d.Vj, d.W, nullptr, blockIdx.x, blockIdx.y, nver, sstride);
+  else if constexpr (sizeof(T) == 4)
+    update_mfma_body<R, false>(d.P, d.ldp, d.Uj, d.Vj, d.W, nullptr, blockIdx.x, blockIdx.y, nver, sstride);
+  else
+    update_f64_body<R>(d.P, d.ldp, d.Uj, d.Vj, d.W, blockIdx.x, blockIdx.y, nver, sstride);
 }
 
 // SPLIT selects the split-bfloat16 products (bfloat16-shadow mode) for the
@@ -950,11 +972,19 @@ hipError_t update_r(T* P, int64_t ldp, int64_t n_pad, const T* Uj, const T* Vj, 
 }
 
 template <typename T, int R>
-hipError_t update_chain_r(const UpdateDesc<T>& d, int nver, int64_t sstride, hipStream_t s) {
+hipError_t update_chain_r(const UpdateDesc<T>& d, int nver, int64_t sstride, hipStream_t s, bool split) {
+  if constexpr (sizeof(T) == 4 && R >= kMfmaUpdateRank) {
+    if (split) {
+      hipLaunchKernelGGL((k_level_update_chain<T, R, true>),
+                         dim3((unsigned)(d.n_pad / kMfmaUpdateTile), (unsigned)(d.n_pad / kMfmaUpdateTile)), dim3(256), 0,
+                         s, d, nver, sstride);
+      return hipGetLastError();
+    }
+  }
   if constexpr (R >= 4) {
     const int tr = sizeof(T) == 4 ? kMfmaUpdateTile : kF64UpdateRows;
     const int tc = sizeof(T) == 4 ? kMfmaUpdateTile : kF64UpdateCols;
-    hipLaunchKernelGGL((k_level_update_chain<T, R>), dim3((unsigned)(d.n_pad / tc), (unsigned)(d.n_pad / tr)), dim3(256),
+    hipLaunchKernelGGL((k_level_update_chain<T, R, false>), dim3((unsigned)(d.n_pad / tc), (unsigned)(d.n_pad / tr)), dim3(256),
                        0, s, d, nver, sstride);
     return hipGetLastError();
   }
@@ -963,15 +993,17 @@ hipError_t update_chain_r(const UpdateDesc<T>& d, int nver, int64_t sstride, hip
 
 // Stand-alone Gram: gram_tiles(n_pad) partials, then their sum into the first.
 template <typename T, int R>
-hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG, hipStream_t s) {
+hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG, hipStream_t s, int nver = 1,
+                  int64_t sstride = 0, int64_t gstride = 0) {
   const int ng = gram_tiles(n_pad);
   const GramDesc<T> g{Uj, Vj, W, (int)n_pad, kGramRows, partG, ng, 0};
-  const dim3 ggrid((unsigned)ng, (unsigned)((R * R + gram_pairs_per_block(R) - 1) / gram_pairs_per_block(R)));
-  hipLaunchKernelGGL((k_gram<T, R>), ggrid, dim3(256), 0, s, g);
+  const dim3 ggrid((unsigned)ng, (unsigned)((R * R + gram_pairs_per_block(R) - 1) / gram_pairs_per_block(R)),
+                   (unsigned)nver);
+  hipLaunchKernelGGL((k_gram<T, R>), ggrid, dim3(256), 0, s, g, sstride, gstride);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const GramSumDesc gs{partG, ng, R * R, 0};
-  hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)((R * R + 255) / 256)), dim3(256), 0, s, gs);
+  hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)((R * R + 255) / 256), (unsigned)nver), dim3(256), 0, s, gs, gstride);
   return hipGetLastError();
 }
 
@@ -1025,19 +1057,19 @@ hipError_t launch_level_update(int R, T* P, int64_t ldp, int64_t n_pad, const T*
 
 template <typename T>
 hipError_t launch_level_update_chain(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU, const T* slabV, int W,
-                                     int nver, int64_t sstride, hipStream_t s) {
+                                     int nver, int64_t sstride, hipStream_t s, bool split) {
   const UpdateDesc<T> d{P, ldp, (int)n_pad, 0, slabU, slabV + (W - R), W, 0, 0, nullptr};
-  if (R == kMaxLevelRank) return update_chain_r<T, kMaxLevelRank>(d, nver, sstride, s);
-  LV_RANK_SWITCH(R, return (update_chain_r<T, RR>(d, nver, sstride, s)))
+  if (R == kMaxLevelRank) return update_chain_r<T, kMaxLevelRank>(d, nver, sstride, s, split);
+  LV_RANK_SWITCH(R, return (update_chain_r<T, RR>(d, nver, sstride, s, split)))
 }
 
 template <typename T>
 hipError_t launch_level_gram(int R, const T* slabU, const T* slabV, int W, int64_t n_pad, double* partG,
-                             hipStream_t s) {
+                             hipStream_t s, int nver, const Strides& vs) {
   const T* Uj = slabU;
   const T* Vj = slabV + (W - R);
-  if (R == kMaxLevelRank) return gram_r<T, kMaxLevelRank>(Uj, Vj, W, n_pad, partG, s);
-  LV_RANK_SWITCH(R, return (gram_r<T, RR>(Uj, Vj, W, n_pad, partG, s)))
+  if (R == kMaxLevelRank) return gram_r<T, kMaxLevelRank>(Uj, Vj, W, n_pad, partG, s, nver, vs.s, vs.g);
+  LV_RANK_SWITCH(R, return (gram_r<T, RR>(Uj, Vj, W, n_pad, partG, s, nver, vs.s, vs.g)))
 }
 
 template <typename T>
@@ -1083,7 +1115,7 @@ hipError_t launch_add(T* dst, const T* src, int64_t count, hipStream_t s, const 
 
 hipError_t launch_gram_sum(double* G, int ng, int count, hipStream_t s) {
   const GramSumDesc d{G, ng, count, 0};
-  hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, d);
+  hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, d, (int64_t)0);
   return hipGetLastError();
 }
 
@@ -1148,11 +1180,11 @@ hipError_t launch_prep_multi(const PrepDesc<T>* ds, int nd, int blocks, hipStrea
   template hipError_t launch_level_tail<T>(int, const T*, const T*, const double*, int, int, int, \
                                            int64_t, T*, T*, int, hipStream_t, int, const Strides&); \
   template hipError_t launch_level_update_chain<T>(int, T*, int64_t, int64_t, const T*, const T*, int, int, int64_t, \
-                                                   hipStream_t);                                  \
+                                                   hipStream_t, bool);                            \
   template hipError_t launch_level_update<T>(int, T*, int64_t, int64_t, const T*, const T*, int,  \
                                              hipStream_t, uint16_t*, bool);                       \
   template hipError_t launch_level_gram<T>(int, const T*, const T*, int, int64_t, double*,        \
-                                           hipStream_t);                                          \
+                                           hipStream_t, int, const Strides&);                     \
   template hipError_t launch_gram_multi<T>(int, const GramDesc<T>*, int, int, hipStream_t);        \
   template hipError_t launch_tail_multi<T>(int, const TailDesc<T>*, int, int, hipStream_t);        \
   template hipError_t launch_update_multi<T>(int, bool, bool, const UpdateDesc<T>*, int, int, hipStream_t); \

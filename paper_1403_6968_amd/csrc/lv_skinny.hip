@@ -149,16 +149,29 @@ __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, cons
     __syncthreads();
     if (cr0 + DEPTH * CS < rend) fetch(pre, pv, cr0 + DEPTH * CS);
 
-    // X rows of the chunk
+    // X rows of the chunk, the tile's columns in quarters: (a + b) + (c + d)
     for (int t = wave; t < 2 * NB; t += 4) {
       const int mb = t % 2, nb = t / 2;
       v16f acc;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll 4
-      for (int ks = 0; ks < TCB / 16; ++ks)
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds8(&sS[mb * 32 + l32][ks * 16 + 8 * lh]),
-                                                       lds8(&sUt[nb * 32 + l32][ks * 16 + 8 * lh]), acc, 0, 0, 0);
+      for (int h = 0; h < 2; ++h) {
+        v16f xq[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) xq[q][v] = 0.f;
+#pragma unroll 2
+        for (int ks = 0; ks < TCB / 64; ++ks)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int c = 16 * ((2 * h + q) * (TCB / 64) + ks) + 8 * lh;
+            xq[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds8(&sS[mb * 32 + l32][c]), lds8(&sUt[nb * 32 + l32][c]),
+                                                            xq[q], 0, 0, 0);
+          }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = h == 0 ? xq[0][v] + xq[1][v] : acc[v] + (xq[0][v] + xq[1][v]);
+        asm volatile("" ::: "memory");   // one half's operands at a time
+      }
       const int c = nb * 32 + l32;
       if (c < R) {
 #pragma unroll
@@ -435,6 +448,381 @@ template <int BN>
 __global__ void __launch_bounds__(256, 2) k_skinny_gemm_multi(const SkinnyDesc* __restrict__ ds, int nd) {
   const SkinnyDesc d = load_desc(ds, find_skinny(ds, nd, (int)blockIdx.x));
   skinny_gemm<BN>(d, (int)blockIdx.x - d.block_begin);
+}
+
+// ---------------------------------------------------------------- shared passes
+//
+// A shadowed level of rank R <= kChain16Rank for T successive updates of a
+// batch: X = S U, Y = S^T V from the bfloat16 values of P as the update finds
+// it, then P += U V^T, T times over, at one read and write of P and one write
+// of the shadow: 10 n^2 / T bytes an update, where k_skinny_bf16 and
+// k_level_update read the shadow, read and write P and write the shadow for
+// each, 12 n^2.  The shadow is not read: it is P rounded.
+//
+// Every sum has the order of those two kernels, so the results are the same
+// bit for bit: an X partial is the sum of the chains over the quarters of a
+// tile's columns, (a + b) + (c + d), a Y partial the chain over the slice's
+// interleaved 64-row chunks, both of v_mfma_f32_32x32x16_bf16 (operands
+// exchanged: a lane then holds consecutive factor columns of one row or
+// column); the delta is the fused multiply-add chain over the factor columns
+// from zero (v_mfma_f32_16x16x4f32 adds its four products in index order with
+// one rounding each; ranks 1 and 2 end in zero products) or, at rank 32, the
+// three split products of update_split_body.
+//
+// Work-group: one 256-column tile's slice, 8 waves, one group per compute unit
+// (LDS); a wave keeps the 64 x 32 block of its columns of a chunk in registers
+// over the T updates and passes its rounded values through LDS to the others.
+// All a chunk needs is requested a chunk ahead and V stays in registers: loads
+// return in order, so an operand asked for behind the next chunk's P would
+// arrive behind it (rank 32: 794 us so against 990 us with operands loaded as
+// they are used).  What bounds it: up to rank 8 the traffic, then the steps
+// between barriers (barrier, LDS reads, matrix instructions in sequence: a
+// group's 8 waves are all there are to overlap).
+//
+// n = 16384 (1.07 GB of P, 0.54 GB of shadow; the traffic alone 430 us), passes
+// by themselves, in us: rank 4 four updates 640, rank 8 706, rank 16 952, rank
+// 32 two updates 604; an update alone 520 to 610 for its two passes.  A batch
+// of 8 rank-4 updates, k = 16: 23.5 -> 9.7 ms.
+//
+// Operands are prepared by k_chain_factors: per update Ut and Vt (bfloat16, R
+// rows of n_pad) and the factors of the delta (U then V: floats, max(R, 4) rows
+// of n_pad; at rank 32 the high and the low bfloat16 parts, n_pad rows of 32).
+constexpr int chain_rows(int R) { return R < 4 ? 4 : R; }
+
+template <int R>
+__device__ __forceinline__ void chain_factors_body(const ChainDesc& d, const float* __restrict__ slab, const int side,
+                                                   const int ver, const int tile) {
+  __shared__ float t[64][R + 1];
+  const int tid = threadIdx.x;
+  const float* src = slab + (int64_t)tile * 64 * d.W;
+  for (int e = tid; e < 64 * R; e += 256) t[e / R][e % R] = src[(int64_t)(e / R) * d.W + e % R];
+  __syncthreads();
+  const int64_t n = d.n_pad, r0 = (int64_t)tile * 64;
+  uint16_t* f16 = d.f16 + ((int64_t)ver * 2 + side) * R * n;
+  for (int e = tid; e < 64 * R; e += 256) f16[(int64_t)(e / 64) * n + r0 + e % 64] = bf16_rne(t[e % 64][e / 64]);
+  if constexpr (R < 32) {
+    constexpr int RK = chain_rows(R);
+    float* f = static_cast<float*>(d.f32) + ((int64_t)ver * 2 + side) * RK * n;
+    for (int e = tid; e < 64 * RK; e += 256) f[(int64_t)(e / 64) * n + r0 + e % 64] = e / 64 < R ? t[e % 64][e / 64] : 0.f;
+  } else {
+    uint16_t* h = static_cast<uint16_t*>(d.f32) + ((int64_t)ver * 2 + side) * 2 * R * n;
+    for (int e = tid; e < 64 * R; e += 256) {
+      const float x = t[e / R][e % R];
+      const uint16_t hi = bf16_rne(x);
+      h[r0 * R + e] = hi;
+      h[n * R + r0 * R + e] = bf16_rne(x - __builtin_bit_cast(float, (uint32_t)hi << 16));
+    }
+  }
+}
+
+template <int R>
+__global__ void __launch_bounds__(256) k_chain_factors(const ChainDesc d) {
+  const int ver = blockIdx.y, side = blockIdx.z;
+  chain_factors_body<R>(d, (side ? d.V : d.U) + ver * d.vs.s, side, ver, blockIdx.x);
+}
+
+constexpr int kChainWaves = 8;
+template <int R, int T>
+__global__ void __launch_bounds__(64 * kChainWaves, 2) k_shadow_chain(const ChainDesc d) {
+  constexpr int NT = 64 * kChainWaves;
+  constexpr int RK = chain_rows(R);
+  constexpr int CH = 64;                      // rows per chunk
+  constexpr int CW = TCB / kChainWaves;       // columns per wave
+  static_assert(CW == 32 && T % 2 == 0, "one 32-column block per wave; the shadow buffers alternate over T + 1 writes");
+  // staged rows, padded so that operand reads touch all banks evenly: Ut of
+  // the tile's columns; per update of a chunk U (floats: RK rows of 64; rank
+  // 32: 64 rows of 32 high and of 32 low parts) and Vt (R rows of 64)
+  constexpr int US = TCB + 8;
+  constexpr int FS = R < 32 ? 80 * 2 : 40, VS = CH + 8;            // row strides in 16-bit units
+  constexpr int FROWS = R < 32 ? RK : 2 * CH;
+  constexpr int OPS = FROWS * FS + R * VS;                         // one update's
+  constexpr int FPR = R < 32 ? 16 : 4;                             // 16-byte pieces of a U row
+  constexpr int PIECES = FROWS * FPR + R * 8;                      // and of one update
+  constexpr int NP = (T * PIECES + NT - 1) / NT;
+  __shared__ __align__(16) uint16_t sS[2 * CH * TCB];
+  __shared__ __align__(16) uint16_t sU[T * R * US];
+  __shared__ __align__(16) uint16_t sO[T * OPS];
+  // X: each wave forms 32 rows over a quarter (R <= 16) or, every other update,
+  // over a half of the tile's columns; the parts are added in LDS after the
+  // next barrier
+  constexpr int PARTS = R <= 16 ? 4 : 2, RX = R < 4 ? 4 : R;
+  __shared__ __align__(16) float sX[2 * PARTS * CH * RX];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = wave_id();
+  const int l32 = lane & 31, lh = lane >> 5, l16 = lane & 15, lq = lane >> 4;
+  const int ct = blockIdx.x, rt = blockIdx.y;
+  const int n_pad = d.n_pad;
+  const int64_t n = n_pad, ldp = d.ldp;
+  const int ns = (n_pad + d.tile_rows - 1) / d.tile_rows;
+  const int nchunks = n_pad / CH;
+  const int col0 = ct * TCB, wc = wave * CW;
+  const int cr = l32 < R ? l32 : R - 1;       // operand rows past R feed results that are not kept
+  if (rt >= nchunks) return;                  // (a slice has a chunk: tile_rows >= 64)
+
+  // the wave's 64 x 32 block: 8 groups of four consecutive columns per lane
+  auto grow = [](auto g) { return g / 2 * 16; };   // group's first row and column
+  auto gcol = [](auto g) { return g % 2 * 16; };
+  const int lrow = l16, lcol = wc + 4 * lq;
+  const unsigned poff = (unsigned)(lrow * ldp + lcol) * 4;
+  // The next chunk's operands, and its values where T R <= 32, are requested a
+  // chunk ahead; beyond, the values once the chunk's are stored: the registers
+  // would spill, and a reload waits for every load before it (rank 16, four
+  // updates: 1288 us spilled, 952 us so).
+  constexpr bool AHEAD = T * R <= 32;
+  f32x4 p[8], pn[AHEAD ? 8 : 1];
+  u16x8 on[NP];
+  auto load = [&](const int ch) {
+    const int64_t r0 = (int64_t)ch * CH;
+    static_for<0, NP>([&](auto i) {
+      const int q = tid + NT * i, t = q / PIECES, e = q % PIECES;
+      if (T * PIECES % NT != 0 && q >= T * PIECES) return;
+      const uint16_t* src;
+      if (e >= FROWS * FPR) {
+        const int f = e - FROWS * FPR;
+        src = d.f16 + ((int64_t)(2 * t + 1) * R + f / 8) * n + r0 + f % 8 * 8;
+      } else if (R < 32) {
+        src = reinterpret_cast<const uint16_t*>(static_cast<const float*>(d.f32) + ((int64_t)(2 * t) * RK + e / FPR) * n + r0 + e % FPR * 4);
+      } else {
+        src = static_cast<const uint16_t*>(d.f32) + ((int64_t)(4 * t) + e / (FPR * CH)) * R * n + r0 * R + e % (FPR * CH) * 8;
+      }
+      on[i] = *reinterpret_cast<const u16x8*>(src);
+    });
+  };
+  auto load_p = [&](auto& dst, const int ch) {
+    const float* src = d.P + (int64_t)ch * CH * ldp + col0;
+    static_for<0, 8>([&](auto g) {
+      dst[g] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(at_byte(src + grow(g) * ldp + gcol(g), poff)));
+    });
+  };
+  auto stage = [&](uint16_t* ops) {
+    static_for<0, NP>([&](auto i) {
+      const int q = tid + NT * i, t = q / PIECES, e = q % PIECES;
+      if (T * PIECES % NT != 0 && q >= T * PIECES) return;
+      const int f = e - FROWS * FPR;
+      const int at = f >= 0 ? FROWS * FS + f / 8 * VS + f % 8 * 8 : e / FPR * FS + e % FPR * 8;
+      *reinterpret_cast<u16x8*>(&ops[t * OPS + at]) = on[i];
+    });
+  };
+  // (the permutation repeats every 16 rows and acts on the column's bits, of
+  // which a group's are zero in the lane's)
+  const int pat = lrow * TCB + (((lcol / 8) ^ tr_swizzle(lrow)) * 8 + lcol % 8);
+  auto put = [&](uint16_t* buf) {
+    static_for<0, 8>([&](auto g) {
+      ushort4 h;
+      h.x = bf16_rne(p[g][0]); h.y = bf16_rne(p[g][1]); h.z = bf16_rne(p[g][2]); h.w = bf16_rne(p[g][3]);
+      *reinterpret_cast<ushort4*>(&buf[grow(g) * TCB + (pat ^ gcol(g))]) = h;
+    });
+  };
+  // piece (4 factor columns) j of a row of X parts
+  auto xat = [](const int row, const int j) { return row * RX + (j ^ ((row * RX / 64) & (RX / 4 - 1))) * 4; };
+  auto sum_x = [&](const float* parts, const int t, const int64_t r0) {
+    constexpr int G = RX / 4;
+    if (CH * G < NT && tid >= CH * G) return;
+    const int row = tid / G, j = tid % G;
+    auto part = [&](const int i) { return *reinterpret_cast<const f32x4*>(&parts[i * CH * RX + xat(row, j)]); };
+    f32x4 x = part(0) + part(1);
+    if constexpr (PARTS == 4) x = x + (part(2) + part(3));
+    float* px = d.partX + t * d.vs.x + ((int64_t)ct * n + r0 + row) * R + 4 * j;
+    if constexpr (R < 4) {
+#pragma unroll
+      for (int c = 0; c < R; ++c) px[c] = x[c];
+    } else {
+      *reinterpret_cast<f32x4*>(px) = x;
+    }
+  };
+  load(rt);
+  if constexpr (AHEAD) load_p(pn, rt);
+  else load_p(p, rt);
+
+  for (int q = tid; q < T * R * (TCB / 8); q += NT) {
+    const int row = q / (TCB / 8), g = q % (TCB / 8);
+    *reinterpret_cast<u16x8*>(&sU[row * US + g * 8]) =
+        *reinterpret_cast<const u16x8*>(d.f16 + ((int64_t)(row / R) * 2 * R + row % R) * n + col0 + g * 8);
+  }
+  // V of the wave's columns (rank 32: operand row m is column m with bits 2 and
+  // 3 exchanged, see the update)
+  constexpr int VN = R < 32 ? RK / 4 : 2;
+  float vv[T][2][R < 32 ? VN : 1];
+  bf16x8 vh[T][2], vl[T][2];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    if constexpr (R < 32) {
+      const float* fv = static_cast<const float*>(d.f32) + ((int64_t)(2 * t + 1) * RK + lq) * n + col0 + wc + l16;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int e = 0; e < VN; ++e) vv[t][b][e] = fv[(int64_t)(4 * e) * n + 16 * b];
+    } else {
+      const uint16_t* hv = static_cast<const uint16_t*>(d.f32) + (int64_t)(4 * t + 2) * R * n +
+                           (int64_t)(col0 + wc + (l32 & 19) + (l32 & 4) * 2 + (l32 & 8) / 2) * R + 8 * lh;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        vh[t][k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(hv + 16 * k));
+        vl[t][k] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(hv + n * R + 16 * k));
+      }
+    }
+  }
+
+  v16f yacc[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) yacc[t][v] = 0.f;
+  stage(sO);
+
+  // A shadow buffer and one of X parts are written again two writes on: the
+  // last readers are then past a barrier in between.
+  int sb = 0;
+  for (int ch = rt; ch < nchunks; ch += ns) {
+    const int64_t r0 = (int64_t)ch * CH;
+    if constexpr (AHEAD) static_for<0, 8>([&](auto g) { p[g] = pn[g]; });
+    if (ch + ns < nchunks) {
+      load(ch + ns);
+      if constexpr (AHEAD) load_p(pn, ch + ns);
+    }
+    static_for<0, T>([&](auto t) {
+      asm volatile("" ::: "memory");   // keeps a later update's operands out of the registers
+      uint16_t* buf = sS + sb * (CH * TCB);
+      const uint16_t* ops = sO + t * OPS;
+      put(buf);
+      __syncthreads();
+      sb ^= 1;
+      if constexpr (t > 0) sum_x(sX + ((t - 1) & 1) * PARTS * CH * RX, t - 1, r0);
+
+      if (PARTS == 4 || (wave >> 2) == (t & 1)) {
+        constexpr int KS = 4;                 // steps of a quarter
+        const int part = (wave >> 1) & (PARTS - 1);
+        const int r = (wave & 1) * 32 + l32;
+        const int rat = r * TCB + (lh ^ tr_swizzle(r)) * 8;
+        const uint16_t* u = sU + (t * R + cr) * US + 8 * lh;
+        v16f x[4 / PARTS];
+#pragma unroll
+        for (int i = 0; i < 4 / PARTS; ++i) {
+#pragma unroll
+          for (int v = 0; v < 16; ++v) x[i][v] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < 4 / PARTS; ++i) {
+          if (i > 0) asm volatile("" ::: "memory");
+#pragma unroll
+          for (int k = 0; k < KS; ++k) {
+            const int c = (part * (4 / PARTS) + i) * KS + k;
+            x[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds8(u + 16 * c), lds8(buf + (rat ^ (16 * c))), x[i], 0, 0, 0);
+          }
+        }
+        if constexpr (PARTS == 2)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) x[0][v] += x[1][v];
+        float* px = sX + ((t & 1) * PARTS + part) * CH * RX;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (8 * q + 4 * lh < R)
+            *reinterpret_cast<f32x4*>(&px[xat(r, 2 * q + lh)]) = f32x4{x[0][4 * q], x[0][4 * q + 1], x[0][4 * q + 2], x[0][4 * q + 3]};
+      }
+      asm volatile("" ::: "memory");
+      const uint16_t* ov = ops + FROWS * FS + cr * VS + 8 * lh;
+#pragma unroll
+      for (int ks = 0; ks < CH / 16; ++ks)
+        yacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds8(ov + 16 * ks), tr_operand<TCB>(buf, ks * 16, wc, lane),
+                                                          yacc[t], 0, 0, 0);
+      // P += U V^T
+      if constexpr (R < 32) {
+        const float* ou = reinterpret_cast<const float*>(ops) + lq * (FS / 2) + l16;
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          float uu[VN];
+#pragma unroll
+          for (int e = 0; e < VN; ++e) uu[e] = ou[4 * e * (FS / 2) + 16 * a];
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < VN; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[t][b][e], uu[e], acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) p[2 * a + b][v] += acc[v];
+          }
+        }
+      } else {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const uint16_t* ou = ops + (32 * a + l32) * FS + 8 * lh;
+          v16f acc;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const bf16x8 uh = lds8(ou + 16 * k), ul = lds8(ou + CH * FS + 16 * k);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh[t][k], ul, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vl[t][k], uh, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vh[t][k], uh, acc, 0, 0, 0);
+          }
+          // A quad of columns of a row per lane, 32 rows wide; exchanging lanes
+          // 16-31 (48-63) of one quad with lanes 0-15 (32-47) of the next leaves
+          // the 16-row groups above, whose lanes cover 64 bytes of a row (32
+          // bytes a row: 794 us, see above; 64: 604 us).
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const auto w = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, (float)acc[8 * h + e]),
+                                                              __builtin_bit_cast(unsigned, (float)acc[8 * h + 4 + e]), false,
+                                                              false);
+              p[4 * a + h][e] += __builtin_bit_cast(float, (unsigned)w[0]);
+              p[4 * a + 2 + h][e] += __builtin_bit_cast(float, (unsigned)w[1]);
+            }
+        }
+      }
+    });
+    {
+      float* dst = d.P + r0 * ldp + col0;
+      static_for<0, 8>([&](auto g) {
+        __builtin_nontemporal_store(p[g], reinterpret_cast<f32x4*>(
+            reinterpret_cast<char*>(dst + grow(g) * ldp + gcol(g)) + poff));
+      });
+    }
+    uint16_t* buf = sS + sb * (CH * TCB);
+    put(buf);
+    if constexpr (!AHEAD)
+      if (ch + ns < nchunks) load_p(p, ch + ns);
+    __syncthreads();
+    sb ^= 1;
+    sum_x(sX + ((T - 1) & 1) * PARTS * CH * RX, T - 1, r0);
+    if (ch + ns < nchunks) stage(sO);   // (this chunk's are no longer read)
+    static_for<0, CH * TCB / 8 / NT>([&](auto i) {
+      const int q = tid + NT * i, r = q / (TCB / 8), g = q % (TCB / 8);
+      *reinterpret_cast<u16x8*>(d.S + (r0 + r) * ldp + col0 + g * 8) =
+          *reinterpret_cast<const u16x8*>(&buf[r * TCB + (g ^ tr_swizzle(r)) * 8]);
+    });
+  }
+
+  static_for<0, T>([&](auto t) {
+    float* py = d.partY + t * d.vs.y + ((int64_t)rt * n + col0 + wc + l32) * R;
+    if constexpr (R < 4) {
+      if (lh == 0)
+#pragma unroll
+        for (int c = 0; c < R; ++c) py[c] = yacc[t][c];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (8 * q + 4 * lh < R)
+          *reinterpret_cast<f32x4*>(py + 8 * q + 4 * lh) =
+              f32x4{yacc[t][4 * q], yacc[t][4 * q + 1], yacc[t][4 * q + 2], yacc[t][4 * q + 3]};
+    }
+  });
+}
+
+template <int R>
+hipError_t shadow_chain_r(const ChainDesc& d, int nver, hipStream_t s) {
+  hipLaunchKernelGGL((k_chain_factors<R>), dim3((unsigned)(d.n_pad / 64), (unsigned)nver, 2), dim3(256), 0, s, d);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)(d.n_pad / TCB), (unsigned)((d.n_pad + d.tile_rows - 1) / d.tile_rows));
+  if (nver == 2) hipLaunchKernelGGL((k_shadow_chain<R, 2>), grid, dim3(64 * kChainWaves), 0, s, d);
+  else if (nver == chain16_updates(R)) hipLaunchKernelGGL((k_shadow_chain<R, chain16_updates(R)>), grid, dim3(64 * kChainWaves), 0, s, d);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 // Update fused into the float skinny pass (R = 16 or 32 factor columns, one
@@ -1068,6 +1456,19 @@ hipError_t launch_skinny_wide_multi(int per, const SkinnyDesc* ds, int nd, int b
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_shadow_chain(int R, const ChainDesc& d, int nver, hipStream_t s) {
+  if (d.n_pad % TCB != 0 || d.tile_rows % CRB != 0) return hipErrorInvalidValue;
+  switch (R) {
+    case 1: return shadow_chain_r<1>(d, nver, s);
+    case 2: return shadow_chain_r<2>(d, nver, s);
+    case 4: return shadow_chain_r<4>(d, nver, s);
+    case 8: return shadow_chain_r<8>(d, nver, s);
+    case 16: return shadow_chain_r<16>(d, nver, s);
+    case 32: return shadow_chain_r<32>(d, nver, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_skinny_f32(int R, const float* P, int64_t ldp, int64_t n_pad, int tile_rows,

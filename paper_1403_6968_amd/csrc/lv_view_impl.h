@@ -348,7 +348,7 @@ struct lv_view {
   // updates of padded rank r_pad (at most the view's) that a chunk of a
   // batch takes: two chunks must fit the slots
   int chunk(int r_pad) const {
-    int c = shadowed() ? 1 : lv::chain_updates(r_pad);   // no shared pass with shadows
+    int c = shadowed() ? lv::kChain16Updates : lv::chain_updates(r_pad);
     while (c > 1 && L.pipe_slots < 2 * c) c /= 2;
     return c;
   }
@@ -400,6 +400,35 @@ struct lv_view {
     const int cols = first ? R : R / 2, cu = R - cols, cv = L.W - R;
     // (a float slab of n_pad x W values fills whole 256-byte units: V's follows U's directly)
     return {slabU<float>(slot) + cu, Ut16(slot) + (int64_t)cu * L.n_pad, L.W, (int)L.n_pad, cols, cv - cu, 0};
+  }
+  // Shared passes of a batch over shadowed levels (rank up to kChain16Rank):
+  // the operand forms and partials of kChain16Updates updates of each such
+  // level, behind the factors above in the same scratch (or nothing, where they
+  // do not fit: those levels then take one update per pass).
+  struct ChainArea { char* at = nullptr; lv::Strides vs; char *f16, *f32, *px, *py, *pg; };
+  ChainArea chain16(int r_pad, int j) const {
+    ChainArea a;
+    const int R = r_pad << j;
+    if (!shadowed() || j >= L.m || R > lv::kChain16Rank) return a;
+    const int64_t n = L.n_pad;
+    const size_t all = L.scratch[1] - L.scratch[0] + (size_t)n * n * sizeof(double), T = lv::kChain16Updates;
+    size_t off = (r_pad << (L.m - 1)) >= lv::kWide16Rank ? (size_t)L.pipe_slots * 4 * L.W * n : 0;
+    char* b = base + L.scratch[0];
+    auto take = [&](size_t bytes) { char* q = b + off; off = lv::align_up(off + bytes); return q; };
+    for (int i = 0; i < L.m && (r_pad << i) <= lv::kChain16Rank; ++i) {
+      const int Q = r_pad << i;
+      const int64_t ns = nrt(i, Q);
+      ChainArea c;
+      c.vs = {(int64_t)(L.slot_stride / L.elem), L.nct * n * Q, ns * n * Q, (int64_t)lv::gram_tiles(n) * Q * Q};
+      c.f16 = take(T * lv::chain_f16_bytes(n, Q));
+      c.f32 = take(T * lv::chain_f32_bytes(n, Q));
+      c.px = take(T * c.vs.x * sizeof(float));
+      c.py = take(T * c.vs.y * sizeof(float));
+      c.pg = take(T * c.vs.g * sizeof(double));
+      if (i == j) a = c;
+    }
+    if (off <= all) a.at = b;
+    return a;
   }
   double* scratch(int i) const { return reinterpret_cast<double*>(base + L.scratch[i]); }
   double* zpad() const { return reinterpret_cast<double*>(base + L.probe); }
