@@ -201,9 +201,11 @@ inline bool sums_fused(int R, int elem) { return R <= kMaxFusedRank && !skinny_o
 // n_pad = 8192 (128 work-groups at 4096, 4 at 512).  The default, kTileRows,
 // therefore stands for 512 rows or as many as give kFillBlocks work-groups
 // (one per compute unit), whichever is less, but not below 8 R rows, so that
-// a slice's Y partial stays under 1/16 of the bytes it streams, nor below
-// `unit` rows: a block of kFusedRowBlock rows for each of the four waves, or a
-// 64-row chunk of the matrix-core passes (`cores`).  A single FP64 update at
+// a slice's Y partial stays under 1/16 of the bytes it streams (matrix-core
+// passes, `cores`, take 32 columns at a time: not below 256 rows; FP32 rank 64
+// at n = 4096, 128 work-groups of 512 rows: 57 us a pass, 256 of 256: 36 us), nor
+// below `unit` rows: a block of kFusedRowBlock rows for each of the four waves,
+// or a 64-row chunk of the matrix-core passes.  A single FP64 update at
 // n = 256: 102 us at 512 rows, 46 us so; the read-only float pass at n = 4096
 // 38 us and 22 us.  Other heights are taken as they are: rounds over many
 // views fill the device anyway and lose by finer slices (32 views of 512 to
@@ -214,16 +216,19 @@ constexpr int kTileRows = 512;      // default rows per tile of a level pass
 // and more bytes of factors per row, whose long row blocks leave one wave per
 // SIMD waiting: OLS row change n = 4096 63 -> 60 us, IncrLin n = 5000 1.63 -> 1.56
 // ms, FP64 rank-3 batch n = 3001 1.90 -> 1.81 ms; the other updating passes
-// lose by it (FP32 update n = 4194 217 -> 228 us).
+// lose by it (FP32 update n = 4194 217 -> 228 us).  Matrix-core passes run two
+// work-groups per compute unit, so they take at most that many (n = 7168, rank
+// 32 from the shadow: 532 of them 40 us, 448 32 us).
 constexpr int kFillBlocks = 256;
 inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, int tile_rows, bool reads = false) {
   if (tile_rows != kTileRows) return tile_rows;
   const int unit = cores ? 64 : 4 * kFusedRowBlock;
   const int64_t nct = n_pad / tile_cols_bytes(elem);
   const int64_t fill = reads || R * elem >= 128 ? 2 * kFillBlocks : kFillBlocks;
-  const int64_t ns = (fill + nct - 1) / nct;
+  const int64_t ns = cores ? (fill > nct ? fill / nct : 1) : (fill + nct - 1) / nct;
   int64_t rows = round_up((n_pad + ns - 1) / ns, unit);
-  if (rows < 8 * R) rows = round_up(8 * R, unit);
+  const int least = cores && 8 * R > 256 ? 256 : 8 * R;
+  if (rows < least) rows = round_up(least, unit);
   return rows < tile_rows ? (int)rows : tile_rows;
 }
 inline int slice_count(int64_t n_pad, int elem, int R, bool cores, int tile_rows, bool reads = false) {

@@ -750,11 +750,11 @@ __device__ __forceinline__ void update_split_body(float* __restrict__ P, const i
   const int l32 = lane & 31, lh = lane >> 5;
   const int row0 = rt * TT, col0 = ct * TT;
 
-  // The old values: requested before the products (their loads overlap the
-  // products); from R = 128 after them, so that the products run without
-  // the 64 registers they occupy (two waves per SIMD instead of one then
-  // hide the latency; see update_min_waves)
-  constexpr bool LATE_P = R >= 128 && !CHAIN;
+  // The old values: requested after the products, which then run without the
+  // 64 registers they occupy, so that two waves per SIMD hide the latency
+  // (requested before: one wave per SIMD; n = 7168, R = 64 124 -> 82 us, R = 32
+  // 92 -> 84 us).  Runs of updates hold them throughout.
+  constexpr bool LATE_P = !CHAIN;
   float p[2][2][16];
   auto load_p = [&]() {
 #pragma unroll
@@ -884,21 +884,20 @@ __device__ __forceinline__ void update_any(const UpdateDesc<T>& d, const int ct,
     update_body<T, R, SH>(d.P, d.ldp, d.n_pad, d.tile_rows, d.Uj, d.Vj, d.W, d.S, ct, rt);
 }
 
-// Float matrix-core ranks: at least two waves per SIMD (the 128 x 128
-// tile's old values stay in registers while its delta is formed).  The
-// split-bfloat16 products from R = 128 too, where the old values are loaded
-// after the products; below, their unrolled chunks fit without a bound.
-template <typename T, int R, bool SPLIT> constexpr int update_min_waves() {
-  return sizeof(T) == 4 && R >= kMfmaUpdateRank && (!SPLIT || R >= 128) ? 2 : 1;
+// Float matrix-core ranks: at least two waves per SIMD (the 128 x 128 tile's
+// old values stay in registers while its delta is formed, or, in the split
+// products, follow it).
+template <typename T, int R> constexpr int update_min_waves() {
+  return sizeof(T) == 4 && R >= kMfmaUpdateRank ? 2 : 1;
 }
 
 template <typename T, int R, bool SH, bool SPLIT>
-__global__ void __launch_bounds__(256, (update_min_waves<T, R, SPLIT>())) k_level_update(const UpdateDesc<T> d) {
+__global__ void __launch_bounds__(256, (update_min_waves<T, R>())) k_level_update(const UpdateDesc<T> d) {
   update_any<T, R, SH, SPLIT>(d, blockIdx.x, blockIdx.y);
 }
 
 template <typename T, int R, bool SH, bool SPLIT>
-__global__ void __launch_bounds__(256, (update_min_waves<T, R, SPLIT>()))
+__global__ void __launch_bounds__(256, (update_min_waves<T, R>()))
 k_level_update_multi(const UpdateDesc<T>* __restrict__ ds, int nd) {
   const int v = find_desc(ds, nd, (int)blockIdx.x);
   const UpdateDesc<T> d = load_desc(ds, v);

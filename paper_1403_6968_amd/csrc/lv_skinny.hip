@@ -62,18 +62,43 @@ __device__ __forceinline__ float fac_or_zero(const float* __restrict__ row, cons
   return c < R ? v : 0.f;
 }
 
+// Piece (16 bytes) g of a staged shadow row r sits at g ^ tr_swizzle(r): 4
+// pieces further per row, one per group of 4 rows.
+__device__ __forceinline__ int tr_swizzle(const int r) { return 4 * (r & 3) | ((r >> 2) & 3); }
+
+// B operand (32x32x16) of rows r0 .. r0 + 15 and columns c0 .. c0 + 31 of a
+// staged block with rows of LD values: lanes 16 g .. 16 g + 15 take rows 8 (g /
+// 2) .. + 7 of columns 16 (g % 2) .. + 15; lane i of a group addresses row i /
+// 4, columns 4 (i % 4) .. + 3 of each 4-row half.
+template <int LD> __device__ __forceinline__ bf16x8 tr_operand(uint16_t* s, const int r0, const int c0, const int lane) {
+  typedef short v4s __attribute__((ext_vector_type(4)));
+  typedef short v8s __attribute__((ext_vector_type(8)));
+  const int li = lane & 15;
+  const int c = c0 + (lane >> 4 & 1) * 16 + li % 4 * 4;
+  v4s h[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int r = r0 + 8 * (lane >> 5) + 4 * e + li / 4;
+    uint16_t* at = s + r * LD + ((c / 8) ^ tr_swizzle(r)) * 8 + c % 8;
+    h[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)at);
+  }
+  return __builtin_bit_cast(bf16x8, (v8s)__builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // Tile: about tile_rows x 256 columns of S (the slices of a column tile
 // interleave by 64-row chunks), walked in chunks through LDS; the next
 // chunk or two of S and of V_j are held in registers while the current one
 // is used.
 // Factor columns are padded with zeros to 32 NB.
-//   X: per chunk, the 2 NB (row half, factor block) 32 x 32 outputs are
-//      shared round-robin by the 4 waves, K = the tile's 256 columns; one
-//      partial per (row, column tile).
+//   X: per chunk, wave w forms rows [32 (w % 2), + 32) of the half w / 2 of the
+//      tile's columns as two chains, one per quarter; the halves are added a
+//      chunk later, (a + b) + (c + d): one partial per (row, column tile).
 //   Y: wave w keeps the accumulators of tile columns [64 w, 64 w + 64) for
 //      every factor block over all chunks of the tile (K = rows); one
 //      partial per (column, row tile).
-// The B operand of Y needs 8 consecutive rows of one column: 8 LDS reads.
+// The B operand of Y needs 8 consecutive rows of one column: transposed reads.
+// n = 7168, R = 32 (103 MB of shadow): 39 us with eight 2-byte reads per Y
+// operand and X on two waves, 32 us so.
 template <int NB>
 __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, const int64_t ldp, const int n_pad,
                                             const int tile_rows, const float* __restrict__ Uj,
@@ -81,9 +106,10 @@ __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, cons
                                             float* __restrict__ partX, float* __restrict__ partY, const int pR,
                                             const int ct, const int rt) {
   constexpr int RP = 32 * NB;
-  __shared__ __align__(16) uint16_t sS[CRB][TCB + SPAD];
+  __shared__ __align__(16) uint16_t sS[CRB * TCB];
   __shared__ __align__(16) uint16_t sUt[RP][TCB + SPAD];
   __shared__ __align__(16) uint16_t sVt[RP][CRB + SPAD];
+  __shared__ __align__(16) float sX[2][NB][CRB * 32];   // halves of X
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -96,6 +122,7 @@ __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, cons
   const int row0 = rt * CRB;
   const int rend = n_pad;
   const int l32 = lane % 32, lh = lane / 32;
+  const int mb = wave & 1, half = wave >> 1;   // X: 32 rows of a chunk, half of the columns
   // chunk staging: thread -> rows tid / 32 + 8 i, 16-byte column group tid % 32
   const int srow = tid / 32, sgrp = tid % 32;
 
@@ -137,24 +164,48 @@ __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, cons
 #pragma unroll
       for (int v = 0; v < 16; ++v) yacc[a][b][v] = 0.f;
 
-  auto chunk = [&](u16x8 (&pre)[CRB / 8], float (&pv)[VPT], const int cr0) {
-    __syncthreads();   // the previous chunk is no longer read
+  // piece (4 factor columns) j of a row of the halves
+  auto xat = [](const int row, const int j) { return row * 32 + (j ^ ((row >> 1) & 7)) * 4; };
+  // X rows of the chunk at r0: both halves
+  auto store_x = [&](const int r0) {
 #pragma unroll
-    for (int i = 0; i < CRB / 8; ++i) *reinterpret_cast<u16x8*>(&sS[srow + 8 * i][sgrp * 8]) = pre[i];
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int row = (tid + 256 * i) / 8, j = tid % 8, c = nb * 32 + 4 * j;
+        if (c >= R) continue;
+        const f32x4 x = *reinterpret_cast<const f32x4*>(&sX[0][nb][xat(row, j)]) +
+                        *reinterpret_cast<const f32x4*>(&sX[1][nb][xat(row, j)]);
+        float* px = partX + ((int64_t)ct * n_pad + r0 + row) * pR + c;
+        if (c + 4 <= R) *reinterpret_cast<f32x4*>(px) = x;
+        else
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (c + e < R) px[e] = x[e];
+      }
+  };
+
+  auto chunk = [&](u16x8 (&pre)[CRB / 8], float (&pv)[VPT], const int cr0) {
+    __syncthreads();   // the previous chunk is no longer read, its halves of X are there
+#pragma unroll
+    for (int i = 0; i < CRB / 8; ++i) {
+      const int r = srow + 8 * i;
+      *reinterpret_cast<u16x8*>(&sS[r * TCB + (sgrp ^ tr_swizzle(r)) * 8]) = pre[i];
+    }
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
       const int idx = tid + 256 * i;
       sVt[idx % RP][idx / RP] = bf16_rne(idx % RP < R ? pv[i] : 0.f);
     }
+    if (cr0 != row0) store_x(cr0 - CS);
     __syncthreads();
     if (cr0 + DEPTH * CS < rend) fetch(pre, pv, cr0 + DEPTH * CS);
 
-    // X rows of the chunk, the tile's columns in quarters: (a + b) + (c + d)
-    for (int t = wave; t < 2 * NB; t += 4) {
-      const int mb = t % 2, nb = t / 2;
-      v16f acc;
+    {
+      const int r = mb * 32 + l32;
+      const int rat = r * TCB + (lh ^ tr_swizzle(r)) * 8;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int nb = 0; nb < NB; ++nb) {
         v16f xq[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q)
@@ -164,20 +215,16 @@ __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, cons
         for (int ks = 0; ks < TCB / 64; ++ks)
 #pragma unroll
           for (int q = 0; q < 2; ++q) {
-            const int c = 16 * ((2 * h + q) * (TCB / 64) + ks) + 8 * lh;
-            xq[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds8(&sS[mb * 32 + l32][c]), lds8(&sUt[nb * 32 + l32][c]),
+            const int c = 16 * ((2 * half + q) * (TCB / 64) + ks);
+            xq[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds8(&sUt[nb * 32 + l32][c + 8 * lh]), lds8(sS + (rat ^ c)),
                                                             xq[q], 0, 0, 0);
           }
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = h == 0 ? xq[0][v] + xq[1][v] : acc[v] + (xq[0][v] + xq[1][v]);
-        asm volatile("" ::: "memory");   // one half's operands at a time
-      }
-      const int c = nb * 32 + l32;
-      if (c < R) {
+        for (int q = 0; q < 4; ++q) {
+          f32x4 x;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int rr = mb * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
-          partX[((int64_t)ct * n_pad + cr0 + rr) * pR + c] = acc[v];
+          for (int e = 0; e < 4; ++e) x[e] = xq[0][4 * q + e] + xq[1][4 * q + e];
+          *reinterpret_cast<f32x4*>(&sX[half][nb][xat(r, 2 * q + lh)]) = x;
         }
       }
     }
@@ -187,11 +234,7 @@ __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, cons
     for (int ks = 0; ks < CRB / 16; ++ks) {
 #pragma unroll
       for (int cbi = 0; cbi < 2; ++cbi) {
-        const int colc = (2 * wave + cbi) * 32 + l32;
-        u16x8 bv;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) bv[e] = sS[ks * 16 + 8 * lh + e][colc];
-        const bf16x8 b = __builtin_bit_cast(bf16x8, bv);
+        const bf16x8 b = tr_operand<TCB>(sS, ks * 16, (2 * wave + cbi) * 32, lane);
 #pragma unroll
         for (int nbr = 0; nbr < NB; ++nbr)
           yacc[nbr][cbi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds8(&sVt[nbr * 32 + l32][ks * 16 + 8 * lh]), b,
@@ -200,24 +243,41 @@ __device__ __forceinline__ void skinny_body(const uint16_t* __restrict__ S, cons
     }
   };
 
+  int last = row0;
   if constexpr (DEPTH == 2) {
     for (int cr0 = row0; cr0 < rend; cr0 += 2 * CS) {
       chunk(preA, pvA, cr0);
-      if (cr0 + CS < rend) chunk(preB, pvB, cr0 + CS);
+      last = cr0;
+      if (cr0 + CS < rend) {
+        chunk(preB, pvB, cr0 + CS);
+        last = cr0 + CS;
+      }
     }
   } else {
-    for (int cr0 = row0; cr0 < rend; cr0 += CS) chunk(preA, pvA, cr0);
+    for (int cr0 = row0; cr0 < rend; cr0 += CS) {
+      chunk(preA, pvA, cr0);
+      last = cr0;
+    }
   }
+  __syncthreads();
+  store_x(last);
 
 #pragma unroll
   for (int nbr = 0; nbr < NB; ++nbr)
 #pragma unroll
     for (int cbi = 0; cbi < 2; ++cbi) {
-      const int col = col0 + (2 * wave + cbi) * 32 + l32;
+      // values 4 q .. 4 q + 3 of a lane are four consecutive factor columns
+      float* py = partY + ((int64_t)rt * n_pad + col0 + (2 * wave + cbi) * 32 + l32) * pR + nbr * 32 + 4 * lh;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int c = nbr * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
-        if (c < R) partY[((int64_t)rt * n_pad + col) * pR + c] = yacc[nbr][cbi][v];
+      for (int q = 0; q < 4; ++q) {
+        const int c = nbr * 32 + 4 * lh + 8 * q;
+        if (c + 4 <= R)
+          *reinterpret_cast<f32x4*>(py + 8 * q) = f32x4{yacc[nbr][cbi][4 * q], yacc[nbr][cbi][4 * q + 1],
+                                                        yacc[nbr][cbi][4 * q + 2], yacc[nbr][cbi][4 * q + 3]};
+        else
+#pragma unroll
+          for (int e = 0; e < 3; ++e)
+            if (c + e < R) py[8 * q + e] = yacc[nbr][cbi][4 * q + e];
       }
     }
 }
@@ -289,29 +349,6 @@ __global__ void __launch_bounds__(256) k_fac16(const Fac16Desc d) { fac16_body(d
 __global__ void __launch_bounds__(256) k_fac16_multi(const Fac16Desc* __restrict__ ds, int nd) {
   const Fac16Desc d = load_desc(ds, find_desc(ds, nd, (int)blockIdx.x));
   fac16_body(d, (int)blockIdx.x - d.block_begin);
-}
-
-// Piece (16 bytes) g of a staged shadow row r sits at g ^ tr_swizzle(r): 4
-// pieces further per row, one per group of 4 rows.
-__device__ __forceinline__ int tr_swizzle(const int r) { return 4 * (r & 3) | ((r >> 2) & 3); }
-
-// B operand (32x32x16) of rows r0 .. r0 + 15 and columns c0 .. c0 + 31 of a
-// staged block with rows of LD values: lanes 16 g .. 16 g + 15 take rows 8 (g /
-// 2) .. + 7 of columns 16 (g % 2) .. + 15; lane i of a group addresses row i /
-// 4, columns 4 (i % 4) .. + 3 of each 4-row half.
-template <int LD> __device__ __forceinline__ bf16x8 tr_operand(uint16_t* s, const int r0, const int c0, const int lane) {
-  typedef short v4s __attribute__((ext_vector_type(4)));
-  typedef short v8s __attribute__((ext_vector_type(8)));
-  const int li = lane & 15;
-  const int c = c0 + (lane >> 4 & 1) * 16 + li % 4 * 4;
-  v4s h[2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    const int r = r0 + 8 * (lane >> 5) + 4 * e + li / 4;
-    uint16_t* at = s + r * LD + ((c / 8) ^ tr_swizzle(r)) * 8 + c % 8;
-    h[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)at);
-  }
-  return __builtin_bit_cast(bf16x8, (v8s)__builtin_shufflevector(h[0], h[1], 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // X = S U and Y = S^T V as two products of their own in one launch, the
