@@ -236,22 +236,28 @@ inline int slice_count(int64_t n_pad, int elem, int R, bool cores, int tile_rows
   return (int)((n_pad + rows - 1) / rows);
 }
 
-// Work-groups of a tail launch / Gram pairs per work-group for rank R.
-// Level ranks from which the tail works on column slices of min(R, 32)
-// columns, one column per lane and kTailRowsPerThread rows per thread.
+// The tail at this level rank: one column per lane and kTailRowsPerThread rows
+// per thread.
 constexpr int kSlicedTailRank = 16;
 constexpr int kTailRowsPerThread = 4;
-inline int tail_slice_cols(int R) { return R < 32 ? R : 32; }
-inline int tail_block_rows(int R) { return 256 / tail_slice_cols(R) * kTailRowsPerThread; }
+inline int tail_block_rows(int R) { return 256 / R * kTailRowsPerThread; }
 // Lanes per output entry of the tail below kSlicedTailRank.
 constexpr int kTailLanes = 8;
+// Ranks whose Gram and tail run on the double matrix cores, the 16-column
+// blocks that a wave of the tail takes (enough waves for the device at the low
+// ranks), the pairs per side of a Gram work-group, and the rows of its tile.
+constexpr int kMfmaGramRank = 32;
+inline __host__ __device__ constexpr int tail_wave_blocks(int R) { return R < 64 ? 1 : R < 256 ? 2 : 4; }
+inline __host__ __device__ constexpr int gram_block(int R) { return R < 64 ? 32 : 64; }
+inline int gram_rows(int R) { return R <= 64 ? kGramRows : R; }
+inline int gram_count(int64_t n_pad, int R) { return (int)((n_pad + gram_rows(R) - 1) / gram_rows(R)); }
 inline int tail_blocks(int64_t n_pad, int R) {
-  return R >= kSlicedTailRank ? (int)(n_pad / tail_block_rows(R)) * (R / tail_slice_cols(R))
+  if (R >= kMfmaGramRank) return (int)(n_pad / 64) * (R / (16 * tail_wave_blocks(R)));
+  return R >= kSlicedTailRank ? (int)(n_pad / tail_block_rows(R))
                               : (int)((n_pad * R * kTailLanes + 255) / 256);
 }
-inline int gram_pairs_per_block(int R) {
-  const int ppt = (R * R + 255) / 256 < 16 ? (R * R + 255) / 256 : 16;
-  return 256 * ppt;
+inline int gram_chunks(int R) {   // work-groups per row tile
+  return R >= kMfmaGramRank ? (R / gram_block(R)) * (R / gram_block(R)) : 1;
 }
 
 // ---- launchers (stream-ordered; return the launch status) ----
@@ -308,7 +314,7 @@ template <typename T>
 hipError_t launch_level_update_chain(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU, const T* slabV, int W,
                                      int nver, int64_t sstride, hipStream_t s, bool split = false);
 
-// Gram V_j^T U_j in double: gram_tiles(n_pad) partials of kGramRows rows,
+// Gram V_j^T U_j in double: gram_count(n_pad, R) partials of gram_rows(R) rows,
 // then their sum in fixed order into partG[0 .. R*R).
 template <typename T>
 hipError_t launch_level_gram(int R, const T* slabU, const T* slabV, int W, int64_t n_pad, double* partG,

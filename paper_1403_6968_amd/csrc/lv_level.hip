@@ -23,29 +23,22 @@
 namespace lv {
 namespace {
 
-// ---------------------------------------------------------------- Gram (ranks > 16)
+// ---------------------------------------------------------------- stand-alone Gram
 // Partial V_j^T U_j over one row tile (double accumulation, rows in index
-// order): factor rows are staged in LDS 16 at a time; block (rt, pc) covers
-// pairs [pc * 256 * PPT, (pc + 1) * 256 * PPT) of the R x R result and thread
-// t owns the pairs base + t, base + t + 256, ...
-template <typename T, int R>
-constexpr int gram_ppt() { return (R * R + 255) / 256 < 16 ? (R * R + 255) / 256 : 16; }
-
+// order), ranks up to 16: factor rows are staged in LDS 16 at a time, a thread
+// owns one pair.
 template <typename T, int R>
 __device__ __forceinline__ void gram_body(const T* __restrict__ Uj, const T* __restrict__ Vj, const int W,
                                           const int n_pad, const int tile_rows, double* __restrict__ partG,
-                                          const int rt, const int pc) {
+                                          const int rt) {
   constexpr int RS = 16;
-  constexpr int PPT = gram_ppt<T, R>();
-  const int pbase = pc * 256 * PPT;
+  static_assert(R * R <= 256, "a pair per thread");
   __shared__ T su[RS][R];
   __shared__ T sv[RS][R];
   const int tid = threadIdx.x;
   const int row0 = rt * tile_rows;
   const int nrows = min(tile_rows, n_pad - row0);
-  double g[PPT];
-#pragma unroll
-  for (int e = 0; e < PPT; ++e) g[e] = 0.0;
+  double g = 0.0;
   for (int i0 = row0; i0 < row0 + nrows; i0 += RS) {
     __syncthreads();
     batched_stage<(RS * R + 255) / 256, 256, T>(
@@ -55,27 +48,87 @@ __device__ __forceinline__ void gram_body(const T* __restrict__ Uj, const T* __r
         tid, RS * R, [&](int idx) { return Vj[(int64_t)(i0 + idx / R) * W + idx % R]; },
         [&](int idx, T v) { sv[idx / R][idx % R] = v; });
     __syncthreads();
+    if (tid < R * R) {
 #pragma unroll
-    for (int e = 0; e < PPT; ++e) {
-      const int pair = pbase + tid + 256 * e;
-      if (pair < R * R) {
-        const int a = pair / R, b = pair % R;
-#pragma unroll
-        for (int rr = 0; rr < RS; ++rr) g[e] = fma((double)sv[rr][a], (double)su[rr][b], g[e]);
-      }
+      for (int rr = 0; rr < RS; ++rr) g = fma((double)sv[rr][tid / R], (double)su[rr][tid % R], g);
     }
   }
+  if (tid < R * R) partG[(int64_t)rt * R * R + tid] = g;
+}
+
+// From rank 32 on the double matrix cores (v_mfma_f64_16x16x4f64, whose four
+// products are added in index order with one rounding each: a partial is the
+// chain over its rows in order).  Work-group: one row tile by GT x GT pairs, 4
+// waves in 2 x 2; a step of four rows is one value of V and of U per lane and
+// block (64-byte segments).  What bounds it: the matrix cores from rank 128,
+// below the launch; the row tiles grow with the rank so that the partials, R^2
+// doubles each, stay behind (rank 256, n = 7168: 59 MB of them in 64-row tiles).
+// n = 7168, rows staged in LDS and vector multiply-adds -> this: rank 64 27 -> 5
+// us, 128 28 -> 9, 256 86 -> 22 (and the sum of the partials 10 -> 5).
+// 16x16x4 layouts: A: lane l holds A[l % 16][l / 16]; B: B[l / 16][l % 16]; C:
+// element v of lane l is C[4 v + l / 16][l % 16].
+typedef double v4d __attribute__((ext_vector_type(4)));
+template <typename T, int R>
+__device__ __forceinline__ void gram_mfma_body(const T* __restrict__ Uj, const T* __restrict__ Vj, const int W,
+                                               const int n_pad, const int tile_rows, double* __restrict__ partG,
+                                               const int rt, const int pc) {
+  constexpr int GT = gram_block(R), NB = GT / 32, NC = R / GT;
+  const int lane = threadIdx.x & 63;
+  const int wave = wave_id();
+  const int l16 = lane & 15, lq = lane >> 4;
+  const int row0 = rt * tile_rows;
+  const int nrows = min(tile_rows, n_pad - row0);
+  const int a0 = pc / NC * GT + (wave >> 1) * (GT / 2), b0 = pc % NC * GT + (wave & 1) * (GT / 2);
+  const T* v = Vj + (int64_t)(row0 + lq) * W + a0 + l16;
+  const T* u = Uj + (int64_t)(row0 + lq) * W + b0 + l16;
+  v4d g[NB][NB];
 #pragma unroll
-  for (int e = 0; e < PPT; ++e) {
-    const int pair = pbase + tid + 256 * e;
-    if (pair < R * R) partG[(int64_t)rt * R * R + pair] = g[e];
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[a][b][e] = 0.0;
+  // 32 rows at a time (tiles are multiples of 64): their loads are in flight
+  // together
+  constexpr int KS = sizeof(T) == 4 ? 8 : 4;
+  for (int r = 0; r < nrows; r += 4 * KS, v += (int64_t)(4 * KS) * W, u += (int64_t)(4 * KS) * W) {
+    T va[KS][NB], ub[KS][NB];
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int a = 0; a < NB; ++a) {
+        va[k][a] = v[(int64_t)(4 * k) * W + 16 * a];
+        ub[k][a] = u[(int64_t)(4 * k) * W + 16 * a];
+      }
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int a = 0; a < NB; ++a)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          g[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)va[k][a], (double)ub[k][b], g[a][b], 0, 0, 0);
   }
+  double* out = partG + (int64_t)rt * R * R + (int64_t)(a0 + lq) * R + b0 + l16;
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[(int64_t)(16 * a + 4 * e) * R + 16 * b] = g[a][b][e];
+}
+
+template <typename T, int R>
+__device__ __forceinline__ void gram_any(const T* __restrict__ Uj, const T* __restrict__ Vj, const int W,
+                                         const int n_pad, const int tile_rows, double* __restrict__ partG, const int rt,
+                                         const int pc) {
+  if constexpr (R >= kMfmaGramRank) gram_mfma_body<T, R>(Uj, Vj, W, n_pad, tile_rows, partG, rt, pc);
+  else gram_body<T, R>(Uj, Vj, W, n_pad, tile_rows, partG, rt);
 }
 
 template <typename T, int R>
 __global__ void __launch_bounds__(256) k_gram(const GramDesc<T> d, const int64_t sstride, const int64_t gstride) {
   const int64_t v = blockIdx.z;
-  gram_body<T, R>(d.Uj + v * sstride, d.Vj + v * sstride, d.W, d.n_pad, d.tile_rows, d.partG + v * gstride, blockIdx.x,
+  gram_any<T, R>(d.Uj + v * sstride, d.Vj + v * sstride, d.W, d.n_pad, d.tile_rows, d.partG + v * gstride, blockIdx.x,
                   blockIdx.y);
 }
 
@@ -84,7 +137,7 @@ __global__ void __launch_bounds__(256) k_gram_multi(const GramDesc<T>* __restric
   const int v = find_desc(ds, nd, (int)blockIdx.x);
   const GramDesc<T> d = load_desc(ds, v);
   const int local = (int)blockIdx.x - d.block_begin;
-  gram_body<T, R>(d.Uj, d.Vj, d.W, d.n_pad, d.tile_rows, d.partG, local % d.nrt, local / d.nrt);
+  gram_any<T, R>(d.Uj, d.Vj, d.W, d.n_pad, d.tile_rows, d.partG, local % d.nrt, local / d.nrt);
 }
 
 // G[idx] = sum over t < ng of G[t * count + idx], in index order, into the
@@ -193,44 +246,92 @@ __device__ __forceinline__ void tail_body(const T* __restrict__ partX, const T* 
       Unew[i * W + c] = (T)(x + ug);
       Vnew[i * W + c] = (T)y;
     }
+  } else if constexpr (R >= kMfmaGramRank) {
+    // Wave: 16 rows by 16 CB columns, U_j G on the double matrix cores (a chain
+    // over d in order from zero, as the vector form; layouts at
+    // gram_mfma_body), G the summed Gram, straight from the cache; then each
+    // lane adds the partials of its 4 CB entries in order (64-byte segments).
+    // What bounds it: the partials, and G's reads at rank 256.  n = 7168, G in
+    // LDS and vector multiply-adds -> this: rank 64 14 -> 8 us, 128 32 -> 18, 256
+    // 154 -> 43; rank 32 (28 and 16 partials) 17 us both ways.
+    constexpr int CB = tail_wave_blocks(R), NC = R / (16 * CB);
+    const int lane = tid & 63;
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int w = blk * 4 + wave_id();
+    const int64_t r0 = (int64_t)(w / NC) * 16;
+    const int c0 = w % NC * 16 * CB;
+    v4d ug[CB];
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ug[b][e] = 0.0;
+    const T* u = Ucur + (r0 + l16) * W + lq;
+    const double* g = partG + (int64_t)lq * R + c0 + l16;
+    constexpr int KS = CB > 2 ? 4 : 8;
+    for (int d = 0; d < R; d += 4 * KS, u += 4 * KS, g += (int64_t)(4 * KS) * R) {
+      T ua[KS];
+      double gb[KS][CB];
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        ua[k] = u[4 * k];
+#pragma unroll
+        for (int b = 0; b < CB; ++b) gb[k][b] = g[(int64_t)(4 * k) * R + 16 * b];
+      }
+#pragma unroll
+      for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+          ug[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ua[k], gb[k][b], ug[b], 0, 0, 0);
+    }
+    const int64_t at = (r0 + lq) * R + c0 + l16;   // entry (row r0 + lq + 4 e, column c0 + l16 + 16 b)
+    auto sums = [&](const T* __restrict__ part, const int count, double (&x)[CB][4]) {
+#pragma unroll
+      for (int b = 0; b < CB; ++b)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[b][e] = 0.0;
+#pragma unroll 2
+      for (int t = 0; t < count; ++t) {
+        T v[CB][4];
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[b][e] = part[(int64_t)t * strideX + at + (int64_t)(4 * e) * R + 16 * b];
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[b][e] += (double)v[b][e];
+      }
+    };
+    double x[CB][4];
+    sums(partX, nct, x);
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        Unew[(r0 + lq + 4 * e) * W + c0 + l16 + 16 * b] = (T)(x[b][e] + ug[b][e]);
+    sums(partY, nrt, x);
+#pragma unroll
+    for (int b = 0; b < CB; ++b)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) Vnew[(r0 + lq + 4 * e) * W + c0 + l16 + 16 * b] = (T)x[b][e];
   } else {
-    // Column slice cs of CW columns: lane column cl = tid % CW, row lane
-    // rl = tid / CW; the thread takes rows rl + TPR q (q < Q) of the
-    // block's RPB rows, so a wave reads whole 128-byte row segments of
-    // every partial and carries Q independent sums.  Each entry sums its
+    // Lane column c = tid % R, row lane rl = tid / R; the thread takes rows rl +
+    // TPR q (q < Q) of the block's RPB rows, so a wave carries Q independent
+    // sums of whole row segments of every partial.  Each entry sums its
     // partials t = 0, 1, ... and its terms d = 0, 1, ... of U_j G in index
     // order.
-    constexpr int CW = R < 32 ? R : 32;
-    constexpr int NS = R / CW;
-    constexpr int TPR = 256 / CW;
+    constexpr int TPR = 256 / R;
     constexpr int Q = kTailRowsPerThread;
     constexpr int RPB = TPR * Q;
-    __shared__ double G[R][CW];
-    const int rb = blk / NS, cs = blk % NS;
-    const int cl = tid % CW, rl = tid / CW;
-    const int c = cs * CW + cl;
+    static_assert(R * R == 256, "an entry of G per thread");
+    __shared__ double G[R][R];
+    const int rb = blk;
+    const int c = tid % R, rl = tid / R;
     {
-      // the G slice: each entry sums its ng partials in order; the loads of
-      // all of a thread's entries for one partial are issued together
-      constexpr int GE = (R * CW + 255) / 256;
-      double g[GE];
-#pragma unroll
-      for (int e = 0; e < GE; ++e) g[e] = 0.0;
-      for (int t = 0; t < ng; ++t) {
-        double v[GE];
-#pragma unroll
-        for (int e = 0; e < GE; ++e) {
-          const int idx = tid + 256 * e;
-          v[e] = idx < R * CW ? partG[(int64_t)t * R * R + (idx / CW) * R + cs * CW + idx % CW] : 0.0;
-        }
-#pragma unroll
-        for (int e = 0; e < GE; ++e) g[e] += v[e];
-      }
-#pragma unroll
-      for (int e = 0; e < GE; ++e) {
-        const int idx = tid + 256 * e;
-        if (idx < R * CW) G[idx / CW][idx % CW] = g[e];
-      }
+      double g = 0.0;
+#pragma unroll 8
+      for (int t = 0; t < ng; ++t) g += partG[(int64_t)t * R * R + tid];
+      G[rl][c] = g;
     }
     __syncthreads();
     int64_t idx[Q];
@@ -262,7 +363,7 @@ __device__ __forceinline__ void tail_body(const T* __restrict__ partX, const T* 
       const int64_t i = (int64_t)rb * RPB + rl + TPR * q;
       double ug = 0.0;
 #pragma unroll 8
-      for (int d = 0; d < R; ++d) ug = fma((double)Ucur[i * W + d], G[d][cl], ug);
+      for (int d = 0; d < R; ++d) ug = fma((double)Ucur[i * W + d], G[d][c], ug);
       Unew[i * W + c] = (T)(x[q] + ug);
       Vnew[i * W + c] = (T)y[q];
     }
@@ -625,7 +726,6 @@ __device__ __forceinline__ void update_mfma_body(float* __restrict__ P, const in
 // 16x16x4 layouts: A: lane l holds A[l % 16][l / 16]; B: B[l / 16][l % 16];
 // C: element v of lane l is C[4 v + l / 16][l % 16].
 constexpr int kF64UpdateRows = 64, kF64UpdateCols = 64;
-typedef double v4d __attribute__((ext_vector_type(4)));
 template <int R>
 __device__ __forceinline__ void update_f64_body(double* __restrict__ P, const int64_t ldp,
                                                 const double* __restrict__ Uj, const double* __restrict__ Vj,
@@ -990,14 +1090,13 @@ hipError_t update_chain_r(const UpdateDesc<T>& d, int nver, int64_t sstride, hip
   return hipErrorInvalidValue;
 }
 
-// Stand-alone Gram: gram_tiles(n_pad) partials, then their sum into the first.
+// Stand-alone Gram: gram_count(n_pad, R) partials, then their sum into the first.
 template <typename T, int R>
 hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG, hipStream_t s, int nver = 1,
                   int64_t sstride = 0, int64_t gstride = 0) {
-  const int ng = gram_tiles(n_pad);
-  const GramDesc<T> g{Uj, Vj, W, (int)n_pad, kGramRows, partG, ng, 0};
-  const dim3 ggrid((unsigned)ng, (unsigned)((R * R + gram_pairs_per_block(R) - 1) / gram_pairs_per_block(R)),
-                   (unsigned)nver);
+  const int ng = gram_count(n_pad, R);
+  const GramDesc<T> g{Uj, Vj, W, (int)n_pad, gram_rows(R), partG, ng, 0};
+  const dim3 ggrid((unsigned)ng, (unsigned)gram_chunks(R), (unsigned)nver);
   hipLaunchKernelGGL((k_gram<T, R>), ggrid, dim3(256), 0, s, g, sstride, gstride);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

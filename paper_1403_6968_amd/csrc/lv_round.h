@@ -175,8 +175,8 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
                                                           Vj + c0, L.W, per, v->partX<T>(j) + c0,
                                                           v->partY<T>(j) + c0, R, L.nct, 0});
           }
-          gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, kGramRows, v->partG(j), gram_tiles(L.n_pad), 0});
-          gsum.push_back({v->partG(j), gram_tiles(L.n_pad), R * R, 0});
+          gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), v->partG(j), gram_count(L.n_pad, R), 0});
+          gsum.push_back({v->partG(j), gram_count(L.n_pad, R), R * R, 0});
           if (v->shadowed() || !skinny_fuses_update(R))
             (v->shadowed() ? updsh : upd)[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W,
                                                         upd_nct, 0, v->shadowed() ? v->shadow(j) : nullptr});
@@ -193,8 +193,8 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
         for (int c0 = 0; c0 < R; c0 += kMaxFusedRank)
           chunks.push_back({v->P<T>(j), L.ldp, (int)L.n_pad, trows, sU + c0, Vj + c0, L.W,
                             v->partX<T>(j) + c0, v->partY<T>(j) + c0, nullptr, R, L.nct, 0});
-        gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, kGramRows, v->partG(j), gram_tiles(L.n_pad), 0});
-        gsum.push_back({v->partG(j), gram_tiles(L.n_pad), R * R, 0});
+        gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), v->partG(j), gram_count(L.n_pad, R), 0});
+        gsum.push_back({v->partG(j), gram_count(L.n_pad, R), R * R, 0});
         upd[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W, upd_nct, 0});
       }
       tail[R].push_back({v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, nrt, (int)L.n_pad, sU, sV, L.W, 0,
@@ -208,7 +208,7 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
     for (auto& kv : skinny32) pl.add(kSkinnyF32, kv.first, kv.second, &skinny_blocks);
     for (auto& kv : gram) {
       const int R = kv.first;
-      const int chunks_per_tile = (R * R + gram_pairs_per_block(R) - 1) / gram_pairs_per_block(R);
+      const int chunks_per_tile = gram_chunks(R);
       pl.add(kGram, R, kv.second, [chunks_per_tile](const GramDesc<T>& d) { return d.nrt * chunks_per_tile; });
     }
     pl.add(kGramSum, 0, gsum, [](const GramSumDesc& d) { return (d.count + 255) / 256; });

@@ -71,3 +71,32 @@ def test_batches_and_rounds_equal_single_updates(n, k, r_max, r):
     group.close()
     for v in (one, batch, rounds):
         v.close()
+
+
+@pytest.mark.parametrize("mode,n,k,r", [
+    ("fp64", 100, 4, 32), ("fp64", 130, 4, 64), ("fp64", 700, 8, 32), ("fp64", 385, 2, 128), ("fp32", 257, 4, 32),
+    ("fp32", 300, 8, 33), ("fp32", 1100, 4, 128)])
+def test_integer_powers_exact_without_shadows(mode, n, k, r):
+    """Gram and tail of ranks 32 to 256 on the double matrix cores: whole
+    numbers stay whole (orders of one and of several row tiles, the last one
+    cut short)."""
+    torch = need_gpu()
+    from paper_1403_6968_amd import linview as lv
+    td = torch.float64 if mode == "fp64" else torch.float32
+    g = synth.rng(12, 0, n, r)
+    A = np.zeros((n, n))
+    A[np.arange(n), g.permutation(n)] = 1.0
+    view = lv.View(dev(A, td), k, r_max=r, mode=lv.LV_FP64 if mode == "fp64" else lv.LV_FP32)
+    P = O.reeval(A, k)
+    for _ in range(2):
+        U = (g.random((n, r)) < 1.5 / n).astype(np.float64)
+        V = (g.random((n, r)) < 1.5 / n).astype(np.float64)
+        dU, dV = O.incr_factors(P, U, V)
+        P = O.incr_update(P, U, V)
+        assert max(np.abs(x).max() for x in [*dU.values(), *dV.values(), *P.values()]) < 2 ** 24
+        view.update(dev(U, td), dev(V, td))
+        got = read_all(view)
+        for i in P:
+            np.testing.assert_array_equal(got[i], P[i], err_msg=f"P_{i}")
+    note(f"exact: {mode} n={n} k={k} r={r}")
+    view.close()
