@@ -205,7 +205,10 @@ inline bool sums_fused(int R, int elem) { return R <= kMaxFusedRank && !skinny_o
 // passes, `cores`, take 32 columns at a time: not below 256 rows; FP32 rank 64
 // at n = 4096, 128 work-groups of 512 rows: 57 us a pass, 256 of 256: 36 us), nor
 // below `unit` rows: a block of kFusedRowBlock rows for each of the four waves,
-// or a 64-row chunk of the matrix-core passes.  A single FP64 update at
+// or a 64-row chunk of the matrix-core passes.  Where 8 R rows leave a vector
+// pass fewer than kFillBlocks work-groups, latency and not the partials bounds
+// it: down to 2 R rows (FP64 rank-4 update, k = 16: n = 256 174 -> 118 us, 1024
+// 173 -> 133 us, 1536 213 -> 194 us; rank 1, n = 512 66 -> 61 us).  A single FP64 update at
 // n = 256: 102 us at 512 rows, 46 us so; the read-only float pass at n = 4096
 // 38 us and 22 us.  Other heights are taken as they are: rounds over many
 // views fill the device anyway and lose by finer slices (32 views of 512 to
@@ -227,7 +230,8 @@ inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, int tile_rows,
   const int64_t fill = reads || R * elem >= 128 ? 2 * kFillBlocks : kFillBlocks;
   const int64_t ns = cores ? (fill > nct ? fill / nct : 1) : (fill + nct - 1) / nct;
   int64_t rows = round_up((n_pad + ns - 1) / ns, unit);
-  const int least = cores && 8 * R > 256 ? 256 : 8 * R;
+  int least = cores && 8 * R > 256 ? 256 : 8 * R;
+  if (!cores && R <= kMaxFusedRank && nct * (n_pad / least) < kFillBlocks) least = 2 * R;
   if (rows < least) rows = round_up(least, unit);
   return rows < tile_rows ? (int)rows : tile_rows;
 }
