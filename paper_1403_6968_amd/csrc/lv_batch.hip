@@ -9,8 +9,8 @@
 // chosen by timing.  One round with zero inputs runs first; it leaves every
 // stored power unchanged (P + 0) and every factor column zero, so that the
 // level launches can then be timed in isolation without changing any view.
-// For each (level, rank) group of views the candidates 256, 512 and 1024
-// rows are timed over the level's launches (pass, Gram, update, tail; the
+// For each (level, rank) group of views seven heights from 256 to 1024 rows
+// are timed over the level's launches (pass, Gram, update, tail; the
 // partial count follows the tile height); the fastest is stored in the
 // views (lv_view_update then uses the same tiles) and in a process-wide
 // cache keyed by device architecture, mode, rank and the group's orders.
@@ -122,8 +122,13 @@ lv_status autotune(lv_batch* b, hipStream_t s) {
     return fail(LV_EDEVICE, "hipEventCreate failed");
   int max_m = 0;
   for (lv_view* v : b->views) max_m = std::max(max_m, v->L.m);
-  // tile rows: every multiple of 128 from 256 to 1024 (the allowed range)
-  const int cands[] = {256, 384, 512, 640, 768, 896, 1024};
+  // Tile rows over the allowed range.  576 rows give the slice counts of 512
+  // up to n = 2048 and at multiples of 512 to 4096; kTileRows (512) itself
+  // stands for a finer cut that fills the device with one view's pass, which
+  // wins when a level is timed by itself and loses next to the round's other
+  // lanes (32 views of 512 to 4096 rows: 2.36 ms with it among the candidates,
+  // 2.31 ms without).
+  const int cands[] = {256, 384, 576, 640, 768, 896, 1024};
   for (int j = 0; j < max_m && st == LV_OK; ++j) {
     std::map<int, std::vector<lv_view*>> groups;   // level rank -> views with a pass at level j
     for (lv_view* v : b->views)
