@@ -2,7 +2,8 @@
 // re-evaluation baseline (double or float): C = A * B, n_pad x n_pad,
 // row-major, n_pad a multiple of 256 (the repeated squarings of Table 1's
 // exponential model, P_i = P_{i/2} P_{i/2}); launch_gemm_rect runs the same
-// kernel on an M x K by K x N product (M, N multiples of 128, K of 16).
+// kernel on an M x K by K x N product (M, N multiples of 128, K of 16), if
+// asked with the summation range split over several work-groups per tile.
 //
 // Block tile 128 x 128 x 16, 256 threads as a 2 x 2 grid of waves, each wave
 // owning a 64 x 64 sub-tile of C built from MFMA blocks:
@@ -50,7 +51,7 @@ constexpr int BM = 128, BN = 128, BK = 16;
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_gemm(const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ldb,
-       T* __restrict__ C, int64_t ldc, int n_pad, const int* __restrict__ gate) {
+       T* __restrict__ C, int64_t ldc, int n_pad, const int* __restrict__ gate, int64_t cstride) {
   if (gate != nullptr && *gate == 0) return;
   using F = Mfma<T>;
   constexpr int M = F::M;
@@ -91,11 +92,14 @@ k_gemm(const T* __restrict__ A, int64_t lda, const T* __restrict__ B, int64_t ld
 #pragma unroll
       for (int v = 0; v < F::NACC; ++v) acc[i][j][v] = T(0);
 
-  const int nk = n_pad / BK;
-  fetch(0);
-  stash(0);
+  // blockIdx.z: this launch's share of the summation range
+  const int steps = n_pad / BK;
+  const int k0 = (int)((int64_t)steps * blockIdx.z / gridDim.z), nk = (int)((int64_t)steps * (blockIdx.z + 1) / gridDim.z);
+  C += blockIdx.z * cstride;
+  fetch(k0 * BK);
+  stash(k0 & 1);
   __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
+  for (int kt = k0; kt < nk; ++kt) {
     const int cur = kt & 1;
     if (kt + 1 < nk) fetch((kt + 1) * BK);
 #pragma unroll
@@ -133,23 +137,23 @@ hipError_t launch_gemm(const T* A, int64_t lda, const T* B, int64_t ldb, T* C, i
                        int64_t n_pad, hipStream_t s, const int* gate) {
   if (n_pad % BM != 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(n_pad / BN), (unsigned)(n_pad / BM));
-  hipLaunchKernelGGL((k_gemm<T>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, (int)n_pad, gate);
+  hipLaunchKernelGGL((k_gemm<T>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, (int)n_pad, gate, (int64_t)0);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_gemm_rect(const T* A, int64_t lda, const T* B, int64_t ldb, T* C, int64_t ldc, int64_t M,
-                            int64_t N, int64_t K, hipStream_t s, const int* gate) {
-  if (M % BM != 0 || N % BN != 0 || K % BK != 0) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(N / BN), (unsigned)(M / BM));
-  hipLaunchKernelGGL((k_gemm<T>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, (int)K, gate);
+                            int64_t N, int64_t K, hipStream_t s, const int* gate, int splits) {
+  if (M % BM != 0 || N % BN != 0 || K % BK != 0 || splits < 1 || splits > K / BK) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(N / BN), (unsigned)(M / BM), (unsigned)splits);
+  hipLaunchKernelGGL((k_gemm<T>), grid, dim3(256), 0, s, A, lda, B, ldb, C, ldc, (int)K, gate, M * ldc);
   return hipGetLastError();
 }
 
 template hipError_t launch_gemm_rect<double>(const double*, int64_t, const double*, int64_t, double*, int64_t,
-                                             int64_t, int64_t, int64_t, hipStream_t, const int*);
+                                             int64_t, int64_t, int64_t, hipStream_t, const int*, int);
 template hipError_t launch_gemm_rect<float>(const float*, int64_t, const float*, int64_t, float*, int64_t,
-                                            int64_t, int64_t, int64_t, hipStream_t, const int*);
+                                            int64_t, int64_t, int64_t, hipStream_t, const int*, int);
 template hipError_t launch_gemm<double>(const double*, int64_t, const double*, int64_t, double*,
                                         int64_t, int64_t, hipStream_t, const int*);
 template hipError_t launch_gemm<float>(const float*, int64_t, const float*, int64_t, float*,

@@ -31,12 +31,21 @@ constexpr int kGlinNarrow = 64;      // p up to this: read-only passes (p padded
 constexpr int kGlinMaxCols = 4096;   // wider p: padded to a multiple of 128, products on the MFMA GEMM
 constexpr int kGlinMaxWidth = 128;   // k * r_pad for incremental evaluation
 
+// Shares of the summation range of a wide product: its 128 x 128 tiles leave
+// most of the device idle at ordinary p (12 at n = 1296, p = 79: 121 us a product
+// unsplit, 18 us in 12 shares; n = 4000, p = 200: 321 and 76 us), so as many as give two work-groups per compute
+// unit, of 128 terms or more.
+inline int64_t glin_splits(int64_t n_pad, int64_t pp) {
+  const int64_t want = 2 * kFillBlocks / ((n_pad / 128) * (pp / 128)), most = n_pad / 128;
+  return want < 1 ? 1 : want < most ? want : most;
+}
+
 // One thread per (row, column) of an n_pad x pp result:
-//   d = sum_t partX[t] + full + sum_c U[row][c] a[c][col]   (double)
+//   d = sum_t partX[t] + sum_c U[row][c] a[c][col]   (double)
 // assign: Tio = d + B (re-evaluation); else Dout = d, Tio += d (hybrid).
 template <typename T>
 __global__ void __launch_bounds__(256)
-k_glin_tail(const T* __restrict__ partX, int nct, const T* __restrict__ full, const T* __restrict__ U, int R,
+k_glin_tail(const T* __restrict__ partX, int nct, const T* __restrict__ U, int R,
             const double* __restrict__ a, const T* __restrict__ B, T* __restrict__ Dout, T* __restrict__ Tio,
             int64_t n_pad, int pp, int assign) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -46,7 +55,6 @@ k_glin_tail(const T* __restrict__ partX, int nct, const T* __restrict__ full, co
   const int64_t stride = n_pad * pp;
   double d = 0.0;
   for (int t = 0; t < nct; ++t) d += (double)partX[t * stride + idx];
-  if (full != nullptr) d += (double)full[idx];
   for (int c = 0; c < R; ++c) d = fma((double)U[row * R + c], a[c * pp + col], d);
   if (assign) {
     Tio[idx] = (T)(d + (double)B[idx]);
@@ -112,7 +120,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
                 sizeof(double));
   g.D[0] = g.D[1] = g.full = g.atbG = g.Y = g.Z = 0;
   if (strategy == LV_GLIN_HYBRID) { g.D[0] = take(np * pp * e); g.D[1] = take(np * pp * e); }
-  if (strategy != LV_GLIN_INCR && g.pp > kGlinNarrow) g.full = take(np * pp * e);
+  if (strategy != LV_GLIN_INCR && g.pp > kGlinNarrow) g.full = take(glin_splits(np, pp) * np * pp * e);
   if (strategy == LV_GLIN_INCR) {
     // Gram partials of a step: one per 64 rows, or per slice of the pass
     const size_t ng = np / kAtbRows * g.r_pad * g.r_pad, nk = gram_partials(g.n_pad, g.elem, kMaxKrylovCols, false, true);
@@ -156,15 +164,16 @@ lv_status glin_build(lv_glin* g, hipStream_t s) {
 }
 
 // out = A M (M n_pad x w, row stride sm) with the OLD A: partials of a
-// read-only pass (w <= 128) or, for wide M (w > 64, a multiple of 128), the
-// full product on the MFMA GEMM.  Returns the partial count (0 for the full
-// product, which goes to `full`).
+// read-only pass (to partX) or, for wide M (w > 64, a multiple of 128), of the
+// MFMA GEMM (to `full`).  Returns the partial count.
 template <typename T>
 lv_status glin_amul(lv_glin* g, const T* M, int w, int sm, hipStream_t s, int* nct_out) {
   const int64_t np = g->n_pad;
   if (w > kGlinNarrow && g->full != 0) {
-    *nct_out = 0;
-    return hip_check(launch_gemm_rect<T>(g->at<T>(g->A), np, M, sm, g->at<T>(g->full), g->pp, np, w, np, s), "A M");
+    *nct_out = (int)glin_splits(np, w);
+    return hip_check(launch_gemm_rect<T>(g->at<T>(g->A), np, M, sm, g->at<T>(g->full), g->pp, np, w, np, s, nullptr,
+                                         *nct_out),
+                     "A M");
   }
   *nct_out = g->nct;
   const int rows = slice_rows(np, g->elem, w, skinny_on_mfma(w, g->elem), kTileRows, true);
@@ -178,16 +187,14 @@ lv_status glin_amul(lv_glin* g, const T* M, int w, int sm, hipStream_t s, int* n
                    "A M");
 }
 
-// The product of glin_amul enters as `nct` partials, or as the full
-// product when with_product is set and nct is 0; with_product = false: no
+// The product of glin_amul enters as `nct` partials; with_product = false: no
 // product term at all (the first hybrid step).
 template <typename T>
 lv_status glin_tail(lv_glin* g, bool with_product, int nct, int R, const double* a, bool assign, T* Dout, T* Tio,
                     hipStream_t s) {
   const int64_t np = g->n_pad;
-  const T* full = with_product && nct == 0 ? g->at<T>(g->full) : nullptr;
   hipLaunchKernelGGL((k_glin_tail<T>), dim3((unsigned)((np * g->pp + 255) / 256)), dim3(256), 0, s,
-                     g->at<T>(g->partX), with_product ? nct : 0, full, g->at<T>(g->sU), R, a, g->at<T>(g->Bb), Dout,
+                     g->at<T>(g->full != 0 ? g->full : g->partX), with_product ? nct : 0, g->at<T>(g->sU), R, a, g->at<T>(g->Bb), Dout,
                      Tio, np, g->pp, assign ? 1 : 0);
   return hip_check(hipGetLastError(), "tail");
 }

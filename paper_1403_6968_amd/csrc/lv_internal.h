@@ -560,10 +560,11 @@ hipError_t launch_prep_multi(const PrepDesc<T>* ds, int nd, int blocks, hipStrea
 template <typename T>
 hipError_t launch_gemm(const T* A, int64_t lda, const T* B, int64_t ldb, T* C, int64_t ldc,
                        int64_t n_pad, hipStream_t s, const int* gate = nullptr);
-// C = A * B for A M x K, B K x N (M, N multiples of 128, K of 16), same kernel.
+// C = A * B for A M x K, B K x N (M, N multiples of 128, K of 16), same kernel;
+// splits > 1: that many partial products, M ldc values apart.
 template <typename T>
 hipError_t launch_gemm_rect(const T* A, int64_t lda, const T* B, int64_t ldb, T* C, int64_t ldc, int64_t M,
-                            int64_t N, int64_t K, hipStream_t s, const int* gate = nullptr);
+                            int64_t N, int64_t K, hipStream_t s, const int* gate = nullptr, int splits = 1);
 
 // ---- drift check (FP64 test of the stored chain P_{j+1} = P_j P_j)
 
