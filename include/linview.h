@@ -162,9 +162,9 @@ lv_status lv_view_update(lv_view* v, const void* U, const void* V, int64_t r,
  * as up to four stages on streams of their own (stage 0 on `stream`; the
  * others are created on the first such call, on the current device) and
  * several updates are in flight, each with a factor-slab pair of the
- * workspace.  In the modes without shadows a level below rank 16 takes up to
- * 16 / rank of them (at most 8) at one read and write of its power, and the
- * top power the whole group.  Every sum and rounding is that of the
+ * workspace.  A level below rank 16 takes up to 16 / rank of them (at most 8; with
+ * shadows 4, at rank 32 2, where the squaring scratch holds their operands)
+ * at one read and write of its power, and the top power the whole group.  Every sum and rounding is that of the
  * sequential order; the call returns with all stages joined into `stream`,
  * so stream order is as for one call of lv_view_update per update.  Not
  * used while kernel timing is on; a periodic drift check falling inside

@@ -104,7 +104,10 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.nct = (int)(g.n_pad / tile_cols_bytes(g.elem));
   g.maxw = strategy == LV_GLIN_INCR ? (int)next_pow2((int64_t)k * g.r_pad) : 1;
   const size_t e = g.elem, np = g.n_pad, pp = g.pp;
-  const int xw = strategy == LV_GLIN_INCR ? g.r_pad : (g.pp <= kGlinNarrow ? g.pp : 1);   // read-only pass width
+  // read-only pass width (incremental evaluation needs r_pad columns only, and
+  // keeps the region no smaller than the other strategies')
+  const int narrow = g.pp <= kGlinNarrow ? g.pp : 1;
+  const int xw = strategy == LV_GLIN_INCR && g.r_pad > narrow ? g.r_pad : narrow;
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
   g.A = take(np * np * e);
