@@ -978,8 +978,10 @@ def main():
                               "frac": achieved / HBM_PEAK_GBPS, "traffic": counter_traffic(n, k, r),
                               "kernel": "k_level_fused (levels 0..m-1)",
                               "avg_launch_ms": fused_ms, "bytes_per_launch": bytes_launch,
-                              # every pass of the timed (pipelined) region: the algorithmic bytes of
-                              # all m + 1 stored powers per update over the region's event time
+                              # the timed (pipelined) region: one read and write of all m + 1 stored
+                              # powers per update over the region's event time.  Several updates of a
+                              # batch share each read and write, so this is the rate that updates one
+                              # by one would need, above what the memory delivers
                               "timed_region_all_passes": {
                                   "GBps": result["hbm_GBps_algorithmic"],
                                   "frac": result["hbm_GBps_algorithmic"] / HBM_PEAK_GBPS}}
