@@ -340,13 +340,17 @@ inline int skinny_blocks_for(int R) { return R <= 32 ? 1 : 2; }   // R <= 64 per
 // factor columns per launch.  The summation ranges are split wide_splits()
 // ways, about two work-groups per compute unit in all and at least 512 rows or
 // columns each, with one partial of X and one of Y per split (n_pad / 512 at
-// most, fewer than the passes over 2-D tiles leave).
+// most, fewer than the passes over 2-D tiles leave).  A split has at most
+// kWideTerms terms whatever the order: its sum is a float chain (see
+// skinny_gemm_body for the bound), while the partials are added in double.
 constexpr int kWide16Rank = 64;
+constexpr int kWideTerms = 2048;
 inline __host__ __device__ int wide_splits(int64_t n_pad) {
   const int64_t tiles = n_pad / 128 * 2;   // X and Y products of a launch
   const int64_t want = (512 + tiles - 1) / tiles, most = n_pad / 512;
+  const int64_t least = (n_pad + kWideTerms - 1) / kWideTerms;
   const int64_t s = want < most ? want : most;
-  return s < 1 ? 1 : (int)s;
+  return (int)(s < least ? least : s);
 }
 inline int wide_cols(int R) { return R < 128 ? R : 128; }
 inline int wide_blocks(int64_t n_pad) { return (int)(2 * (n_pad / 128)) * wide_splits(n_pad); }

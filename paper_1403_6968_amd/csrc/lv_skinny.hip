@@ -367,7 +367,15 @@ __global__ void __launch_bounds__(256) k_fac16_multi(const Fac16Desc* __restrict
 // 59 us, R = 256 226 -> 118 us, and the tail that adds the partials 51 -> 32 us
 // and 228 -> 153 us at R = 128 and 256.  At R = 32 the 2-D pass stays (39 us;
 // from bfloat16 factors 46 us).
-constexpr int kGemmTile = 128, kGemmStep = 64;
+// A split's sum is kept in two stages, so that a longer range costs no
+// accuracy: chains of kGemmRun steps (192 terms, 12 matrix instructions), added
+// up in float (at most 11 of them, kWideTerms terms).  The variance of a
+// chain's rounding error grows with its length: in units of one instruction's,
+// half the 12 instructions plus half the 11 additions, 11.5 for X and for Y,
+// where one float chain per 256 columns (X) and per 512 rows (Y), the partials
+// of a pass over 2-D tiles, has 8 and 16.  A rank-32 update at n = 7157, k = 16
+// (three such levels): 982 us with one chain per split, 1004 us so.
+constexpr int kGemmTile = 128, kGemmStep = 64, kGemmRun = 3;
 template <int BN, bool YP>
 __device__ __forceinline__ void skinny_gemm_body(const SkinnyDesc& d, uint16_t* sS, uint16_t* sF, const int tile,
                                                  const int split, const int splits) {
@@ -402,48 +410,64 @@ __device__ __forceinline__ void skinny_gemm_body(const SkinnyDesc& d, uint16_t* 
   // rows of 8 pieces (128 bytes): two rows apart by one piece
   auto piece = [](const int r, const int g) { return r * KS + (g ^ ((r >> 1) & 7)) * 8; };
   fetch(s0);
-  v16f acc[2][WB];
+  v16f sum[2][WB];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < WB; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+      for (int v = 0; v < 16; ++v) sum[a][b][v] = 0.f;
 
-  for (int st = s0; st < s1; ++st) {
-    __syncthreads();
-    static_for<0, SP>([&](auto i) {
-      const int q = tid + 256 * i;
-      if constexpr (YP) {
-        const int r = q / (TM / 8);
-        *reinterpret_cast<u16x8*>(&sS[r * TM + ((q % (TM / 8)) ^ tr_swizzle(r)) * 8]) = ps[i];
-      } else {
-        *reinterpret_cast<u16x8*>(&sS[piece(q / 8, q % 8)]) = ps[i];
+  for (int st = s0; st < s1;) {
+    const int run = min(st + kGemmRun, s1);
+    v16f acc[2][WB];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < WB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    for (; st < run; ++st) {
+      __syncthreads();
+      static_for<0, SP>([&](auto i) {
+        const int q = tid + 256 * i;
+        if constexpr (YP) {
+          const int r = q / (TM / 8);
+          *reinterpret_cast<u16x8*>(&sS[r * TM + ((q % (TM / 8)) ^ tr_swizzle(r)) * 8]) = ps[i];
+        } else {
+          *reinterpret_cast<u16x8*>(&sS[piece(q / 8, q % 8)]) = ps[i];
+        }
+      });
+      static_for<0, FP>([&](auto i) {
+        const int q = tid + 256 * i;
+        *reinterpret_cast<u16x8*>(&sF[piece(q / 8, q % 8)]) = pf[i];
+      });
+      __syncthreads();
+      if (st + 1 < s1) fetch(st + 1);
+#pragma unroll
+      for (int ks = 0; ks < KS / 16; ++ks) {
+        bf16x8 so[2], fo[WB];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          if constexpr (YP) so[a] = tr_operand<TM>(sS, ks * 16, wm * 64 + a * 32, lane);
+          else so[a] = lds8(&sS[piece(wm * 64 + a * 32 + l32, 2 * ks + lh)]);
+        }
+#pragma unroll
+        for (int b = 0; b < WB; ++b) fo[b] = lds8(&sF[piece(wn * 32 * WB + b * 32 + l32, 2 * ks + lh)]);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < WB; ++b)
+            acc[a][b] = YP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[b], so[a], acc[a][b], 0, 0, 0)
+                           : __builtin_amdgcn_mfma_f32_32x32x16_bf16(so[a], fo[b], acc[a][b], 0, 0, 0);
       }
-    });
-    static_for<0, FP>([&](auto i) {
-      const int q = tid + 256 * i;
-      *reinterpret_cast<u16x8*>(&sF[piece(q / 8, q % 8)]) = pf[i];
-    });
-    __syncthreads();
-    if (st + 1 < s1) fetch(st + 1);
-#pragma unroll
-    for (int ks = 0; ks < KS / 16; ++ks) {
-      bf16x8 so[2], fo[WB];
-#pragma unroll
-      for (int a = 0; a < 2; ++a) {
-        if constexpr (YP) so[a] = tr_operand<TM>(sS, ks * 16, wm * 64 + a * 32, lane);
-        else so[a] = lds8(&sS[piece(wm * 64 + a * 32 + l32, 2 * ks + lh)]);
-      }
-#pragma unroll
-      for (int b = 0; b < WB; ++b) fo[b] = lds8(&sF[piece(wn * 32 * WB + b * 32 + l32, 2 * ks + lh)]);
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < WB; ++b)
-          acc[a][b] = YP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo[b], so[a], acc[a][b], 0, 0, 0)
-                         : __builtin_amdgcn_mfma_f32_32x32x16_bf16(so[a], fo[b], acc[a][b], 0, 0, 0);
     }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < WB; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sum[a][b][v] += acc[a][b][v];
   }
 #pragma unroll
   for (int a = 0; a < 2; ++a)
@@ -456,11 +480,11 @@ __device__ __forceinline__ void skinny_gemm_body(const SkinnyDesc& d, uint16_t* 
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           *reinterpret_cast<f32x4*>(py + 8 * q) =
-              f32x4{acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
+              f32x4{sum[a][b][4 * q], sum[a][b][4 * q + 1], sum[a][b][4 * q + 2], sum[a][b][4 * q + 3]};
       } else {
         float* px = d.partX + ((int64_t)split * n_pad + m + 4 * lh) * pR + c + l32;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) px[(8 * (v / 4) + v % 4) * pR] = acc[a][b][v];
+        for (int v = 0; v < 16; ++v) px[(8 * (v / 4) + v % 4) * pR] = sum[a][b][v];
       }
     }
 }
