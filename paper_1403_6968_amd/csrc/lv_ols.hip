@@ -423,8 +423,6 @@ void layout_ols(lv_ols& o, int64_t m, int64_t n, int64_t p, lv_mode mode) {
   o.Qk = take(np * 4 * e);
   o.Rs = take(np * 2 * e);
   o.Ss = take(np * 2 * e);
-  o.partX = take((size_t)o.nct * np * 4 * e);
-  o.partY = take((size_t)o.nrt * np * 4 * e);
   o.vec = take(np * 5 * sizeof(double));
   o.pXu = take((mp / kAtbRows) * np * sizeof(double));
   o.pUu = take((mp / kAtbRows) * sizeof(double));
@@ -439,6 +437,10 @@ void layout_ols(lv_ols& o, int64_t m, int64_t n, int64_t p, lv_mode mode) {
   o.C64 = take(np * pp * sizeof(double));
   o.B64 = take(np * pp * sizeof(double));
   o.total = off;
+  // the updates' partials lie where creation inverts X^T X (32 n_pad^2 bytes;
+  // both have n_pad / 16 partials of 4 n_pad values at most)
+  o.partX = o.Z;
+  o.partY = align_up(o.partX + (size_t)o.nct * np * 4 * e);
 }
 
 // Re-evaluation from the stored X and Y: Z = X^T X and C = X^T Y in double,
