@@ -114,15 +114,14 @@ struct lv_chain {
   lv_mode mode;
   std::vector<int> pw;       // stored powers, pw[0] = 1
   std::vector<int> Wd;       // padded slab width of each stored matrix
-  struct Step { int c, a, b; };
-  std::vector<Step> steps;   // products in evaluation order (indices into pw)
+  // products in evaluation order (indices into pw); of a step's passes, the
+  // rows per slice, the slices and the places of the partials
+  struct Step { int c, a, b, rows = 0, nrt = 0; size_t x = 0, xd = 0, y = 0, g = 0; };
+  std::vector<Step> steps;
   std::vector<int> left_last;   // last step that reads a stored matrix as P_a (-1: none)
   std::vector<char> done;       // matrices that an update's steps have updated already
-  // rows per slice of a pass of rank R, and its slices
-  int rows(int R) const { return slice_rows(n_pad, elem, R, skinny_on_mfma(R, elem), kTileRows); }
-  int nrt(int R) const { return (int)((n_pad + rows(R) - 1) / rows(R)); }
   std::vector<size_t> P, sU, sV;
-  size_t partX = 0, partY = 0, partXd = 0, partG = 0, d64[3] = {};
+  size_t d64[3] = {};
   size_t total = 0;
   char* base = nullptr;
   int64_t updates = 0;
@@ -130,10 +129,10 @@ struct lv_chain {
   template <typename T> T* Pm(int i) const { return reinterpret_cast<T*>(base + P[i]); }
   template <typename T> T* U(int i) const { return reinterpret_cast<T*>(base + sU[i]); }
   template <typename T> T* V(int i) const { return reinterpret_cast<T*>(base + sV[i]); }
-  template <typename T> T* pX() const { return reinterpret_cast<T*>(base + partX); }
-  template <typename T> T* pY() const { return reinterpret_cast<T*>(base + partY); }
-  template <typename T> T* pXd() const { return reinterpret_cast<T*>(base + partXd); }
-  double* pG() const { return reinterpret_cast<double*>(base + partG); }
+  template <typename T> T* pX(const Step& q) const { return reinterpret_cast<T*>(base + q.x); }
+  template <typename T> T* pXd(const Step& q) const { return reinterpret_cast<T*>(base + q.xd); }   // not wanted
+  template <typename T> T* pY(const Step& q) const { return reinterpret_cast<T*>(base + q.y); }
+  double* pG(const Step& q) const { return reinterpret_cast<double*>(base + q.g); }
   double* d(int i) const { return reinterpret_cast<double*>(base + d64[i]); }
 };
 
@@ -209,13 +208,32 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
     c.sU[i] = off; off = align_up(off + slab);
     c.sV[i] = off; off = align_up(off + slab);
   }
-  c.partX = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
-  c.partXd = off; off = align_up(off + (size_t)c.nct * c.n_pad * maxW * c.elem);
-  c.partY = off; off = align_up(off + (size_t)c.n_pad * slice_cols(c.n_pad, c.elem, maxW) * c.elem);
-  const size_t ng = (size_t)(c.n_pad / kAtbRows) * maxG, nk = gram_partials(c.n_pad, c.elem, kMaxKrylovCols);
-  c.partG = off; off = align_up(off + (ng > nk ? ng : nk) * sizeof(double));
-  if (mode == LV_FP32 && ns > 1)
-    for (int i = 0; i < 3; ++i) { c.d64[i] = off; off = align_up(off + (size_t)c.n_pad * c.n_pad * sizeof(double)); }
+  // Last the region that an update's partials and creation's double matrices
+  // share, sized for both and for whole-width passes over kTileRows rows.
+  const size_t work = off, np = c.n_pad, e = c.elem;
+  for (size_t cols : {(size_t)c.nct * maxW, (size_t)c.nct * maxW, (np + kTileRows - 1) / kTileRows * maxW})
+    off = align_up(off + np * cols * e);
+  off = align_up(off + np / kAtbRows * maxG * sizeof(double));
+  if (mode == LV_FP32 && ns > 1) {
+    for (int i = 0; i < 3; ++i) {
+      c.d64[i] = work + i * align_up(np * np * sizeof(double));
+      off = align_up(off + np * np * sizeof(double));
+    }
+  }
+  for (auto& q : c.steps) {
+    const size_t w = (size_t)c.pw[q.a] * c.r_pad;
+    const bool cores = skinny_on_mfma((int)w, c.elem);
+    auto place = [&](int64_t nrt) {
+      q.nrt = (int)nrt;
+      q.x = work;
+      q.xd = align_up(q.x + c.nct * np * w * e);
+      q.y = align_up(q.xd + c.nct * np * w * e);
+      q.g = align_up(q.y + nrt * np * w * e);
+      return q.g + (w <= (size_t)kMaxKrylovCols ? nrt : np / kAtbRows) * w * w * sizeof(double) - work;
+    };
+    q.rows = fitted_rows(c.n_pad, slice_rows(c.n_pad, c.elem, (int)w, cores, kTileRows), cores, off - work, place);
+    place((c.n_pad + q.rows - 1) / q.rows);
+  }
   c.total = off;
   return LV_OK;
 }
@@ -277,41 +295,41 @@ lv_status step_products(lv_chain* c, const lv_chain::Step& q, hipStream_t s, int
   const T* Va = c->V<T>(q.a);
   *updated = false;
   if (w <= kMaxKrylovCols) {
-    *ng = c->nrt(w);
+    *ng = q.nrt;
     if (q.a == q.b)
-      return hip_check(launch_fused_xgram<T>(w, c->Pm<T>(q.a), np, np, c->rows(w), M, Wb, Va, Wa, c->pX<T>(),
-                                             c->pY<T>(), c->pG(), s), "P U, P^T V");
+      return hip_check(launch_fused_xgram<T>(w, c->Pm<T>(q.a), np, np, q.rows, M, Wb, Va, Wa, c->pX<T>(q),
+                                             c->pY<T>(q), c->pG(q), s), "P U, P^T V");
     if (Wb <= kMaxFusedRank && c->left_last[q.b] < 0) {
       *updated = true;
-      return hip_check(launch_krylov_step<T>(Wb, w, c->Pm<T>(q.a), c->Pm<T>(q.b), np, np, c->rows(w), c->rows(w), M,
-                                             c->U<T>(q.b), c->V<T>(q.b), Wb, Va, Wa, c->pX<T>(), c->pY<T>(), c->pG(),
+      return hip_check(launch_krylov_step<T>(Wb, w, c->Pm<T>(q.a), c->Pm<T>(q.b), np, np, q.rows, q.rows, M,
+                                             c->U<T>(q.b), c->V<T>(q.b), Wb, Va, Wa, c->pX<T>(q), c->pY<T>(q), c->pG(q),
                                              s), "P_a U_b, P_b^T V_a, P_b += U_b V_b^T");
     }
-    lv_status st = hip_check(launch_fused_xgram<T>(w, c->Pm<T>(q.a), np, np, c->rows(w), M, Wb, Va, Wa, c->pX<T>(),
-                                                   nullptr, c->pG(), s), "P_a U_b");
+    lv_status st = hip_check(launch_fused_xgram<T>(w, c->Pm<T>(q.a), np, np, q.rows, M, Wb, Va, Wa, c->pX<T>(q),
+                                                   nullptr, c->pG(q), s), "P_a U_b");
     if (st != LV_OK) return st;
-    return hip_check(launch_level_readonly<T>(w, c->Pm<T>(q.b), np, np, c->rows(w), Va, Va, Wa, c->pXd<T>(),
-                                              c->pY<T>(), s), "P_b^T V_a");
+    return hip_check(launch_level_readonly<T>(w, c->Pm<T>(q.b), np, np, q.rows, Va, Va, Wa, c->pXd<T>(q),
+                                              c->pY<T>(q), s), "P_b^T V_a");
   }
   // wider: the float matrix cores form only what is asked, the vector pass
-  // sends the unused product to the discard buffer
+  // that forms Y sends X to the discard buffer
   auto pass = [&](const T* P, const T* op1, const T* op2, int W, T* px, T* py, int want) -> hipError_t {
     if (skinny_on_mfma(w, (int)sizeof(T)))
-      return launch_skinny_f32(w, reinterpret_cast<const float*>(P), np, np, c->rows(w),
+      return launch_skinny_f32(w, reinterpret_cast<const float*>(P), np, np, q.rows,
                                reinterpret_cast<const float*>(op1), reinterpret_cast<const float*>(op2), W,
                                reinterpret_cast<float*>(px), reinterpret_cast<float*>(py), s, want);
-    return launch_level_readonly<T>(w, P, np, np, c->rows(w), op1, op2, W, px, py, s);
+    return launch_level_readonly<T>(w, P, np, np, q.rows, op1, op2, W, px, py, s);
   };
   *ng = 1;
   lv_status st = LV_OK;
   if (q.a == q.b) {
-    st = hip_check(pass(c->Pm<T>(q.a), M, Va, Wa, c->pX<T>(), c->pY<T>(), kWantX | kWantY), "P U, P^T V");
+    st = hip_check(pass(c->Pm<T>(q.a), M, Va, Wa, c->pX<T>(q), c->pY<T>(q), kWantX | kWantY), "P U, P^T V");
   } else {
-    st = hip_check(pass(c->Pm<T>(q.a), M, M, Wb, c->pX<T>(), c->pY<T>(), kWantX), "P_a U_b");
-    if (st == LV_OK) st = hip_check(pass(c->Pm<T>(q.b), Va, Va, Wa, c->pXd<T>(), c->pY<T>(), kWantY), "P_b^T V_a");
+    st = hip_check(pass(c->Pm<T>(q.a), M, M, Wb, c->pX<T>(q), nullptr, kWantX), "P_a U_b");
+    if (st == LV_OK) st = hip_check(pass(c->Pm<T>(q.b), Va, Va, Wa, c->pXd<T>(q), c->pY<T>(q), kWantY), "P_b^T V_a");
   }
   if (st != LV_OK) return st;
-  return hip_check(launch_atb<T>(w, w, Va, Wa, M, Wb, np, c->pG(), s), "V_a^T U_b");
+  return hip_check(launch_atb<T>(w, w, Va, Wa, M, Wb, np, c->pG(q), s), "V_a^T U_b");
 }
 
 template <typename T>
@@ -329,7 +347,7 @@ lv_status chain_update(lv_chain* c, const T* U, const T* V, int r, int64_t ldu, 
     st = step_products<T>(c, q, s, &ng, &updated);
     if (updated) done[q.b] = 1;
     if (st == LV_OK)
-      st = hip_check(launch_krylov_tail<T>(w, c->pX<T>(), c->nct, c->pY<T>(), c->nrt(w), c->pG(), ng, c->U<T>(q.a),
+      st = hip_check(launch_krylov_tail<T>(w, c->pX<T>(q), c->nct, c->pY<T>(q), q.nrt, c->pG(q), ng, c->U<T>(q.a),
                                            c->Wd[q.a], c->U<T>(q.b), c->V<T>(q.b), c->Wd[q.b], c->pw[q.b] * c->r_pad,
                                            c->U<T>(q.c), c->V<T>(q.c), c->Wd[q.c], np, s), "chain tail");
   }

@@ -153,7 +153,7 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
   static_assert(!SP || (UPD && XE == 0 && XD == 0), "the sums pass updates and forms no X");
   static_assert(TT == 1 || (UPD && !SP && XE == 0 && XD == 0), "several updates: the plain pass only");
   static_assert(SP || RY == R, "Y has the factors' columns");
-  static_assert(WY || (!UPD && R <= 8), "passes without Y read only");
+  static_assert(WY || !UPD, "passes without Y read only");
   static_assert(SP || NX <= 64, "one lane per X sum");
   constexpr bool LF = !SP && XE == 0 && XD == 0 && (C > 8 || TT > 1);
   constexpr int CH = R < 4 ? R : 4;             // factor columns read at a time (LF)
@@ -314,11 +314,12 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
 #pragma unroll
           for (int t = 0; t < RB; ++t) {
             T vi[CH], x[CH];
-            load_row<T, CH>(fac_y + (t * TT + v) * R + c0, vi);
+            if constexpr (WY) load_row<T, CH>(fac_y + (t * TT + v) * R + c0, vi);
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
+              if constexpr (WY)
 #pragma unroll
-              for (int q = 0; q < EPL; ++q) yacc[v][q][c0 + c] = fma(p[t].v[q], vi[c], yacc[v][q][c0 + c]);
+                for (int q = 0; q < EPL; ++q) yacc[v][q][c0 + c] = fma(p[t].v[q], vi[c], yacc[v][q][c0 + c]);
               x[c] = p[t].v[0] * uc[c].v[0];
 #pragma unroll
               for (int q = 1; q < EPL; ++q) x[c] = fma(p[t].v[q], uc[c].v[q], x[c]);
@@ -481,6 +482,12 @@ __global__ void __launch_bounds__(256, (fused_min_waves<R, TT>())) k_level_fused
   fused_body<T, R, TT, UPD>(d, blockIdx.x, blockIdx.y, vs);
 }
 
+// Read-only: X = P Uj alone.
+template <typename T, int R>
+__global__ void __launch_bounds__(256) k_level_x(const FusedDesc<T> d) {
+  fused_body<T, R, 1, false, 0, false, 0, R, false, false>(d, blockIdx.x, blockIdx.y);
+}
+
 // The same pass with gridDim.y below the slice count: row slices rt =
 // blockIdx.y, blockIdx.y + gridDim.y, ... one after the other (fewer,
 // longer-lived work-groups; every slice is summed exactly as with one
@@ -536,6 +543,12 @@ __global__ void __launch_bounds__(256) k_level_fused_multi(const FusedDesc<T>* _
 template <typename T, int R, int TT, bool UPD>
 hipError_t fused_launch(const FusedDesc<T>& d, hipStream_t s, int slice_groups = 0, const Strides& vs = {}) {
   const int ns = (d.n_pad + d.tile_rows - 1) / d.tile_rows;
+  if constexpr (!UPD) {
+    if (d.partY == nullptr) {
+      hipLaunchKernelGGL((k_level_x<T, R>), dim3((unsigned)d.nct, (unsigned)ns), dim3(256), 0, s, d);
+      return hipGetLastError();
+    }
+  }
   if constexpr (UPD && R <= 8 && TT == 1) {
     if (slice_groups > 0 && slice_groups < ns) {
       hipLaunchKernelGGL((k_level_fused_grouped<T, R, TT, UPD>), dim3((unsigned)d.nct, (unsigned)slice_groups),
@@ -738,9 +751,9 @@ hipError_t launch_fused_multi(int R, bool chunk, const FusedDesc<T>* ds, int nd,
   return hipGetLastError();
 }
 
-// Read-only pass: partial X = P Uop and Y = P^T Vop for R columns (row
-// stride R), P unchanged: the fused kernel without its update and Gram, in
-// 16-column chunks above 16.
+// Read-only pass: partial X = P Uop and, with a non-null partY, Y = P^T Vop
+// for R columns (row stride R), P unchanged: the fused kernel without its
+// update and Gram, in 16-column chunks above 16.
 template <typename T>
 hipError_t launch_level_readonly(int R, const T* P, int64_t ldp, int64_t n_pad, int tile_rows, const T* Uop,
                                  const T* Vop, int W, T* partX, T* partY, hipStream_t s) {
@@ -760,7 +773,7 @@ hipError_t launch_level_readonly(int R, const T* P, int64_t ldp, int64_t n_pad, 
     d.Uj += kMaxFusedRank;
     d.Vj += kMaxFusedRank;
     d.partX += kMaxFusedRank;
-    d.partY += kMaxFusedRank;
+    if (d.partY != nullptr) d.partY += kMaxFusedRank;
   }
   return hipSuccess;
 }

@@ -410,8 +410,8 @@ hipError_t launch_to_bf16(const float* P, uint16_t* S, int64_t count, hipStream_
 
 // ---- sums of powers (views with LV_WITH_SUMS)
 
-// Read-only pass: partial X = P Uop, Y = P^T Vop for R columns (row stride
-// R), P unchanged (fused kernel without its update).
+// Read-only pass: partial X = P Uop and, with a non-null partY, Y = P^T Vop for
+// R columns (row stride R), P unchanged (fused kernel without its update).
 template <typename T>
 hipError_t launch_level_readonly(int R, const T* P, int64_t ldp, int64_t n_pad, int tile_rows, const T* Uop,
                                  const T* Vop, int W, T* partX, T* partY, hipStream_t s);

@@ -56,6 +56,17 @@ inline size_t gram_partials(int64_t n_pad, int elem, int R, bool chained = false
   return most;
 }
 
+// Rows per slice of a pass at the default height: `rows` (slice_rows), or as
+// many more, up to the plain kTileRows, as it takes for the partials of ns
+// slices, bytes(ns), to fit in room bytes: workspaces hold the partials of
+// kTileRows rows, and the finer cut only where idle regions take the rest.
+template <typename F>
+inline int fitted_rows(int64_t n_pad, int rows, bool cores, size_t room, F bytes) {
+  const int unit = cores ? 64 : 4 * kFusedRowBlock;
+  while (rows < kTileRows && bytes((n_pad + rows - 1) / rows) > room) rows += unit;
+  return rows < kTileRows ? rows : kTileRows;
+}
+
 struct Layout {
   int64_t n_pad = 0, ldp = 0;
   int m = 0, r_pad = 0, W = 0, elem = 0, nct = 0, tile_rows = 0;

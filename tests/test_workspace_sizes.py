@@ -11,6 +11,12 @@ import pytest
 OLS = [((256, 256, 1, 0), 3238400), ((600, 300, 4, 0), 13943552), ((1024, 1024, 1, 1), 42310400),
        ((8192, 4096, 16, 1), 746504960), ((1500, 700, 64, 0), 35882496)]
 
+# (n, k, r_max, mode, model, s) -> bytes
+CHAIN = [((300, 1, 8, 0, 1, 0), 2457856), ((300, 2, 4, 0, 2, 2), 4588544), ((300, 1, 8, 1, 1, 0), 1163520),
+         ((512, 2, 1, 0, 1, 0), 4292864), ((512, 4, 1, 0, 1, 0), 8626432), ((1024, 12, 1, 0, 1, 0), 104777728),
+         ((4096, 12, 1, 1, 1, 0), 1221959680), ((700, 16, 2, 0, 2, 4), 32243712), ((1500, 8, 16, 1, 2, 2), 120913920),
+         ((65536, 3, 32, 0, 1, 0), 180640284672), ((600, 16, 8, 0, 0, 0), 38043648)]
+
 
 @pytest.fixture(scope="module")
 def lib():
@@ -21,3 +27,8 @@ def lib():
 @pytest.mark.parametrize("args,most", OLS)
 def test_ols(lib, args, most):
     assert 0 < lib.lv_ols_footprint(*args) <= most
+
+
+@pytest.mark.parametrize("args,most", CHAIN)
+def test_chain(lib, args, most):
+    assert 0 < lib.lv_chain_footprint(*args) <= most
