@@ -71,7 +71,8 @@ struct lv_glin {
   int64_t n, n_pad;
   int k, p, pp, r_max, r_pad, elem, nct, strategy, maxw;
   lv_mode mode;
-  size_t A, Tb, Bb, D[2], sU, sV, partX, partY, full, atbA, atbG, Y, Z, A64, gT[2], gB, total;
+  int splits, rows;   // shares of a wide product; rows per slice of an incremental step
+  size_t A, Tb, Bb, D[2], sU, sV, partX, full, atbA, atbG, Y, Z, A64, gT[2], gB, total;
   size_t Toff(int i) const { return Tb + (size_t)i * align_up((size_t)n_pad * pp * elem); }
   int64_t Tstride() const { return (int64_t)(align_up((size_t)n_pad * pp * elem) / elem); }
   char* base = nullptr;
@@ -103,39 +104,62 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
   g.pp = p <= kGlinNarrow ? (int)next_pow2(p) : (int)round_up(p, 128);
   g.nct = (int)(g.n_pad / tile_cols_bytes(g.elem));
   g.maxw = strategy == LV_GLIN_INCR ? (int)next_pow2((int64_t)k * g.r_pad) : 1;
-  const size_t e = g.elem, np = g.n_pad, pp = g.pp;
-  // read-only pass width (incremental evaluation needs r_pad columns only, and
-  // keeps the region no smaller than the other strategies')
-  const int narrow = g.pp <= kGlinNarrow ? g.pp : 1;
-  const int xw = strategy == LV_GLIN_INCR && g.r_pad > narrow ? g.r_pad : narrow;
+  const size_t e = g.elem, np = g.n_pad, pp = g.pp, r = g.r_pad;
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t at = off; off = align_up(off + bytes); return at; };
   g.A = take(np * np * e);
   g.Tb = off;
   for (int i = 0; i <= k; ++i) take(np * pp * e);      // T_0 .. T_k
   g.Bb = take(np * pp * e);
-  g.sU = take(np * g.r_pad * e);
-  g.sV = take(np * g.r_pad * e);
-  g.partX = take((size_t)g.nct * np * xw * e);
-  g.partY = take(np * slice_cols(g.n_pad, g.elem, xw, false, true) * e);
-  const size_t pairs = (size_t)g.r_pad * pp;
-  g.atbA = take((strategy == LV_GLIN_INCR ? (size_t)k * vtt_tiles(g.n_pad, (int)pairs) : np / kAtbRows) * pairs *
-                sizeof(double));
-  g.D[0] = g.D[1] = g.full = g.atbG = g.Y = g.Z = 0;
-  if (strategy == LV_GLIN_HYBRID) { g.D[0] = take(np * pp * e); g.D[1] = take(np * pp * e); }
-  if (strategy != LV_GLIN_INCR && g.pp > kGlinNarrow) g.full = take(glin_splits(np, pp) * np * pp * e);
-  if (strategy == LV_GLIN_INCR) {
-    // Gram partials of a step: one per 64 rows, or per slice of the pass
-    const size_t ng = np / kAtbRows * g.r_pad * g.r_pad, nk = gram_partials(g.n_pad, g.elem, kMaxKrylovCols, false, true);
-    g.atbG = take((ng > nk ? ng : nk) * sizeof(double));
-    g.Y = take(np * g.maxw * e);                            // f^q(U) in columns q r .. q r + r - 1
-    g.Z = take((size_t)k * g.r_pad * pp * e);               // V^T T_i in rows (k - 1 - i) r ..
-  }
+  g.sU = take(np * r * e);
+  g.sV = take(np * r * e);
+  // Last the region that creation's double matrices and an update's buffers
+  // share.  It has a size for both side by side where the wide product is
+  // not split and a step takes a slice per kTileRows rows; more shares and finer
+  // slices have to fit in it.
+  const size_t work = off;
   g.A64 = take(mode == LV_FP32 ? np * np * sizeof(double) : 0);
   g.gT[0] = take(np * pp * sizeof(double));
   g.gT[1] = take(np * pp * sizeof(double));
   g.gB = take(np * pp * sizeof(double));
+  const bool incr = strategy == LV_GLIN_INCR, wide = !incr && g.pp > kGlinNarrow;
+  const size_t xw = incr ? g.maxw : wide ? 1 : pp, nrt = (np + kTileRows - 1) / kTileRows;
+  take(g.nct * np * xw * e);
+  take(nrt * np * xw * e);
+  take(np / kAtbRows * r * pp * sizeof(double));
+  if (strategy == LV_GLIN_HYBRID) { take(np * pp * e); take(np * pp * e); }
+  if (wide) take(np * pp * e);
+  if (incr) {
+    take(np / kAtbRows * r * g.maxw * sizeof(double));
+    for (int i = 2; i <= k; ++i) take(np * g.maxw * e);
+    for (int i = 1; i <= k; ++i) take(g.maxw * pp * e);
+  }
   g.total = off;
+  const size_t room = off - work;
+  // an update's buffers with the given shares of a wide product and slices of an
+  // incremental step; returns their size
+  g.D[0] = g.D[1] = g.full = g.atbG = g.Y = g.Z = 0;
+  auto place = [&](int64_t splits, int64_t ns) {
+    off = work;
+    g.partX = take(wide ? 0 : g.nct * np * (incr ? r : pp) * e);
+    const size_t pairs = r * pp;
+    g.atbA = take((incr ? (size_t)k * vtt_tiles(g.n_pad, (int)pairs) : np / kAtbRows) * pairs * sizeof(double));
+    if (strategy == LV_GLIN_HYBRID) { g.D[0] = take(np * pp * e); g.D[1] = take(np * pp * e); }
+    if (wide) g.full = take(splits * np * pp * e);
+    if (incr) {
+      g.atbG = take((r <= (size_t)kMaxKrylovCols ? ns : np / kAtbRows) * r * r * sizeof(double));
+      g.Y = take(k > 1 ? np * g.maxw * e : 0);                // f^q(U) in columns q r .. q r + r - 1
+      g.Z = take((size_t)k * r * pp * e);                     // V^T T_i in rows (k - 1 - i) r ..
+    }
+    return off - work;
+  };
+  g.splits = wide ? (int)glin_splits(g.n_pad, pp) : 1;
+  g.rows = fitted_rows(g.n_pad, slice_rows(g.n_pad, g.elem, (int)r, false, kTileRows, true), false, room,
+                       [&](int64_t ns) { return place(1, ns); });
+  const int64_t ns = (g.n_pad + g.rows - 1) / g.rows;
+  while (g.splits > 1 && place(g.splits, ns) > room) --g.splits;
+  const size_t used = place(g.splits, ns);
+  g.total = work + (used > room ? used : room);
 }
 
 // Creation: T_i = A T_{i-1} + B in double from the double A, each rounded once.
@@ -173,7 +197,7 @@ template <typename T>
 lv_status glin_amul(lv_glin* g, const T* M, int w, int sm, hipStream_t s, int* nct_out) {
   const int64_t np = g->n_pad;
   if (w > kGlinNarrow && g->full != 0) {
-    *nct_out = (int)glin_splits(np, w);
+    *nct_out = g->splits;
     return hip_check(launch_gemm_rect<T>(g->at<T>(g->A), np, M, sm, g->at<T>(g->full), g->pp, np, w, np, s, nullptr,
                                          *nct_out),
                      "A M");
@@ -183,10 +207,10 @@ lv_status glin_amul(lv_glin* g, const T* M, int w, int sm, hipStream_t s, int* n
   if (skinny_on_mfma(w, (int)sizeof(T)))
     return hip_check(launch_skinny_f32(w, reinterpret_cast<const float*>(g->at<T>(g->A)), np, np, rows,
                                        reinterpret_cast<const float*>(M), reinterpret_cast<const float*>(M), sm,
-                                       g->at<float>(g->partX), g->at<float>(g->partY), s, kWantX),
+                                       g->at<float>(g->partX), nullptr, s, kWantX),
                      "A M");
-  return hip_check(launch_level_readonly<T>(w, g->at<T>(g->A), np, np, rows, M, M, sm, g->at<T>(g->partX),
-                                            g->at<T>(g->partY), s),
+  return hip_check(launch_level_readonly<T>(w, g->at<T>(g->A), np, np, rows, M, M, sm, g->at<T>(g->partX), nullptr,
+                                            s),
                    "A M");
 }
 
@@ -246,7 +270,7 @@ lv_status glin_update(lv_glin* g, const T* U, const T* V, int r, int64_t ldu, in
   T* Z = g->at<T>(g->Z);
   double* G = g->d64(g->atbG);
   st = hip_check(launch_vtt<T>(R, pp, sV, g->at<T>(g->Toff(0)), g->Tstride(), k, np, g->d64(g->atbA), Z, s), "V^T T");
-  const int rows = slice_rows(np, g->elem, R, false, kTileRows, true);
+  const int rows = g->rows;
   for (int q = 1; q < k && st == LV_OK; ++q) {
     const T* M = q == 1 ? sU : Y + (q - 1) * R;
     const int sm = q == 1 ? R : W;

@@ -17,6 +17,12 @@ CHAIN = [((300, 1, 8, 0, 1, 0), 2457856), ((300, 2, 4, 0, 2, 2), 4588544), ((300
          ((4096, 12, 1, 1, 1, 0), 1221959680), ((700, 16, 2, 0, 2, 4), 32243712), ((1500, 8, 16, 1, 2, 2), 120913920),
          ((65536, 3, 32, 0, 1, 0), 180640284672), ((600, 16, 8, 0, 0, 0), 38043648)]
 
+# (n, k, r_max, mode, p, strategy) -> bytes
+GLIN = [((2048, 1, 1, 0, 200, 0), 63340544), ((2048, 4, 1, 0, 200, 1), 84312064), ((1024, 1, 1, 1, 1000, 0), 54689792),
+        ((1024, 16, 1, 1, 1, 0), 12714240), ((1024, 16, 1, 0, 16, 1), 12732416), ((65536, 1, 1, 0, 64, 2), 34898190848),
+        ((1024, 1, 1, 1, 64, 2), 14983680), ((5000, 16, 1, 1, 16, 2), 337260544), ((700, 4, 2, 0, 7, 0), 5580288),
+        ((500, 3, 4, 0, 1000, 2), 36802560), ((500, 9, 2, 1, 130, 1), 13678592), ((300, 2, 64, 0, 4096, 2), 148897792)]
+
 
 @pytest.fixture(scope="module")
 def lib():
@@ -32,3 +38,8 @@ def test_ols(lib, args, most):
 @pytest.mark.parametrize("args,most", CHAIN)
 def test_chain(lib, args, most):
     assert 0 < lib.lv_chain_footprint(*args) <= most
+
+
+@pytest.mark.parametrize("args,most", GLIN)
+def test_linear_general_form(lib, args, most):
+    assert 0 < lib.lv_glin_footprint(*args) <= most
