@@ -330,10 +330,12 @@ lv_status lv_view_timing(lv_view* v, lv_timing* out);
  * tail, so it fixes the summation order of the update.  Default 512, which
  * stands for at most 512 rows: a matrix too small to fill the device with
  * 512-row tiles is cut finer (by its order, element type and the update's
- * rank alone).  Other heights are taken as they are.  lv_batch_create sets it
- * by autotuning.  Allowed values: multiples of 64
- * in [256, 1024].  Two views with equal tiles, inputs and updates hold equal
- * values bit for bit whichever entry point applies the updates. */
+ * rank alone).  Other heights are taken as they are; LV_TILE_ROWS_512 is 512
+ * rows as they are.  lv_batch_create sets heights by autotuning.  Allowed
+ * values: multiples of 64 in [256, 1024], and LV_TILE_ROWS_512.  Two views
+ * with equal tiles, inputs and updates hold equal values bit for bit
+ * whichever entry point applies the updates. */
+#define LV_TILE_ROWS_512 513
 lv_status lv_view_tile_rows(const lv_view* v, int level, int* rows);
 lv_status lv_view_set_tile_rows(lv_view* v, int level, int rows);
 
@@ -401,7 +403,8 @@ lv_status lv_batch_tuning(const lv_batch* b, int* tuned_groups, int* cache_hits)
 /* The autotuner's choices persist across processes through a JSON file: a
  * flat object mapping "arch|m<mode>|R<level rank>|n:<n bucket>:..." (the
  * device architecture, the mode, the level rank and the orders of the
- * group's views, each rounded up to a power of two) to tile rows.
+ * group's views, each rounded up to a power of two) to tile rows,
+ * 512 meaning LV_TILE_ROWS_512.
  * lv_tune_cache_save writes the process cache (atomically, by rename);
  * lv_tune_cache_load merges a file into it (*entries = entries read; an
  * entry whose tile rows lv_view_set_tile_rows would refuse makes the whole

@@ -433,7 +433,7 @@ lv_status gfac_skip(lv_view* v, int ru, const T* sU, const T* sV, hipStream_t s)
                                  reinterpret_cast<const float*>(Yp), reinterpret_cast<const float*>(Yp), sp,
                                  v->partXT<float>(), v->partYT<float>(), s, kWantX);
       return launch_level_readonly<T>(wp, v->P<T>(L.m), L.ldp, L.n_pad,
-                                      slice_rows(L.n_pad, L.elem, wp, v->on_cores(wp), kTileRows), Yp, Yp, sp, v->partXT<T>(),
+                                      v->default_rows(wp), Yp, Yp, sp, v->partXT<T>(),
                                       v->partYT<T>(), s);
     });
     AtbJobs<T> jobs;
@@ -870,7 +870,7 @@ lv_status create_view(const void* A, int64_t n, int64_t lda, int k, int r_max, l
   v->n = n; v->k = k; v->r_max = r_max; v->mode = mode; v->L = L;
   v->base = static_cast<char*>(workspace); v->ws_bytes = ws_bytes;
   v->updates = 0; v->reanchors = 0;
-  for (int j = 0; j < kMaxLevel; ++j) v->tile_rows[j] = L.tile_rows;
+  for (int& rows : v->tile_rows) rows = kTileRows;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (L.sums) {
     // the sum factor slabs start at zero: the W columns of level 0 are read as
@@ -1187,7 +1187,7 @@ lv_status lv_view_tile_rows(const lv_view* v, int level, int* rows) {
 lv_status lv_view_set_tile_rows(lv_view* v, int level, int rows) {
   if (!v) return fail(LV_EINVAL, "view is NULL");
   if (level < 0 || level >= v->L.m) return fail(LV_EINVAL, "level %d has no level pass (levels 0..%d)", level, v->L.m - 1);
-  if (rows < kMinTileRows || rows > kMaxTileRows || rows % 64 != 0)
+  if (rows != LV_TILE_ROWS_512 && (rows < kMinTileRows || rows > kMaxTileRows || rows % 64 != 0))
     return fail(LV_EINVAL, "tile rows %d not a multiple of 64 in [%d, %d]", rows, kMinTileRows, kMaxTileRows);
   v->tile_rows[level] = rows;
   return LV_OK;
@@ -1409,7 +1409,7 @@ lv_status lv_powers_update_noalloc(void* const* powers, int64_t n, int64_t ld, i
   lv_view v;
   v.n = n; v.k = k; v.r_max = (int)r; v.mode = mode; v.L = L; v.L.ldp = ld;
   v.base = base; v.ws_bytes = kNoAllocScratchBytes; v.updates = 0; v.reanchors = 0;
-  for (int j = 0; j < kMaxLevel; ++j) v.tile_rows[j] = L.tile_rows;
+  for (int& rows : v.tile_rows) rows = kTileRows;
   for (int j = 0; j <= m; ++j) v.pext[j] = static_cast<char*>(powers[j]);
   hipStream_t s = static_cast<hipStream_t>(stream);
   return mode == LV_FP64

@@ -122,13 +122,12 @@ lv_status autotune(lv_batch* b, hipStream_t s) {
     return fail(LV_EDEVICE, "hipEventCreate failed");
   int max_m = 0;
   for (lv_view* v : b->views) max_m = std::max(max_m, v->L.m);
-  // Tile rows over the allowed range.  576 rows give the slice counts of 512
-  // up to n = 2048 and at multiples of 512 to 4096; kTileRows (512) itself
-  // stands for a finer cut that fills the device with one view's pass, which
-  // wins when a level is timed by itself and loses next to the round's other
-  // lanes (32 views of 512 to 4096 rows: 2.36 ms with it among the candidates,
-  // 2.31 ms without).
-  const int cands[] = {256, 384, 576, 640, 768, 896, 1024};
+  // tile rows: every multiple of 128 from 256 to 1024 (the allowed range) as it is.  The
+  // default's finer cut, which fills the device with one view's pass, is not
+  // among them: it wins when a level is timed by itself and loses next to the
+  // round's other lanes (32 views of 512 to 4096 rows: 2.36 ms with it, 2.31 ms
+  // without).
+  const int cands[] = {256, 384, LV_TILE_ROWS_512, 640, 768, 896, 1024};
   for (int j = 0; j < max_m && st == LV_OK; ++j) {
     std::map<int, std::vector<lv_view*>> groups;   // level rank -> views with a pass at level j
     for (lv_view* v : b->views)
@@ -212,7 +211,7 @@ lv_status lv_tune_cache_save(const char* path) {
   std::fprintf(f, "{\n");
   size_t i = 0;
   for (auto& kv : copy)
-    std::fprintf(f, "  \"%s\": %d%s\n", kv.first.c_str(), kv.second, ++i < copy.size() ? "," : "");
+    std::fprintf(f, "  \"%s\": %d%s\n", kv.first.c_str(), kv.second == LV_TILE_ROWS_512 ? 512 : kv.second, ++i < copy.size() ? "," : "");
   std::fprintf(f, "}\n");
   const bool ok = std::fclose(f) == 0;
   if (!ok || std::rename(tmp.c_str(), path) != 0) return fail(LV_EINVAL, "cannot write %s", path);
@@ -244,7 +243,7 @@ lv_status lv_tune_cache_load(const char* path, int* entries) {
     const long rows = std::strtol(text.c_str() + colon + 1, &end, 10);
     if (end == text.c_str() + colon + 1 || rows < kMinTileRows || rows > kMaxTileRows || rows % 64 != 0)
       return fail(LV_EINVAL, "%s: bad tile rows for %s", path, text.substr(q0 + 1, q1 - q0 - 1).c_str());
-    add[text.substr(q0 + 1, q1 - q0 - 1)] = (int)rows;
+    add[text.substr(q0 + 1, q1 - q0 - 1)] = rows == 512 ? LV_TILE_ROWS_512 : (int)rows;
     pos = (size_t)(end - text.c_str());
   }
   {

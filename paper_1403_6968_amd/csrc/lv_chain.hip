@@ -231,7 +231,7 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
       q.g = align_up(q.y + nrt * np * w * e);
       return q.g + (w <= (size_t)kMaxKrylovCols ? nrt : np / kAtbRows) * w * w * sizeof(double) - work;
     };
-    q.rows = fitted_rows(c.n_pad, slice_rows(c.n_pad, c.elem, (int)w, cores, kTileRows), cores, off - work, place);
+    q.rows = fitted_rows(c.n_pad, slice_rows(c.n_pad, c.elem, (int)w, cores), cores, off - work, place);
     place((c.n_pad + q.rows - 1) / q.rows);
   }
   c.total = off;

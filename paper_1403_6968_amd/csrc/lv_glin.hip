@@ -154,7 +154,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
     return off - work;
   };
   g.splits = wide ? (int)glin_splits(g.n_pad, pp) : 1;
-  g.rows = fitted_rows(g.n_pad, slice_rows(g.n_pad, g.elem, (int)r, false, kTileRows, true), false, room,
+  g.rows = fitted_rows(g.n_pad, slice_rows(g.n_pad, g.elem, (int)r, false, true), false, room,
                        [&](int64_t ns) { return place(1, ns); });
   const int64_t ns = (g.n_pad + g.rows - 1) / g.rows;
   while (g.splits > 1 && place(g.splits, ns) > room) --g.splits;
@@ -203,7 +203,7 @@ lv_status glin_amul(lv_glin* g, const T* M, int w, int sm, hipStream_t s, int* n
                      "A M");
   }
   *nct_out = g->nct;
-  const int rows = slice_rows(np, g->elem, w, skinny_on_mfma(w, g->elem), kTileRows, true);
+  const int rows = slice_rows(np, g->elem, w, skinny_on_mfma(w, g->elem), true);
   if (skinny_on_mfma(w, (int)sizeof(T)))
     return hip_check(launch_skinny_f32(w, reinterpret_cast<const float*>(g->at<T>(g->A)), np, np, rows,
                                        reinterpret_cast<const float*>(M), reinterpret_cast<const float*>(M), sm,

@@ -198,9 +198,9 @@ inline bool sums_fused(int R, int elem) { return R <= kMaxFusedRank && !skinny_o
 // Rows per slice of a level pass of rank R over a matrix of padded order
 // n_pad, for a view's tile rows.  The passes take (column tile, row slice)
 // work-groups, and 512-row slices leave most of the device idle below
-// n_pad = 8192 (128 work-groups at 4096, 4 at 512).  The default, kTileRows,
-// therefore stands for 512 rows or as many as give kFillBlocks work-groups
-// (one per compute unit), whichever is less, but not below 8 R rows, so that
+// n_pad = 8192 (128 work-groups at 4096, 4 at 512).  The default height,
+// kTileRows, therefore stands for 512 rows or as many as give kFillBlocks
+// work-groups (one per compute unit), whichever is less, but not below 8 R rows, so that
 // a slice's Y partial stays under 1/16 of the bytes it streams (matrix-core
 // passes, `cores`, take 32 columns at a time: not below 256 rows; FP32 rank 64
 // at n = 4096, 128 work-groups of 512 rows: 57 us a pass, 256 of 256: 36 us), nor
@@ -213,7 +213,7 @@ inline bool sums_fused(int R, int elem) { return R <= kMaxFusedRank && !skinny_o
 // 38 us and 22 us.  Other heights are taken as they are: rounds over many
 // views fill the device anyway and lose by finer slices (32 views of 512 to
 // 4096: 2.34 ms with tuned heights, 2.52 ms when every height was cut).
-constexpr int kTileRows = 512;      // default rows per tile of a level pass
+constexpr int kTileRows = 512;      // default rows per tile: the most rows of the default cut
 //
 // Twice as many work-groups for passes that only read (`reads`) and for 128
 // and more bytes of factors per row, whose long row blocks leave one wave per
@@ -223,8 +223,7 @@ constexpr int kTileRows = 512;      // default rows per tile of a level pass
 // work-groups per compute unit, so they take at most that many (n = 7168, rank
 // 32 from the shadow: 532 of them 40 us, 448 32 us).
 constexpr int kFillBlocks = 256;
-inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, int tile_rows, bool reads = false) {
-  if (tile_rows != kTileRows) return tile_rows;
+inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, bool reads = false) {
   const int unit = cores ? 64 : 4 * kFusedRowBlock;
   const int64_t nct = n_pad / tile_cols_bytes(elem);
   const int64_t fill = reads || R * elem >= 128 ? 2 * kFillBlocks : kFillBlocks;
@@ -233,10 +232,10 @@ inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, int tile_rows,
   int least = cores && 8 * R > 256 ? 256 : 8 * R;
   if (!cores && R <= kMaxFusedRank && nct * (n_pad / least) < kFillBlocks) least = 2 * R;
   if (rows < least) rows = round_up(least, unit);
-  return rows < tile_rows ? (int)rows : tile_rows;
+  return rows < kTileRows ? (int)rows : kTileRows;
 }
-inline int slice_count(int64_t n_pad, int elem, int R, bool cores, int tile_rows, bool reads = false) {
-  const int rows = slice_rows(n_pad, elem, R, cores, tile_rows, reads);
+inline int slice_count(int64_t n_pad, int elem, int R, bool cores, bool reads = false) {
+  const int rows = slice_rows(n_pad, elem, R, cores, reads);
   return (int)((n_pad + rows - 1) / rows);
 }
 

@@ -407,7 +407,7 @@ void layout_ols(lv_ols& o, int64_t m, int64_t n, int64_t p, lv_mode mode) {
   o.n_pad = round_up(n, kPadOrder);
   o.pp = (int)next_pow2(p);
   o.nct = (int)(o.n_pad / tile_cols_bytes(o.elem));
-  o.rows = slice_rows(o.n_pad, o.elem, 4, false, kTileRows, true);
+  o.rows = slice_rows(o.n_pad, o.elem, 4, false, true);
   o.nrt = (int)((o.n_pad + o.rows - 1) / o.rows);
   const size_t e = o.elem, np = o.n_pad, mp = o.m_pad, pp = o.pp;
   size_t off = 0;

@@ -38,8 +38,8 @@ inline size_t slice_cols(int64_t n_pad, int elem, int R, bool chained = false, b
   size_t most = 0;
   for (int q = 1; q <= R; q *= 2) {
     const bool cores = skinny_on_mfma(q, elem);   // (a level on shadows has no more slices)
-    for (const int rows : {kMinTileRows, kTileRows}) {
-      const size_t c = (size_t)slice_count(n_pad, elem, q, cores, rows, reads) * q * (chained ? chain_updates(q) : 1);
+    for (const int ns : {(int)(n_pad / kMinTileRows), slice_count(n_pad, elem, q, cores, reads)}) {
+      const size_t c = (size_t)ns * q * (chained ? chain_updates(q) : 1);
       most = c > most ? c : most;
     }
   }
@@ -48,8 +48,8 @@ inline size_t slice_cols(int64_t n_pad, int elem, int R, bool chained = false, b
 inline size_t gram_partials(int64_t n_pad, int elem, int R, bool chained = false, bool reads = false) {
   size_t most = (size_t)gram_tiles(n_pad) * R * R;
   for (int q = 1; q <= R && gram_in_pass(q, elem); q *= 2) {
-    for (const int rows : {kMinTileRows, kTileRows}) {
-      const size_t c = (size_t)slice_count(n_pad, elem, q, false, rows, reads) * q * q * (chained ? chain_updates(q) : 1);
+    for (const int ns : {(int)(n_pad / kMinTileRows), slice_count(n_pad, elem, q, false, reads)}) {
+      const size_t c = (size_t)ns * q * q * (chained ? chain_updates(q) : 1);
       most = c > most ? c : most;
     }
   }
@@ -69,7 +69,7 @@ inline int fitted_rows(int64_t n_pad, int rows, bool cores, size_t room, F bytes
 
 struct Layout {
   int64_t n_pad = 0, ldp = 0;
-  int m = 0, r_pad = 0, W = 0, elem = 0, nct = 0, tile_rows = 0;
+  int m = 0, r_pad = 0, W = 0, elem = 0, nct = 0;
   size_t P[kMaxLevel + 1] = {};
   size_t slabU = 0, slabV = 0;   // the update's factor slabs (every level's U_j, V_j)
   // factor-slab pairs of the pipelined batch (plain views with m >= 2): slot
@@ -166,7 +166,6 @@ inline Layout make_layout(int64_t n, int k, int r_max, lv_mode mode, int flags =
   L.m = ilog2(k);
   L.r_pad = (int)next_pow2(r_max);
   L.W = k * L.r_pad;
-  L.tile_rows = kTileRows;
   L.nct = (int)(L.n_pad / tile_cols_bytes(L.elem));
   size_t off = 0;
   const size_t mat = (size_t)L.n_pad * L.ldp * L.elem;
@@ -319,13 +318,18 @@ struct lv_view {
   double drift_tau = 0.0;
   int64_t drift_checks = 0;
   // Rows per tile of the level pass of each level below the top (set by the
-  // batch autotuner or lv_view_set_tile_rows; every path uses the same value,
-  // which fixes the reduction order of the partial sums).
+  // batch autotuner or lv_view_set_tile_rows; kTileRows: the cut of slice_rows;
+  // every path uses the same value, which fixes the reduction order of the
+  // partial sums).
   int tile_rows[lv::kMaxLevel];
   // rows per slice and slices of the level's pass of rank R
   bool on_cores(int R) const { return shadowed() || lv::skinny_on_mfma(R, L.elem); }
-  int rows(int j, int R) const { return lv::slice_rows(L.n_pad, L.elem, R, on_cores(R), tile_rows[j]); }
-  int nrt(int j, int R) const { return lv::slice_count(L.n_pad, L.elem, R, on_cores(R), tile_rows[j]); }
+  int default_rows(int R) const { return lv::slice_rows(L.n_pad, L.elem, R, on_cores(R)); }
+  int rows(int j, int R) const {
+    const int t = tile_rows[j];
+    return t == lv::kTileRows ? default_rows(R) : t == LV_TILE_ROWS_512 ? 512 : t;
+  }
+  int nrt(int j, int R) const { const int r = rows(j, R); return (int)((L.n_pad + r - 1) / r); }
 
   // Kernel timing (diagnostics): event pairs per launch kind, resolved by
   // lv_view_timing.

@@ -29,6 +29,7 @@ LV_MODEL_EXP, LV_MODEL_LIN, LV_MODEL_SKIP = 0, 1, 2
 LV_OLS_BETA, LV_OLS_INVERSE, LV_OLS_X = 0, 1, 2
 LV_GENERAL_HYBRID, LV_GENERAL_FACTORED = 0, 1
 LV_GLIN_REEVAL, LV_GLIN_HYBRID, LV_GLIN_INCR = 0, 1, 2
+LV_TILE_ROWS_512 = 513
 LV_STREAM_RMW, LV_STREAM_COPY, LV_STREAM_READ, LV_STREAM_WRITE = 0, 1, 2, 3
 
 _MODE_DTYPE = {LV_FP64: torch.float64, LV_FP32: torch.float32, LV_FP32_BF16SHADOW: torch.float32}
@@ -556,7 +557,8 @@ class View:
         return lv_view_timing(self.handle)
 
     def tile_rows(self) -> list[int]:
-        """Rows per tile of the level pass of each level below the top."""
+        """Rows per tile of the level pass of each level below the top (512:
+        the default's cut, at most 512 rows; LV_TILE_ROWS_512: 512 rows)."""
         return [lv_view_tile_rows(self.handle, j) for j in range(len(self.powers()) - 1)]
 
     def set_tile_rows(self, rows) -> None:
