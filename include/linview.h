@@ -100,9 +100,9 @@ const char* lv_last_error(void);
 /* Exact workspace size in bytes for a view of order n, power k and largest
  * update rank r_max.  Returns 0 if the arguments are invalid (same rules as
  * lv_view_create).  The layout is: the m + 1 stored powers (padded order),
- * m + 1 factor slabs (U_j, V_j of every level), per-level reduction
- * partials, the bfloat16 shadows (LV_FP32_BF16SHADOW) and a double-precision
- * squaring scratch (both float modes). */
+ * m + 1 factor slabs (U_j, V_j of every level), the bfloat16 shadows
+ * (LV_FP32_BF16SHADOW) and working storage: the double-precision squaring
+ * scratch (both float modes), reduction partials, a batch's slabs. */
 size_t lv_view_footprint(int64_t n, int k, int r_max, lv_mode mode);
 
 /* Create a view of A^k (Table 1 exponential model; ReevalExp).
@@ -140,6 +140,12 @@ lv_status lv_view_create(const void* A, int64_t n, int64_t lda, int k, int r_max
 
 /* lv_view_footprint / lv_view_create with creation flags (0 = as those). */
 size_t lv_view_footprint_ex(int64_t n, int k, int r_max, lv_mode mode, int flags);
+/* Workspace in which an LV_FP64 view's default tiles (lv_view_tile_rows) are
+ * cut as finely as its order asks: up to a fifth more than
+ * lv_view_footprint_ex at small orders with few powers, next to nothing more at
+ * large ones, and the same in the other modes, whose workspaces always hold the
+ * finer cut.  A view uses what its workspace has beyond the footprint. */
+size_t lv_view_footprint_full(int64_t n, int k, int r_max, lv_mode mode, int flags);
 lv_status lv_view_create_ex(const void* A, int64_t n, int64_t lda, int k, int r_max,
                             lv_mode mode, int flags, void* workspace, size_t ws_bytes,
                             void* stream, lv_view** out);
@@ -161,10 +167,14 @@ lv_status lv_view_update(lv_view* v, const void* U, const void* V, int64_t r,
  * factors that level j-1 of update t assembles (App. A), so the levels run
  * as up to four stages on streams of their own (stage 0 on `stream`; the
  * others are created on the first such call, on the current device) and
- * several updates are in flight, each with a factor-slab pair of the
- * workspace.  A level below rank 16 takes up to 16 / rank of them (at most 8; with
- * shadows 4, at rank 32 2, where the squaring scratch holds their operands)
- * at one read and write of its power, and the top power the whole group.  Every sum and rounding is that of the
+ * several updates are in flight, each with a factor-slab pair.  A level
+ * below rank 16 takes up to 16 / rank of them (at most 8; with shadows 4, at
+ * rank 32 2) at one read and write of its power, and the top power the whole
+ * group.  The slabs and partial sums of the updates in flight lie where
+ * creation squares, in the workspace; where that is too small for all of them
+ * (LV_FP64; float views up to n = 1000 or so) fewer updates share a pass, or none,
+ * unless the caller lends more (lv_view_set_batch_workspace).  Every sum and
+ * rounding is that of the
  * sequential order; the call returns with all stages joined into `stream`,
  * so stream order is as for one call of lv_view_update per update.  Not
  * used while kernel timing is on; a periodic drift check falling inside
@@ -173,6 +183,15 @@ lv_status lv_view_update(lv_view* v, const void* U, const void* V, int64_t r,
 lv_status lv_view_update_batch(lv_view* v, const void* U, const void* V, int64_t r,
                                int64_t count, int64_t ldu, int64_t ldv,
                                int64_t strideU, int64_t strideV, void* stream);
+
+/* Device memory that the caller lends for lv_view_update_batch, so that
+ * the largest groups share each pass: lv_view_batch_bytes is its full size (0 if the
+ * workspace already holds it), of which a part serves for smaller groups.
+ * workspace: 256-byte aligned, borrowed until the next call (NULL: none) or
+ * lv_view_destroy; the stream of the last batch must have passed it by then.
+ * The results do not depend on it. */
+size_t lv_view_batch_bytes(const lv_view* v);
+lv_status lv_view_set_batch_workspace(lv_view* v, void* workspace, size_t ws_bytes);
 
 /* Pick the view's tile rows (the same at every level) by measurement:
  * for each allowed height 256, 384, ..., 1024 times `trial_updates` zero
@@ -241,6 +260,9 @@ lv_status lv_view_read_sum(const lv_view* v, int index, void* out, int64_t ldo, 
 #define LV_GENERAL_FACTORED 1
 size_t lv_view_footprint_general(int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy,
                                  int s);
+/* As lv_view_footprint_full. */
+size_t lv_view_footprint_general_full(int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy,
+                                      int s);
 lv_status lv_view_create_general(const void* A, int64_t n, int64_t lda, int k, int r_max,
                                  lv_mode mode, const void* T0, int64_t ldt, const void* B,
                                  int64_t ldb, int64_t p, int strategy, int s, void* workspace,
@@ -330,7 +352,7 @@ lv_status lv_view_timing(lv_view* v, lv_timing* out);
  * tail, so it fixes the summation order of the update.  Default 512, which
  * stands for at most 512 rows: a matrix too small to fill the device with
  * 512-row tiles is cut finer (by its order, element type and the update's
- * rank alone).  Other heights are taken as they are; LV_TILE_ROWS_512 is 512
+ * rank; LV_FP64: as far as the workspace holds the partial sums).  Other heights are taken as they are; LV_TILE_ROWS_512 is 512
  * rows as they are.  lv_batch_create sets heights by autotuning.  Allowed
  * values: multiples of 64 in [256, 1024], and LV_TILE_ROWS_512.  Two views
  * with equal tiles, inputs and updates hold equal values bit for bit

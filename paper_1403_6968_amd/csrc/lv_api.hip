@@ -250,18 +250,18 @@ lv_status timed(lv_view* v, int kind, hipStream_t s, const char* what, F&& launc
 // 0 has Q_0 = 0 and S_0 = I: only the tail runs.  (X_s = P_j Q_j came from
 // the powers' pass or from its own read-only pass before it.)
 template <typename T>
-lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStream_t s) {
+lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, const LevelMem& mem, hipStream_t s) {
   const Layout& L = v->L;
   lv_status st = LV_OK;
   if (j > 0 && sums_fused(R, (int)sizeof(T))) {
     // one pass over S_j: Y = S_j^T V_j (old S_j), S_j += Q_j W_j^T
     st = timed(v, 0, s, "sums: pass", [&] {
       return launch_sums_fused<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(), v->slabW<T>(), sV,
-                                  L.W, v->partYs<T>(j), s);
+                                  L.W, as<T>(mem.ys), s);
     });
     if (st == LV_OK && !L.general)   // general-form views formed it with their own products
       st = timed(v, 0, s, "sums: gram", [&] {
-        return launch_gram_cols<T>(R, sV + (L.W - R), v->slabQ<T>(), L.W, L.n_pad, v->partGs(j), s);
+        return launch_gram_cols<T>(R, sV + (L.W - R), v->slabQ<T>(), L.W, L.n_pad, as<double>(mem.gs), s);
       });
     if (st != LV_OK) return st;
   } else if (j > 0) {
@@ -269,13 +269,13 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
       if (skinny_on_mfma(R, (int)sizeof(T)))
         return launch_skinny_f32(R, reinterpret_cast<const float*>(v->S<T>(j)), L.ldp, L.n_pad, v->rows(j, R),
                                  v->slabQ<float>(), reinterpret_cast<const float*>(sV), L.W,
-                                 reinterpret_cast<float*>(v->partX<T>(j)), v->partYs<float>(j), s, kWantY);
+                                 as<float>(mem.x), as<float>(mem.ys), s, kWantY);
       return launch_level_readonly<T>(R, v->S<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(),
-                                      sV + (L.W - R), L.W, v->partX<T>(j), v->partYs<T>(j), s);
+                                      sV + (L.W - R), L.W, as<T>(mem.x), as<T>(mem.ys), s);
     });
     if (st == LV_OK && !L.general)   // general-form views formed it with their own products
       st = timed(v, 0, s, "sums: gram", [&] {
-        return launch_gram_cols<T>(R, sV + (L.W - R), v->slabQ<T>(), L.W, L.n_pad, v->partGs(j), s);
+        return launch_gram_cols<T>(R, sV + (L.W - R), v->slabQ<T>(), L.W, L.n_pad, as<double>(mem.gs), s);
       });
     if (st == LV_OK)
       st = timed(v, 0, s, "sums: update", [&] {
@@ -284,7 +284,7 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
     if (st != LV_OK) return st;
   }
   return timed(v, 1, s, "sums: tail", [&] {
-    return launch_sums_tail<T>(R, v->partXs<T>(j), v->partYs<T>(j), v->partGs(j), L.nct, v->nrt(j, R), L.n_pad,
+    return launch_sums_tail<T>(R, as<T>(mem.xs), as<T>(mem.ys), as<double>(mem.gs), L.nct, v->nrt(j, R), L.n_pad,
                                v->slabQ<T>(), v->slabW<T>(), sU, sV, L.W, j == 0, s);
   });
 }
@@ -294,16 +294,16 @@ lv_status sums_level(lv_view* v, int j, int R, const T* sU, const T* sV, hipStre
 // rank 16 up on the matrix cores (X only), else the read-only vector pass
 // (its transposed product is discarded).
 template <typename T>
-lv_status general_pass(lv_view* v, int j, hipStream_t s) {
+lv_status general_pass(lv_view* v, int j, const LevelMem& mem, hipStream_t s) {
   const Layout& L = v->L;
   const T* Dj = v->D<T>(j & 1);
   return timed(v, 0, s, "general: P D", [&] {
     if (skinny_on_mfma(L.pp, (int)sizeof(T)))
-      return launch_skinny_f32(L.pp, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->rows(j, L.pp),
+      return launch_skinny_f32(L.pp, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->xrows(L.pp),
                                reinterpret_cast<const float*>(Dj), reinterpret_cast<const float*>(Dj), L.pp,
-                               v->partXT<float>(), v->partYT<float>(), s, kWantX);
-    return launch_level_readonly<T>(L.pp, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, L.pp), Dj, Dj, L.pp,
-                                    v->partXT<T>(), v->partYT<T>(), s);
+                               as<float>(mem.xt), nullptr, s, kWantX);
+    return launch_level_readonly<T>(L.pp, v->P<T>(j), L.ldp, L.n_pad, v->xrows(L.pp), Dj, Dj, L.pp, as<T>(mem.xt),
+                                    nullptr, s);
   });
 }
 
@@ -313,7 +313,7 @@ lv_status general_pass(lv_view* v, int j, hipStream_t s) {
 // W_0 = 0), D_{2^(j+1)} = X + U_j a + Q_j b, T_{2^(j+1)} += D.  With
 // j < 0 the first step: D_1 = U (V^T T_0), T_1 += D_1.
 template <typename T>
-lv_status general_tail(lv_view* v, int j, int R, const T* sU, const T* sV, hipStream_t s) {
+lv_status general_tail(lv_view* v, int j, int R, const T* sU, const T* sV, const LevelMem& mem, hipStream_t s) {
   const Layout& L = v->L;
   const bool first = j < 0;
   const T* src = first ? v->T0<T>() : v->Tg<T>(j);
@@ -322,12 +322,12 @@ lv_status general_tail(lv_view* v, int j, int R, const T* sU, const T* sV, hipSt
   jobs.add(R, L.pp, Vj, L.W, src, L.pp, v->atbA());
   if (j > 0) {
     jobs.add(R, L.pp, v->slabW<T>() + (L.W - R), L.W, v->Bg<T>(), L.pp, v->atbB());
-    jobs.add(R, R, v->slabQ<T>(), L.W, Vj, L.W, v->partGs(j));   // the sums' Gram Q_j^T V_j
+    jobs.add(R, R, v->slabQ<T>(), L.W, Vj, L.W, as<double>(mem.gs));   // the sums' Gram Q_j^T V_j
   }
   const lv_status st = timed(v, 0, s, "general: V^T T, W^T B, Q^T V", [&] { return launch_atb_jobs<T>(jobs, L.n_pad, s); });
   if (st != LV_OK) return st;
   return timed(v, 1, s, "general: tail", [&] {
-    return launch_general_tail<T>(v->partXT<T>(), first ? 0 : L.nct, sU, j > 0 ? v->slabQ<T>() : nullptr, L.W, R,
+    return launch_general_tail<T>(as<T>(mem.xt), first ? 0 : L.nct, sU, j > 0 ? v->slabQ<T>() : nullptr, L.W, R,
                                   v->atbA(), v->atbB(), v->D<T>((j + 1) & 1), v->Tg<T>(j + 1), L.n_pad, L.pp, s);
   });
 }
@@ -359,18 +359,17 @@ lv_status gfac_first(lv_view* v, int ru, const T* sV, hipStream_t s) {
 // Level j, before the powers' update: X = P_j Y_j with the OLD P_j (the
 // float matrix cores from width 16, X only; else the read-only vector pass).
 template <typename T>
-lv_status gfac_pass(lv_view* v, int j, int ru, const T* sU, hipStream_t s) {
+lv_status gfac_pass(lv_view* v, int j, int ru, const T* sU, const LevelMem& mem, hipStream_t s) {
   const Layout& L = v->L;
   const T* Yj = j == 0 ? sU : v->Yf<T>(j);
   const int sy = j == 0 ? L.W : L.WY[j];
   const int R = gW(ru, j);
   return timed(v, 0, s, "general: P Y", [&] {
     if (skinny_on_mfma(R, (int)sizeof(T)))
-      return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->rows(j, R),
+      return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->xrows(R),
                                reinterpret_cast<const float*>(Yj), reinterpret_cast<const float*>(Yj), sy,
-                               v->partXT<float>(), v->partYT<float>(), s, kWantX);
-    return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), Yj, Yj, sy, v->partXT<T>(),
-                                    v->partYT<T>(), s);
+                               as<float>(mem.xt), nullptr, s, kWantX);
+    return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->xrows(R), Yj, Yj, sy, as<T>(mem.xt), nullptr, s);
   });
 }
 
@@ -378,7 +377,7 @@ lv_status gfac_pass(lv_view* v, int j, int ru, const T* sU, hipStream_t s) {
 // tail (Q_j intact): G = V_j^T Y_j, a = V_j^T T_j (old T_j), b = W_j^T B
 // (j > 0), then Y_{j+1} = [U_j, X + U_j G, Q_j] and Z_{j+1}^T = [a; Z_j^T; b].
 template <typename T>
-lv_status gfac_tail(lv_view* v, int j, int R, int ru, const T* sU, const T* sV, hipStream_t s) {
+lv_status gfac_tail(lv_view* v, int j, int R, int ru, const T* sU, const T* sV, const LevelMem& mem, hipStream_t s) {
   const Layout& L = v->L;
   const T* Yj = j == 0 ? sU : v->Yf<T>(j);
   const int sy = j == 0 ? L.W : L.WY[j];
@@ -389,13 +388,13 @@ lv_status gfac_tail(lv_view* v, int j, int R, int ru, const T* sU, const T* sV, 
   jobs.add(R, L.pp, Vj, L.W, v->Tg<T>(j), L.pp, v->atbA());
   if (j > 0) {
     jobs.add(R, L.pp, v->slabW<T>() + (L.W - R), L.W, v->Bg<T>(), L.pp, v->atbB());
-    jobs.add(R, R, v->slabQ<T>(), L.W, Vj, L.W, v->partGs(j));   // the sums' Gram Q_j^T V_j
+    jobs.add(R, R, v->slabQ<T>(), L.W, Vj, L.W, as<double>(mem.gs));   // the sums' Gram Q_j^T V_j
   }
   lv_status st = timed(v, 0, s, "general: V^T [Y, T], W^T B, Q^T V", [&] { return launch_atb_jobs<T>(jobs, L.n_pad, s); });
   if (st == LV_OK)
     st = timed(v, 1, s, "general: Y", [&] {
       // X = P_j Y_j: at level 0 (Y_0 = U_0) the partials of the powers' pass
-      return launch_gfac_y<T>(j == 0 ? v->partX<T>(0) : v->partXT<T>(), L.nct, wj, sU, j > 0 ? v->slabQ<T>() : nullptr,
+      return launch_gfac_y<T>(j == 0 ? as<T>(mem.x) : as<T>(mem.xt), L.nct, wj, sU, j > 0 ? v->slabQ<T>() : nullptr,
                               L.W, R, v->atbG(), wj, gw(ru, j), v->Yf<T>(j + 1), L.WY[j + 1], L.n_pad, s);
     });
   if (st == LV_OK)
@@ -414,6 +413,7 @@ lv_status gfac_tail(lv_view* v, int j, int R, int ru, const T* sU, const T* sV, 
 template <typename T>
 lv_status gfac_skip(lv_view* v, int ru, const T* sU, const T* sV, hipStream_t s) {
   const Layout& L = v->L;
+  char* const xt = v->base + L.work;   // the levels are done
   const int Rm = ru << L.m;
   const T* Vm = sV + (L.W - Rm);
   lv_status st = LV_OK;
@@ -429,12 +429,10 @@ lv_status gfac_skip(lv_view* v, int ru, const T* sU, const T* sV, hipStream_t s)
     const T* Tp = q > 1 ? v->Tskp<T>(q - 1) : v->Tg<T>(L.m);
     st = timed(v, 0, s, "general: P_s Y", [&] {
       if (skinny_on_mfma(wp, (int)sizeof(T)))
-        return launch_skinny_f32(wp, reinterpret_cast<const float*>(v->P<T>(L.m)), L.ldp, L.n_pad, kTileRows,
+        return launch_skinny_f32(wp, reinterpret_cast<const float*>(v->P<T>(L.m)), L.ldp, L.n_pad, v->xrows(wp),
                                  reinterpret_cast<const float*>(Yp), reinterpret_cast<const float*>(Yp), sp,
-                                 v->partXT<float>(), v->partYT<float>(), s, kWantX);
-      return launch_level_readonly<T>(wp, v->P<T>(L.m), L.ldp, L.n_pad,
-                                      v->default_rows(wp), Yp, Yp, sp, v->partXT<T>(),
-                                      v->partYT<T>(), s);
+                                 as<float>(xt), nullptr, s, kWantX);
+      return launch_level_readonly<T>(wp, v->P<T>(L.m), L.ldp, L.n_pad, v->xrows(wp), Yp, Yp, sp, as<T>(xt), nullptr, s);
     });
     AtbJobs<T> jobs;
     jobs.add(Rm, wp, Vm, L.W, Yp, sp, v->atbG());
@@ -443,7 +441,7 @@ lv_status gfac_skip(lv_view* v, int ru, const T* sU, const T* sV, hipStream_t s)
       st = timed(v, 0, s, "general: V_s^T [Y, T]", [&] { return launch_atb_jobs<T>(jobs, L.n_pad, s); });
     if (st == LV_OK)
       st = timed(v, 1, s, "general: Y (skip)", [&] {
-        return launch_gfac_y<T>(v->partXT<T>(), L.nct, wp, sU, L.m > 0 ? v->slabQ<T>() : nullptr, L.W, Rm,
+        return launch_gfac_y<T>(as<T>(xt), L.nct, wp, sU, L.m > 0 ? v->slabQ<T>() : nullptr, L.W, Rm,
                                 v->atbG(), wp, gwsk(L, ru, q - 1), v->Yskp<T>(q), L.WYsk(q), L.n_pad, s);
       });
     if (st == LV_OK)
@@ -477,21 +475,21 @@ lv_status gfac_finish(lv_view* v, int ru, const T* sU, hipStream_t s) {
 
 // Level j of nver (2 or 4) successive updates of a batch in the bfloat16-shadow
 // mode (factors in successive slots): one pass, then Gram and tail of all.
-lv_status shadow_chain_step(lv_view* v, int j, int r_pad, float* sU, float* sV, hipStream_t s, int nver) {
+lv_status shadow_chain_step(lv_view* v, int j, int r_pad, float* sU, float* sV, const LevelMem& mem, hipStream_t s,
+                            int nver) {
   const Layout& L = v->L;
   const int R = r_pad << j;
-  const auto a = v->chain16(r_pad, j);
-  float *px = reinterpret_cast<float*>(a.px), *py = reinterpret_cast<float*>(a.py);
-  double* pg = reinterpret_cast<double*>(a.pg);
+  float *px = as<float>(mem.x), *py = as<float>(mem.y);
+  double* pg = as<double>(mem.g);
   lv_status st = timed(v, 0, s, "level pass", [&] {
     return launch_shadow_chain(R, {v->P<float>(j), v->shadow(j), L.ldp, (int)L.n_pad, v->rows(j, R), sU, sV + (L.W - R),
-                                   L.W, reinterpret_cast<uint16_t*>(a.f16), a.f32, px, py, a.vs}, nver, s);
+                                   L.W, as<uint16_t>(mem.f16), mem.f32, px, py, mem.vs}, nver, s);
   });
   if (st == LV_OK)
-    st = timed(v, 0, s, "gram", [&] { return launch_level_gram<float>(R, sU, sV, L.W, L.n_pad, pg, s, nver, a.vs); });
+    st = timed(v, 0, s, "gram", [&] { return launch_level_gram<float>(R, sU, sV, L.W, L.n_pad, pg, s, nver, mem.vs); });
   if (st == LV_OK)
     st = timed(v, 1, s, "level tail", [&] {
-      return launch_level_tail<float>(R, px, py, pg, L.nct, v->nrt(j, R), 1, L.n_pad, sU, sV, L.W, s, nver, a.vs);
+      return launch_level_tail<float>(R, px, py, pg, L.nct, v->nrt(j, R), 1, L.n_pad, sU, sV, L.W, s, nver, mem.vs);
     });
   return st;
 }
@@ -501,18 +499,20 @@ lv_status shadow_chain_step(lv_view* v, int j, int r_pad, float* sU, float* sV, 
 // for float storage at large level rank and with bfloat16 shadows, the
 // read-only skinny pass, the Gram and the update pass), then the sums' and
 // the general form's level steps.  Stream-ordered on s.
-// nver > 1 (pipelined batches, vector levels): nver successive updates, whose
-// slabs follow sU, sV at the slots' stride, in one pass and one tail.
+// mem: the level's working storage.  nver > 1 (pipelined batches): nver
+// successive updates, whose slabs follow sU, sV at the slots' stride, in one
+// pass and one tail.
 template <typename T>
-lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, bool pipelined = false, int nver = 1) {
+lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, const LevelMem& mem, hipStream_t s,
+                     bool pipelined = false, int nver = 1) {
   const Layout& L = v->L;
   lv_status st = LV_OK;
   const int R = r_pad << j;
   if constexpr (sizeof(T) == 4)
-    if (nver > 1 && v->shadowed()) return shadow_chain_step(v, j, r_pad, sU, sV, s, nver);
+    if (nver > 1 && v->shadowed()) return shadow_chain_step(v, j, r_pad, sU, sV, mem, s, nver);
   const int nrt = v->nrt(j, R);
-  const Strides vs = {(int64_t)(L.slot_stride / sizeof(T)), (int64_t)L.nct * L.n_pad * R, (int64_t)nrt * L.n_pad * R,
-                      (int64_t)nrt * R * R};
+  T *px = as<T>(mem.x), *py = as<T>(mem.y);
+  double* pg = as<double>(mem.g);
   // The general form's product with the OLD P_j: P_j D_j (hybrid) or P_j Y_j
   // (factored; at level 0 Y_0 = U_0, so the powers' own X serves).  It
   // rides on the powers' fused pass when the X width allows, like P_j Q_j
@@ -523,18 +523,18 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
   const int xd = !gen_op ? 0 : L.gfac ? gW(r_pad, j) : L.pp;
   const bool d_in_pass = gen_op && vec_level && fused_extra_fits(R, q_in_pass, xd);
   if (gen_op && !d_in_pass) {
-    st = L.gfac ? gfac_pass<T>(v, j, r_pad, sU, s) : general_pass<T>(v, j, s);
+    st = L.gfac ? gfac_pass<T>(v, j, r_pad, sU, mem, s) : general_pass<T>(v, j, mem, s);
     if (st != LV_OK) return st;
   }
   if (L.sums && j > 0 && !q_in_pass) {
     // sums: X_s = P_j Q_j with the OLD P_j, before this level's update
     st = timed(v, 0, s, "sums: P Q", [&] {
       if (skinny_on_mfma(R, (int)sizeof(T)))
-        return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->rows(j, R),
-                                 v->slabQ<float>(), reinterpret_cast<const float*>(sV), L.W, v->partXs<float>(j),
-                                 v->partYs<float>(j), s, kWantX);
-      return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), v->slabQ<T>(),
-                                      sV + (L.W - R), L.W, v->partXs<T>(j), v->partYs<T>(j), s);
+        return launch_skinny_f32(R, reinterpret_cast<const float*>(v->P<T>(j)), L.ldp, L.n_pad, v->xrows(R),
+                                 v->slabQ<float>(), reinterpret_cast<const float*>(sV), L.W, as<float>(mem.xs), nullptr,
+                                 s, kWantX);
+      return launch_level_readonly<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->xrows(R), v->slabQ<T>(), sV + (L.W - R), L.W,
+                                      as<T>(mem.xs), nullptr, s);
     });
     if (st != LV_OK) return st;
   }
@@ -548,24 +548,23 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
       // at R = 16 the skinny pass applies the update itself (one read of
       // P_j), else the update pass follows
       const bool fused_upd = !v->shadowed() && skinny_fuses_update(R);
-      const int slot = (int)((reinterpret_cast<char*>(sU) - v->base - L.slabU) / L.slot_stride);
       if (v->wide16(R))
         st = timed(v, 0, s, "bf16 factors", [&] {
-          return launch_fac16(v->fac16(R, j == 0 || R / 2 < kWide16Rank, slot), s);
+          return launch_fac16(v->fac16(R, j == 0 || R / 2 < kWide16Rank, sU, mem.ut), s);
         });
       if (st == LV_OK) st = timed(v, 0, s, "skinny", [&] {
         if (v->wide16(R))
-          return launch_skinny_wide(v->shadow(j), L.ldp, L.n_pad, v->Ut16(slot), v->Vt16(slot) + (int64_t)(L.W - R) * L.n_pad, R, v->partX<float>(j),
-                                    v->partY<float>(j), s);
+          return launch_skinny_wide(v->shadow(j), L.ldp, L.n_pad, mem.ut, mem.vt + (int64_t)(L.W - R) * L.n_pad, R, px, py,
+                                    s);
         return v->shadowed() ? launch_skinny_bf16(R, v->shadow(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W,
-                                                  v->partX<float>(j), v->partY<float>(j), s)
+                                                  px, py, s)
                              : launch_skinny_f32(R, v->P<float>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W,
-                                                 v->partX<float>(j), v->partY<float>(j), s, kWantX | kWantY,
+                                                 px, py, s, kWantX | kWantY,
                                                  fused_upd);
       });
       if (st == LV_OK)
         st = timed(v, 0, s, "gram", [&] {
-          return launch_level_gram<float>(R, sU, sV, L.W, L.n_pad, v->partG(j), s);
+          return launch_level_gram<float>(R, sU, sV, L.W, L.n_pad, pg, s);
         });
       if (st == LV_OK && !fused_upd)
         st = timed(v, 0, s, "update", [&] {
@@ -574,9 +573,9 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
         });
       if (st == LV_OK)
         st = timed(v, 1, s, "level tail", [&] {
-          const int px = v->wide16(R) ? wide_splits(L.n_pad) : L.nct;
-          const int py = v->wide16(R) ? wide_splits(L.n_pad) : nrt;
-          return launch_level_tail<float>(R, v->partX<float>(j), v->partY<float>(j), v->partG(j), px, py, 1,
+          const int nx = v->wide16(R) ? wide_splits(L.n_pad) : L.nct;
+          const int ny = v->wide16(R) ? wide_splits(L.n_pad) : nrt;
+          return launch_level_tail<float>(R, px, py, pg, nx, ny, 1,
                                            L.n_pad, sU, sV, L.W, s);
         });
     }
@@ -586,23 +585,23 @@ lv_status level_step(lv_view* v, int j, int r_pad, T* sU, T* sV, hipStream_t s, 
       if (q_in_pass || d_in_pass) {
         const T* Dop = !d_in_pass ? nullptr : L.gfac ? v->Yf<T>(j) : v->D<T>(j & 1);
         const int ldd = L.gfac ? L.WY[j] : L.pp;
-        return launch_level_fused_x<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W, v->partX<T>(j),
-                                       v->partY<T>(j), v->partG(j), q_in_pass ? v->slabQ<T>() : nullptr,
-                                       v->partXs<T>(j), Dop, ldd, d_in_pass ? xd : 0, v->partXT<T>(), s);
+        return launch_level_fused_x<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W, px,
+                                       py, pg, q_in_pass ? v->slabQ<T>() : nullptr,
+                                       as<T>(mem.xs), Dop, ldd, d_in_pass ? xd : 0, as<T>(mem.xt), s);
       }
-      return launch_level_fused<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W, v->partX<T>(j),
-                                   v->partY<T>(j), v->partG(j), s, pipelined ? pipe_slice_groups(L.nct, nrt) : 0, nver,
-                                   vs);
+      return launch_level_fused<T>(R, v->P<T>(j), L.ldp, L.n_pad, v->rows(j, R), sU, sV, L.W, px,
+                                   py, pg, s, pipelined ? pipe_slice_groups(L.nct, nrt) : 0, nver,
+                                   mem.vs);
     });
     if (st == LV_OK)
       st = timed(v, 1, s, "level tail", [&] {
-        return launch_level_tail<T>(R, v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, nrt,
-                                    gram_in_pass(R, (int)sizeof(T)) ? nrt : 1, L.n_pad, sU, sV, L.W, s, nver, vs);
+        return launch_level_tail<T>(R, px, py, pg, L.nct, nrt,
+                                    gram_in_pass(R, (int)sizeof(T)) ? nrt : 1, L.n_pad, sU, sV, L.W, s, nver, mem.vs);
       });
   }
   if (st == LV_OK && L.general)
-    st = L.gfac ? gfac_tail<T>(v, j, R, r_pad, sU, sV, s) : general_tail<T>(v, j, R, sU, sV, s);
-  if (st == LV_OK && L.sums) st = sums_level<T>(v, j, R, sU, sV, s);
+    st = L.gfac ? gfac_tail<T>(v, j, R, r_pad, sU, sV, mem, s) : general_tail<T>(v, j, R, sU, sV, mem, s);
+  if (st == LV_OK && L.sums) st = sums_level<T>(v, j, R, sU, sV, mem, s);
   return st;
 }
 
@@ -628,8 +627,9 @@ lv_status update_one(lv_view* v, const T* U, const T* V, int r, int64_t ldu, int
   T* sV = v->slabV<T>();
   lv_status st = hip_check(launch_prep<T>(U, ldu, V, ldv, v->n, r, r_pad, sU, sV, L.W, L.n_pad, s), "prep");
   if (st == LV_OK && L.general)
-    st = L.gfac ? gfac_first<T>(v, r_pad, sV, s) : general_tail<T>(v, -1, r_pad, sU, sV, s);
-  for (int j = 0; j < L.m && st == LV_OK; ++j) st = level_step<T>(v, j, r_pad, sU, sV, s);
+    st = L.gfac ? gfac_first<T>(v, r_pad, sV, s) : general_tail<T>(v, -1, r_pad, sU, sV, {}, s);
+  for (int j = 0; j < L.m && st == LV_OK; ++j)
+    st = level_step<T>(v, j, r_pad, sU, sV, v->level_mem(r_pad << j, v->nrt(j, r_pad << j)), s);
   if (st == LV_OK && L.nsk > 0) st = gfac_skip<T>(v, r_pad, sU, sV, s);
   if (st == LV_OK) st = top_step<T>(v, r_pad, sU, sV, s);
   if (st == LV_OK && L.sums && L.m > 0)
@@ -647,34 +647,52 @@ lv_status update_one(lv_view* v, const T* U, const T* V, int r, int64_t ldu, int
 // (contiguous level ranges, at most kPipeStreams), each on a stream of its
 // own (stage 0 on the caller's stream), and successive updates flow through
 // them: while a stage works on update t the earlier stages already work on
-// t+1, t+2, ...  Each update in flight holds one of pipe_slots factor-slab
-// pairs; a slab is reused only after the top level of the update that held
-// it has finished.
+// t+1, t+2, ...  Each update in flight holds one factor-slab pair of the
+// batch's plan (lv_view::plan_batch); a slab is reused only after the top level
+// of the update that held it has finished.
 //
 // Level j of an update reads P_j and that update's factors only, and level
 // j - 1 does not wait for it: a level can take several updates in turn before
-// the next level sees the first.  Updates therefore go through in chunks of
-// chunk(r_pad), and a vector level's pass takes chain_updates(R) of a chunk at
-// one read and write of P_j (fused_body), the top update the whole chunk.
+// the next level sees the first.  Updates therefore go through in chunks, and
+// a level's pass takes several of a chunk at one read and write of P_j
+// (fused_body, k_shadow_chain), the top update the whole chunk.
 // Every sum and rounding is that of the sequential order, so the results
 // are bit-identical to it.
 inline int pipe_stage(const lv_view* v, int j) { return j * v->pipe_nstages / v->L.m; }
 
-lv_status pipe_setup(lv_view* v) {
+// Stage streams and events, and the events of `slots` slots.
+lv_status pipe_setup(lv_view* v, int slots) {
+  auto mk = [](hipEvent_t* e) { return *e != nullptr || hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess; };
+  for (; v->pipe_events < slots; ++v->pipe_events) {
+    const int sl = v->pipe_events;
+    bool ok = mk(&v->pfree[sl]);
+    for (int j = 0; j + 1 < v->L.m && ok; ++j) ok = mk(&v->pready[j][sl]);
+    if (!ok) return fail(LV_EDEVICE, "hipEventCreateWithFlags failed");
+  }
   if (v->pipe_nstages > 0) return LV_OK;
   const int ns = v->L.m < kPipeStreams ? v->L.m : kPipeStreams;
   for (int q = 1; q < ns; ++q)
     if (hipStreamCreateWithFlags(&v->pstream[q], hipStreamNonBlocking) != hipSuccess)
       return fail(LV_EDEVICE, "hipStreamCreateWithFlags failed");
-  auto mk = [](hipEvent_t* e) { return hipEventCreateWithFlags(e, hipEventDisableTiming) == hipSuccess; };
   bool ok = mk(&v->pfork);
   for (int q = 0; q < ns && ok; ++q) ok = mk(&v->pjoin[q]);
-  for (int sl = 0; sl < v->L.pipe_slots && ok; ++sl) {
-    ok = mk(&v->pfree[sl]);
-    for (int j = 0; j + 1 < v->L.m && ok; ++j) ok = mk(&v->pready[j][sl]);
-  }
   if (!ok) return fail(LV_EDEVICE, "hipEventCreateWithFlags failed");
   v->pipe_nstages = ns;
+  return LV_OK;
+}
+
+// The updates of a batch one after the other.
+template <typename T>
+lv_status update_batch_sequential(lv_view* v, const char* U, const char* V, int r, int64_t count, int64_t ldu,
+                                  int64_t ldv, int64_t strideU, int64_t strideV, hipStream_t s) {
+  for (int64_t t = 0; t < count; ++t) {
+    lv_status st = update_one<T>(v, reinterpret_cast<const T*>(U) + t * strideU, reinterpret_cast<const T*>(V) + t * strideV,
+                                 r, ldu, ldv, s);
+    if (st != LV_OK) return st;
+    v->updates += 1;
+    st = periodic_drift(v, s);
+    if (st != LV_OK) return st;
+  }
   return LV_OK;
 }
 
@@ -699,19 +717,17 @@ template <typename T>
 lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r, int64_t count, int64_t ldu,
                                  int64_t ldv, int64_t strideU, int64_t strideV, hipStream_t s) {
   const Layout& L = v->L;
-  lv_status st = pipe_setup(v);
-  if (st != LV_OK) return st;
-  st = pipe_fork(v, s);
-  if (st != LV_OK) return st;
   const int r_pad = (int)next_pow2(r);
   const int Rm = r_pad << L.m;
-  // the slots hold D chunks of C updates; one update in flight per stage is
-  // enough where each has passes of its own (more only widen the working set:
-  // rank-4 shadow batches n = 8192 23.46 ms with 5, 23.74 ms with 12)
-  const int C = v->chunk(r_pad);
-  const int D = C > 1 ? std::min(L.pipe_slots / C, v->shadowed() ? kPipeChunks : L.pipe_slots)
-                      : std::min(L.pipe_slots, std::min(L.m + 1, 5));
+  const BatchPlan plan = v->plan_batch(r_pad);
+  const int C = plan.C, D = plan.D;
+  if (C == 0) return update_batch_sequential<T>(v, U, V, r, count, ldu, ldv, strideU, strideV, s);
+  lv_status st = pipe_setup(v, C * D);
+  if (st == LV_OK) st = pipe_fork(v, s);
+  if (st != LV_OK) return st;
   const int64_t sstride = (int64_t)(L.slot_stride / sizeof(T));
+  auto slabU = [&](int slot) { return as<T>(plan.slabs + (size_t)slot * L.slot_stride); };
+  auto slabV = [&](int slot) { return slabU(slot) + L.n_pad * L.W; };
   auto stream_of = [&](int j) { const int q = pipe_stage(v, j); return q == 0 ? s : v->pstream[q]; };
   auto ev = [&](hipError_t e, const char* what) { return e == hipSuccess ? LV_OK : fail(LV_EDEVICE, "%s failed", what); };
   int64_t chunk = 0;
@@ -726,7 +742,7 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
     // the slots are free once the top level of chunk - D is done with them
     if (chunk >= D) st = ev(hipStreamWaitEvent(s, v->pfree[slot], 0), "hipStreamWaitEvent");
     if (st == LV_OK)
-      st = hip_check(launch_prep<T>(Ut, ldu, Vt, ldv, v->n, r, r_pad, v->slabU<T>(slot), v->slabV<T>(slot), L.W, L.n_pad,
+      st = hip_check(launch_prep<T>(Ut, ldu, Vt, ldv, v->n, r, r_pad, slabU(slot), slabV(slot), L.W, L.n_pad,
                                     s, cnt, strideU, strideV, sstride),
                      "prep");
     for (int j = 0; j < L.m && st == LV_OK; ++j) {
@@ -736,16 +752,19 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
       const int R = r_pad << j;
       // groups of the chunk's updates that share the level's pass: halving
       // with the level's rank, so each lies inside one of the level below
-      const int most = v->shadowed() ? (v->chain16(r_pad, j).at ? chain16_updates(R) : 1)
-                       : fused_vector_level(R, (int)sizeof(T), false) ? chain_updates(R) : 1;
+      const int most = plan.most[j];
+      LevelMem mem = plan.lev[j];
       for (int a = 0, g = 0; a < cnt && st == LV_OK; a += g) {
         for (g = most; g > cnt - a; g /= 2) {}
         const int last = slot + a + g - 1;
         // the event of the lower level's group that holds the last update
         // is recorded on its own last slot
         if (waits) st = ev(hipStreamWaitEvent(sj, v->pready[j - 1][v->pgroup[j - 1][last]], 0), "hipStreamWaitEvent");
-        if (st == LV_OK)
-          st = level_step<T>(v, j, r_pad, v->slabU<T>(slot + a), v->slabV<T>(slot + a), sj, true, g);
+        if (st == LV_OK) {
+          mem.ut = as<uint16_t>(plan.fac + (size_t)(slot + a) * v->fac_bytes());
+          mem.vt = mem.ut + (int64_t)L.W * L.n_pad;
+          st = level_step<T>(v, j, r_pad, slabU(slot + a), slabV(slot + a), mem, sj, true, g);
+        }
         for (int q = a; q < a + g; ++q) v->pgroup[j][slot + q] = last;
         if (st == LV_OK && tells) st = ev(hipEventRecord(v->pready[j][last], sj), "hipEventRecord");
       }
@@ -754,12 +773,12 @@ lv_status update_batch_pipelined(lv_view* v, const char* U, const char* V, int r
     if (cnt > 1 && Rm <= kMaxLevelRank) {
       // the chunk's top updates in one read and write of P_m
       if (st == LV_OK)
-        st = hip_check(launch_level_update_chain<T>(Rm, v->P<T>(L.m), L.ldp, L.n_pad, v->slabU<T>(slot),
-                                                    v->slabV<T>(slot), L.W, cnt, sstride, st_top, v->shadowed()),
+        st = hip_check(launch_level_update_chain<T>(Rm, v->P<T>(L.m), L.ldp, L.n_pad, slabU(slot),
+                                                    slabV(slot), L.W, cnt, sstride, st_top, v->shadowed()),
                        "top update");
     } else {
       for (int a = 0; a < cnt && st == LV_OK; ++a)
-        st = top_step<T>(v, r_pad, v->slabU<T>(slot + a), v->slabV<T>(slot + a), st_top);
+        st = top_step<T>(v, r_pad, slabU(slot + a), slabV(slot + a), st_top);
     }
     if (st == LV_OK) st = ev(hipEventRecord(v->pfree[slot], st_top), "hipEventRecord");
     if (st != LV_OK) break;
@@ -838,6 +857,15 @@ size_t lv_view_footprint(int64_t n, int k, int r_max, lv_mode mode) {
   return lv_view_footprint_ex(n, k, r_max, mode, 0);
 }
 
+size_t lv_view_footprint_full(int64_t n, int k, int r_max, lv_mode mode, int flags) {
+  lv_view v;
+  v.ws_bytes = lv_view_footprint_ex(n, k, r_max, mode, flags);
+  if (v.ws_bytes == 0) return 0;
+  v.mode = mode;
+  v.L = make_layout(n, k, r_max, mode, flags);
+  return v.set_cuts();
+}
+
 lv_status lv_view_create(const void* A, int64_t n, int64_t lda, int k, int r_max, lv_mode mode,
                          void* workspace, size_t ws_bytes, void* stream, lv_view** out) {
   return lv_view_create_ex(A, n, lda, k, r_max, mode, 0, workspace, ws_bytes, stream, out);
@@ -871,6 +899,7 @@ lv_status create_view(const void* A, int64_t n, int64_t lda, int k, int r_max, l
   v->base = static_cast<char*>(workspace); v->ws_bytes = ws_bytes;
   v->updates = 0; v->reanchors = 0;
   for (int& rows : v->tile_rows) rows = kTileRows;
+  v->set_cuts();
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (L.sums) {
     // the sum factor slabs start at zero: the W columns of level 0 are read as
@@ -964,6 +993,15 @@ size_t lv_view_footprint_general(int64_t n, int k, int r_max, lv_mode mode, int6
   return make_layout(n, sp, r_max, mode, LV_WITH_SUMS, (int)p, strategy == LV_GENERAL_FACTORED, k).total;
 }
 
+size_t lv_view_footprint_general_full(int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy, int s) {
+  lv_view v;
+  v.ws_bytes = lv_view_footprint_general(n, k, r_max, mode, p, strategy, s);
+  if (v.ws_bytes == 0) return 0;
+  v.mode = mode;
+  v.L = make_layout(n, s == 0 ? k : s, r_max, mode, LV_WITH_SUMS, (int)p, strategy == LV_GENERAL_FACTORED, k);
+  return v.set_cuts();
+}
+
 lv_status lv_view_create_general(const void* A, int64_t n, int64_t lda, int k, int r_max, lv_mode mode,
                                  const void* T0, int64_t ldt, const void* B, int64_t ldb, int64_t p, int strategy,
                                  int s, void* workspace, size_t ws_bytes, void* stream, lv_view** out) {
@@ -1011,24 +1049,22 @@ lv_status lv_view_update_batch(lv_view* v, const void* U, const void* V, int64_t
   if (count > 1 && (strideU < v->n * ldu || strideV < v->n * ldv))
     return fail(LV_EINVAL, "strides smaller than one n x r factor");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (count > 1 && v->pipeline && !v->timing && v->L.pipe_slots > 1)
-    return v->mode == LV_FP64
-               ? update_batch_pipelined<double>(v, static_cast<const char*>(U), static_cast<const char*>(V), (int)r,
-                                                count, ldu, ldv, strideU, strideV, s)
-               : update_batch_pipelined<float>(v, static_cast<const char*>(U), static_cast<const char*>(V), (int)r,
-                                               count, ldu, ldv, strideU, strideV, s);
-  const size_t es = v->L.elem;
-  for (int64_t t = 0; t < count; ++t) {
-    const char* Ut = static_cast<const char*>(U) + (size_t)(t * strideU) * es;
-    const char* Vt = static_cast<const char*>(V) + (size_t)(t * strideV) * es;
-    st = v->mode == LV_FP64
-             ? update_one<double>(v, reinterpret_cast<const double*>(Ut), reinterpret_cast<const double*>(Vt), (int)r, ldu, ldv, s)
-             : update_one<float>(v, reinterpret_cast<const float*>(Ut), reinterpret_cast<const float*>(Vt), (int)r, ldu, ldv, s);
-    if (st != LV_OK) return st;
-    v->updates += 1;
-    st = periodic_drift(v, s);
-    if (st != LV_OK) return st;
-  }
+  const auto run = [&](auto zero) {
+    using T = decltype(zero);
+    return (count > 1 && v->pipeline && !v->timing && v->L.piped ? update_batch_pipelined<T> : update_batch_sequential<T>)(
+        v, static_cast<const char*>(U), static_cast<const char*>(V), (int)r, count, ldu, ldv, strideU, strideV, s);
+  };
+  return v->mode == LV_FP64 ? run(double(0)) : run(float(0));
+}
+
+size_t lv_view_batch_bytes(const lv_view* v) { return v ? v->lend_bytes() : 0; }
+
+lv_status lv_view_set_batch_workspace(lv_view* v, void* workspace, size_t ws_bytes) {
+  g_err[0] = 0;
+  if (!v) return fail(LV_EINVAL, "view is NULL");
+  if (reinterpret_cast<uintptr_t>(workspace) % kAlign) return fail(LV_ENOMEM, "workspace is not %zu-byte aligned", kAlign);
+  v->lent = static_cast<char*>(workspace);
+  v->lent_bytes = workspace ? ws_bytes : 0;
   return LV_OK;
 }
 
@@ -1217,19 +1253,13 @@ lv_status lv_view_autotune(lv_view* v, int pipelined, int64_t trial_updates, voi
   v->pipeline = pipelined != 0;
   const char* Z = v->base + v->L.zfac;
   const int r = v->L.r_pad;
-  auto run = [&](int64_t count) -> lv_status {
-    if (v->pipeline && v->L.pipe_slots > 1)
-      return v->mode == LV_FP64 ? update_batch_pipelined<double>(v, Z, Z, r, count, r, r, 0, 0, s)
-                                : update_batch_pipelined<float>(v, Z, Z, r, count, r, r, 0, 0, s);
-    for (int64_t t = 0; t < count; ++t) {
-      const lv_status st = v->mode == LV_FP64
-                               ? update_one<double>(v, reinterpret_cast<const double*>(Z),
-                                                    reinterpret_cast<const double*>(Z), r, r, r, s)
-                               : update_one<float>(v, reinterpret_cast<const float*>(Z),
-                                                   reinterpret_cast<const float*>(Z), r, r, r, s);
-      if (st != LV_OK) return st;
-    }
-    return LV_OK;
+  auto run = [&](int64_t count) {
+    const auto of = [&](auto zero) {
+      using T = decltype(zero);
+      return (v->pipeline && v->L.piped ? update_batch_pipelined<T> : update_batch_sequential<T>)(v, Z, Z, r, count, r, r, 0,
+                                                                                                 0, s);
+    };
+    return v->mode == LV_FP64 ? of(double(0)) : of(float(0));
   };
   lv_status st = LV_OK;
   float best = 0.0f;
@@ -1410,6 +1440,7 @@ lv_status lv_powers_update_noalloc(void* const* powers, int64_t n, int64_t ld, i
   v.n = n; v.k = k; v.r_max = (int)r; v.mode = mode; v.L = L; v.L.ldp = ld;
   v.base = base; v.ws_bytes = kNoAllocScratchBytes; v.updates = 0; v.reanchors = 0;
   for (int& rows : v.tile_rows) rows = kTileRows;
+  v.set_cuts();
   for (int j = 0; j <= m; ++j) v.pext[j] = static_cast<char*>(powers[j]);
   hipStream_t s = static_cast<hipStream_t>(stream);
   return mode == LV_FP64

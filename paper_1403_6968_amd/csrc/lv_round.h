@@ -139,6 +139,9 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
       const int R = L.r_pad << j;
       const int trows = j < L.m ? v->rows(j, R) : 0;
       const int nrt = j < L.m ? v->nrt(j, R) : 0;
+      const LevelMem mem = j < L.m ? v->level_mem(R, nrt) : LevelMem{};
+      T *px = as<T>(mem.x), *py = as<T>(mem.y);
+      double* pg = as<double>(mem.g);
       T* sU = v->slabU<T>();
       T* sV = v->slabV<T>();
       const T* Vj = sV + (L.W - R);
@@ -152,52 +155,51 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
       if constexpr (sizeof(T) == 4) {
         if (v->shadowed() || skinny_on_mfma(R, 4)) {
           if (v->wide16(R)) {
-            fac.push_back(v->fac16(R, j == 0 || R / 2 < kWide16Rank, 0));
+            fac.push_back(v->fac16(R, j == 0 || R / 2 < kWide16Rank, sU, mem.ut));
             const int per = wide_cols(R);
             for (int c0 = 0; c0 < R; c0 += per)
-              wide[per].push_back(wide_desc(v->shadow(j), L.ldp, L.n_pad, v->Ut16(0),
-                                            v->Vt16(0) + (int64_t)(L.W - R) * L.n_pad, R, c0, v->partX<float>(j),
-                                            v->partY<float>(j)));
+              wide[per].push_back(wide_desc(v->shadow(j), L.ldp, L.n_pad, mem.ut,
+                                            mem.vt + (int64_t)(L.W - R) * L.n_pad, R, c0, px, py));
           } else if (v->shadowed()) {
             const int per = R <= 64 ? R : 64;
             for (int c0 = 0; c0 < R; c0 += per)
               skinny[skinny_blocks_for(per)].push_back({v->shadow(j), L.ldp, (int)L.n_pad, trows, sU + c0, Vj + c0,
-                                                        L.W, per, v->partX<T>(j) + c0, v->partY<T>(j) + c0, R,
+                                                        L.W, per, px + c0, py + c0, R,
                                                         L.nct, 0});
           } else if (skinny_fuses_update(R)) {
             // the skinny pass applies the update too (class + 2: the fused kernels)
             skinny32[2 + skinny_f32_blocks(R)].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, trows, sU, Vj, L.W, R,
-                                                          v->partX<T>(j), v->partY<T>(j), R, L.nct, 0});
+                                                          px, py, R, L.nct, 0});
           } else {
             const int per = R <= 32 ? R : 32;
             for (int c0 = 0; c0 < R; c0 += per)
               skinny32[skinny_f32_blocks(per)].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, trows, sU + c0,
-                                                          Vj + c0, L.W, per, v->partX<T>(j) + c0,
-                                                          v->partY<T>(j) + c0, R, L.nct, 0});
+                                                          Vj + c0, L.W, per, px + c0,
+                                                          py + c0, R, L.nct, 0});
           }
-          gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), v->partG(j), gram_count(L.n_pad, R), 0});
-          gsum.push_back({v->partG(j), gram_count(L.n_pad, R), R * R, 0});
+          gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), pg, gram_count(L.n_pad, R), 0});
+          gsum.push_back({pg, gram_count(L.n_pad, R), R * R, 0});
           if (v->shadowed() || !skinny_fuses_update(R))
             (v->shadowed() ? updsh : upd)[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W,
                                                         upd_nct, 0, v->shadowed() ? v->shadow(j) : nullptr});
           const bool wd = v->wide16(R);
-          tail[R].push_back({v->partX<T>(j), v->partY<T>(j), v->partG(j), wd ? wide_splits(L.n_pad) : L.nct,
+          tail[R].push_back({px, py, pg, wd ? wide_splits(L.n_pad) : L.nct,
                              wd ? wide_splits(L.n_pad) : nrt, (int)L.n_pad, sU, sV, L.W, 0, 1});
           continue;
         }
       }
       if (R <= kMaxFusedRank) {
-        fused[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, trows, sU, Vj, L.W, v->partX<T>(j),
-                            v->partY<T>(j), v->partG(j), R, L.nct, 0});
+        fused[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, trows, sU, Vj, L.W, px,
+                            py, pg, R, L.nct, 0});
       } else {
         for (int c0 = 0; c0 < R; c0 += kMaxFusedRank)
           chunks.push_back({v->P<T>(j), L.ldp, (int)L.n_pad, trows, sU + c0, Vj + c0, L.W,
-                            v->partX<T>(j) + c0, v->partY<T>(j) + c0, nullptr, R, L.nct, 0});
-        gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), v->partG(j), gram_count(L.n_pad, R), 0});
-        gsum.push_back({v->partG(j), gram_count(L.n_pad, R), R * R, 0});
+                            px + c0, py + c0, nullptr, R, L.nct, 0});
+        gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), pg, gram_count(L.n_pad, R), 0});
+        gsum.push_back({pg, gram_count(L.n_pad, R), R * R, 0});
         upd[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W, upd_nct, 0});
       }
-      tail[R].push_back({v->partX<T>(j), v->partY<T>(j), v->partG(j), L.nct, nrt, (int)L.n_pad, sU, sV, L.W, 0,
+      tail[R].push_back({px, py, pg, L.nct, nrt, (int)L.n_pad, sU, sV, L.W, 0,
                          gram_in_pass(R, L.elem) ? nrt : 1});
     }
     for (auto& kv : fused) pl.add(kFused, kv.first, kv.second, &fused_blocks<T>);

@@ -52,6 +52,7 @@ EXPORTED = (
     "lv_server_poll", "lv_server_drain", "lv_server_stats", "lv_server_destroy",
     "lv_stream_probe", "lv_powers_update_noalloc", "lv_view_set_drift_check", "lv_server_set_admission_queue",
     "lv_tune_cache_save", "lv_tune_cache_load", "lv_tune_cache_clear",
+    "lv_view_footprint_full", "lv_view_footprint_general_full", "lv_view_batch_bytes", "lv_view_set_batch_workspace",
 )
 
 
@@ -175,6 +176,10 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         "lv_powers_update_noalloc": (I32, [c.POINTER(P), I64, I64, I32, I32, P, P, I64, I64, I64, P]),
         "lv_view_set_drift_check": (I32, [P, I64, c.c_double, P, P]),
         "lv_server_set_admission_queue": (I32, [P, I32]),
+        "lv_view_footprint_full": (SZ, [I64, I32, I32, I32, I32]),
+        "lv_view_footprint_general_full": (SZ, [I64, I32, I32, I32, I64, I32, I32]),
+        "lv_view_batch_bytes": (SZ, [P]),
+        "lv_view_set_batch_workspace": (I32, [P, P, SZ]),
         "lv_tune_cache_save": (I32, [c.c_char_p]),
         "lv_tune_cache_load": (I32, [c.c_char_p, c.POINTER(I32)]),
         "lv_tune_cache_clear": (None, []),
@@ -226,6 +231,10 @@ def lv_view_footprint(n: int, k: int, r_max: int, mode: int, flags: int = 0) -> 
     return int(load().lv_view_footprint_ex(n, k, r_max, mode, flags))
 
 
+def lv_view_footprint_full(n: int, k: int, r_max: int, mode: int, flags: int = 0) -> int:
+    return int(load().lv_view_footprint_full(n, k, r_max, mode, flags))
+
+
 def lv_view_create(A: torch.Tensor, k: int, r_max: int, mode: int, workspace: torch.Tensor,
                    stream=None, flags: int = 0) -> ctypes.c_void_p:
     lib = load()
@@ -244,6 +253,11 @@ def lv_view_create(A: torch.Tensor, k: int, r_max: int, mode: int, workspace: to
 def lv_view_footprint_general(n: int, k: int, r_max: int, mode: int, p: int,
                               strategy: int = LV_GENERAL_HYBRID, s: int = 0) -> int:
     return int(load().lv_view_footprint_general(n, k, r_max, mode, p, strategy, s))
+
+
+def lv_view_footprint_general_full(n: int, k: int, r_max: int, mode: int, p: int,
+                                   strategy: int = LV_GENERAL_HYBRID, s: int = 0) -> int:
+    return int(load().lv_view_footprint_general_full(n, k, r_max, mode, p, strategy, s))
 
 
 def lv_view_create_general(A: torch.Tensor, k: int, r_max: int, mode: int, T0: torch.Tensor,
@@ -295,6 +309,19 @@ def lv_view_update_batch(view, U: torch.Tensor, V: torch.Tensor, dtype, stream=N
     _check(load().lv_view_update_batch(view, U.data_ptr(), V.data_ptr(), U.shape[2], U.shape[0],
                                        ldu, ldv, U.stride(0), V.stride(0),
                                        _stream(stream, U.device)))
+
+
+def lv_view_batch_bytes(view) -> int:
+    return int(load().lv_view_batch_bytes(view))
+
+
+def lv_view_set_batch_workspace(view, workspace) -> None:
+    """workspace: a contiguous device tensor, kept by the caller, or None."""
+    if workspace is not None and (workspace.device.type != "cuda" or not workspace.is_contiguous()):
+        raise ValueError("workspace must be a contiguous device tensor")
+    _check(load().lv_view_set_batch_workspace(
+        view, None if workspace is None else workspace.data_ptr(),
+        0 if workspace is None else workspace.numel() * workspace.element_size()))
 
 
 def lv_view_read(view, power: int, out: torch.Tensor, dtype, stream=None) -> None:
@@ -475,10 +502,11 @@ class View:
         self.device = A.device
         self.flags = LV_WITH_SUMS if sums or general is not None else 0
         self.p = 0
+        self.batch_workspace = None   # lent on the first batch that needs it
         if general is not None:
             T0, B = general
             self.p = T0.shape[1]
-            nbytes = lv_view_footprint_general(self.n, k, r_max, mode, self.p, strategy, skip)
+            nbytes = lv_view_footprint_general_full(self.n, k, r_max, mode, self.p, strategy, skip)
             if nbytes == 0:
                 _check(load().lv_view_create_general(None, self.n, self.n, k, r_max, mode, None, self.p, None,
                                                      self.p, self.p, strategy, skip, None, 0, None,
@@ -486,7 +514,7 @@ class View:
             self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=A.device)
             self.handle = lv_view_create_general(A, k, r_max, mode, T0, B, self.workspace, stream, strategy, skip)
             return
-        nbytes = lv_view_footprint(self.n, k, r_max, mode, self.flags)
+        nbytes = lv_view_footprint_full(self.n, k, r_max, mode, self.flags)
         if nbytes == 0:
             # Reproduce the library's validation message.
             _check(load().lv_view_create_ex(None, self.n, self.n, k, r_max, mode, self.flags, None, 0, None,
@@ -498,7 +526,29 @@ class View:
         lv_view_update(self.handle, U, V, self.dtype, stream)
 
     def update_batch(self, U: torch.Tensor, V: torch.Tensor, stream=None) -> None:
+        if U.dim() == 3 and U.shape[0] > 1:
+            self._lend(stream)
         lv_view_update_batch(self.handle, U, V, self.dtype, stream)
+
+    def _lend(self, stream=None) -> None:
+        """Lend the view the memory that its workspace lacks for the largest
+        groups of a batch, allocated on the batch's stream; without it (device
+        memory full, a graph being captured) fewer updates share a pass."""
+        if self.batch_workspace is not None:
+            return
+        nbytes = lv_view_batch_bytes(self.handle)
+        if nbytes == 0:
+            return
+        if stream is not None and not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(_stream(stream, self.device), device=self.device)
+        try:
+            with torch.cuda.stream(stream):
+                if torch.cuda.is_current_stream_capturing():
+                    return
+                self.batch_workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:
+            return
+        lv_view_set_batch_workspace(self.handle, self.batch_workspace)
 
     def read(self, power: int | None = None, stream=None) -> torch.Tensor:
         power = self.kp if power is None else power
@@ -551,6 +601,8 @@ class View:
 
     def autotune(self, pipelined: bool = True, trial_updates: int = 24, stream=None) -> int:
         """Tile rows chosen by timing zero updates (the view is unchanged)."""
+        if pipelined:
+            self._lend(stream)
         return lv_view_autotune(self.handle, pipelined, trial_updates, stream, self.device)
 
     def timing(self) -> dict:

@@ -23,6 +23,18 @@ GLIN = [((2048, 1, 1, 0, 200, 0), 63340544), ((2048, 4, 1, 0, 200, 1), 84312064)
         ((1024, 1, 1, 1, 64, 2), 14983680), ((5000, 16, 1, 1, 16, 2), 337260544), ((700, 4, 2, 0, 7, 0), 5580288),
         ((500, 3, 4, 0, 1000, 2), 36802560), ((500, 9, 2, 1, 130, 1), 13678592), ((300, 2, 64, 0, 4096, 2), 148897792)]
 
+# (n, k, r_max, mode, flags) -> bytes
+VIEW = [((256, 16, 1, 0, 0), 3069440), ((512, 16, 1, 0, 0), 11565056), ((512, 2, 1, 0, 0), 4260608),
+        ((512, 4, 8, 0, 0), 7750144), ((1024, 8, 3, 0, 0), 38554112), ((8192, 16, 1, 0, 0), 2790086144),
+        ((512, 16, 1, 1, 0), 9940992), ((1024, 16, 1, 1, 0), 39001344), ((8192, 16, 1, 1, 0), 2453460480),
+        ((1, 256, 2, 1, 0), 12532992), ((7157, 16, 32, 2, 0), 3257770496), ((1500, 16, 4, 2, 0), 112586240),
+        ((300, 4, 8, 0, 1), 14389760), ((1024, 16, 3, 1, 1), 80933376), ((2000, 1, 5, 0, 0), 33997312)]
+# (n, k, r_max, mode, p, strategy, s) -> bytes
+GENERAL = [((300, 4, 8, 0, 7, 0, 0), 14963200), ((1024, 16, 3, 1, 7, 0, 0), 81818112),
+           ((1024, 2, 16, 0, 1, 1, 0), 49111552), ((4096, 16, 1, 1, 1000, 1, 0), 1494935040),
+           ((1024, 16, 1, 0, 64, 1, 4), 67992576), ((700, 16, 2, 2, 130, 1, 8), 55794176),
+           ((2500, 16, 1, 0, 33, 0, 0), 601020416)]
+
 
 @pytest.fixture(scope="module")
 def lib():
@@ -43,3 +55,21 @@ def test_chain(lib, args, most):
 @pytest.mark.parametrize("args,most", GLIN)
 def test_linear_general_form(lib, args, most):
     assert 0 < lib.lv_glin_footprint(*args) <= most
+
+
+@pytest.mark.parametrize("args,most", VIEW)
+def test_view(lib, args, most):
+    got = lib.lv_view_footprint_ex(*args)
+    assert 0 < got <= most
+    assert got <= lib.lv_view_footprint_full(*args) <= 1.25 * got
+    if args[3] != 0:   # the squaring scratch holds the finer cut
+        assert lib.lv_view_footprint_full(*args) == got
+
+
+@pytest.mark.parametrize("args,most", GENERAL)
+def test_general_form(lib, args, most):
+    got = lib.lv_view_footprint_general(*args)
+    assert 0 < got <= most
+    assert got <= lib.lv_view_footprint_general_full(*args) <= 1.25 * got
+    if args[3] != 0:
+        assert lib.lv_view_footprint_general_full(*args) == got
