@@ -58,7 +58,7 @@ __device__ __forceinline__ uint16_t bf16_rne(float x) { return __builtin_bit_cas
 // Columns covered by one tile of the level pass: a wave reads a 1 KiB row
 // segment with one 16-byte vector per lane.
 template <typename T> constexpr int tile_cols() { return 64 * (16 / (int)sizeof(T)); }
-inline int tile_cols_bytes(int elem) { return 64 * (16 / elem); }
+inline __host__ __device__ constexpr int tile_cols_bytes(int elem) { return 64 * (16 / elem); }
 
 // ---- work descriptors ----
 // One descriptor per (view, kernel) in a launch.  A single-view launch passes
@@ -83,23 +83,25 @@ template <typename T> struct FusedDesc {
   int Wd = 0, Wy = 0;
   T* partX3 = nullptr;                  //   (Ud) and its partials
 };
+// (pointers before counts: a round's tables hold one of each per view and level)
 template <typename T> struct GramDesc {
-  const T* Uj; const T* Vj; int W; int n_pad; int tile_rows; double* partG;
-  int nrt; int block_begin;             // blocks: nrt x pair chunks
+  const T* Uj; const T* Vj; double* partG; int W; int n_pad;
+  int nrt; int block_begin;             // blocks: nrt x pair chunks (row tiles of gram_rows)
 };
 template <typename T> struct TailDesc {
-  const T* partX; const T* partY; const double* partG; int nct; int nrt; int n_pad;
-  T* slabU; T* slabV; int W; int block_begin;   // blocks: ceil(n_pad * R / 256)
-  int ng;                                       // Gram partials to add (1: already summed)
+  const T* partX; const T* partY; const double* partG; T* slabU; T* slabV;
+  int nct; int nrt; int n_pad; int W; int block_begin;   // blocks: ceil(n_pad * R / 256)
+  int ng;                                                // Gram partials to add (1: already summed)
 };
 // Sum of ng Gram partials (count doubles each) into the first.
 struct GramSumDesc {
   double* G; int ng; int count; int block_begin;   // blocks: ceil(count / 256)
 };
 template <typename T> struct UpdateDesc {
-  T* P; int64_t ldp; int n_pad; int tile_rows; const T* Uj; const T* Vj; int W;
-  int nct; int block_begin;             // blocks: nct x ceil(n_pad / tile_rows)
+  T* P; int64_t ldp; const T* Uj; const T* Vj;
   uint16_t* S;                          // bfloat16 shadow of P rewritten by the pass, or null
+  int n_pad; int tile_rows; int W;
+  int block_begin;                      // blocks: column tiles x ceil(n_pad / tile_rows)
 };
 // Products a read-only skinny pass forms.
 constexpr int kWantX = 1, kWantY = 2;
@@ -124,8 +126,8 @@ struct Fac16Desc {
 };
 inline int fac16_blocks(const Fac16Desc& d) { return d.n_pad / 64 * (d.cols / 32) * 2; }
 template <typename T> struct PrepDesc {
-  const T* U; int64_t ldu; const T* V; int64_t ldv; int64_t n; int r; int r_pad;
-  T* slabU; T* slabV; int W; int64_t n_pad; int block_begin;   // blocks: ceil(n_pad * r_pad / 256)
+  const T* U; int64_t ldu; const T* V; int64_t ldv; int64_t n; T* slabU; T* slabV; int64_t n_pad;
+  int r; int r_pad; int W; int block_begin;   // blocks: ceil(n_pad * r_pad / 256)
 };
 
 // Descriptor v of a multi-view launch, read through the constant address
@@ -156,7 +158,7 @@ constexpr int kUpdateTileRows = 256;
 constexpr int kMaxLevelRank = 256;
 constexpr int kMfmaUpdateRank = 32;
 constexpr int kMfmaUpdateTile = 128;
-inline bool update_on_mfma(int R, int elem) { return elem == 4 && R >= kMfmaUpdateRank; }
+inline __host__ __device__ constexpr bool update_on_mfma(int R, int elem) { return elem == 4 && R >= kMfmaUpdateRank; }
 inline int update_tile_rows(int R, int elem) { return update_on_mfma(R, elem) ? kMfmaUpdateTile : kUpdateTileRows; }
 // Work-groups a single-view streaming pass aims for, and the rows per
 // (interleaved) slice of the vector update pass that give about that many
@@ -171,7 +173,7 @@ inline int update_slice_rows(int R, int elem, int64_t n_pad) {
   ns = ns < 1 ? 1 : ns > ns_max ? ns_max : ns;
   return (int)((n_pad + ns - 1) / ns);
 }
-inline int update_tile_cols(int R, int elem) { return update_on_mfma(R, elem) ? kMfmaUpdateTile : tile_cols_bytes(elem); }
+inline __host__ __device__ constexpr int update_tile_cols(int R, int elem) { return update_on_mfma(R, elem) ? kMfmaUpdateTile : tile_cols_bytes(elem); }
 // Rows per partial of the stand-alone Gram kernel, and its partial count.
 constexpr int kGramRows = 64;
 inline int gram_tiles(int64_t n_pad) { return (int)(n_pad / kGramRows); }
@@ -252,7 +254,7 @@ constexpr int kTailLanes = 8;
 constexpr int kMfmaGramRank = 32;
 inline __host__ __device__ constexpr int tail_wave_blocks(int R) { return R < 64 ? 1 : R < 256 ? 2 : 4; }
 inline __host__ __device__ constexpr int gram_block(int R) { return R < 64 ? 32 : 64; }
-inline int gram_rows(int R) { return R <= 64 ? kGramRows : R; }
+inline __host__ __device__ constexpr int gram_rows(int R) { return R <= 64 ? kGramRows : R; }
 inline int gram_count(int64_t n_pad, int R) { return (int)((n_pad + gram_rows(R) - 1) / gram_rows(R)); }
 inline int tail_blocks(int64_t n_pad, int R) {
   if (R >= kMfmaGramRank) return (int)(n_pad / 64) * (R / (16 * tail_wave_blocks(R)));

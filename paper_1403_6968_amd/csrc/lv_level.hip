@@ -128,7 +128,7 @@ __device__ __forceinline__ void gram_any(const T* __restrict__ Uj, const T* __re
 template <typename T, int R>
 __global__ void __launch_bounds__(256) k_gram(const GramDesc<T> d, const int64_t sstride, const int64_t gstride) {
   const int64_t v = blockIdx.z;
-  gram_any<T, R>(d.Uj + v * sstride, d.Vj + v * sstride, d.W, d.n_pad, d.tile_rows, d.partG + v * gstride, blockIdx.x,
+  gram_any<T, R>(d.Uj + v * sstride, d.Vj + v * sstride, d.W, d.n_pad, gram_rows(R), d.partG + v * gstride, blockIdx.x,
                   blockIdx.y);
 }
 
@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(256) k_gram_multi(const GramDesc<T>* __restric
   const int v = find_desc(ds, nd, (int)blockIdx.x);
   const GramDesc<T> d = load_desc(ds, v);
   const int local = (int)blockIdx.x - d.block_begin;
-  gram_any<T, R>(d.Uj, d.Vj, d.W, d.n_pad, d.tile_rows, d.partG, local % d.nrt, local / d.nrt);
+  gram_any<T, R>(d.Uj, d.Vj, d.W, d.n_pad, gram_rows(R), d.partG, local % d.nrt, local / d.nrt);
 }
 
 // G[idx] = sum over t < ng of G[t * count + idx], in index order, into the
@@ -1002,7 +1002,8 @@ k_level_update_multi(const UpdateDesc<T>* __restrict__ ds, int nd) {
   const int v = find_desc(ds, nd, (int)blockIdx.x);
   const UpdateDesc<T> d = load_desc(ds, v);
   const int local = (int)blockIdx.x - d.block_begin;
-  update_any<T, R, SH, SPLIT>(d, local % d.nct, local / d.nct);
+  const int nct = d.n_pad / update_tile_cols(R, (int)sizeof(T));
+  update_any<T, R, SH, SPLIT>(d, local % nct, local / nct);
 }
 
 // ---------------------------------------------------------------- small kernels
@@ -1052,7 +1053,7 @@ hipError_t update_r(T* P, int64_t ldp, int64_t n_pad, const T* Uj, const T* Vj, 
                     hipStream_t s, uint16_t* S, bool split) {
   const int tile_rows = update_slice_rows(R, (int)sizeof(T), n_pad);
   const int nct = (int)(n_pad / update_tile_cols(R, (int)sizeof(T)));
-  const UpdateDesc<T> d{P, ldp, (int)n_pad, tile_rows, Uj, Vj, W, nct, 0, S};
+  const UpdateDesc<T> d{P, ldp, Uj, Vj, S, (int)n_pad, tile_rows, W, 0};
   const dim3 grid((unsigned)nct, (unsigned)((n_pad + tile_rows - 1) / tile_rows));
   if constexpr (sizeof(T) == 4) {
     if (S != nullptr && split)
@@ -1095,7 +1096,7 @@ template <typename T, int R>
 hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG, hipStream_t s, int nver = 1,
                   int64_t sstride = 0, int64_t gstride = 0) {
   const int ng = gram_count(n_pad, R);
-  const GramDesc<T> g{Uj, Vj, W, (int)n_pad, gram_rows(R), partG, ng, 0};
+  const GramDesc<T> g{Uj, Vj, partG, W, (int)n_pad, ng, 0};
   const dim3 ggrid((unsigned)ng, (unsigned)gram_chunks(R), (unsigned)nver);
   hipLaunchKernelGGL((k_gram<T, R>), ggrid, dim3(256), 0, s, g, sstride, gstride);
   hipError_t e = hipGetLastError();
@@ -1108,7 +1109,7 @@ hipError_t gram_r(const T* Uj, const T* Vj, int W, int64_t n_pad, double* partG,
 template <typename T, int R>
 hipError_t tail_r(const T* partX, const T* partY, const double* partG, int nct, int nrt, int ng,
                   int64_t n_pad, T* slabU, T* slabV, int W, hipStream_t s, int nver, const Strides& vs) {
-  const TailDesc<T> d{partX, partY, partG, nct, nrt, (int)n_pad, slabU, slabV, W, 0, ng};
+  const TailDesc<T> d{partX, partY, partG, slabU, slabV, nct, nrt, (int)n_pad, W, 0, ng};
   hipLaunchKernelGGL((k_level_tail<T, R>), dim3((unsigned)tail_blocks(n_pad, R), (unsigned)nver), dim3(256), 0, s, d,
                      vs);
   return hipGetLastError();
@@ -1128,7 +1129,7 @@ template <typename T>
 hipError_t launch_prep(const T* U, int64_t ldu, const T* V, int64_t ldv, int64_t n, int r,
                        int r_pad, T* slabU, T* slabV, int W, int64_t n_pad, hipStream_t s, int nver, int64_t strideU,
                        int64_t strideV, int64_t sstride) {
-  const PrepDesc<T> d{U, ldu, V, ldv, n, r, r_pad, slabU, slabV, W, n_pad, 0};
+  const PrepDesc<T> d{U, ldu, V, ldv, n, slabU, slabV, n_pad, r, r_pad, W, 0};
   hipLaunchKernelGGL((k_prep<T>), dim3((unsigned)((n_pad * r_pad + 255) / 256), (unsigned)nver), dim3(256), 0, s, d,
                      strideU, strideV, sstride);
   return hipGetLastError();
@@ -1156,7 +1157,7 @@ hipError_t launch_level_update(int R, T* P, int64_t ldp, int64_t n_pad, const T*
 template <typename T>
 hipError_t launch_level_update_chain(int R, T* P, int64_t ldp, int64_t n_pad, const T* slabU, const T* slabV, int W,
                                      int nver, int64_t sstride, hipStream_t s, bool split) {
-  const UpdateDesc<T> d{P, ldp, (int)n_pad, 0, slabU, slabV + (W - R), W, 0, 0, nullptr};
+  const UpdateDesc<T> d{P, ldp, slabU, slabV + (W - R), nullptr, (int)n_pad, 0, W, 0};
   if (R == kMaxLevelRank) return update_chain_r<T, kMaxLevelRank>(d, nver, sstride, s, split);
   LV_RANK_SWITCH(R, return (update_chain_r<T, RR>(d, nver, sstride, s, split)))
 }

@@ -56,7 +56,7 @@ struct Plan {
     if (ds.empty()) return;
     int b = 0;
     for (auto& d : ds) { d.block_begin = b; b += blocks_of(d); }
-    const size_t off = align_up(bytes.size());
+    const size_t off = (bytes.size() + 63) / 64 * 64;
     bytes.resize(off + ds.size() * sizeof(D));
     std::memcpy(bytes.data() + off, ds.data(), ds.size() * sizeof(D));
     launches.push_back({kind, lane, level, R, off, (int)ds.size(), b});
@@ -66,8 +66,8 @@ struct Plan {
 template <typename T> int fused_blocks(const FusedDesc<T>& d) {
   return d.nct * ((d.n_pad + d.tile_rows - 1) / d.tile_rows);
 }
-template <typename T> int update_blocks(const UpdateDesc<T>& d) {
-  return d.nct * ((d.n_pad + d.tile_rows - 1) / d.tile_rows);
+template <typename T> int update_blocks(const UpdateDesc<T>& d, int R) {
+  return d.n_pad / update_tile_cols(R, sizeof(T)) * ((d.n_pad + d.tile_rows - 1) / d.tile_rows);
 }
 inline int skinny_blocks(const SkinnyDesc& d) { return d.nct * ((d.n_pad + d.tile_rows - 1) / d.tile_rows); }
 template <typename T> int prep_blocks(const PrepDesc<T>& d) {
@@ -91,7 +91,7 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
     lv_view* v = views[i];
     const Layout& L = v->L;
     prep.push_back({static_cast<const T*>(in[i].U), in[i].ldu, static_cast<const T*>(in[i].V), in[i].ldv, v->n,
-                    in[i].r, L.r_pad, v->slabU<T>(), v->slabV<T>(), L.W, L.n_pad, 0});
+                    v->slabU<T>(), v->slabV<T>(), L.n_pad, in[i].r, L.r_pad, L.W, 0});
     max_m = L.m > max_m ? L.m : max_m;
   }
   pl.add(kPrep, 0, prep, &prep_blocks<T>);
@@ -146,10 +146,9 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
       T* sV = v->slabV<T>();
       const T* Vj = sV + (L.W - R);
       const int upd_rows = update_tile_rows(R, L.elem);
-      const int upd_nct = (int)(L.n_pad / update_tile_cols(R, L.elem));
       if (j == L.m) {
-        (v->shadowed() ? updsplit : upd)[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W,
-                                                       upd_nct, 0});
+        (v->shadowed() ? updsplit : upd)[R].push_back({v->P<T>(j), L.ldp, sU, Vj, nullptr, (int)L.n_pad,
+                                                       upd_rows, L.W, 0});
         continue;
       }
       if constexpr (sizeof(T) == 4) {
@@ -177,14 +176,15 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
                                                           Vj + c0, L.W, per, px + c0,
                                                           py + c0, R, L.nct, 0});
           }
-          gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), pg, gram_count(L.n_pad, R), 0});
+          gram[R].push_back({sU, Vj, pg, L.W, (int)L.n_pad, gram_count(L.n_pad, R), 0});
           gsum.push_back({pg, gram_count(L.n_pad, R), R * R, 0});
           if (v->shadowed() || !skinny_fuses_update(R))
-            (v->shadowed() ? updsh : upd)[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W,
-                                                        upd_nct, 0, v->shadowed() ? v->shadow(j) : nullptr});
+            (v->shadowed() ? updsh : upd)[R].push_back({v->P<T>(j), L.ldp, sU, Vj,
+                                                        v->shadowed() ? v->shadow(j) : nullptr, (int)L.n_pad, upd_rows,
+                                                        L.W, 0});
           const bool wd = v->wide16(R);
-          tail[R].push_back({px, py, pg, wd ? wide_splits(L.n_pad) : L.nct,
-                             wd ? wide_splits(L.n_pad) : nrt, (int)L.n_pad, sU, sV, L.W, 0, 1});
+          tail[R].push_back({px, py, pg, sU, sV, wd ? wide_splits(L.n_pad) : L.nct,
+                             wd ? wide_splits(L.n_pad) : nrt, (int)L.n_pad, L.W, 0, 1});
           continue;
         }
       }
@@ -195,11 +195,11 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
         for (int c0 = 0; c0 < R; c0 += kMaxFusedRank)
           chunks.push_back({v->P<T>(j), L.ldp, (int)L.n_pad, trows, sU + c0, Vj + c0, L.W,
                             px + c0, py + c0, nullptr, R, L.nct, 0});
-        gram[R].push_back({sU, Vj, L.W, (int)L.n_pad, gram_rows(R), pg, gram_count(L.n_pad, R), 0});
+        gram[R].push_back({sU, Vj, pg, L.W, (int)L.n_pad, gram_count(L.n_pad, R), 0});
         gsum.push_back({pg, gram_count(L.n_pad, R), R * R, 0});
-        upd[R].push_back({v->P<T>(j), L.ldp, (int)L.n_pad, upd_rows, sU, Vj, L.W, upd_nct, 0});
+        upd[R].push_back({v->P<T>(j), L.ldp, sU, Vj, nullptr, (int)L.n_pad, upd_rows, L.W, 0});
       }
-      tail[R].push_back({px, py, pg, L.nct, nrt, (int)L.n_pad, sU, sV, L.W, 0,
+      tail[R].push_back({px, py, pg, sU, sV, L.nct, nrt, (int)L.n_pad, L.W, 0,
                          gram_in_pass(R, L.elem) ? nrt : 1});
     }
     for (auto& kv : fused) pl.add(kFused, kv.first, kv.second, &fused_blocks<T>);
@@ -214,9 +214,13 @@ Plan make_plan(const std::vector<lv_view*>& views, const std::vector<RoundInput>
       pl.add(kGram, R, kv.second, [chunks_per_tile](const GramDesc<T>& d) { return d.nrt * chunks_per_tile; });
     }
     pl.add(kGramSum, 0, gsum, [](const GramSumDesc& d) { return (d.count + 255) / 256; });
-    for (auto& kv : upd) pl.add(kUpdate, kv.first, kv.second, &update_blocks<T>);
-    for (auto& kv : updsh) pl.add(kUpdateShadow, kv.first, kv.second, &update_blocks<T>);
-    for (auto& kv : updsplit) pl.add(kUpdateSplit, kv.first, kv.second, &update_blocks<T>);
+    for (auto* u : {&upd, &updsh, &updsplit}) {
+      const Kind kind = u == &upd ? kUpdate : u == &updsh ? kUpdateShadow : kUpdateSplit;
+      for (auto& kv : *u) {
+        const int R = kv.first;
+        pl.add(kind, R, kv.second, [R](const UpdateDesc<T>& d) { return update_blocks(d, R); });
+      }
+    }
     for (auto& kv : tail) {
       const int R = kv.first;
       pl.add(kTail, R, kv.second, [R](const TailDesc<T>& d) { return tail_blocks(d.n_pad, R); });

@@ -123,3 +123,29 @@ def test_general_form_views(mode, n, k, r, p, strategy, s):
     err = O.maxrel(out[0][0], x)
     note(f"general {mode} n={n} k={k} r={r} p={p} strategy={strategy} s={s}: T maxrel {err:.2e}")
     assert err < {"fp64": 1e-10, "fp32": 1e-4, "shadow": 5e-3}[mode]
+
+
+@pytest.mark.parametrize("mode,specs,count,most", [
+    (2, [(256, 2, 64)], 1, 132864), (2, [(256, 2, 64)], 40, 5262848), (2, [(300, 4, 32), (256, 16, 8)], 1, 155904),
+    (2, [(256, 16, 8)], 64, 1136128), (2, [(300, 16, 32)], 8, 1073920), (1, [(256, 16, 1), (300, 8, 3)], 16, 263424),
+    (0, [(256, 16, 2)], 32, 299776), (1, [(512, 16, 8)], 32, 1095424), (2, [(256, 8, 16)], 50, 1698816)])
+def test_rounds(mode, specs, count, most):
+    """The tables of a round are no larger than they were (bytes pinned as in
+    test_workspace_sizes.py), and a round runs on a workspace of that size."""
+    torch = need_gpu()
+    from paper_1403_6968_amd import linview as lv
+    td = torch.float64 if mode == 0 else torch.float32
+    views = [lv.View(torch.zeros(n, n, dtype=td, device="cuda"), k, r_max=r, mode=mode)
+             for _ in range(count) for n, k, r in specs]
+    assert lv.lv_batch_footprint(views) <= most
+    buf, ws = _guarded(torch, most // 256 * 256)
+    batch = lv.lv_batch_create(views, ws)
+    one = torch.ones(specs[0][0], 1, dtype=td, device="cuda")
+    lv.lv_batch_stage(batch, 0, one, one, td, device=one.device)
+    lv.lv_batch_update(batch, device=one.device)
+    assert bool((views[0].read(1) == 1).all())
+    assert all(float(v.read(1).abs().max()) == 0 for v in views[1:])
+    assert _intact(buf)
+    lv.lv_batch_destroy(batch)
+    for v in views:
+        v.close()
