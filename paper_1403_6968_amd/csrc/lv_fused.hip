@@ -187,8 +187,8 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
 
   // entry e = (t TT + v) R + c of a block's factor rows (row t, update v,
   // column c) sits in lane e % 64 of f[e / 64]; foff: byte offset of the
-  // lane's entry from the block's first factor row (32 bits: eight slabs of
-  // the largest order and width stay below 2^31 bytes)
+  // lane's entry from the block's first factor row (32 bits: lv_view_impl.h has
+  // the bound of the last update's)
   unsigned foff[FN], foffy[SP ? FN : 1];
 #pragma unroll
   for (int f = 0; f < FN; ++f) {
@@ -473,12 +473,12 @@ __device__ __forceinline__ void fused_body(const FusedDesc<T>& d, const int ct, 
   }
 }
 
-// Two waves per SIMD for the widest passes over several updates, which would
+// Two waves per SIMD for passes over several updates: the widest would
 // otherwise take a few registers more than that leaves.
-template <int R, int TT> constexpr int fused_min_waves() { return TT > 1 ? 2 : 1; }
+template <int TT> constexpr int fused_min_waves() { return TT > 1 ? 2 : 1; }
 
 template <typename T, int R, int TT, bool UPD>
-__global__ void __launch_bounds__(256, (fused_min_waves<R, TT>())) k_level_fused(const FusedDesc<T> d, const Strides vs) {
+__global__ void __launch_bounds__(256, (fused_min_waves<TT>())) k_level_fused(const FusedDesc<T> d, const Strides vs) {
   fused_body<T, R, TT, UPD>(d, blockIdx.x, blockIdx.y, vs);
 }
 

@@ -23,6 +23,14 @@ constexpr size_t kAlign = 256;
 constexpr int64_t kMaxOrder = 65536;
 constexpr int kMaxK = 1024;
 constexpr int kMaxWidth = 2 * kMaxLevelRank;   // k * r_pad: width of the top-level factors
+// A pass over several updates addresses their factor entries by 32-bit byte
+// offsets from the first one's block: the last update's slab pair and a row
+// block of it stay below 2^31 (a pair's rows are widest in floats, and as long
+// in doubles, whose width stops at kMaxLevelRank).
+static_assert(((kChainUpdates - 1) * 2 * kMaxOrder + kFusedRowBlock) * kMaxWidth * (int64_t)sizeof(float) < (int64_t(1) << 31) &&
+                  ((kChainUpdates - 1) * 2 * kMaxOrder + kFusedRowBlock) * kMaxLevelRank * (int64_t)sizeof(double) <
+                      (int64_t(1) << 31),
+              "32-bit offsets of a shared pass");
 constexpr int kMinTileRows = 256;   // tile rows a level pass may be set to:
 constexpr int kMaxTileRows = 1024;  //   multiples of 64 in [256, 1024]
 
