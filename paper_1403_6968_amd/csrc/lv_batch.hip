@@ -84,8 +84,6 @@ namespace {
 std::mutex g_tune_mu;
 std::map<std::string, int> g_tune_cache;
 
-bool is_pass(Kind k) { return k == kFused || k == kChunk || k == kSkinny || k == kSkinnyF32; }
-
 lv_status upload_plan(lv_batch* b, hipStream_t s) {
   lv_status st = hip_check(hipMemcpyAsync(b->base + b->bl.stage_bytes, b->bl.plan.bytes.data(), b->bl.plan.bytes.size(),
                                           hipMemcpyHostToDevice, s), "upload descriptors");

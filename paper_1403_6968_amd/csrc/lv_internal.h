@@ -236,10 +236,6 @@ inline int slice_rows(int64_t n_pad, int elem, int R, bool cores, bool reads = f
   if (rows < least) rows = round_up(least, unit);
   return rows < kTileRows ? (int)rows : kTileRows;
 }
-inline int slice_count(int64_t n_pad, int elem, int R, bool cores, bool reads = false) {
-  const int rows = slice_rows(n_pad, elem, R, cores, reads);
-  return (int)((n_pad + rows - 1) / rows);
-}
 
 // The tail at this level rank: one column per lane and kTailRowsPerThread rows
 // per thread.
@@ -542,8 +538,6 @@ inline int vtt_tiles(int64_t n_pad, int pairs) { return (int)(n_pad / vtt_rows(p
 template <typename T>
 hipError_t launch_vtt(int R, int pp, const T* V, const T* Tm, int64_t tstride, int cnt, int64_t n_pad, double* part,
                       T* Z, hipStream_t s);
-// G[0 .. count) = sum over t < ng of G[t count + ...] (fixed order).
-hipError_t launch_gram_sum(double* G, int ng, int count, hipStream_t s);
 
 // Multi-view launches over device descriptor arrays (nd descriptors,
 // `blocks` work-groups in total).  `chunk` selects the read-only skinny pass
