@@ -629,6 +629,10 @@ typedef struct lv_chain lv_chain;
 /* Workspace bytes; 0 for invalid arguments (s is ignored unless the model
  * is LV_MODEL_SKIP). */
 size_t lv_chain_footprint(int64_t n, int k, int r_max, lv_mode mode, int model, int s);
+/* Workspace in which the passes take as many row slices as fill the device;
+ * an LV_FP64 chain of few powers and small order takes fewer in the smallest
+ * one (up to 6% on an update). */
+size_t lv_chain_footprint_full(int64_t n, int k, int r_max, lv_mode mode, int model, int s);
 lv_status lv_chain_create(const void* A, int64_t n, int64_t lda, int k, int r_max, lv_mode mode,
                           int model, int s, void* workspace, size_t ws_bytes, void* stream,
                           lv_chain** out);
@@ -711,6 +715,10 @@ void lv_ols_destroy(lv_ols* o);
 typedef struct lv_glin lv_glin;
 
 size_t lv_glin_footprint(int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy);
+/* Workspace in which wide products (p > 64) are split into as many shares as fill
+ * the device; in LV_FP64 the smallest one holds four or so (n = 1300, p = 79,
+ * k = 8: 520 us per re-evaluation, 256 us in the full one). */
+size_t lv_glin_footprint_full(int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy);
 lv_status lv_glin_create(const void* A, int64_t n, int64_t lda, int k, int r_max, lv_mode mode,
                          const void* T0, int64_t ldt, const void* B, int64_t ldb, int64_t p,
                          int strategy, void* workspace, size_t ws_bytes, void* stream, lv_glin** out);

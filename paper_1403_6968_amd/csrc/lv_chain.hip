@@ -185,7 +185,10 @@ lv_status check_chain(int64_t n, int k, int r_max, lv_mode mode, int model, int 
   return LV_OK;
 }
 
-lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, int model, int s) {
+// The layout in a workspace of ws_bytes, or of the smallest size; *full (may be
+// null) receives the size that holds every slice.
+lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, int model, int s, size_t ws_bytes = 0,
+                       size_t* full = nullptr) {
   c.n = n; c.k = k; c.s = model == LV_MODEL_SKIP ? s : 0; c.model = model; c.r_max = r_max; c.mode = mode;
   c.r_pad = (int)next_pow2(r_max);
   c.elem = mode == LV_FP64 ? 8 : 4;
@@ -220,6 +223,9 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
       off = align_up(off + np * np * sizeof(double));
     }
   }
+  c.total = off;
+  const size_t room = (ws_bytes > off ? ws_bytes : off) - work;
+  size_t all = off;
   for (auto& q : c.steps) {
     const size_t w = (size_t)c.pw[q.a] * c.r_pad;
     const bool cores = skinny_on_mfma((int)w, c.elem);
@@ -231,10 +237,13 @@ lv_status layout_chain(lv_chain& c, int64_t n, int k, int r_max, lv_mode mode, i
       q.g = align_up(q.y + nrt * np * w * e);
       return q.g + (w <= (size_t)kMaxKrylovCols ? nrt : np / kAtbRows) * w * w * sizeof(double) - work;
     };
-    q.rows = fitted_rows(c.n_pad, slice_rows(c.n_pad, c.elem, (int)w, cores), cores, off - work, place);
+    const int want = slice_rows(c.n_pad, c.elem, (int)w, cores);
+    const size_t bytes = work + place((c.n_pad + want - 1) / want);
+    all = bytes > all ? bytes : all;
+    q.rows = fitted_rows(c.n_pad, want, cores, room, place);
     place((c.n_pad + q.rows - 1) / q.rows);
   }
-  c.total = off;
+  if (full) *full = all;
   return LV_OK;
 }
 
@@ -369,6 +378,13 @@ size_t lv_chain_footprint(int64_t n, int k, int r_max, lv_mode mode, int model, 
   return c.total;
 }
 
+size_t lv_chain_footprint_full(int64_t n, int k, int r_max, lv_mode mode, int model, int s) {
+  if (check_chain(n, k, r_max, mode, model, s) != LV_OK) return 0;
+  lv_chain c;
+  size_t full = 0;
+  return layout_chain(c, n, k, r_max, mode, model, s, 0, &full) == LV_OK ? full : 0;
+}
+
 lv_status lv_chain_create(const void* A, int64_t n, int64_t lda, int k, int r_max, lv_mode mode, int model, int s,
                           void* workspace, size_t ws_bytes, void* stream, lv_chain** out) {
   g_err[0] = 0;
@@ -382,7 +398,7 @@ lv_status lv_chain_create(const void* A, int64_t n, int64_t lda, int k, int r_ma
     return fail(LV_ENOMEM, "workspace is not %zu-byte aligned", kAlign);
   lv_chain* c = new (std::nothrow) lv_chain();
   if (!c) return fail(LV_ENOMEM, "host allocation of the chain handle failed");
-  st = layout_chain(*c, n, k, r_max, mode, model, s);
+  st = layout_chain(*c, n, k, r_max, mode, model, s, ws_bytes);
   if (st == LV_OK && ws_bytes < c->total) st = fail(LV_ENOMEM, "workspace has %zu bytes, needs %zu", ws_bytes, c->total);
   if (st != LV_OK) { delete c; return st; }
   c->base = static_cast<char*>(workspace);

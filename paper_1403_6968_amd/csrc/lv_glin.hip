@@ -96,7 +96,9 @@ lv_status check_glin(int64_t n, int k, int r_max, lv_mode mode, int64_t p, int s
   return LV_OK;
 }
 
-void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy) {
+// The layout in a workspace of ws_bytes, or of the smallest size; returns the
+// size that holds every share and slice.
+size_t layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy, size_t ws_bytes = 0) {
   g.n = n; g.k = k; g.r_max = r_max; g.mode = mode; g.p = (int)p; g.strategy = strategy;
   g.elem = mode == LV_FP64 ? 8 : 4;
   g.n_pad = round_up(n, kPadOrder);
@@ -135,7 +137,7 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
     for (int i = 1; i <= k; ++i) take(g.maxw * pp * e);
   }
   g.total = off;
-  const size_t room = off - work;
+  const size_t room = (ws_bytes > off ? ws_bytes : off) - work;
   // an update's buffers with the given shares of a wide product and slices of an
   // incremental step; returns their size
   g.D[0] = g.D[1] = g.full = g.atbG = g.Y = g.Z = 0;
@@ -154,12 +156,13 @@ void layout_glin(lv_glin& g, int64_t n, int k, int r_max, lv_mode mode, int64_t 
     return off - work;
   };
   g.splits = wide ? (int)glin_splits(g.n_pad, pp) : 1;
-  g.rows = fitted_rows(g.n_pad, slice_rows(g.n_pad, g.elem, (int)r, false, true), false, room,
-                       [&](int64_t ns) { return place(1, ns); });
+  const int want = slice_rows(g.n_pad, g.elem, (int)r, false, true);
+  const size_t all = work + place(g.splits, (g.n_pad + want - 1) / want);
+  g.rows = fitted_rows(g.n_pad, want, false, room, [&](int64_t ns) { return place(1, ns); });
   const int64_t ns = (g.n_pad + g.rows - 1) / g.rows;
   while (g.splits > 1 && place(g.splits, ns) > room) --g.splits;
-  const size_t used = place(g.splits, ns);
-  g.total = work + (used > room ? used : room);
+  place(g.splits, ns);
+  return all > g.total ? all : g.total;
 }
 
 // Creation: T_i = A T_{i-1} + B in double from the double A, each rounded once.
@@ -306,6 +309,12 @@ size_t lv_glin_footprint(int64_t n, int k, int r_max, lv_mode mode, int64_t p, i
   return g.total;
 }
 
+size_t lv_glin_footprint_full(int64_t n, int k, int r_max, lv_mode mode, int64_t p, int strategy) {
+  if (check_glin(n, k, r_max, mode, p, strategy) != LV_OK) return 0;
+  lv_glin g;
+  return layout_glin(g, n, k, r_max, mode, p, strategy);
+}
+
 lv_status lv_glin_create(const void* A, int64_t n, int64_t lda, int k, int r_max, lv_mode mode, const void* T0,
                          int64_t ldt, const void* B, int64_t ldb, int64_t p, int strategy, void* workspace,
                          size_t ws_bytes, void* stream, lv_glin** out) {
@@ -319,7 +328,7 @@ lv_status lv_glin_create(const void* A, int64_t n, int64_t lda, int k, int r_max
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign) return fail(LV_ENOMEM, "workspace is not %zu-byte aligned", kAlign);
   lv_glin* g = new (std::nothrow) lv_glin();
   if (!g) return fail(LV_ENOMEM, "host allocation of the handle failed");
-  layout_glin(*g, n, k, r_max, mode, p, strategy);
+  layout_glin(*g, n, k, r_max, mode, p, strategy, ws_bytes);
   if (ws_bytes < g->total) {
     const size_t need = g->total;
     delete g;

@@ -52,7 +52,7 @@ EXPORTED = (
     "lv_server_poll", "lv_server_drain", "lv_server_stats", "lv_server_destroy",
     "lv_stream_probe", "lv_powers_update_noalloc", "lv_view_set_drift_check", "lv_server_set_admission_queue",
     "lv_tune_cache_save", "lv_tune_cache_load", "lv_tune_cache_clear",
-    "lv_view_footprint_full", "lv_view_footprint_general_full", "lv_view_batch_bytes", "lv_view_set_batch_workspace",
+    "lv_chain_footprint_full", "lv_glin_footprint_full", "lv_view_footprint_full", "lv_view_footprint_general_full", "lv_view_batch_bytes", "lv_view_set_batch_workspace",
 )
 
 
@@ -178,6 +178,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         "lv_server_set_admission_queue": (I32, [P, I32]),
         "lv_view_footprint_full": (SZ, [I64, I32, I32, I32, I32]),
         "lv_view_footprint_general_full": (SZ, [I64, I32, I32, I32, I64, I32, I32]),
+        "lv_chain_footprint_full": (SZ, [I64, I32, I32, I32, I32, I32]),
+        "lv_glin_footprint_full": (SZ, [I64, I32, I32, I32, I64, I32]),
         "lv_view_batch_bytes": (SZ, [P]),
         "lv_view_set_batch_workspace": (I32, [P, P, SZ]),
         "lv_tune_cache_save": (I32, [c.c_char_p]),
@@ -853,7 +855,7 @@ class Chain:
         self.mode, self.dtype = mode, _MODE_DTYPE[mode]
         self.n, self.k, self.device = A.shape[0], k, A.device
         lib = load()
-        nbytes = int(lib.lv_chain_footprint(self.n, k, r_max, mode, model, s))
+        nbytes = int(lib.lv_chain_footprint_full(self.n, k, r_max, mode, model, s))
         if nbytes == 0:
             _check(lib.lv_chain_create(None, self.n, self.n, k, r_max, mode, model, s, None, 0, None,
                                        ctypes.byref(ctypes.c_void_p())))
@@ -975,7 +977,7 @@ class GLin:
         self.mode, self.dtype = mode, _MODE_DTYPE[mode]
         self.n, self.k, self.p, self.device = A.shape[0], k, T0.shape[1], A.device
         lib = load()
-        nbytes = int(lib.lv_glin_footprint(self.n, k, r_max, mode, self.p, strategy))
+        nbytes = int(lib.lv_glin_footprint_full(self.n, k, r_max, mode, self.p, strategy))
         if nbytes == 0:
             _check(lib.lv_glin_create(None, self.n, self.n, k, r_max, mode, None, self.p, None, self.p, self.p,
                                       strategy, None, 0, None, ctypes.byref(ctypes.c_void_p())))

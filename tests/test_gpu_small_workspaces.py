@@ -5,6 +5,8 @@ bit for bit, and no byte outside the buffers touched."""
 
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -149,3 +151,54 @@ def test_rounds(mode, specs, count, most):
     lv.lv_batch_destroy(batch)
     for v in views:
         v.close()
+
+
+def _small(torch, lv, kind, A, T0, B, k, r, mode, model, s, strategy, td):
+    """A chain or linear general form on the smallest workspace; returns (buffer, handle)."""
+    lib, n, h = lv.load(), A.shape[0], ctypes.c_void_p()
+    if kind == "chain":
+        buf, ws = _guarded(torch, lib.lv_chain_footprint(n, k, r, mode, model, s))
+        lv._check(lib.lv_chain_create(A.data_ptr(), n, n, k, r, mode, model, s, ws.data_ptr(), ws.numel(),
+                                      lv._stream(None, A.device), ctypes.byref(h)))
+    else:
+        p = T0.shape[1]
+        buf, ws = _guarded(torch, lib.lv_glin_footprint(n, k, r, mode, p, strategy))
+        lv._check(lib.lv_glin_create(A.data_ptr(), n, n, k, r, mode, T0.data_ptr(), p, B.data_ptr(), p, p, strategy,
+                                     ws.data_ptr(), ws.numel(), lv._stream(None, A.device), ctypes.byref(h)))
+    return buf, h
+
+
+@pytest.mark.parametrize("kind,n,k,r,model,s,strategy,p,dtype", [
+    ("chain", 512, 2, 1, 1, 0, 0, 0, "f64"), ("chain", 300, 4, 8, 1, 0, 0, 0, "f64"), ("chain", 520, 8, 2, 2, 4, 0, 0, "f64"),
+    ("chain", 700, 12, 1, 1, 0, 0, 0, "f32"), ("glin", 1000, 3, 1, 0, 0, 0, 130, "f64"), ("glin", 600, 4, 2, 0, 0, 1, 79, "f64"),
+    ("glin", 512, 2, 8, 0, 0, 2, 3, "f64"), ("glin", 300, 5, 1, 0, 0, 1, 16, "f32")])
+def test_models(kind, n, k, r, model, s, strategy, p, dtype):
+    """Against the same handle on its full workspace: other slices, so another
+    order of the same sums; the tolerances of the modes, a tenth of them."""
+    torch = need_gpu()
+    from paper_1403_6968_amd import linview as lv
+    lib = lv.load()
+    td, nd, mode = (torch.float64, np.float64, 0) if dtype == "f64" else (torch.float32, np.float32, 1)
+    A = dev(np.asarray(synth.gaussian_matrix(n, seed=n, config=4), nd), td)
+    Us, Vs = (np.asarray(x, nd) for x in synth.update_factors(n, r, 3, seed=n, config=4))
+    T0 = B = None
+    if kind == "glin":
+        T0, B = (dev(np.asarray(x, nd), td) for x in synth.general_operands(n, p, seed=n, config=5))
+    buf, h = _small(torch, lv, kind, A, T0, B, k, r, mode, model, s, strategy, td)
+    full = lv.Chain(A, k, r_max=r, model=model, s=s) if kind == "chain" else lv.GLin(A, k, T0, B, r_max=r, strategy=strategy)
+    update = lib.lv_chain_update if kind == "chain" else lib.lv_glin_update
+    read = lib.lv_chain_read if kind == "chain" else lib.lv_glin_read
+    st = lv._stream(None, A.device)
+    for t in range(3):
+        U, V = dev(Us[t], td), dev(Vs[t], td)
+        lv._check(update(h, U.data_ptr(), V.data_ptr(), r, r, r, st))
+        full.update(U, V)
+        torch.cuda.synchronize()
+    cols = n if kind == "chain" else p
+    for i in (full.powers() if kind == "chain" else range(1, k + 1)):
+        out = torch.empty(n, cols, dtype=td, device="cuda")
+        lv._check(read(h, i, out.data_ptr(), cols, st))
+        assert O.maxrel(host(out), host(full.read(i))) < (1e-11 if dtype == "f64" else 1e-5), i
+    assert _intact(buf)
+    (lib.lv_chain_destroy if kind == "chain" else lib.lv_glin_destroy)(h)
+    full.close()

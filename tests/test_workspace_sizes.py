@@ -49,12 +49,16 @@ def test_ols(lib, args, most):
 
 @pytest.mark.parametrize("args,most", CHAIN)
 def test_chain(lib, args, most):
-    assert 0 < lib.lv_chain_footprint(*args) <= most
+    got = lib.lv_chain_footprint(*args)
+    assert 0 < got <= most
+    assert got <= lib.lv_chain_footprint_full(*args) <= 1.5 * got
 
 
 @pytest.mark.parametrize("args,most", GLIN)
 def test_linear_general_form(lib, args, most):
-    assert 0 < lib.lv_glin_footprint(*args) <= most
+    got = lib.lv_glin_footprint(*args)
+    assert 0 < got <= most
+    assert got <= lib.lv_glin_footprint_full(*args) <= 2.1 * got
 
 
 @pytest.mark.parametrize("args,most", VIEW)
