@@ -12,8 +12,6 @@ namespace lv {
 // row of P_j or U_j produces zero rows of every product), so no kernel needs
 // bounds checks.
 constexpr int kPadOrder = 256;
-// A tile's row count and the padded order are multiples of 4 waves x 16-row
-// blocks in the fused level pass.
 // Largest level rank handled by the register-resident fused pass; larger
 // ranks run the skinny products in chunks of this many factor columns.
 constexpr int kMaxFusedRank = 16;

@@ -171,10 +171,9 @@ __global__ void __launch_bounds__(256) k_gram_sum_multi(const GramSumDesc* __res
 // Per output (row i, column c): x = sum of the column tiles' partial X and
 // y = sum of the row tiles' partial Y, each added in tile order in double
 // (loads in batches of 8), ug = sum_d U_j[i][d] G[d][c] in double.
-// R < 64: one thread per (row, c), the whole G in LDS.  R >= 64: a block
-// covers 64 rows x a 32-column slice and holds only G's slice (R x 32
-// doubles), each thread 8 rows of one column.  Same sums in the same order
-// either way.
+// R < kSlicedTailRank: kTailLanes lanes per entry.  R = 16: one column per lane,
+// kTailRowsPerThread rows per thread.  Both hold G in LDS.  From rank
+// kMfmaGramRank U_j G is formed on the double matrix cores.
 template <typename T>
 __device__ __forceinline__ double sum_partials(const T* __restrict__ part, const int64_t stride, const int64_t idx,
                                                const int count) {
@@ -721,7 +720,9 @@ __device__ __forceinline__ void update_mfma_body(float* __restrict__ P, const in
 
 // The same for runs of successive updates in double storage, any rank from 4
 // (v_mfma_f64_16x16x4f64, whose four products are added in index order with
-// one rounding each: the vector kernel's chain bit for bit).  Tile 64 x 64;
+// one rounding each: the vector kernel's chain bit for bit).  The next slab's
+// factors, requested a step ahead, keep 80 bytes a lane in scratch from rank 16.
+// Tile 64 x 64;
 // wave (wm, wn) owns 32 x 32 of it as 2 x 2 blocks of 16 x 16.
 // 16x16x4 layouts: A: lane l holds A[l % 16][l / 16]; B: B[l / 16][l % 16];
 // C: element v of lane l is C[4 v + l / 16][l % 16].

@@ -543,7 +543,7 @@ __global__ void __launch_bounds__(256, 2) k_skinny_gemm_multi(const SkinnyDesc* 
 // n = 16384 (1.07 GB of P, 0.54 GB of shadow; the traffic alone 430 us), passes
 // by themselves, in us: rank 4 four updates 640, rank 8 706, rank 16 952, rank
 // 32 two updates 604; an update alone 520 to 610 for its two passes.  A batch
-// of 8 rank-4 updates, k = 16: 23.5 -> 9.7 ms.
+// of 8 rank-4 updates, k = 16: 23.5 -> 9.4 ms.
 //
 // Operands are prepared by k_chain_factors: per update Ut and Vt (bfloat16, R
 // rows of n_pad) and the factors of the delta (U then V: floats, max(R, 4) rows
@@ -629,7 +629,8 @@ __global__ void __launch_bounds__(64 * kChainWaves, 2) k_shadow_chain(const Chai
   // The next chunk's operands, and its values where T R <= 32, are requested a
   // chunk ahead; beyond, the values once the chunk's are stored: the registers
   // would spill, and a reload waits for every load before it (rank 16, four
-  // updates: 1288 us spilled, 952 us so).
+  // updates: 1288 us spilled, 952 us so; four updates at ranks 1, 2 and 4 still
+  // keep 5, 3 and 9 registers in scratch).
   constexpr bool AHEAD = T * R <= 32;
   f32x4 p[8], pn[AHEAD ? 8 : 1];
   u16x8 on[NP];
