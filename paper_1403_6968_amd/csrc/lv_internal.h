@@ -213,6 +213,12 @@ inline bool sums_fused(int R, int elem) { return R <= kMaxFusedRank && !skinny_o
 // 38 us and 22 us.  Other heights are taken as they are: rounds over many
 // views fill the device anyway and lose by finer slices (32 views of 512 to
 // 4096: 2.34 ms with tuned heights, 2.52 ms when every height was cut).
+//   Pass and tail of one update by the rule against the best of 64, 128, 256 and
+// 512 rows, us: FP32 n = 512 rank 1 13 (14), rank 8 17 (22), rank 32 54 (39);
+// n = 2048 17 (17), 23 (23), 61 (53); n = 4096 33 (33), 47 (43), 91 (91); n = 8192
+// 96 (97), 111 (113), 227 (228); n = 16384 391 (366), 439 (438), 802 (798); FP64
+// ranks 1 to 16 and n = 512 to 8192 within 5%.  The 256-row limit of the
+// matrix-core passes costs most, at n <= 2048.
 constexpr int kTileRows = 512;      // default rows per tile: the most rows of the default cut
 //
 // Twice as many work-groups for passes that only read (`reads`) and for 128

@@ -374,7 +374,9 @@ __global__ void __launch_bounds__(256) k_fac16_multi(const Fac16Desc* __restrict
 // half the 12 instructions plus half the 11 additions, 11.5 for X and for Y,
 // where one float chain per 256 columns (X) and per 512 rows (Y), the partials
 // of a pass over 2-D tiles, has 8 and 16.  A rank-32 update at n = 7157, k = 16
-// (three such levels): 982 us with one chain per split, 1004 us so.
+// (three such levels): 982 to 1005 us with one chain per split, 1004 to 1022 us
+// so; the products by themselves then R = 64 48 -> 54 us, R = 128 59 -> 56 to 69
+// us, R = 256 118 -> 137 us.
 constexpr int kGemmTile = 128, kGemmStep = 64, kGemmRun = 3;
 template <int BN, bool YP>
 __device__ __forceinline__ void skinny_gemm_body(const SkinnyDesc& d, uint16_t* sS, uint16_t* sF, const int tile,
